@@ -283,3 +283,109 @@ def tolerance(case):
     if case["T"] <= 16:
         return {"rel": 1e-5, "max": 1e-4} if case.get("abits") else {"rel": 5e-4, "max": 1.2e-2}
     return {"rel": 4e-5, "max": 2e-3}
+
+
+# ---- the same results in 64 bits ------------------------------------------------------------------------------------
+def _quantised(W):
+    """Eight-bit codes (fp64 [N, G, 128]), group scales and zero points ([N, G, 1]) of fp32 weights: the recursion
+    c = clamp(floor(R / s + z)), R -= s ((c - z) + 1/2), s /= 4 over four two-bit slices, step by step in 64 bits."""
+    w = W.view(W.shape[0], -1, 128)
+    lo, hi = w.amin(dim=2, keepdim=True), w.amax(dim=2, keepdim=True)
+    span = torch.maximum(hi - lo, torch.maximum(lo.abs(), hi.abs()).mul(2.0 ** -16).clamp(min=2.0 ** -100))
+    s0 = span * 0.25
+    z0 = (-lo.double() / s0.double()).float().double()
+    R, s, code = w.double(), s0.double(), 0.0
+    for e in range(4):
+        z = z0 if e == 0 else 2.0
+        c = (R / s + z).floor_().clamp_(0.0, 3.0)
+        code = code * 4.0 + c
+        R = R - s * ((c - z) + 0.5)
+        s = s * 0.25
+    return code, s0.double(), z0
+
+
+def _linear(X, W, bits):
+    """X [T, K] times the weights rebuilt from the leading bits[i] bits of every code, fp64 [T, N]; W in row blocks."""
+    Y = torch.zeros((X.shape[0], W.shape[0]), dtype=torch.float64, device=DEVICE)
+    x, used = X.double(), torch.unique(bits).tolist()
+    for n in range(0, W.shape[0], 2048):
+        code, s0, z0 = _quantised(W[n:n + 2048])
+        for b in used:
+            rows = torch.nonzero(bits == b).flatten()
+            rebuilt = s0 * (((code * 2.0 ** (b - 8)).floor_() + 0.5) * 2.0 ** (2 - b) - z0)
+            Y[rows, n:n + 2048] = x[rows] @ rebuilt.view(rebuilt.shape[0], -1).T
+    return Y
+
+
+def _routed(choice, slices):
+    """Precision array, tokens grouped by the two-bit slices that they need, where the groups begin; bits of a token.
+    A precision is named by its slices less one, or, where a slice ends inside a two-bit digit, by its bits less one."""
+    ends = np.cumsum([int(c) for c in slices])
+    bits = torch.tensor(ends, device=DEVICE)[choice]
+    digits = (bits + 1) // 2
+    prec = bits - 1 if (ends % 2).any() else digits - 1
+    offsets = torch.stack([(digits <= d).sum() for d in range(5)])
+    return [prec, torch.sort(digits, stable=True)[1], offsets], bits
+
+
+def _choice(X, Wr, br):
+    return torch.argmax(X.double() @ Wr.double().T + br.double(), dim=1)
+
+
+def _quantised_tokens(X, abits, shift, scale):
+    """Per-token quantiser, one fp32 operation a step as it is defined: integers, row scales, the router's input."""
+    t = (X.float() - shift) / scale
+    top = float(2 ** abits - 1)
+    lo, hi = t.amin(dim=1, keepdim=True).clamp(max=0.0), t.amax(dim=1, keepdim=True).clamp(min=0.0)
+    step = (hi - lo).clamp(min=2.0 ** -100) / torch.full_like(lo, top)
+    zero = torch.round(-lo / step).clamp(0.0, top)
+    whole = (torch.round(t / step) + zero).clamp(0.0, top) - zero
+    return whole, step.flatten(), ((whole * step) * scale + shift).to(torch.bfloat16)
+
+
+def exact(case, seed):
+    gen = torch.Generator(device=DEVICE)
+    gen.manual_seed(seed)
+    kind = case["kind"]
+    if kind == "encode":
+        return None  # bytes
+    if kind in ("block", "mlp"):
+        slices, abits = case.get("slices", "2222"), case.get("abits", 0)
+        stages = _mlp_stages(case) if kind == "mlp" else _block_stages(case) * case["layers"]
+        out = []
+        for Ns, K in stages:
+            # drawn as _Stage draws them
+            X = _tokens(gen, case["T"], K, "tokens" if kind == "mlp" else "channels")
+            routers = [_router(gen, K, case["mix"], "tokens" if kind == "mlp" else "channels", len(slices)) for _ in Ns]
+            W = [_weights(gen, N, K) for N in Ns]
+            factor, seen, act = 1.0, X, []
+            if abits:
+                shift = 0.1 * torch.randn((K,), generator=gen, device=DEVICE)
+                scale = torch.exp(0.3 * torch.randn((K,), generator=gen, device=DEVICE))
+                whole, step, seen = _quantised_tokens(X, abits, shift, scale)
+                X, factor, act = whole, step.double()[:, None], [[whole, step, seen]]
+            for (Wr, br), w in zip(routers, W):
+                routing, bits = _routed(_choice(seen, Wr, br), slices)
+                out.append(routing + [factor * _linear(X, w, bits)])
+            out += act
+        # one list a stage, its projections first
+        per, nested = [len(Ns) + (1 if abits else 0) for Ns, _ in stages], []
+        for n in per:
+            nested.append(out[:n])
+            out = out[n:]
+        return nested
+    if kind == "stage":
+        X = _tokens(gen, case["T"], case["K"], "channels")
+        Wr, br = _router(gen, case["K"], case["mix"], "channels")
+        routing, bits = _routed(_choice(X, Wr, br), "2222")
+        return [routing], [_linear(X, _weights(gen, case["N"], case["K"]), bits)]
+    K, H = case["K"], case["H"]
+    X = _tokens(gen, case["T"], K, "tokens")
+    W1 = torch.randn((H, K), generator=gen, device=DEVICE) / math.sqrt(K)
+    b1 = 0.1 * torch.randn((H,), generator=gen, device=DEVICE)
+    W2 = 2.0 * torch.randn((4, H), generator=gen, device=DEVICE) / math.sqrt(H)
+    b2 = 0.5 - 0.5 * torch.arange(4, dtype=torch.float32, device=DEVICE)
+    scores = (X.double() @ W1.double().T + b1.double()).clamp_(min=0.0) @ W2.double().T + b2.double()
+    choice = torch.cumprod((scores[:, 1:] > 0.0).long(), dim=1).sum(dim=1)
+    routing, bits = _routed(choice, "2222")
+    return routing + [_linear(X, _weights(gen, N, K), bits) for N in (case["N"], case["N2"])]
