@@ -77,11 +77,41 @@ __global__ __launch_bounds__(256) void encode_kernel(const float* __restrict__ W
   uint32_t word[kSlices] = {0u, 0u, 0u, 0u};
   if (real) {
     const double s0d = (double)s0, z0d = (double)z0;
+    // The four codes of a weight are the base-4 digits of ONE eight-bit code, floor(64 (w / s0 + z0)) cut off at 0 and
+    // 255, as long as no rounding of the step-by-step recursion carries a step over a whole number.  That form needs
+    // one division per thread where the recursion needs four IEEE fp64 divisions per weight.  In units of u, the
+    // recursion's accumulated rounding is at most 64 x 2^-53 x 8 (|w / s0| + |z0| + 4) (two roundings of that size
+    // before the first floor, three in the first remainder, terms of at most 4 afterwards) and that of u itself less
+    // than half of it: a weight whose u is further than `slack`, 64 x 2^-53 x 32 of the same sum, from every whole
+    // number gets the same digits either way; any other, and one whose u is not finite, runs the recursion itself.
+    // 11008 x 4096: 128 us with the recursion for every weight (bound by the divisions), 51 us now: 228 MB at
+    // 4.4 TB/s, where a plain copy reaches 5.1.
+    const double inv64 = 64.0 / s0d, z64 = 64.0 * z0d;
+    uint32_t near = 0u;
+    uint32_t code[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const double a = (double)w[i] * inv64;
+      const double u = a + z64;
+      const double f = floor(u);
+      const double slack = (fabs(a) + fabs(z64) + 256.0) * 0x1p-48;
+      const double r = u - f;
+      near |= (r > slack && r < 1.0 - slack) ? 0u : 1u << i;
+      code[i] = (uint32_t)(int)fmin(fmax(f, 0.0), 255.0);
+    }
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int step = i >> 3, s = i & 7;
       const int field = 16 * (s & 1) + 4 * (s >> 1) + 2 * step;
-      double R = (double)w[i];
+#pragma unroll
+      for (int e = 0; e < kSlices; ++e)
+        word[e] |= ((code[i] >> (6 - 2 * e)) & 3u) << ((field + 2 - 2 * e) & 31);
+    }
+#pragma unroll 1
+    for (; near != 0u; near &= near - 1u) {
+      const int i = __ffs((int)near) - 1, step = i >> 3, s = i & 7;
+      const int field = 16 * (s & 1) + 4 * (s >> 1) + 2 * step;
+      double R = (double)W[n * K + kbase + 32 * step + s];
       double se = s0d;
 #pragma unroll
       for (int e = 0; e < kSlices; ++e) {
@@ -89,7 +119,8 @@ __global__ __launch_bounds__(256) void encode_kernel(const float* __restrict__ W
         double q = floor(R / se + ze);
         q = fmin(fmax(q, 0.0), 3.0);
         R = R - se * ((q - ze) + 0.5);
-        word[e] |= (uint32_t)q << ((field + 2 - 2 * e) & 31);
+        const int at = (field + 2 - 2 * e) & 31;
+        word[e] = (word[e] & ~(3u << at)) | ((uint32_t)q << at);
         se = se * 0.25;
       }
     }

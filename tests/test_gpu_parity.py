@@ -44,6 +44,33 @@ def test_encode_blob_is_bit_exact(mbq, N, K):
         np.testing.assert_allclose(What, ref, rtol=2e-7, atol=1e-12)
 
 
+@pytest.mark.parametrize("offset", [0.0, -128.0, 1000.0, -3.0])
+@pytest.mark.parametrize("ulps", [0, 1, -1])
+def test_encode_weights_on_code_boundaries(mbq, offset, ulps):
+    """Weights on the boundaries between two codes of some slice (every multiple of 1/64 of the first step), or one
+    float next to them, with small and large zero points: the blob is the recursion's, bit for bit."""
+    N, K = 18, 384
+    rng = np.random.default_rng([N, K, 5])
+    m = rng.integers(0, 257, size=(N, K // 128, 128))
+    m[..., 3], m[..., 77] = 0, 256  # both ends of the range in every group
+    step = np.exp2(rng.integers(-9, -5, size=(N, K // 128, 1)))
+    W = (offset + m / 64.0 * step).astype(np.float32)
+    if ulps:
+        moved = np.nextafter(W, np.float32(np.inf if ulps > 0 else -np.inf), dtype=np.float32)
+        W = np.where(rng.random(W.shape) < 0.5, moved, W)
+    W = W.reshape(N, K)
+    codes, s0, z0 = O.encode(W)
+    blob = mbq.mbq_encode(dev(W))
+    torch.cuda.synchronize()
+    assert np.array_equal(blob.cpu().numpy(), O.pack_blob(codes, s0, z0))
+    Wg = W.reshape(N, K // 128, 128)
+    s0 = ((Wg.max(axis=2) - Wg.min(axis=2)) / np.float32(8.0)).astype(np.float32)  # half the weights saturate
+    z0 = (-Wg.min(axis=2) / s0 - np.float32(1.0)).astype(np.float32)
+    codes, _, _ = O.encode(W, s0, z0)
+    blob = mbq.mbq_encode_with_params(dev(W), dev(s0), dev(z0))
+    assert np.array_equal(blob.cpu().numpy(), O.pack_blob(codes, s0, z0))
+
+
 @pytest.mark.parametrize("N,K,keep", [(3, 128, 0.7), (130, 1280, 0.6), (272, 4096, 0.9)])
 def test_encode_with_external_parameters(mbq, N, K, keep):
     """Calibrated (clipped) base-slice parameters handed in: blob bit-exact with the oracle's, weights outside the range
