@@ -167,47 +167,34 @@ static bool takes_stationary_kernel(int64_t T, const Shape& sh) {
   return knob(3) != 1 && (knob(3) == 2 || sh.KB <= 32 || sh.NT >= 128 || (T > 32 && sh.NT >= 32));
 }
 
-// Above the decode limit the register-stationary kernel still beats the prefill kernel for a while: it walks the
-// weights once per 32 sorted tokens, the prefill kernel unpacks them once per bucket into 256-row tiles that are
-// mostly empty at these token counts.  Measured, stationary / prefill in us per call:
-//   4096 x 4096: 31 / 36 at 65 tokens, 25 / 39 at 128, 49 / 43 at 192;  14336 x 4096: 80 / 98, 68 / 102, 116 / 111;
-//   4096 x 14336: 97 / 96, 82 / 106, 147 / 106;  28672 x 8192: 212 / 351, 237 / 370, 365 / 391;
-//   1024 x 4096: 12 / 29, 12 / 33, 16 / 34, and 25 / 52 at 512 tokens.
-// AUTO takes it up to 128 tokens, and up to 512 for matrices of at most 2048 code blocks of 16 x 256.
-constexpr int kMaxStationaryTokens = 128, kMaxStationaryTokensSmall = 512;
-constexpr int64_t kSmallMatrixBlocks = 2048;
-// From there to 256 tokens the better kernel depends on the precision mix (see mix_prefers_stationary): both are
-// launched and the device decides.
-constexpr int kMaxByMixTokens = 256;
+// Above the decode limit the register-stationary kernel still beats the prefill kernel on small matrices: it walks the
+// weights once per 32 sorted tokens without a pre-kernel and fills the chip with fewer columns.  Measured, stationary /
+// prefill in us per call (uniform mix):
+//   2048 x 2048: 15.6 / 19.8 at 80 tokens, 12.1 / 21.6 at 128, 16.8 / 29.5 at 256;  1024 x 4096: 12 / 20, 12 / 23, 17 / 31;
+//   4096 x 4096: 30 / 26, 25 / 31, 42 / 47, and 46 / 39 at 192;
+//   14336 x 4096: 79 / 49, 69 / 54, 129 / 82;  4096 x 14336: 96 / 46, 84 / 53, 135 / 77;
+//   28672 x 8192: 223 / 169, 252 / 189, 448 / 262;  8192 x 28672: 306 / 143, 264 / 150, 488 / 237.
+// AUTO takes it up to 512 tokens for matrices of at most 2048 code blocks of 16 x 256, up to 128 tokens for at most 8192
+// (4096 x 4096 has 4096, 14336 x 4096 14336).
+constexpr int64_t kMaxStationaryTokens = 128, kMaxStationaryTokensSmall = 512;
+constexpr int64_t kSmallMatrixBlocks = 2048, kMiddleMatrixBlocks = 8192;
 constexpr int kAlgoStationary = 100;  // internal: what AUTO resolves to in those ranges
-constexpr int kAlgoByMix = 101;
 static int resolve_auto(int64_t T, const Shape& sh) {
   if (T <= kMaxDecodeTokens) return MBQ_ALGO_DECODE;
-  const int limit = (int64_t)sh.NT * sh.KB <= kSmallMatrixBlocks ? kMaxStationaryTokensSmall : kMaxStationaryTokens;
-  const bool can = knob(3) == 0 && takes_stationary_kernel(T, sh);
-  if (T <= limit && can) return kAlgoStationary;
-  // (up to 32 column blocks: with more, the stationary kernel's per-chunk prologues cost it the advantage - 8192 x
-  // 28672 at 256 tokens on the skewed mix 0.49 ms against 0.48)
-  if (T <= kMaxByMixTokens && can && sh.KB <= 32) return kAlgoByMix;
-  return MBQ_ALGO_PREFILL;
+  const int64_t blocks = (int64_t)sh.NT * sh.KB;
+  const int64_t limit = blocks <= kSmallMatrixBlocks    ? kMaxStationaryTokensSmall
+                        : blocks <= kMiddleMatrixBlocks ? kMaxStationaryTokens
+                                                        : 0;
+  return (T <= limit && knob(3) == 0 && takes_stationary_kernel(T, sh)) ? kAlgoStationary : MBQ_ALGO_PREFILL;
 }
 
-// algo is DECODE (T <= 64), PREFILL, SIMPLE, kAlgoStationary or kAlgoByMix here
+// algo is DECODE (T <= 64), PREFILL, SIMPLE or kAlgoStationary here
 mbq_status dispatch_linear(const uint16_t* X, int64_t T, const void* blob, const Shape& sh, const int32_t* prec,
                            const int32_t* perm, const int32_t* offsets, float* Y, void* ws, int algo,
                            hipStream_t s) {
   switch (algo) {
     case MBQ_ALGO_SIMPLE:
       return launch_linear_simple(X, T, blob, sh, prec, Y, s);
-    case kAlgoByMix: {
-      ZeroList zl;
-      decode16_zero_list(T, 1, &sh, &Y, &zl);
-      mbq_status st = launch_zero_outputs(zl, s);
-      if (st != MBQ_OK) return st;
-      st = launch_linear_decode16_group(X, T, 1, &blob, &sh, &prec, &perm, &Y, s, nullptr, nullptr, &offsets);
-      if (st != MBQ_OK) return st;
-      return launch_linear_prefill(X, T, blob, sh, perm, offsets, Y, ws, s, true);
-    }
     case kAlgoStationary: {
       ZeroList zl;
       decode16_zero_list(T, 1, &sh, &Y, &zl);
@@ -717,7 +704,27 @@ mbq_status mbq_linear_group(const uint16_t* X, int64_t T, int64_t K, int n_proj,
                                           nullptr);
     }
   }
+  // the matrices that take the prefill kernel share a launch; the others follow one by one
+  const void* pf_blob[MBQ_MAX_GROUP];
+  Shape pf_shape[MBQ_MAX_GROUP];
+  const int32_t* pf_perm[MBQ_MAX_GROUP];
+  const int32_t* pf_offsets[MBQ_MAX_GROUP];
+  float* pf_Y[MBQ_MAX_GROUP];
+  int n_pf = 0;
+  for (int i = 0; i < n_proj; ++i)
+    if (algo_of[i] == MBQ_ALGO_PREFILL) {
+      pf_blob[n_pf] = blob_host[i];
+      pf_shape[n_pf] = sh[i];
+      pf_perm[n_pf] = perm_host[i];
+      pf_offsets[n_pf] = offsets_host[i];
+      pf_Y[n_pf++] = Y_host[i];
+    }
+  if (n_pf > 0) {
+    mbq_status st = launch_linear_prefill_group(X, T, n_pf, pf_blob, pf_shape, pf_perm, pf_offsets, pf_Y, ws, s);
+    if (st != MBQ_OK) return st;
+  }
   for (int i = 0; i < n_proj; ++i) {
+    if (algo_of[i] == MBQ_ALGO_PREFILL) continue;
     mbq_status st =
         dispatch_linear(X, T, blob_host[i], sh[i], prec_host[i], perm_host[i], offsets_host[i], Y_host[i], ws, algo_of[i], s);
     if (st != MBQ_OK) return st;

@@ -370,6 +370,52 @@ def test_prefill_tile_shapes(mbq, N, K, T, mix):
     assert_output_close(Y, Yref, f"prefill N={N} K={K} T={T}")
 
 
+@pytest.mark.parametrize("counts", [(1, 16, 17, 32), (33, 64, 65, 96), (97, 128, 129, 1), (0, 0, 200, 257), (127, 0, 191, 63)])
+@pytest.mark.parametrize("Ns,K", [((257,), 128), ((16, 300), 2048), ((1, 255, 64), 4352)])
+def test_prefill_remainders_and_groups(mbq, counts, Ns, K):
+    """Buckets that end at the edges of the 16-, 32-, 64-, 96- and 128-row tiles, K of one group, of exactly one pass of
+    the zero-point update and of two passes and a rest, several matrices with orders of their own in one launch."""
+    T = sum(counts)
+    xb = tokens(T, K, [T, K, 71])
+    X = dev_bf16(xb).reshape(T, K)
+    blobs, routing, refs = [], [], []
+    for i, N in enumerate(Ns):
+        W = make_weight(N, K, [71, N, K, i], 4.0)
+        codes, s0, z0 = O.encode(W)
+        prec = np.repeat(np.arange(4), np.roll(counts, i)).astype(np.int32)
+        np.random.default_rng([71, T, i]).shuffle(prec)
+        perm, offsets = O.bucket(prec)
+        blobs.append(mbq.mbq_encode(dev(W)))
+        routing.append((dev(prec), dev(perm), dev(offsets)))
+        refs.append(O.linear(xb, codes, s0, z0, prec))
+    Ys = mbq.mbq_linear_group(X, blobs, list(Ns), K, routing, algo=ALGOS["prefill"])
+    torch.cuda.synchronize()
+    for i in range(len(Ns)):
+        assert_output_close(Ys[i].cpu().numpy(), refs[i], f"prefill group matrix {i}")
+
+
+def test_prefill_above_four_gibibytes_of_activations(mbq):
+    """Row offsets of the tile kernel are 32-bit; from 4 GiB of activations on it reads a sorted copy instead."""
+    T, K, N = 131200, 16384, 40
+    assert T * K * 2 > 2 ** 32
+    W = make_weight(N, K, [73, N], 4.0)
+    blob = mbq.mbq_encode(dev(W))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(73)
+    X = torch.empty((T, K), dtype=torch.bfloat16, device="cuda")
+    for t in range(0, T, 8200):
+        X[t:t + 8200] = torch.randn((8200, K), generator=gen, device="cuda").to(torch.bfloat16)
+    prec = torch.randint(0, 4, (T,), generator=gen, device="cuda", dtype=torch.int32)
+    perm = torch.sort(prec.long(), stable=True)[1].int()
+    offsets = torch.stack([(prec < q).sum() for q in range(5)]).int()
+    Y = mbq.mbq_linear(X, blob, N, K, prec, perm, offsets, algo=ALGOS["prefill"])
+    pick = torch.cat([torch.arange(0, 40), torch.arange(60000, 60040), torch.arange(T - 40, T)]).cuda()
+    for p in range(4):
+        rows = pick[prec[pick] == p]
+        ref = X[rows].double() @ mbq.mbq_dequant(blob, N, K, p).double().T
+        assert_output_close(Y[rows].cpu().numpy(), ref.cpu().numpy(), f"precision {p}")
+
+
 @pytest.mark.parametrize("splits", [2, 3, 4, 7])
 def test_prefill_k_split(mbq, splits):
     """The K range of a tile cut into workgroups that add their partial sums into a zeroed Y."""
