@@ -105,17 +105,124 @@ __device__ __forceinline__ double wave_sum4(const double (&acc)[4], int lane) {
   return v;
 }
 
-// One workgroup of 256 threads scores TPW consecutive tokens (Sec. 4.2 Eq. 4).  The K axis
-// is split over the threads in chunks of 8 columns; each thread keeps 4 x TPW fp64 partial
-// sums (bf16 x fp32 products are exact in fp64), reduced over the wavefront (wave_sum4) and
-// over the four wavefronts through LDS.  The workgroup that finishes last (a ticket counter in
-// the workspace, cleared ahead of the launch) then buckets all tokens.
+constexpr int kRouteGroupMax = MBQ_MAX_GROUP;
+
+struct RouteOut {
+  const float* Wr;
+  const float* br;
+  int32_t* prec;
+  int32_t* perm;
+  int32_t* offsets;
+  double* logits;
+};
+struct RouteGroup {
+  RouteOut r[kRouteGroupMax];
+  RouteView view;
+};
+
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+// The product of 16 token rows with 16 weight rows in fp64 on the matrix cores, by NW wavefronts that take the K axis in
+// blocks of 32 columns in turn.  One v_mfma_f64_16x16x4 takes A[token i][k] from lane i + 16 k and B[k][unit j] from lane
+// j + 16 k, so a lane reads 8 consecutive columns of its token's row and of its unit's row (16-byte loads) and feeds them
+// to 8 MFMAs, column c of every lane quarter forming the K = 4 of MFMA c (bf16 x fp32 products are exact in fp64).
+// The result lane l, register r is D[token 4 r + l / 16][unit l % 16].
+// A wavefront's chain is load, eight MFMAs, load: what bounds small launches is the number of trips to memory one after
+// the other, so sixteen wavefronts share a tile and two blocks are requested at a time.
+template <int NW>
+__device__ __forceinline__ f64x4 tile_product(const uint16_t* __restrict__ xrow, const float* __restrict__ wrow, int64_t K,
+                                              int wave, int lane) {
+  f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+  auto feed = [&](const uint4& xv, const float4& wa, const float4& wb) {
+    const double x[8] = {bf16_lo(xv.x), bf16_hi(xv.x), bf16_lo(xv.y), bf16_hi(xv.y),
+                         bf16_lo(xv.z), bf16_hi(xv.z), bf16_lo(xv.w), bf16_hi(xv.w)};
+    const double w[8] = {wa.x, wa.y, wa.z, wa.w, wb.x, wb.y, wb.z, wb.w};
+#pragma unroll
+    for (int c = 0; c < 8; ++c) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x[c], w[c], acc, 0, 0, 0);
+  };
+  constexpr int kStep = NW * 32;
+  int64_t k0 = (int64_t)wave * 32;  // (K is a multiple of 128: a block of 32 is there or not, for all lanes alike)
+  const int at = (lane >> 4) * 8;
+#pragma unroll 1
+  for (; k0 + kStep < K; k0 += 2 * kStep) {
+    const int64_t k = k0 + at;
+    const uint4 xa = *reinterpret_cast<const uint4*>(xrow + k), xb = *reinterpret_cast<const uint4*>(xrow + k + kStep);
+    const float4 wa0 = *reinterpret_cast<const float4*>(wrow + k), wa1 = *reinterpret_cast<const float4*>(wrow + k + 4);
+    const float4 wb0 = *reinterpret_cast<const float4*>(wrow + k + kStep);
+    const float4 wb1 = *reinterpret_cast<const float4*>(wrow + k + kStep + 4);
+    feed(xa, wa0, wa1);
+    feed(xb, wb0, wb1);
+  }
+  if (k0 < K) {
+    const int64_t k = k0 + at;
+    feed(*reinterpret_cast<const uint4*>(xrow + k), *reinterpret_cast<const float4*>(wrow + k),
+         *reinterpret_cast<const float4*>(wrow + k + 4));
+  }
+  return acc;
+}
+constexpr int kTileWaves = 16;
+
+// General router, many tokens: one workgroup scores 16 tokens for ALL routers of the call (up to four of up to four outputs
+// each are the 16 weight rows of a tile), so the tokens are read once per stage.  Its time is that of one tile's fp64
+// MFMAs, about 3.1 ns x K, while a compute unit has at most one tile (T <= 4096): taken above 1024 tokens.  7B-shaped
+// stages at 2048 tokens 26 us on average, where a launch of vector code per router took 31; 70B-shaped ones at 4096 tokens
+// 59 us instead of 132 a stage; at 256 tokens it would be 52 instead of 23.
+__global__ __launch_bounds__(64 * kTileWaves) void route_kernel(const uint16_t* __restrict__ X, int64_t T, int64_t K,
+                                                                const RouteGroup group, int n) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t tok0 = (int64_t)blockIdx.x * 16;
+  const int P = group.view.P;
+  __shared__ double s_part[kTileWaves][64][4];
+  __shared__ double s_logit[16][16];
+  {
+    const int unit = lane & 15;
+    const int64_t tok = (tok0 + unit < T) ? tok0 + unit : T - 1;  // valid rows either way; surplus results are dropped
+    const int j = (unit >> 2) < n ? unit >> 2 : 0;
+    const float* Wr = j == 0 ? group.r[0].Wr : j == 1 ? group.r[1].Wr : j == 2 ? group.r[2].Wr : group.r[3].Wr;
+    const f64x4 acc = tile_product<kTileWaves>(X + tok * K, Wr + (int64_t)min(unit & 3, P - 1) * K, K, wave, lane);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) s_part[wave][lane][r] = acc[r];
+  }
+  __syncthreads();
+  if (tid < 256) {
+    const int l = tid >> 2, r = tid & 3;  // one result of the 16 x 16 tile per thread
+    double v = 0.0;
+#pragma unroll
+    for (int w = 0; w < kTileWaves; ++w) v += s_part[w][l][r];
+    s_logit[4 * r + (l >> 4)][l & 15] = v;
+  }
+  __syncthreads();
+  if (tid < 64) {
+    const int64_t tok = tok0 + (tid & 15);
+    const int j = tid >> 4;
+    if (j < n && tok < T) {
+      const RouteOut& out = group.r[j];
+      double best = 0.0;
+      int arg = 0;
+#pragma unroll
+      for (int q = 0; q < kP; ++q) {
+        if (q < P) {
+          const double s = s_logit[tid & 15][4 * j + q] + (double)out.br[q];
+          if (out.logits) out.logits[tok * P + q] = s;
+          if (q == 0 || s > best) {  // strict: the first maximum wins ties
+            best = s;
+            arg = q;
+          }
+        }
+      }
+      out.prec[tok] = group.view.value[arg];
+    }
+  }
+}
+
+// General router, fewer tokens: a workgroup of 256 threads scores TPW consecutive tokens for router blockIdx.y.  The K axis
+// is split over the threads in chunks of 8 columns; each thread keeps 4 x TPW fp64 partial sums (bf16 x fp32 products are
+// exact in fp64), reduced over the wavefront (wave_sum4) and over the four wavefronts through LDS.
 template <int TPW>
-__global__ __launch_bounds__(256) void route_kernel(const uint16_t* __restrict__ X, int64_t T, int64_t K,
-                                                    const float* __restrict__ Wr, const float* __restrict__ br,
-                                                    int32_t* prec, int32_t* __restrict__ perm,
-                                                    int32_t* __restrict__ offsets, double* __restrict__ logits,
-                                                    unsigned int* __restrict__ ticket, const RouteView view) {
+__global__ __launch_bounds__(256) void route_rows_kernel(const uint16_t* __restrict__ X, int64_t T, int64_t K,
+                                                         const RouteGroup group) {
+  const RouteOut& out = group.r[blockIdx.y];
+  const int P = group.view.P;
   const int64_t tok0 = (int64_t)blockIdx.x * TPW;
   const int tid = threadIdx.x;
   double acc[TPW][kP];
@@ -128,7 +235,7 @@ __global__ __launch_bounds__(256) void route_kernel(const uint16_t* __restrict__
     float w[kP][8];
 #pragma unroll
     for (int q = 0; q < kP; ++q) {
-      const float4* src = reinterpret_cast<const float4*>(Wr + (int64_t)min(q, view.P - 1) * K + k);  // rows past P: unused
+      const float4* src = reinterpret_cast<const float4*>(out.Wr + (int64_t)min(q, P - 1) * K + k);  // rows past P: unused
       float4 a = src[0], b = src[1];
       w[q][0] = a.x; w[q][1] = a.y; w[q][2] = a.z; w[q][3] = a.w;
       w[q][4] = b.x; w[q][5] = b.y; w[q][6] = b.z; w[q][7] = b.w;
@@ -147,7 +254,6 @@ __global__ __launch_bounds__(256) void route_kernel(const uint16_t* __restrict__
     }
   }
   __shared__ double red[4][TPW][kP];
-  __shared__ unsigned int s_ticket;
   const int lane = tid & 63, wave = tid >> 6;
 #pragma unroll
   for (int t = 0; t < TPW; ++t) {
@@ -160,26 +266,28 @@ __global__ __launch_bounds__(256) void route_kernel(const uint16_t* __restrict__
     int arg = 0;
 #pragma unroll
     for (int q = 0; q < kP; ++q) {
-      if (q < view.P) {
-        const double s = ((red[0][tid][q] + red[1][tid][q]) + (red[2][tid][q] + red[3][tid][q])) + (double)br[q];
-        if (logits) logits[(tok0 + tid) * view.P + q] = s;
+      if (q < P) {
+        const double s = ((red[0][tid][q] + red[1][tid][q]) + (red[2][tid][q] + red[3][tid][q])) + (double)out.br[q];
+        if (out.logits) out.logits[(tok0 + tid) * P + q] = s;
         if (q == 0 || s > best) {  // strict: the first maximum wins ties
           best = s;
           arg = q;
         }
       }
     }
-    prec[tok0 + tid] = view.value[arg];
-    __threadfence();  // publish this workgroup's choices before taking a ticket
+    out.prec[tok0 + tid] = group.view.value[arg];
   }
-  __syncthreads();
-  if (tid == 0) s_ticket = atomicAdd(ticket, 1u);
-  __syncthreads();
-  if (s_ticket != gridDim.x - 1) return;
-  // last workgroup: every token's precision is visible now
-  __threadfence();
-  bucket_by_workgroup<4>(prec, T, perm, offsets, view.shift);
-  if (tid == 0) *ticket = 0u;  // leave the counter ready for the next call
+}
+
+// The stable counting sort behind a launch that wrote precisions: one workgroup per router.
+struct SortGroup {
+  const int32_t* prec[kRouteGroupMax];
+  int32_t* perm[kRouteGroupMax];
+  int32_t* offsets[kRouteGroupMax];
+};
+__global__ __launch_bounds__(1024) void sort_kernel(const SortGroup g, int64_t T, int shift) {
+  const int j = blockIdx.x;
+  bucket_by_workgroup<16>(g.prec[j], T, g.perm[j], g.offsets[j], shift);
 }
 
 // Small batches (T <= 128; the packed meeting word below up to kSmallRouteTokens), one or several routers over the same activations
@@ -190,21 +298,6 @@ __global__ __launch_bounds__(256) void route_kernel(const uint16_t* __restrict__
 // arrives last holds every token's precision in the returned value and buckets them with
 // wavefront ballots, without fences or a second pass over memory.  The word is cleared ahead of the launch.
 constexpr int kSmallRouteTokens = 28;
-constexpr int kRouteGroupMax = MBQ_MAX_GROUP;
-
-struct RouteOut {
-  const float* Wr;
-  const float* br;
-  int32_t* prec;
-  int32_t* perm;
-  int32_t* offsets;
-  double* logits;
-};
-struct RouteGroup {
-  RouteOut r[kRouteGroupMax];
-  RouteView view;
-};
-
 //
 // The launch can carry the activation preparation of the FP4-operand decode kernel along: plane
 // blockIdx.y == n_routers of the grid prepares 256-column block blockIdx.x with its first
@@ -359,31 +452,19 @@ static mbq_status clear_counters(void* ws, hipStream_t stream) {
   return hip_status(hipGetLastError(), "clear_counters_kernel launch");
 }
 
-// T = 0: only the (all-zero) offsets have to be written.
-__global__ __launch_bounds__(64) void bucket_kernel(const int32_t* __restrict__ prec, int64_t T,
-                                                    int32_t* __restrict__ perm, int32_t* __restrict__ offsets) {
-  bucket_by_workgroup<1>(prec, T, perm, offsets);
+static mbq_status launch_sort(int n, const int32_t* const* prec, int32_t* const* perm, int32_t* const* offsets, int64_t T,
+                              int shift, hipStream_t stream) {
+  SortGroup g;
+  for (int i = 0; i < kRouteGroupMax; ++i) {
+    g.prec[i] = prec[i < n ? i : 0];
+    g.perm[i] = perm[i < n ? i : 0];
+    g.offsets[i] = offsets[i < n ? i : 0];
+  }
+  hipLaunchKernelGGL(sort_kernel, dim3((unsigned)n), dim3(1024), 0, stream, g, T, shift);
+  return hip_status(hipGetLastError(), "sort_kernel launch");
 }
 
-static mbq_status launch_route_one(const uint16_t* X, int64_t T, int64_t K, const float* Wr, const float* br,
-                                   int32_t* prec, int32_t* perm, int32_t* offsets, double* logits,
-                                   unsigned int* ticket, hipStream_t stream, const RouteView& view) {
-  if (T == 0) {
-    hipLaunchKernelGGL(bucket_kernel, dim3(1), dim3(64), 0, stream, prec, T, perm, offsets);
-    return hip_status(hipGetLastError(), "bucket_kernel launch");
-  }
-  if (T <= 256) {
-    hipLaunchKernelGGL(route_kernel<1>, dim3((unsigned)T), dim3(256), 0, stream, X, T, K, Wr, br, prec, perm,
-                       offsets, logits, ticket, view);
-  } else {
-    hipLaunchKernelGGL(route_kernel<4>, dim3((unsigned)((T + 3) / 4)), dim3(256), 0, stream, X, T, K, Wr, br,
-                       prec, perm, offsets, logits, ticket, view);
-  }
-  return hip_status(hipGetLastError(), "route_kernel launch");
-}
-
-// Workspace: the ticket counter of the general kernels at byte 0, the per-router words of the
-// small-batch kernel from byte 64.
+// Workspace: the per-router words of the small-batch kernel from byte 64.
 bool route_can_carry_prep(int64_t T) { return T >= 1 && T <= kSmallRouteTokens && knob(4) != 1; }
 // one launch for all routers of a call: up to two tokens per lane of the sorting wavefront
 static bool route_small_supports(int64_t T) { return T >= 1 && T <= 128 && knob(4) != 1; }
@@ -398,19 +479,19 @@ mbq_status launch_route_group(const uint16_t* X, int64_t T, int64_t K, int n, co
                               int32_t* const* offsets, double* const* logits, void* ws, hipStream_t stream,
                               void* prep, int prep_blocks, const ZeroList* zl, bool defer_bucket,
                               const RouteView& view, const uint16_t* Xprep) {
-  unsigned int* ticket = reinterpret_cast<unsigned int*>(ws);
-  if (T > 0 && !(defer_bucket && route_small_supports(T))) {  // a launch that sorts meets through the counters
-    mbq_status st = clear_counters(ws, stream);
-    if (st != MBQ_OK) return st;
+  if (T == 0) return launch_sort(n, prec, perm, offsets, 0, 0, stream);  // the (all-zero) offsets
+  RouteGroup g;
+  g.view = view;
+  for (int i = 0; i < kRouteGroupMax; ++i) {
+    const int j = i < n ? i : 0;
+    g.r[i] = RouteOut{Wr[j], br[j], prec[j], perm[j], offsets[j], logits ? logits[j] : nullptr};
   }
   if (route_small_supports(T)) {
-    if (!route_can_carry_prep(T)) prep = nullptr;
-    RouteGroup g;
-    g.view = view;
-    for (int i = 0; i < kRouteGroupMax; ++i) {
-      const int j = i < n ? i : 0;
-      g.r[i] = RouteOut{Wr[j], br[j], prec[j], perm[j], offsets[j], logits ? logits[j] : nullptr};
+    if (!defer_bucket) {  // a launch that sorts meets through the counters
+      mbq_status st = clear_counters(ws, stream);
+      if (st != MBQ_OK) return st;
     }
+    if (!route_can_carry_prep(T)) prep = nullptr;
     unsigned long long* words = reinterpret_cast<unsigned long long*>(reinterpret_cast<char*>(ws) + 64);
     bool clears = false;  // outputs to clear also without a preparation: the extra plane then only clears
     if (zl)
@@ -422,12 +503,15 @@ mbq_status launch_route_group(const uint16_t* X, int64_t T, int64_t K, int n, co
                        (plane && zl) ? *zl : ZeroList{}, defer_bucket ? 1 : 0, Xprep ? Xprep : X);
     return hip_status(hipGetLastError(), "route_small_kernel launch");
   }
-  for (int i = 0; i < n; ++i) {
-    mbq_status st = launch_route_one(X, T, K, Wr[i], br[i], prec[i], perm[i], offsets[i],
-                                     logits ? logits[i] : nullptr, ticket, stream, view);
-    if (st != MBQ_OK) return st;
-  }
-  return MBQ_OK;
+  if (T <= 256)
+    hipLaunchKernelGGL(route_rows_kernel<1>, dim3((unsigned)T, (unsigned)n), dim3(256), 0, stream, X, T, K, g);
+  else if (T <= 1024)
+    hipLaunchKernelGGL(route_rows_kernel<4>, dim3((unsigned)((T + 3) / 4), (unsigned)n), dim3(256), 0, stream, X, T, K, g);
+  else
+    hipLaunchKernelGGL(route_kernel, dim3((unsigned)((T + 15) / 16)), dim3(64 * kTileWaves), 0, stream, X, T, K, g, n);
+  mbq_status st = hip_status(hipGetLastError(), "route_kernel launch");
+  if (st != MBQ_OK) return st;
+  return launch_sort(n, prec, perm, offsets, T, view.shift, stream);
 }
 
 mbq_status launch_route(const uint16_t* X, int64_t T, int64_t K, const float* Wr, const float* br,
@@ -445,13 +529,12 @@ mbq_status launch_route(const uint16_t* X, int64_t T, int64_t K, const float* Wr
 // slice is always active (shared-expert slice); a token's precision is the number of leading
 // active residual slices, so that it names a prefix of slices like every other path here.
 //
-// Two launches.  Hidden layer: a workgroup of 256 threads produces eight hidden units of TPW consecutive
+// Three launches.  Hidden layer: a workgroup of 256 threads produces eight hidden units of TPW consecutive
 // tokens (grid = token groups x hidden chunks, so small batches still fill the chip): the K axis is
 // split over the threads in chunks of 8 columns (bf16 x fp32 products are exact in fp64, accumulation
 // in fp64), partial sums meet through wavefront shuffles and LDS, bias and ReLU are applied and the
 // hidden vector goes to the workspace.  Scores: one thread per (token, slice) forms the score in a
-// fixed order, one thread per token decides, and the workgroup that finishes last buckets all tokens
-// (same ticket scheme as route_kernel).
+// fixed order, one thread per token decides; sort_kernel buckets the tokens.
 constexpr int kMlpHiddenChunk = 8;
 constexpr int kMlpMaxHidden = 512;
 
@@ -511,46 +594,31 @@ __global__ __launch_bounds__(256) void route_mlp_hidden_kernel(const uint16_t* _
   }
 }
 
-// Hidden layer of larger batches on the fp64 matrix cores.  A workgroup of four wavefronts owns a tile
-// of 16 tokens x 16 hidden units; the K axis is dealt to the wavefronts in blocks of 32 columns.  One
-// v_mfma_f64_16x16x4 takes A[token i][k] from lane i + 16 k and B[k][unit j] from lane j + 16 k, so a
-// lane reads 8 consecutive columns of its token row and of its unit's weight row (16-byte loads) and
-// feeds them to 8 MFMAs, column c of every lane quarter forming the K = 4 of MFMA c.  The result lane
-// l, register r is D[token 4 r + l / 16][unit l % 16]; the four partial tiles meet in LDS.
-typedef double f64x4 __attribute__((ext_vector_type(4)));
-
-__global__ __launch_bounds__(256) void route_mlp_hidden_mfma_kernel(const uint16_t* __restrict__ X, int64_t T,
-                                                                    int64_t K, const float* __restrict__ W1,
-                                                                    const float* __restrict__ b1, int H,
-                                                                    double* __restrict__ hidden) {
+// Hidden layer of larger batches on the fp64 matrix cores (tile_product): a workgroup owns a tile of 16 tokens x 16 hidden
+// units.
+__global__ __launch_bounds__(64 * kTileWaves) void route_mlp_hidden_mfma_kernel(const uint16_t* __restrict__ X, int64_t T,
+                                                                               int64_t K, const float* __restrict__ W1,
+                                                                               const float* __restrict__ b1, int H,
+                                                                               double* __restrict__ hidden) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t tok0 = (int64_t)blockIdx.x * 16;
   const int h0 = (int)blockIdx.y * 16;
   const int64_t tok = (tok0 + (lane & 15) < T) ? tok0 + (lane & 15) : T - 1;  // valid rows either way;
   const int h = (h0 + (lane & 15) < H) ? h0 + (lane & 15) : H - 1;            // surplus results are dropped
-  const uint16_t* xrow = X + tok * K;
-  const float* wrow = W1 + (int64_t)h * K;
-  f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-  for (int64_t k = (int64_t)wave * 32 + (lane >> 4) * 8; k < K; k += 4 * 32) {
-    const uint4 xv = *reinterpret_cast<const uint4*>(xrow + k);
-    const float4 wa = *reinterpret_cast<const float4*>(wrow + k);
-    const float4 wb = *reinterpret_cast<const float4*>(wrow + k + 4);
-    const double x[8] = {bf16_lo(xv.x), bf16_hi(xv.x), bf16_lo(xv.y), bf16_hi(xv.y),
-                         bf16_lo(xv.z), bf16_hi(xv.z), bf16_lo(xv.w), bf16_hi(xv.w)};
-    const double w[8] = {wa.x, wa.y, wa.z, wa.w, wb.x, wb.y, wb.z, wb.w};
-#pragma unroll
-    for (int c = 0; c < 8; ++c) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x[c], w[c], acc, 0, 0, 0);
-  }
-  __shared__ double s_part[4][64][4];
+  const f64x4 acc = tile_product<kTileWaves>(X + tok * K, W1 + (int64_t)h * K, K, wave, lane);
+  __shared__ double s_part[kTileWaves][64][4];
 #pragma unroll
   for (int r = 0; r < 4; ++r) s_part[wave][lane][r] = acc[r];
   __syncthreads();
-  {
+  if (tid < 256) {
     const int l = tid >> 2, r = tid & 3;  // one result of the 16 x 16 tile per thread
     const int64_t t = tok0 + 4 * r + (l >> 4);
     const int hu = h0 + (l & 15);
     if (t < T && hu < H) {
-      const double pre = ((s_part[0][l][r] + s_part[1][l][r]) + (s_part[2][l][r] + s_part[3][l][r])) + (double)b1[hu];
+      double pre = 0.0;
+#pragma unroll
+      for (int w = 0; w < kTileWaves; ++w) pre += s_part[w][l][r];
+      pre += (double)b1[hu];
       hidden[t * H + hu] = pre > 0.0 ? pre : 0.0;
     }
   }
@@ -560,19 +628,31 @@ __global__ __launch_bounds__(256) void route_mlp_hidden_mfma_kernel(const uint16
 __global__ __launch_bounds__(256) void route_mlp_score_kernel(const double* __restrict__ hidden, int64_t T, int H,
                                                               const float* __restrict__ W2,
                                                               const float* __restrict__ b2, double delta,
-                                                              int32_t* prec, int32_t* __restrict__ perm,
-                                                              int32_t* __restrict__ offsets,
-                                                              double* __restrict__ scores,
-                                                              unsigned int* __restrict__ ticket) {
+                                                              int32_t* __restrict__ prec,
+                                                              double* __restrict__ scores) {
   const int tid = threadIdx.x;
   const int64_t tok = (int64_t)blockIdx.x * 64 + (tid >> 2);
   const int e = tid & 3;
   __shared__ double s_score[64][kP];
-  __shared__ unsigned int s_ticket;
   if (tok < T) {
     const double* hrow = hidden + tok * H;
+    const float* wrow = W2 + (int64_t)e * H;
     double s = 0.0;
-    for (int j = 0; j < H; ++j) s = fma(hrow[j], (double)W2[(int64_t)e * H + j], s);
+    // (sixteen units' loads at a time: one after the other they took 12 us at H = 64)
+    int j = 0;
+#pragma unroll 1
+    for (; j + 16 <= H; j += 16) {
+      double hv[16];
+      float wv[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        hv[i] = hrow[j + i];
+        wv[i] = wrow[j + i];
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s = fma(hv[i], (double)wv[i], s);
+    }
+    for (; j < H; ++j) s = fma(hrow[j], (double)wrow[j], s);
     s += (double)b2[e];
     s_score[tid >> 2][e] = s;
     if (scores) scores[tok * kP + e] = s;
@@ -585,43 +665,31 @@ __global__ __launch_bounds__(256) void route_mlp_score_kernel(const double* __re
       if (p == q - 1 && (s_score[tid][q] - delta) > 0.0) p = q;  // strict: a score on the threshold is inactive
     }
     prec[(int64_t)blockIdx.x * 64 + tid] = p;
-    __threadfence();  // publish this workgroup's choices before taking a ticket
   }
-  __syncthreads();
-  if (tid == 0) s_ticket = atomicAdd(ticket, 1u);
-  __syncthreads();
-  if (s_ticket != gridDim.x - 1) return;
-  __threadfence();
-  bucket_by_workgroup<4>(prec, T, perm, offsets);
-  if (tid == 0) *ticket = 0u;
 }
 
-// ws: the ticket counter in the first 256 bytes, then the hidden layer, fp64 [T][H]
+// ws: 256 spare bytes, then the hidden layer, fp64 [T][H]
 size_t route_mlp_workspace_bytes(int64_t T, int H) { return 256 + (size_t)T * (size_t)H * sizeof(double); }
 
 mbq_status launch_route_mlp(const uint16_t* X, int64_t T, int64_t K, const float* W1, const float* b1, int H,
                             const float* W2, const float* b2, double delta, int32_t* prec, int32_t* perm,
                             int32_t* offsets, double* scores, void* ws, hipStream_t stream) {
-  unsigned int* ticket = reinterpret_cast<unsigned int*>(ws);
   double* hidden = reinterpret_cast<double*>(reinterpret_cast<char*>(ws) + 256);
-  if (T == 0) {
-    hipLaunchKernelGGL(bucket_kernel, dim3(1), dim3(64), 0, stream, prec, T, perm, offsets);
-    return hip_status(hipGetLastError(), "bucket_kernel launch");
-  }
-  mbq_status st = clear_counters(ws, stream);
-  if (st != MBQ_OK) return st;
+  if (T == 0) return launch_sort(1, &prec, &perm, &offsets, 0, 0, stream);  // the (all-zero) offsets
   const unsigned chunks = (unsigned)((H + kMlpHiddenChunk - 1) / kMlpHiddenChunk);
   if (T <= 256)
     hipLaunchKernelGGL(route_mlp_hidden_kernel<1>, dim3((unsigned)T, chunks), dim3(256), 0, stream, X, T, K, W1, b1,
                        H, hidden);
   else
     hipLaunchKernelGGL(route_mlp_hidden_mfma_kernel, dim3((unsigned)((T + 15) / 16), (unsigned)((H + 15) / 16)),
-                       dim3(256), 0, stream, X, T, K, W1, b1, H, hidden);
-  st = hip_status(hipGetLastError(), "route_mlp_hidden_kernel launch");
+                       dim3(64 * kTileWaves), 0, stream, X, T, K, W1, b1, H, hidden);
+  mbq_status st = hip_status(hipGetLastError(), "route_mlp_hidden_kernel launch");
   if (st != MBQ_OK) return st;
   hipLaunchKernelGGL(route_mlp_score_kernel, dim3((unsigned)((T + 63) / 64)), dim3(256), 0, stream, hidden, T, H, W2,
-                     b2, delta, prec, perm, offsets, scores, ticket);
-  return hip_status(hipGetLastError(), "route_mlp_score_kernel launch");
+                     b2, delta, prec, scores);
+  st = hip_status(hipGetLastError(), "route_mlp_score_kernel launch");
+  if (st != MBQ_OK) return st;
+  return launch_sort(1, &prec, &perm, &offsets, T, 0, stream);
 }
 int route_mlp_max_hidden() { return kMlpMaxHidden; }
 

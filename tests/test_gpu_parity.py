@@ -416,6 +416,23 @@ def test_prefill_above_four_gibibytes_of_activations(mbq):
         assert_output_close(Y[rows].cpu().numpy(), ref.cpu().numpy(), f"precision {p}")
 
 
+@pytest.mark.parametrize("T,K,n", [(129, 128, 1), (257, 640, 3), (1024, 384, 2), (1025, 128, 4), (1041, 4224, 1), (2064, 640, 3)])
+def test_route_group_above_128_tokens(mbq, T, K, n):
+    """The general routers on both sides of their token limits, odd token counts, one 128-column block (most wavefronts
+    of a tile without work) and odd numbers of blocks: precisions, order and offsets of every router of the call."""
+    xb = tokens(T, K, [T, K, 79])
+    rng = np.random.default_rng([T, K, 79])
+    Wr = [(rng.standard_normal((4, K)) / np.sqrt(K)).astype(np.float32) for _ in range(n)]
+    br = [rng.standard_normal(4).astype(np.float32) * 0.3 for _ in range(n)]
+    got = mbq.mbq_route_group(dev_bf16(xb).reshape(T, K), [dev(w) for w in Wr], [dev(b) for b in br])
+    torch.cuda.synchronize()
+    for i in range(n):
+        _, prec_ref, gap = O.route(xb, Wr[i], br[i])
+        prec = got[i][0].cpu().numpy()
+        compare_routing(prec, prec_ref, gap, f"router {i}")
+        check_bucket(prec, got[i][1].cpu().numpy(), got[i][2].cpu().numpy())
+
+
 @pytest.mark.parametrize("splits", [2, 3, 4, 7])
 def test_prefill_k_split(mbq, splits):
     """The K range of a tile cut into workgroups that add their partial sums into a zeroed Y."""
