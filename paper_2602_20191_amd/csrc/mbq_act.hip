@@ -4,17 +4,9 @@
 //
 // This translation unit is compiled with -ffp-contract=off: every step of the quantiser is one fp32 operation
 // (the codes must not depend on how the compiler fuses them).
-#include "mbq_common.h"
+#include "mbq_act_quant.h"
 
 namespace mbq {
-
-__device__ __forceinline__ float bf16_value(uint32_t bits16) { return __uint_as_float(bits16 << 16); }
-// round to nearest even; finite inputs
-__device__ __forceinline__ uint32_t bf16_bits(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return u >> 16;
-}
 
 // One workgroup per token.  Pass 1 finds the row's extremes (zero included), pass 2 writes the codes.  kHold > 0: the
 // row fits in kHold chunks of eight values per thread and the transformed values of pass 1 stay in registers;
@@ -26,119 +18,45 @@ __global__ __launch_bounds__(kThreads) void act_quant_kernel(const uint16_t* __r
                                                         const float* __restrict__ let_scale,
                                                         uint16_t* __restrict__ Xint, float* __restrict__ row_scale,
                                                         uint16_t* __restrict__ Xr) {
-#pragma clang fp contract(off)
   const int64_t row = blockIdx.x;
   const int tid = threadIdx.x;
   const uint4* x8 = reinterpret_cast<const uint4*>(X + row * K);  // eight bf16 values per load
   const int n8 = (int)(K >> 3);
-  const bool let = let_scale != nullptr;
-
-  auto transformed = [&](int j, float t[8]) {
-    const uint4 v = x8[j];
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+  float lo = 0.f, hi = 0.f;
+  auto widen = [&](const float t[8]) {
 #pragma unroll
-    for (int h = 0; h < 4; ++h) {
-      t[2 * h] = bf16_value(w[h] & 0xFFFFu);
-      t[2 * h + 1] = bf16_value(w[h] >> 16);
-    }
-    if (let) {
-      const float4 d0 = reinterpret_cast<const float4*>(let_shift)[2 * j];
-      const float4 d1 = reinterpret_cast<const float4*>(let_shift)[2 * j + 1];
-      const float4 s0 = reinterpret_cast<const float4*>(let_scale)[2 * j];
-      const float4 s1 = reinterpret_cast<const float4*>(let_scale)[2 * j + 1];
-      const float d[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
-      const float s[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
-#pragma unroll
-      for (int h = 0; h < 8; ++h) t[h] = (t[h] - d[h]) / s[h];
+    for (int h = 0; h < 8; ++h) {
+      lo = fminf(lo, t[h]);
+      hi = fmaxf(hi, t[h]);
     }
   };
-
-  float lo = 0.f, hi = 0.f;
   float held[kHold > 0 ? kHold : 1][8];
   if constexpr (kHold > 0) {
 #pragma unroll
     for (int c = 0; c < kHold; ++c) {
       const int j = tid + c * kThreads;
       if (j < n8) {
-        transformed(j, held[c]);
-#pragma unroll
-        for (int h = 0; h < 8; ++h) {
-          lo = fminf(lo, held[c][h]);
-          hi = fmaxf(hi, held[c][h]);
-        }
+        act::transformed8(x8, j, let_shift, let_scale, held[c]);
+        widen(held[c]);
       }
     }
   } else {
     for (int j = tid; j < n8; j += kThreads) {
       float t[8];
-      transformed(j, t);
-#pragma unroll
-      for (int h = 0; h < 8; ++h) {
-        lo = fminf(lo, t[h]);
-        hi = fmaxf(hi, t[h]);
-      }
+      act::transformed8(x8, j, let_shift, let_scale, t);
+      widen(t);
     }
   }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    lo = fminf(lo, __shfl_xor(lo, off));
-    hi = fmaxf(hi, __shfl_xor(hi, off));
-  }
-  constexpr int kWavefronts = kThreads / 64;
-  __shared__ float s_lo[kWavefronts], s_hi[kWavefronts];
-  if ((tid & 63) == 0) {
-    s_lo[tid >> 6] = lo;
-    s_hi[tid >> 6] = hi;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int w = 0; w < kWavefronts; ++w) {
-    lo = fminf(lo, s_lo[w]);
-    hi = fmaxf(hi, s_hi[w]);
-  }
-
-  const float top = (float)((1 << abits) - 1);
-  const float rng = fmaxf(hi - lo, 0x1p-100f);
-  const float scale = rng / top;
-  const float zp = fminf(fmaxf(rintf((-lo) / scale), 0.f), top);
-  if (tid == 0) row_scale[row] = scale;
+  const act::Code code = act::row_code<kThreads>(lo, hi, abits, tid);
+  if (tid == 0) row_scale[row] = code.scale;
 
   uint4* out8 = reinterpret_cast<uint4*>(Xint + row * K);
   uint4* xr8 = Xr ? reinterpret_cast<uint4*>(Xr + row * K) : nullptr;
   auto write_chunk = [&](int j, const float t[8]) {
     float xi[8];
-#pragma unroll
-    for (int h = 0; h < 8; ++h) {
-      const float q = fminf(fmaxf(rintf(t[h] / scale) + zp, 0.f), top);
-      xi[h] = q - zp;  // an integer of at most abits bits and a sign: exact in bf16
-    }
-    uint4 o;
-    o.x = bf16_bits(xi[0]) | (bf16_bits(xi[1]) << 16);
-    o.y = bf16_bits(xi[2]) | (bf16_bits(xi[3]) << 16);
-    o.z = bf16_bits(xi[4]) | (bf16_bits(xi[5]) << 16);
-    o.w = bf16_bits(xi[6]) | (bf16_bits(xi[7]) << 16);
-    out8[j] = o;
-    if (xr8) {
-      float r[8];
-#pragma unroll
-      for (int h = 0; h < 8; ++h) r[h] = xi[h] * scale;
-      if (let) {
-        const float4 d0 = reinterpret_cast<const float4*>(let_shift)[2 * j];
-        const float4 d1 = reinterpret_cast<const float4*>(let_shift)[2 * j + 1];
-        const float4 s0 = reinterpret_cast<const float4*>(let_scale)[2 * j];
-        const float4 s1 = reinterpret_cast<const float4*>(let_scale)[2 * j + 1];
-        const float d[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
-        const float s[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
-#pragma unroll
-        for (int h = 0; h < 8; ++h) r[h] = r[h] * s[h] + d[h];
-      }
-      uint4 p;
-      p.x = bf16_bits(r[0]) | (bf16_bits(r[1]) << 16);
-      p.y = bf16_bits(r[2]) | (bf16_bits(r[3]) << 16);
-      p.z = bf16_bits(r[4]) | (bf16_bits(r[5]) << 16);
-      p.w = bf16_bits(r[6]) | (bf16_bits(r[7]) << 16);
-      xr8[j] = p;
-    }
+    act::whole8(t, code, xi);
+    out8[j] = act::pack8(xi);
+    if (xr8) xr8[j] = act::rebuilt8(xi, code, j, let_shift, let_scale);
   };
   if constexpr (kHold > 0) {
 #pragma unroll
@@ -149,7 +67,7 @@ __global__ __launch_bounds__(kThreads) void act_quant_kernel(const uint16_t* __r
   } else {
     for (int j = tid; j < n8; j += kThreads) {
       float t[8];
-      transformed(j, t);
+      act::transformed8(x8, j, let_shift, let_scale, t);
       write_chunk(j, t);
     }
   }
@@ -212,13 +130,21 @@ mbq_status launch_act_quant(const uint16_t* X, int64_t T, int64_t K, int abits, 
                             const float* let_scale, uint16_t* Xint, float* row_scale, uint16_t* Xr,
                             hipStream_t stream) {
   // up to 16384 columns a row is held in registers by 512 threads (four chunks of eight values each)
-  if (K <= 512 * 4 * 8)
-    hipLaunchKernelGGL((act_quant_kernel<512, 4>), dim3((unsigned)T), dim3(512), 0, stream, X, K, abits, let_shift,
+  if (K <= act::kHeldColumns)
+    hipLaunchKernelGGL((act_quant_kernel<act::kHeldThreads, act::kHeldChunks>), dim3((unsigned)T), dim3(act::kHeldThreads), 0, stream, X, K, abits, let_shift,
                        let_scale, Xint, row_scale, Xr);
   else
     hipLaunchKernelGGL((act_quant_kernel<256, 0>), dim3((unsigned)T), dim3(256), 0, stream, X, K, abits, let_shift,
                        let_scale, Xint, row_scale, Xr);
   return hip_status(hipGetLastError(), "act_quant_kernel launch");
+}
+
+// The router launch of a stage can quantise the activations itself: rows that its workgroups hold in registers, and
+// results that do not lie in the rows that other workgroups still read.
+bool act_carried(const ActArgs& aq, int64_t T, int64_t K) {
+  const uintptr_t x = (uintptr_t)aq.X, bytes = (uintptr_t)(T * K * 2);
+  auto apart = [&](const void* p, uintptr_t n) { return (uintptr_t)p + n <= x || x + bytes <= (uintptr_t)p; };
+  return K <= act::kHeldColumns && apart(aq.Xint, bytes) && apart(aq.Xr, bytes) && apart(aq.row_scale, (uintptr_t)(T * 4));
 }
 
 mbq_status launch_scale_rows(float* Y, int64_t T, int64_t N, const float* row_scale, const float* bias,

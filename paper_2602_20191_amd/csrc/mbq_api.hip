@@ -4,6 +4,7 @@
 
 #include <atomic>
 
+#include "mbq_act_quant.h"
 #include "mbq_bench.h"
 #include "mbq_common.h"
 
@@ -88,13 +89,30 @@ struct ViewScope {
   explicit ViewScope(const RouteView* v) : saved(t_view) { t_view = v; }
   ~ViewScope() { t_view = saved; }
 };
-// The activations the linear kernels of a routed stage multiply when they are not the router's input (the
-// activation-quantised stage call sets it for the duration of the call it forwards to; null: the router's input).
-static thread_local const uint16_t* t_linear_X = nullptr;
-struct LinearInputScope {
-  explicit LinearInputScope(const uint16_t* x) { t_linear_X = x; }
-  ~LinearInputScope() { t_linear_X = nullptr; }
+// What the activation-quantised stage call adds to the stage call it forwards to: the linear kernels multiply the
+// integers, the quantiser runs inside the router launch or in a launch ahead of it, and the linear launch may scale the
+// output rows itself (then `scaled` is set and no launch follows).  Null outside such a call.
+struct ActStage {
+  ActArgs aq;
+  const float* const* bias;
+  bool scaled;
 };
+static thread_local ActStage* t_act = nullptr;
+struct ActScope {
+  explicit ActScope(ActStage* a) { t_act = a; }
+  ~ActScope() { t_act = nullptr; }
+};
+// the quantiser's own launch, where the router launch does not carry it; `aq` is left null then
+static mbq_status act_ahead(int64_t T, int64_t K, bool may_carry, const ActArgs** aq, hipStream_t s) {
+  *aq = nullptr;
+  if (!t_act) return MBQ_OK;
+  const ActArgs& a = t_act->aq;
+  if (may_carry && act_carried(a, T, K)) {
+    *aq = &a;
+    return MBQ_OK;
+  }
+  return launch_act_quant(a.X, T, K, a.abits, a.shift, a.scale, a.Xint, a.row_scale, a.Xr, s);
+}
 // cfg -> view; the configurations this library runs are those that cut the blob's eight-bit code
 static bool make_view(const mbq_config* cfg, RouteView* v, const char* who) {
   if (!cfg) {
@@ -484,7 +502,8 @@ mbq_status mbq_routed_linear_group(const uint16_t* X, int64_t T, int64_t K, int 
                                    void* ws_route, size_t ws_route_bytes, void* ws_linear, size_t ws_linear_bytes,
                                    int algo, void* stream) {
   ApiScope scope;
-  const uint16_t* XL = t_linear_X ? t_linear_X : X;  // what the linear kernels multiply
+  const uint16_t* XL = t_act ? t_act->aq.Xint : X;  // what the linear kernels multiply
+  const ActArgs* aq = nullptr;
   if (t_view->shift != 0 || t_view->group != kGroup) {
     // A configuration with an odd cumulative width: the precision arrays count bits.  The loader-wavefront decode
     // kernels understand that (one token tile); every other shape goes through the slow
@@ -561,12 +580,14 @@ mbq_status mbq_routed_linear_group(const uint16_t* X, int64_t T, int64_t K, int 
     if (ok && knob(3) == 0 && decode_f4_supports(T, sh[0]) && route_can_carry_prep(T)) {
       ZeroList zl;
       decode_f4_zero_list(T, n_proj, sh, Y_host, &zl);
-      mbq_status st = launch_route_group(X, T, K, n_proj, Wr_host, br_host, prec_host, perm_host, offsets_host,
-                                         nullptr, ws_route, (hipStream_t)stream, ws_linear, sh[0].KB, &zl, true,
-                                         *t_view, XL);
+      mbq_status st = act_ahead(T, K, true, &aq, (hipStream_t)stream);
+      if (st != MBQ_OK) return st;
+      st = launch_route_group(X, T, K, n_proj, Wr_host, br_host, prec_host, perm_host, offsets_host, nullptr, ws_route,
+                              (hipStream_t)stream, ws_linear, sh[0].KB, &zl, true, *t_view, XL, aq);
       if (st != MBQ_OK) return st;
       return launch_linear_decode_f4(T, n_proj, blob_host, sh, prec_host, Y_host, ws_linear, (hipStream_t)stream,
-                                     perm_host, offsets_host);
+                                     perm_host, offsets_host, nullptr, false, t_act ? t_act->aq.row_scale : nullptr,
+                                     t_act ? t_act->bias : nullptr, t_act ? &t_act->scaled : nullptr);
     }
     // up to 128 tokens with every matrix on the register-stationary kernel: the router launch only writes the
     // precisions (no meeting of its workgroups), the linear launch sorts the tokens itself
@@ -579,8 +600,10 @@ mbq_status mbq_routed_linear_group(const uint16_t* X, int64_t T, int64_t K, int 
       if (all) {
         ZeroList zl;  // outputs the linear launch adds into: cleared by a plane of the router launch
         decode16_zero_list(T, n_proj, sh, Y_host, &zl);
-        mbq_status st = launch_route_group(X, T, K, n_proj, Wr_host, br_host, prec_host, perm_host, offsets_host,
-                                           nullptr, ws_route, (hipStream_t)stream, nullptr, 0, &zl, true, *t_view);
+        mbq_status st = act_ahead(T, K, true, &aq, (hipStream_t)stream);
+        if (st != MBQ_OK) return st;
+        st = launch_route_group(X, T, K, n_proj, Wr_host, br_host, prec_host, perm_host, offsets_host, nullptr, ws_route,
+                                (hipStream_t)stream, nullptr, 0, &zl, true, *t_view, nullptr, aq);
         if (st != MBQ_OK) return st;
         return launch_linear_decode16_group(XL, T, n_proj, blob_host, sh, prec_host, perm_host, Y_host,
                                             (hipStream_t)stream, perm_host, offsets_host);
@@ -588,7 +611,10 @@ mbq_status mbq_routed_linear_group(const uint16_t* X, int64_t T, int64_t K, int 
     }
   }
   // otherwise exactly the two calls (they check the arguments)
-  mbq_status st = mbq_route_group(X, T, K, n_proj, Wr_host, br_host, P, prec_host, perm_host, offsets_host,
+  mbq_status st = MBQ_OK;
+  if (T > 0) st = act_ahead(T, K, false, &aq, (hipStream_t)stream);
+  if (st != MBQ_OK) return st;
+  st = mbq_route_group(X, T, K, n_proj, Wr_host, br_host, P, prec_host, perm_host, offsets_host,
                                   ws_route, ws_route_bytes, stream);
   if (st != MBQ_OK) return st;
   return mbq_linear_group(XL, T, K, n_proj, blob_host, N_host, prec_host, perm_host, offsets_host, Y_host, ws_linear,
@@ -889,8 +915,9 @@ mbq_status mbq_routed_linear_group_cfg(const uint16_t* X, int64_t T, int64_t K, 
                                  stream);
 }
 
-mbq_status mbq_act_quant(const uint16_t* X, int64_t T, int64_t K, int abits, const float* let_shift,
-                         const float* let_scale, uint16_t* Xint, float* row_scale, uint16_t* Xr, void* stream) {
+static mbq_status check_act_quant(const uint16_t* X, int64_t T, int64_t K, int abits, const float* let_shift,
+                                  const float* let_scale, const uint16_t* Xint, const float* row_scale,
+                                  const uint16_t* Xr) {
   if (T < 0 || K <= 0 || K % kGroup != 0 || T > (int64_t)1 << 24 || K > (int64_t)1 << 24) {
     set_error("mbq_act_quant: bad sizes (T=%lld, K=%lld; K must be a multiple of %d)", (long long)T, (long long)K,
               kGroup);
@@ -910,6 +937,13 @@ mbq_status mbq_act_quant(const uint16_t* X, int64_t T, int64_t K, int abits, con
     set_error("mbq_act_quant: null or misaligned pointer (16-byte alignment for X, Xint, Xr, shift and scale)");
     return MBQ_ERR_INVALID_ARG;
   }
+  return MBQ_OK;
+}
+
+mbq_status mbq_act_quant(const uint16_t* X, int64_t T, int64_t K, int abits, const float* let_shift,
+                         const float* let_scale, uint16_t* Xint, float* row_scale, uint16_t* Xr, void* stream) {
+  const mbq_status st = check_act_quant(X, T, K, abits, let_shift, let_scale, Xint, row_scale, Xr);
+  if (st != MBQ_OK || T == 0) return st;
   return launch_act_quant(X, T, K, abits, let_shift, let_scale, Xint, row_scale, Xr, (hipStream_t)stream);
 }
 
@@ -935,15 +969,16 @@ mbq_status mbq_routed_linear_group_act(const uint16_t* X, int64_t T, int64_t K, 
       set_error("mbq_routed_linear_group_act: bad N or null Y for projection %d", i);
       return MBQ_ERR_INVALID_ARG;
     }
-  mbq_status st = mbq_act_quant(X, T, K, abits, let_shift, let_scale, Xint, row_scale, Xr, stream);
+  mbq_status st = check_act_quant(X, T, K, abits, let_shift, let_scale, Xint, row_scale, Xr);
   if (st != MBQ_OK) return st;
+  ActStage stage = {{X, let_shift, let_scale, Xint, row_scale, Xr, abits}, bias_host, false};
   {
-    LinearInputScope linear_input(Xint);
+    ActScope act_scope(&stage);
     st = mbq_routed_linear_group(Xr, T, K, n_proj, Wr_host, br_host, P, blob_host, N_host, prec_host, perm_host,
                                  offsets_host, Y_host, ws_route, ws_route_bytes, ws_linear, ws_linear_bytes, algo,
                                  stream);
   }
-  if (st != MBQ_OK || T == 0) return st;
+  if (st != MBQ_OK || T == 0 || stage.scaled) return st;
   return launch_scale_rows_group(n_proj, Y_host, T, N_host, row_scale, bias_host, (hipStream_t)stream);
 }
 

@@ -108,7 +108,10 @@ mbq_status launch_route_group(const uint16_t* X, int64_t T, int64_t K, int n, co
                               const float* const* br, int32_t* const* prec, int32_t* const* perm,
                               int32_t* const* offsets, double* const* logits, void* ws, hipStream_t stream,
                               void* prep, int prep_blocks, const ZeroList* zl, bool defer_bucket,
-                              const RouteView& view = kDefaultView, const uint16_t* Xprep = nullptr);
+                              const RouteView& view = kDefaultView, const uint16_t* Xprep = nullptr,
+                              const struct ActArgs* aq = nullptr);
+// aq: the launch also quantises the activations (act_carried); only where the call defers its sort
+bool act_carried(const struct ActArgs& aq, int64_t T, int64_t K);
 bool route_can_carry_prep(int64_t T);
 bool route_defers_sort(int64_t T);
 mbq_status launch_route_mlp(const uint16_t* X, int64_t T, int64_t K, const float* W1, const float* b1, int H,
@@ -167,11 +170,13 @@ __device__ inline void zero_share(const ZeroList& zl, int part, int parts, int t
 size_t decode_f4_workspace_bytes(int64_t T, const Shape& sh);
 mbq_status launch_decode_f4_prep(const uint16_t* X, int64_t T, int64_t K, int KB, void* ws, const ZeroList& zl,
                                  hipStream_t stream);
-// perm/offsets (arrays of n, or null): the launch also sorts the tokens of every matrix by precision
+// perm/offsets (arrays of n, or null): the launch also sorts the tokens of every matrix by precision.
+// row_scale: output row i is to be multiplied by row_scale[i] (and bias[j][n] added); a launch that does so sets *scaled.
 mbq_status launch_linear_decode_f4(int64_t T, int n, const void* const* blobs, const Shape* shapes,
                                    const int32_t* const* prec, float* const* Y, const void* ws, hipStream_t stream,
                                    int32_t* const* perm, int32_t* const* offsets, unsigned long long* stamps = nullptr,
-                                   bool bit_view = false);
+                                   bool bit_view = false, const float* row_scale = nullptr,
+                                   const float* const* bias = nullptr, bool* scaled = nullptr);
 // bit_view (the precision arrays hold bits - 1, see RouteView) is understood by the one-token-tile kernels only
 bool decode_f4_takes_bit_view(int64_t T, const Shape& sh);
 // timeline build of the ring kernel: workgroups it launches at most, and 8-byte slots each of them writes

@@ -23,6 +23,7 @@ struct Proj {
   float* Y;
   size_t slice_vec;  // uint4 per slice
   int64_t N;
+  const float* bias; // with Group::row_scale: added to every scaled row (null: nothing)
   int tile_begin;    // index of this matrix's first tile in the joint list
   int pad;
 };
@@ -31,6 +32,7 @@ struct Group {
   int n;
   int tiles;
   unsigned long long* stamps;  // timeline build of the kernel only: where the stamps go
+  const float* row_scale;      // one-part launches: output row i is multiplied by row_scale[i] (null: left alone)
   int bit_view;                // the precision arrays hold bits - 1 instead of digit precisions (see RouteView)
 };
 
@@ -63,6 +65,14 @@ __device__ inline floatx4 slice_group(const intx8* A, uint32_t w_lo, uint32_t w_
     D = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A[piece], B, D, 0 /* A: FP8 E4M3 */, 4 /* B: FP4 */, E,
                                                          piece == 0 ? sa : sa2, E, sb);
   return D;
+}
+
+// one multiplication and one addition, rounded one by one as the launch that scales rows on its own rounds them
+__device__ __forceinline__ float scaled_row(float y, float scale, bool has_bias, float bias) {
+#pragma clang fp contract(off)
+  y = y * scale;
+  if (has_bias) y = y + bias;
+  return y;
 }
 
 // Stable counting sort of the T <= 64 tokens of one matrix by precision (Sec. 4.3, token permutation),

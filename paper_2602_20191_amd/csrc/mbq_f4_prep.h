@@ -25,26 +25,17 @@ constexpr size_t kPrepBytesPerBlock = kPrepVecPerBlock * 16 + 2 * 16 * 4 + 16 * 
 // 16 c + 8 step + 4 h + j hold column 128 g + 64 (qa & 1) + 32 step + 8 (2 c + (qa >> 1)) + 2 j + h
 // of the block, which is where the FP4 operand built from lane group 2 c + (qa >> 1) of the packed
 // tile puts the matching weight.
-// `token` is the row of X that is row m = lane % 16 of the tile (-1: no token, zeros); `base` is where
-// the prepared block goes.
-__device__ inline void prep_block_rows(const uint16_t* __restrict__ X, int token, int64_t K, char* __restrict__ base,
-                                       int kb, int lane) {
-  const int m = lane & 15, qa = lane >> 4;
+// raw[g][c][step] are the eight bf16 values from that column on.  kNear, kFar: distances in lanes to the other sub-blocks
+// of the token (qa ^ 1, qa ^ 2); `base` is where the prepared block goes.
+__device__ __forceinline__ int prep_column(int qa, int g, int c, int step) {  // within the block
+  return 128 * g + 64 * (qa & 1) + 32 * step + 8 * (2 * c + (qa >> 1));
+}
+template <int kNear, int kFar>
+__device__ __forceinline__ void prep_values(const uint4 (&raw)[2][2][2], int m, int qa, char* __restrict__ base) {
   uint4* out = reinterpret_cast<uint4*>(base);
   float* sums = reinterpret_cast<float*>(base + kPrepVecPerBlock * 16);
   int* scl = reinterpret_cast<int*>(base + kPrepVecPerBlock * 16 + 2 * 16 * 4);
 
-  uint4 raw[2][2][2];  // [group][c][step]
-#pragma unroll
-  for (int g = 0; g < 2; ++g)
-#pragma unroll
-    for (int c = 0; c < 2; ++c)
-#pragma unroll
-      for (int step = 0; step < 2; ++step) {
-        const int64_t col = (int64_t)kb * kTileK + 128 * g + 64 * (qa & 1) + 32 * step + 8 * (2 * c + (qa >> 1));
-        raw[g][c][step] = (token >= 0 && col < K) ? *reinterpret_cast<const uint4*>(X + (int64_t)token * K + col)
-                                                  : uint4{0u, 0u, 0u, 0u};
-      }
   // largest exponent of the token's block
   uint32_t mx = 0u;
 #pragma unroll
@@ -60,8 +51,8 @@ __device__ inline void prep_block_rows(const uint16_t* __restrict__ X, int token
           mx = max(mx, (u[t] << 16) & 0x7F800000u);
         }
       }
-  mx = max(mx, (uint32_t)__shfl_xor((int)mx, 16, 64));
-  mx = max(mx, (uint32_t)__shfl_xor((int)mx, 32, 64));
+  mx = max(mx, (uint32_t)__shfl_xor((int)mx, kNear, 64));
+  mx = max(mx, (uint32_t)__shfl_xor((int)mx, kFar, 64));
   // scale the largest element into [2^7, 2^8): below the FP8 (E4M3) maximum 448
   int scale_byte = (int)(mx >> 23) - 7;  // = 127 + k, x = 2^k * scaled
   scale_byte = min(max(scale_byte, 1 + kPieceShift), 254);
@@ -99,17 +90,35 @@ __device__ inline void prep_block_rows(const uint16_t* __restrict__ X, int token
             v[h][3] = (v[h][3] - __builtin_amdgcn_cvt_f32_fp8(packed, 3)) * (float)(1 << kPieceShift);
           }
       }
-    sum += __shfl_xor(sum, 16, 64);
-    sum += __shfl_xor(sum, 32, 64);
+    sum += __shfl_xor(sum, kNear, 64);
+    sum += __shfl_xor(sum, kFar, 64);
     if (qa == 0) sums[16 * g + m] = sum;
 #pragma unroll
     for (int piece = 0; piece < kPieces; ++piece) {
-      uint4* dst = out + (size_t)(g * kPieces + piece) * 128 + lane;
+      uint4* dst = out + (size_t)(g * kPieces + piece) * 128 + 16 * qa + m;
       const int* r = piece_regs[piece];
       dst[0] = uint4{(uint32_t)r[0], (uint32_t)r[1], (uint32_t)r[2], (uint32_t)r[3]};
       dst[64] = uint4{(uint32_t)r[4], (uint32_t)r[5], (uint32_t)r[6], (uint32_t)r[7]};
     }
   }
+}
+
+// `token` is the row of X that is row m = lane % 16 of the tile (-1: no token, zeros).
+__device__ inline void prep_block_rows(const uint16_t* __restrict__ X, int token, int64_t K, char* __restrict__ base,
+                                       int kb, int lane) {
+  const int qa = lane >> 4;
+  uint4 raw[2][2][2];  // [group][c][step]
+#pragma unroll
+  for (int g = 0; g < 2; ++g)
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int step = 0; step < 2; ++step) {
+        const int64_t col = (int64_t)kb * kTileK + prep_column(qa, g, c, step);
+        raw[g][c][step] = (token >= 0 && col < K) ? *reinterpret_cast<const uint4*>(X + (int64_t)token * K + col)
+                                                  : uint4{0u, 0u, 0u, 0u};
+      }
+  prep_values<16, 32>(raw, lane & 15, qa, base);
 }
 
 // One token tile in original order: row m is token m.

@@ -284,7 +284,7 @@ mbq_status launch_decode_f4_prep(const uint16_t* X, int64_t T, int64_t K, int KB
 mbq_status launch_linear_decode_f4(int64_t T, int n, const void* const* blobs, const Shape* shapes,
                                    const int32_t* const* prec, float* const* Y, const void* ws, hipStream_t stream,
                                    int32_t* const* perm, int32_t* const* offsets, unsigned long long* stamps,
-                                   bool bit_view) {
+                                   bool bit_view, const float* row_scale, const float* const* bias, bool* scaled) {
   f4::Group g;
   int tiles = 0;
   for (int i = 0; i < MBQ_MAX_GROUP; ++i) {
@@ -300,6 +300,7 @@ mbq_status launch_linear_decode_f4(int64_t T, int n, const void* const* blobs, c
     g.p[i].N = sh.N;
     g.p[i].tile_begin = tiles;
     g.p[i].pad = 0;
+    g.p[i].bias = bias ? bias[j] : nullptr;
     if (i < n) tiles += sh.NT;
   }
   g.n = n;
@@ -307,6 +308,10 @@ mbq_status launch_linear_decode_f4(int64_t T, int n, const void* const* blobs, c
   g.stamps = stamps;
   g.bit_view = bit_view ? 1 : 0;
   const Shape& s0 = shapes[0];
+  // rows are scaled where a launch stores whole sums: one part of the K axis (two addends would be scaled one by one)
+  const bool scales = row_scale && scaled && !stamps && !bit_view && decode_f4_ws_supports(s0.KB, tiles) && decode_f4_ws_parts(s0.KB) == 1;
+  g.row_scale = scales ? row_scale : nullptr;
+  if (scales) *scaled = true;
   if (decode_f4_ws_supports(s0.KB, tiles)) return launch_linear_decode_f4_ws(T, g, s0.KB, ws, stream);
   if (stamps) {
     set_error("the timeline build exists for K <= 8192 only");

@@ -122,7 +122,10 @@ static_assert(kWsRing % 8 == 0, "the loader checks the slots in groups of eight"
 // it in kChunks chunks of at most 16 blocks - all its tiles for the first chunk, then the activations of the second
 // chunk, all its tiles again - and keeps the tiles' sums of the earlier chunks in LDS (at most kWsChunkTiles tiles per
 // workgroup; the ring gives up a quarter of its slots for them).  The parts still meet by adding two addends.
-template <int CPW, int S, bool kStamp, bool kBits = false, int kChunks = 1>
+// kScale (one part): output row i is multiplied by g.row_scale[i] and the matrix's bias added before it is stored.  Both
+// are loaded ahead (the scales once, the bias at the top of a tile): at the store, behind the weight stream, a load takes
+// longer than the launch that this saves.
+template <int CPW, int S, bool kStamp, bool kBits = false, int kChunks = 1, bool kScale = false>
 __global__ __launch_bounds__(576) void decode_f4_ws_kernel(const char* __restrict__ prep, int T, int KB,
                                                            const f4::Group g) {
   using namespace f4;
@@ -130,6 +133,7 @@ __global__ __launch_bounds__(576) void decode_f4_ws_kernel(const char* __restric
   static_assert(S == 1 || S == 2, "one or two parts");
   static_assert(CPW == 1 || CPW == 2, "one or two blocks per wavefront");
   static_assert(kChunks == 1 || (CPW == 2 && S == 2 && !kStamp), "the chunked variant: two parts, two blocks per wavefront");
+  static_assert(!kScale || (S == 1 && !kStamp && !kBits && kChunks == 1), "rows are scaled where whole sums are stored");
   constexpr int kRing = kChunks > 1 ? kWsRing - 8 : kWsRing;
   __shared__ __attribute__((aligned(16))) float s_held[kChunks > 1 ? kWsChunkTiles : 1][64][4];  // sums of earlier chunks
   __shared__ __attribute__((aligned(1024))) char ring[kRing * kWsSlotBytes];
@@ -180,6 +184,7 @@ __global__ __launch_bounds__(576) void decode_f4_ws_kernel(const char* __restric
   // The per-matrix facts are fetched from the argument block once, all at the same time, and kept in scalar registers:
   // looking a matrix up later (when the tile list crosses into it) then costs selects, not a chain of dependent loads.
   const char* m_codes[MBQ_MAX_GROUP];
+  const float* m_bias[MBQ_MAX_GROUP] = {nullptr, nullptr, nullptr, nullptr};
   const char* m_meta[MBQ_MAX_GROUP];
   float* m_Y[MBQ_MAX_GROUP];
   size_t m_slice_bytes[MBQ_MAX_GROUP];
@@ -187,6 +192,10 @@ __global__ __launch_bounds__(576) void decode_f4_ws_kernel(const char* __restric
 #pragma unroll
   for (int i = 0; i < MBQ_MAX_GROUP; ++i) {
     m_codes[i] = reinterpret_cast<const char*>(g.p[i].codes);
+    if constexpr (kScale) {
+      m_bias[i] = g.p[i].bias;
+      asm volatile("" : "+s"(m_bias[i]));
+    }
     m_meta[i] = reinterpret_cast<const char*>(g.p[i].meta);
     m_Y[i] = g.p[i].Y;
     m_slice_bytes[i] = g.p[i].slice_vec * 16u;
@@ -399,6 +408,11 @@ __global__ __launch_bounds__(576) void decode_f4_ws_kernel(const char* __restric
     }
     };
     load_activations(kb_first, kChunks > 1 ? min(nbc, nb) : nb);
+    floatx4 row_scale = {1.f, 1.f, 1.f, 1.f};
+    if constexpr (kScale) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) row_scale[i] = g.row_scale[min(4 * kq + i, T - 1)];
+    }
     find_pmax();
     stamp(1);
     if (blockIdx.x == 0 && wave == 0) {  // one wavefront of the launch sorts the tokens, where the caller wants them sorted
@@ -414,6 +428,7 @@ __global__ __launch_bounds__(576) void decode_f4_ws_kernel(const char* __restric
       // the matrix of the current tile, looked up when the tile list crosses into it
       int cs_t = bid, cs_next_begin = 0, cs_pm = 0, cs_N = 0, cs_col0 = 0;
       float* cs_Y = nullptr;
+      const float* cs_bias = nullptr;
       uint32_t cs_gate = 0u;  // A scale gate of this lane's token (row m of the A operand): slice e counts iff e <= its precision
       uint32_t cs_gate_lo = 0u;  // kBits: cs_gate gates the high bits of the codes, this one the low bits
       floatx4 cs_kp = zero4;  // 0.5 - 1.5 q_p of the output rows 4 kq + i
@@ -422,6 +437,7 @@ __global__ __launch_bounds__(576) void decode_f4_ws_kernel(const char* __restric
         cs_pm = uniform(pmax_of(j));
         cs_N = uniform(MBQ_PICK(m_N, j));
         cs_Y = uniform(MBQ_PICK(m_Y, j));
+        if constexpr (kScale) cs_bias = uniform(MBQ_PICK(m_bias, j));
         cs_col0 = uniform((cs_t - MBQ_PICK(m_begin, j)) * kTileN);
         cs_next_begin = uniform(next_begin_of(j));
         const int plj = j == 0 ? pl[0] : j == 1 ? pl[1] : j == 2 ? pl[2] : pl[3];
@@ -461,6 +477,12 @@ __global__ __launch_bounds__(576) void decode_f4_ws_kernel(const char* __restric
         asm volatile("" : "+s"(cs_t), "+s"(cs_next_begin), "+s"(cs_pm), "+s"(cs_N), "+s"(cs_col0), "+s"(cs_Y), "+s"(rb),
                      "+s"(rlap));
         const int pm = cs_pm;
+        bool cs_has_bias = false;
+        float bias_here = 0.f;
+        if constexpr (kScale) {
+          cs_has_bias = cs_bias != nullptr;
+          if (cs_has_bias) bias_here = cs_bias[min(cs_col0 + m, cs_N - 1)];
+        }
         floatx4 acc = zero4;
 #pragma unroll
         for (int c = 0; c < CPW; ++c) {
@@ -603,6 +625,7 @@ __global__ __launch_bounds__(576) void decode_f4_ws_kernel(const char* __restric
               if (r < T) {
                 // (explicitly global: through a generic pointer these would be FLAT instructions)
                 float* dst = &cs_Y[(int64_t)r * cs_N + col];
+                if constexpr (kScale) sum[i] = scaled_row(sum[i], row_scale[i], cs_has_bias, bias_here);
                 if constexpr (S == 1) asm volatile("global_store_dword %0, %1, off" ::"v"(dst), "v"(sum[i]) : "memory");
                 else asm volatile("global_atomic_add_f32 %0, %1, off" ::"v"(dst), "v"(sum[i]) : "memory");
               }
@@ -687,6 +710,11 @@ mbq_status launch_linear_decode_f4_ws(int64_t T, const f4::Group& g, int KB, con
     if (S == 1 && cpw == 1) MBQ_WS(1, 1, true);
     else if (S == 1) MBQ_WS(2, 1, true);
     else MBQ_WS(2, 2, true);
+  } else if (g.row_scale) {  // (only where there is one part: see launch_linear_decode_f4)
+    if (cpw == 1)
+      hipLaunchKernelGGL((decode_f4_ws_kernel<1, 1, false, false, 1, true>), dim3(grid), dim3(576), 0, stream, prep, (int)T, KB, g);
+    else
+      hipLaunchKernelGGL((decode_f4_ws_kernel<2, 1, false, false, 1, true>), dim3(grid), dim3(576), 0, stream, prep, (int)T, KB, g);
   } else {
     if (S == 1 && cpw == 1) MBQ_WS(1, 1, false);
     else if (S == 1) MBQ_WS(2, 1, false);

@@ -1,5 +1,6 @@
 // Router scores + argmax (paper Sec. 4.2 Eq. 4, read as one linear map to four
 // logits) and the token permutation by precision (Sec. 4.3, challenge 3).
+#include "mbq_act_quant.h"
 #include "mbq_common.h"
 #include "mbq_f4_prep.h"
 
@@ -304,15 +305,25 @@ constexpr int kSmallRouteTokens = 28;
 // wavefront (prep == nullptr: no such plane).  defer_bucket: only the precisions are written; the linear
 // kernel that follows sorts the tokens (it reads every precision anyway), which takes the atomic
 // round trip and the sort out of this launch.
+//
+// kAct (K <= 16384): the activation-quantised stage in the same launch.  A workgroup holds its token's whole row, so it
+// quantises the row itself (each router's workgroup again, router 0 writes the results out) and scores the rebuilt
+// values from registers; the preparation plane then works a token at a time too, from integers in LDS.  Quantiser and
+// router as two launches took 5.1 + 4.9 us a stage, most of it launching; together 5.6 us at K = 4096, 9 at K = 11008.
+// Together with the row scaling in the linear launch: 7B-shaped block, 16 tokens, 4-bit activations 108.5 -> 103 us; 2048
+// x 5120 block at 8 tokens 67 -> 55 us, 4096 x 11008 with kv / 4 at 64 tokens 196 -> 188 us.
+template <bool kAct>
 __global__ __launch_bounds__(512) void route_small_kernel(const uint16_t* __restrict__ X, int T, int64_t K,
                                                           RouteGroup group, int n_routers,
                                                           unsigned long long* words, char* prep, int prep_blocks,
                                                           const ZeroList zl, int defer_bucket,
-                                                          const uint16_t* __restrict__ Xprep) {
+                                                          const uint16_t* __restrict__ Xprep, const ActArgs aq) {
   // Xprep: the activations the linear kernel multiplies (X itself, except in the activation-quantised variant,
   // where the routers read the rebuilt activations and the linear kernel the integers)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if ((int)blockIdx.y == n_routers) {
+  const int tok = blockIdx.x;
+  const bool plane = (int)blockIdx.y == n_routers;
+  if (!kAct && plane) {
     if (wave == 0) {
       if ((int)blockIdx.x < prep_blocks) f4::prep_block(Xprep, T, K, prep, (int)blockIdx.x, lane);
     } else {
@@ -320,38 +331,112 @@ __global__ __launch_bounds__(512) void route_small_kernel(const uint16_t* __rest
     }
     return;
   }
-  if ((int)blockIdx.x >= T) return;
-  const RouteOut& out = group.r[blockIdx.y];
-  const int tok = blockIdx.x;
-  const uint16_t* x = X + (int64_t)tok * K;
+  if (kAct && plane) {
+    zero_share(zl, (int)blockIdx.x, (int)gridDim.x, tid, 512);
+    if (prep == nullptr || tok >= 16) return;
+  } else if (tok >= T) {
+    return;
+  }
+  const RouteOut& out = group.r[plane ? 0 : blockIdx.y];
   const float* __restrict__ Wr = out.Wr;
   double acc[kP] = {0.0, 0.0, 0.0, 0.0};
-  for (int64_t k = (int64_t)tid * 8; k < K; k += 2 * 4096) {
-    const bool two = k + 4096 < K;
-    const int64_t k2 = two ? k + 4096 : k;  // a valid address either way
-    const uint4 xa = *reinterpret_cast<const uint4*>(x + k);
-    const uint4 xb = *reinterpret_cast<const uint4*>(x + k2);
-    float4 wa[kP][2], wb[kP][2];
+  auto load_w = [&](int64_t k, float4 (&w)[kP][2]) {
 #pragma unroll
     for (int q = 0; q < kP; ++q) {
       const int64_t row = min(q, group.view.P - 1);  // rows past P do not exist: re-read the last one, never used
-      const float4* sa = reinterpret_cast<const float4*>(Wr + row * K + k);
-      const float4* sb = reinterpret_cast<const float4*>(Wr + row * K + k2);
-      wa[q][0] = sa[0]; wa[q][1] = sa[1];
-      wb[q][0] = sb[0]; wb[q][1] = sb[1];
+      const float4* s = reinterpret_cast<const float4*>(Wr + row * K + k);
+      w[q][0] = s[0]; w[q][1] = s[1];
     }
-    auto add = [&](const uint4& xv, const float4 (&w)[kP][2]) {
-      const float xs[8] = {bf16_lo(xv.x), bf16_hi(xv.x), bf16_lo(xv.y), bf16_hi(xv.y),
-                           bf16_lo(xv.z), bf16_hi(xv.z), bf16_lo(xv.w), bf16_hi(xv.w)};
+  };
+  auto add = [&](const uint4& xv, const float4 (&w)[kP][2]) {
+    const float xs[8] = {bf16_lo(xv.x), bf16_hi(xv.x), bf16_lo(xv.y), bf16_hi(xv.y),
+                         bf16_lo(xv.z), bf16_hi(xv.z), bf16_lo(xv.w), bf16_hi(xv.w)};
 #pragma unroll
-      for (int q = 0; q < kP; ++q) {
-        const float ws[8] = {w[q][0].x, w[q][0].y, w[q][0].z, w[q][0].w, w[q][1].x, w[q][1].y, w[q][1].z, w[q][1].w};
+    for (int q = 0; q < kP; ++q) {
+      const float ws[8] = {w[q][0].x, w[q][0].y, w[q][0].z, w[q][0].w, w[q][1].x, w[q][1].y, w[q][1].z, w[q][1].w};
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[q] = fma((double)xs[j], (double)ws[j], acc[q]);
+      for (int j = 0; j < 8; ++j) acc[q] = fma((double)xs[j], (double)ws[j], acc[q]);
+    }
+  };
+  if constexpr (kAct) {
+    constexpr int kChunks = act::kHeldChunks, kThreads = act::kHeldThreads;
+    static_assert(kThreads == 512, "the thread count of this launch");
+    __shared__ uint4 s_row[act::kHeldColumns / 8];  // integers of the row (preparation plane)
+    const int n8 = (int)(K >> 3);
+    const uint4* x8 = reinterpret_cast<const uint4*>(aq.X + (int64_t)min(tok, T - 1) * K);
+    float held[kChunks][8], lo = 0.f, hi = 0.f;
+#pragma unroll
+    for (int c = 0; c < kChunks; ++c) {
+      const int j = tid + c * kThreads;
+      if (j < n8) {
+        act::transformed8(x8, j, aq.shift, aq.scale, held[c]);
+#pragma unroll
+        for (int h = 0; h < 8; ++h) {
+          lo = fminf(lo, held[c][h]);
+          hi = fmaxf(hi, held[c][h]);
+        }
       }
-    };
-    add(xa, wa);
-    if (two) add(xb, wb);
+    }
+    float4 w[kP][2];
+    if (!plane && tid < n8) load_w((int64_t)tid * 8, w);  // on their way while the workgroup meets
+    const act::Code code = act::row_code<kThreads>(lo, hi, aq.abits, tid);
+    if (plane) {
+#pragma unroll
+      for (int c = 0; c < kChunks; ++c) {
+        const int j = tid + c * kThreads;
+        if (j < n8) {
+          float xi[8];
+          act::whole8(held[c], code, xi);
+          s_row[j] = (tok < T) ? act::pack8(xi) : uint4{0u, 0u, 0u, 0u};  // rows without a token are zeros
+        }
+      }
+      __syncthreads();
+      const int kb = tid >> 2, qa = tid & 3;
+      if (kb < prep_blocks) {
+        uint4 raw[2][2][2];
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+#pragma unroll
+          for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int step = 0; step < 2; ++step) {
+              const int col = kb * kTileK + f4::prep_column(qa, g, c, step);
+              raw[g][c][step] = (col < K) ? s_row[col >> 3] : uint4{0u, 0u, 0u, 0u};
+            }
+        f4::prep_values<1, 2>(raw, tok, qa, prep + (size_t)kb * f4::kPrepBytesPerBlock);
+      }
+      return;
+    }
+    const bool writes = blockIdx.y == 0;
+    if (writes && tid == 0) aq.row_scale[tok] = code.scale;
+#pragma unroll
+    for (int c = 0; c < kChunks; ++c) {
+      const int j = tid + c * kThreads;
+      if (j < n8) {
+        if (c > 0) load_w((int64_t)j * 8, w);
+        float xi[8];
+        act::whole8(held[c], code, xi);
+        const uint4 xr = act::rebuilt8(xi, code, j, aq.shift, aq.scale);
+        if (writes) {
+          reinterpret_cast<uint4*>(aq.Xint + (int64_t)tok * K)[j] = act::pack8(xi);
+          reinterpret_cast<uint4*>(aq.Xr + (int64_t)tok * K)[j] = xr;
+        }
+        add(xr, w);
+      }
+    }
+  } else {
+    const uint16_t* x = X + (int64_t)tok * K;
+    for (int64_t k = (int64_t)tid * 8; k < K; k += 2 * 4096) {
+      const bool two = k + 4096 < K;
+      const int64_t k2 = two ? k + 4096 : k;  // a valid address either way
+      const uint4 xa = *reinterpret_cast<const uint4*>(x + k);
+      const uint4 xb = *reinterpret_cast<const uint4*>(x + k2);
+      float4 wa[kP][2], wb[kP][2];
+      load_w(k, wa);
+      load_w(k2, wb);
+      add(xa, wa);
+      if (two) add(xb, wb);
+    }
   }
   __shared__ double red[8][kP];
   {
@@ -478,7 +563,7 @@ mbq_status launch_route_group(const uint16_t* X, int64_t T, int64_t K, int n, co
                               const float* const* br, int32_t* const* prec, int32_t* const* perm,
                               int32_t* const* offsets, double* const* logits, void* ws, hipStream_t stream,
                               void* prep, int prep_blocks, const ZeroList* zl, bool defer_bucket,
-                              const RouteView& view, const uint16_t* Xprep) {
+                              const RouteView& view, const uint16_t* Xprep, const ActArgs* aq) {
   if (T == 0) return launch_sort(n, prec, perm, offsets, 0, 0, stream);  // the (all-zero) offsets
   RouteGroup g;
   g.view = view;
@@ -497,10 +582,17 @@ mbq_status launch_route_group(const uint16_t* X, int64_t T, int64_t K, int n, co
     if (zl)
       for (int i = 0; i < kRouteGroupMax; ++i) clears = clears || zl->p[i] != nullptr;
     const bool plane = prep != nullptr || clears;
-    const unsigned gx = (prep && prep_blocks > (int)T) ? (unsigned)prep_blocks : (unsigned)T;
-    hipLaunchKernelGGL(route_small_kernel, dim3(gx, (unsigned)n + (plane ? 1u : 0u)), dim3(512), 0, stream, X, (int)T,
-                       K, g, n, words, reinterpret_cast<char*>(prep), prep ? prep_blocks : 0,
-                       (plane && zl) ? *zl : ZeroList{}, defer_bucket ? 1 : 0, Xprep ? Xprep : X);
+    if (aq) {  // (the plane prepares a token per workgroup, all 16 rows of the tile)
+      const unsigned gx = (prep && T < 16) ? 16u : (unsigned)T;
+      hipLaunchKernelGGL(route_small_kernel<true>, dim3(gx, (unsigned)n + (plane ? 1u : 0u)), dim3(512), 0, stream, X,
+                         (int)T, K, g, n, words, reinterpret_cast<char*>(prep), prep ? prep_blocks : 0,
+                         (plane && zl) ? *zl : ZeroList{}, defer_bucket ? 1 : 0, Xprep, *aq);
+    } else {
+      const unsigned gx = (prep && prep_blocks > (int)T) ? (unsigned)prep_blocks : (unsigned)T;
+      hipLaunchKernelGGL(route_small_kernel<false>, dim3(gx, (unsigned)n + (plane ? 1u : 0u)), dim3(512), 0, stream, X,
+                         (int)T, K, g, n, words, reinterpret_cast<char*>(prep), prep ? prep_blocks : 0,
+                         (plane && zl) ? *zl : ZeroList{}, defer_bucket ? 1 : 0, Xprep ? Xprep : X, ActArgs{});
+    }
     return hip_status(hipGetLastError(), "route_small_kernel launch");
   }
   if (T <= 256)

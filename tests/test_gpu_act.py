@@ -115,6 +115,38 @@ def test_stage_of_the_variant(mbq, abits, T, K, Ns):
         assert_output_close(Ys[i].cpu().numpy(), want, f"W-A stage abits={abits} matrix {i}")
 
 
+@pytest.mark.parametrize("K", [128, 384, 4224, 16384, 16512])
+@pytest.mark.parametrize("T", [1, 5, 16, 40])
+@pytest.mark.parametrize("in_place", [False, True])
+def test_stage_with_the_quantiser_inside_the_router_launch(mbq, K, T, in_place):
+    """The one-call stage against the separate calls, bit for bit, where its launches differ: rows that fit a workgroup's
+    registers and rows that do not, one and two parts of the K axis, with and without a preparation plane, a bias for one
+    of two matrices only, no transform, and the router's input written over the activations (which needs the quantiser's
+    own launch: other workgroups still read those rows)."""
+    rng = np.random.default_rng([K, T, 29])
+    Ns = (40, 272)
+    X = dev_bf16(activations(T, K, [T, K, 29])).reshape(T, K)
+    delta, s = (None, None) if K == 384 else (dev(p) for p in let_params(K, [K, 31]))
+    Wr = [dev((rng.standard_normal((4, K)) / np.sqrt(K)).astype(np.float32)) for _ in Ns]
+    br = [dev(rng.normal(0, 0.3, size=4).astype(np.float32)) for _ in Ns]
+    blobs = [mbq.mbq_encode(dev(make_weight(N, K, [89, N, K], 4.0))) for N in Ns]
+    bias = [None, dev(rng.standard_normal(Ns[1]).astype(np.float32))]
+    want_act = mbq.mbq_act_quant(X, 4, delta, s)
+    want_routing = mbq.mbq_route_group(want_act[2], Wr, br)
+    want = mbq.mbq_linear_group(want_act[0], blobs, list(Ns), K, want_routing)
+    for Y, b in zip(want, bias):
+        mbq.mbq_scale_rows(Y, want_act[1], b)
+    X1 = X.clone()
+    act = (torch.empty_like(X), torch.empty((T,), dtype=torch.float32, device="cuda"), X1 if in_place else torch.empty_like(X))
+    routing, Ys, _ = mbq.mbq_routed_linear_group_act(X1, 4, delta, s, Wr, br, blobs, list(Ns), bias=bias, act=act)
+    torch.cuda.synchronize()
+    for a, b in zip(act, want_act):
+        assert torch.equal(a, b)
+    for i in range(2):
+        assert all(torch.equal(a, b) for a, b in zip(routing[i], want_routing[i])), i
+        assert torch.equal(Ys[i], want[i]), i
+
+
 def test_scale_rows_alone_and_empty_inputs(mbq):
     rng = np.random.default_rng(3)
     Y = rng.standard_normal((37, 130)).astype(np.float32)
