@@ -38,9 +38,9 @@ STAGES = (("q", "k", "v"), ("o",), ("gate", "up"), ("down",))   # projections th
 # WRITE_SIZE runs of `bench.py --probe decode`, scaled by what the same counters read for a plain 256 MiB copy
 # (FETCH_SIZE x2.000, WRITE_SIZE x1.000); see profiles/decode_linear_hbm_traffic_llama2_7b_batch16.txt
 MEASURED_TRAFFIC_BYTES_PER_LAUNCH = {16: 53.10e6}
-# HBM bytes per mbq_linear call (gather pre-kernel + tile kernel), mean over the three linears, same counters and scale
+# HBM bytes per mbq_linear call (group-sum pre-kernel + tile kernel), mean over the three linears, same counters and scale
 # factors from `bench.py --probe prefill` / `--probe prefill70b`; see profiles/prefill_hbm_traffic.txt
-MEASURED_PREFILL_TRAFFIC_BYTES_PER_CALL = {"configs[2]": 653.8e6, "70b": 3498.4e6}
+MEASURED_PREFILL_TRAFFIC_BYTES_PER_CALL = {"configs[2]": 773.1e6, "70b": 4169.7e6}
 
 
 def algorithmic_bytes(N, K, T, pmax):
@@ -603,7 +603,7 @@ def extra_measurements(mbq, torch, dev, cfg, layers, stages, T_main):
             "workload": "the block of the main line with 4-bit per-token activations: quantise, route on the rebuilt "
                         "activations, routed linears on the integers, row scaling; one stage call each",
             "ms_per_step": ms, "tokens_per_s": T / (ms * 1e-3),
-            "launches_per_step": 4 * len(stages),
+            "launches_per_step": 2 * len(stages) + 1,  # router (+ quantiser) and linear; one scales the rows of `down`
             "launch": f"hipgraph, {per_replay} steps per replay" if graphs else "eager"}
         for st in stages:
             mbq.mbq_routed_linear_group(st["X"], st["Wr"], st["br"], [l["blobs"][0] for l in st["layers"]], st["Ns"],
