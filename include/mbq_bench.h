@@ -32,8 +32,8 @@ mbq_status mbq_bench_copy(const void* src, void* dst, size_t bytes, int waves_of
 mbq_status mbq_bench_read(const void* src, size_t bytes, int waves_of_workgroups, void* sink, void* stream);
 
 /*
- * mbq_bench_mfma_loop - the matrix-core rate this chip sustains on the prefill kernel's
- * instruction (v_mfma_f32_32x32x16_bf16) with operands read from LDS: one workgroup of 8 wavefronts
+ * mbq_bench_mfma_loop - the bf16 matrix-core rate this chip sustains with an LDS-fed loop
+ * (v_mfma_f32_32x32x16_bf16, operands read from LDS): one workgroup of 8 wavefronts
  * per compute unit, every wavefront runs `steps` steps of 16 MFMAs on a 128 x 64 accumulator tile
  * (4 x 2 MFMA tiles, fragments re-read from LDS each step); with_barrier != 0 adds one workgroup
  * barrier per step.  *flops_host receives the flops of the launch (2 x 32 x 32 x 16 per MFMA).
