@@ -212,10 +212,11 @@ mbq_status mbq_threshold_quantile(const double* scores, int64_t T, int E, double
  * inside the 1e-3 bar, none at all for blocks without such a spread.  The scale is an 8-bit exponent: a block whose
  * largest element is under 2^-115 (bf16 subnormals and their neighbours) is scaled by 2^122 at most, and its elements
  * are then rounded to multiples of 2^-135, an eighth of bf16's subnormal spacing.
- * Reproducibility.  The decode kernels (up to 64 tokens, and on with AUTO while it keeps them) give the same bits on
- * every call and in grouped and single calls.  The tiled GEMM does too unless a launch with few tiles splits K into
- * more than two parts: those partial sums are added with float atomics in whatever order they arrive, and results
- * then agree to rounding, not bit for bit.
+ * Reproducibility.  The same call gives the same bits every time: no sum depends on the order in which workgroups
+ * arrive.  Grouped and single calls give the same bits as well, with one exception: the tiled GEMM cuts a matrix along K
+ * into several parts where a launch would have few tiles; one or two parts are the matrix's own choice, but where it
+ * would take more alone, the matrices of a group may be cut into fewer, and grouped and single results then agree to
+ * rounding, not bit for bit.
  */
 mbq_status mbq_linear(const uint16_t* X, int64_t T, const void* blob, int64_t N, int64_t K,
                       const int32_t* prec, const int32_t* perm, const int32_t* offsets, float* Y,
@@ -245,7 +246,7 @@ mbq_status mbq_linear_static(const uint16_t* X, int64_t T, const void* blob, int
  * of them while every matrix takes a decode kernel (up to 64 tokens, 128 with AUTO on matrices
  * that keep the register-stationary kernel; Sec. 4.3, fused launch for the projections of a
  * layer), otherwise one launch sequence per matrix.  Results are those of n_proj separate
- * mbq_linear calls (bit for bit where mbq_linear is reproducible, see there).
+ * mbq_linear calls (bit for bit but for one case of the tiled GEMM, see Reproducibility there).
  *   blob_host, prec_host, perm_host, offsets_host, Y_host : HOST arrays of n_proj DEVICE
  *   pointers (meaning as in mbq_linear); N_host : HOST array of the n_proj row counts.  The
  *   arrays are read before the call returns.  1 <= n_proj <= MBQ_MAX_GROUP.

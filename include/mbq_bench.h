@@ -82,7 +82,8 @@ mbq_status mbq_bench_decode_timeline(int64_t T, int64_t K, int n_proj, const voi
  *   knob 3: decode kernel choice: 0 automatic, 1 multi-tile kernel, 2 register-stationary kernel (both switch the
  *           FP4-operand kernels of T <= 16 off)
  *   knob 4: 1 = route small batches with the general router kernel too
- *   knob 5: K split of the prefill kernel (1..8 workgroups per tile, partial sums added into Y), 0 = automatic
+ *   knob 5: K split of the prefill kernel (1..8 workgroups per tile, fewer where the rows are short or the workspace has
+ *           no room for their partial sums), 0 = automatic
  *   knob 7: 3 = the 17..64-token register-stationary kernel takes one token tile per workgroup
  */
 mbq_status mbq_set_knob(int knob, int value);

@@ -53,7 +53,8 @@ constexpr int kBM = 128, kBN = 256;
 constexpr int kRowBytes = 2 * kGroup;         // one group of one token: 16 chunks of 16 bytes, swizzled by the row
 constexpr int kStageBytes = kBM * kRowBytes;  // 32 KiB, two stages
 constexpr int kOffsetBytes = 8 * 256 * 4;     // row offsets of the 8-bit tiles
-constexpr int kPadRows = 256;                 // spare rows of the sorted copy (inputs of 4 GiB and more, see below)
+constexpr int kPadRows = 256;                 // rows of the workspace beyond those of the activations
+constexpr int kMaxSplits = 8;
 
 // A matrix of a launch.
 struct Proj {
@@ -64,22 +65,38 @@ struct Proj {
   const int32_t* offsets;
   float* Y;
   int64_t N;
-  int NT;           // 16-row code tiles
-  int cols;         // column tiles of kBN
-  int block_begin;  // index of this matrix's first workgroup
+  float* slot;         // T x N arrays of partial sums besides Y, slot_floats apart
+  int64_t slot_floats;
+  int NT;              // 16-row code tiles
+  int cols;            // column tiles of kBN
+  int splits, slots;   // parts along K, arrays that take them (Y is the first)
+  int block_begin;     // index of this matrix's first workgroup
 };
 struct Group {
   Proj p[MBQ_MAX_GROUP];
   int n;
 };
 
-// ---- pre-kernel: Sx[token][g] = sum_{k in g} X[token][k]; outputs that the tile kernel adds into are cleared; sorted
+// ---- pre-kernel: Sx[token][g] = sum_{k in g} X[token][k]; arrays that the tile kernel adds into are cleared (zl:
+// outputs, zs: arrays of the workspace); sorted
 // copy Xs[r][:] = X[perm[r]][:] where one is wanted --------------------------------------------------------------
+__device__ inline void clear_share(const ZeroList& zl) {
+  const int64_t at = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
+#pragma unroll
+  for (int j = 0; j < MBQ_MAX_GROUP; ++j) {
+    float* p = zl.p[j];
+    if (p == nullptr) continue;
+    const int64_t n = zl.n[j], n4 = (reinterpret_cast<uintptr_t>(p) & 15) == 0 ? n >> 2 : 0;
+    for (int64_t i = at; i < n4; i += step) reinterpret_cast<floatx4*>(p)[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int64_t i = 4 * n4 + at; i < n; i += step) p[i] = 0.f;
+  }
+}
 __global__ __launch_bounds__(256) void prefill_prep_kernel(const uint16_t* __restrict__ X, int64_t K,
                                                            float* __restrict__ Sx, const ZeroList zl,
-                                                           const int32_t* __restrict__ perm, uint16_t* __restrict__ Xs) {
+                                                           const ZeroList zs, const int32_t* __restrict__ perm, uint16_t* __restrict__ Xs) {
   const int64_t r = blockIdx.x;
-  zero_share(zl, (int)blockIdx.x, (int)gridDim.x, (int)threadIdx.x, 256);
+  clear_share(zl);
+  clear_share(zs);
   const int64_t token = perm ? perm[r] : r;
   const uint4* src = reinterpret_cast<const uint4*>(X + token * K);
   const int chunks = (int)(K >> 3);  // a multiple of 16: groups of 16 lanes are whole
@@ -93,6 +110,35 @@ __global__ __launch_bounds__(256) void prefill_prep_kernel(const uint16_t* __res
 #pragma unroll
     for (int off = 8; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
     if ((threadIdx.x & 15) == 0) Sx[token * (K >> 7) + (c >> 4)] = s;
+  }
+}
+
+// ---- post-kernel of launches that cut K into more than two parts: Y += array 1, += array 2, .. in that order ----
+struct Fold {
+  float* Y[MBQ_MAX_GROUP];
+  const float* slot[MBQ_MAX_GROUP];
+  int64_t slot_floats[MBQ_MAX_GROUP];
+  int64_t n[MBQ_MAX_GROUP];  // floats of Y
+  int slots[MBQ_MAX_GROUP];
+};
+__global__ __launch_bounds__(256) void prefill_fold_kernel(const Fold f) {
+  const int j = blockIdx.y;
+  float* __restrict__ Y = f.Y[j];
+  const float* __restrict__ slot = f.slot[j];
+  const int64_t n = f.n[j], at = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
+  const int extra = f.slots[j] - 1;
+  if (extra <= 0) return;
+  const bool wide = (reinterpret_cast<uintptr_t>(Y) & 15) == 0;  // (the arrays of the workspace always are)
+  const int64_t n4 = wide ? n >> 2 : 0;
+  for (int64_t i = at; i < n4; i += step) {
+    floatx4 v = reinterpret_cast<const floatx4*>(Y)[i];
+    for (int e = 0; e < extra; ++e) v += reinterpret_cast<const floatx4*>(slot + e * f.slot_floats[j])[i];
+    reinterpret_cast<floatx4*>(Y)[i] = v;
+  }
+  for (int64_t i = 4 * n4 + at; i < n; i += step) {
+    float v = Y[i];
+    for (int e = 0; e < extra; ++e) v += slot[e * f.slot_floats[j] + i];
+    Y[i] = v;
   }
 }
 
@@ -131,10 +177,12 @@ struct __attribute__((packed, aligned(4))) Sums4 {
 // One tile: rows row0 .. row0 + rows - 1 of the sorted tokens, columns 256 ntile_n ..; groups g0 .. g0 + G - 1.
 // P = precision index of the tokens, MR = 16-row tiles (16 MR >= rows).
 // gather: X is in token order and rows are fetched through perm; otherwise X is the sorted copy.
+// halfway: when the zero-point term is removed, see remove_offsets.
+// out: the T x N array the tile goes to; accumulate: it is added there (two parts of K share the array).
 template <int P, int MR>
 __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, int KB, bool gather, const Proj& M,
                                      const float* __restrict__ Sx, int row0, int rows, int ntile_n, char* smem, int g0,
-                                     int G, bool accumulate) {
+                                     int G, bool halfway, float* out, bool accumulate) {
   constexpr float kOff = (P == 3) ? 0.f : 256.f;
   constexpr float kHalf = 0.5f * (float)(1 << (2 * (3 - P)));
   const int tid = threadIdx.x, lane = tid & 63;
@@ -240,13 +288,17 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
 #pragma unroll
   for (int c = 0; c < 4; ++c) m_cur[c] = scale_mantissa(s_cur[c]);
 
-  // The zero-point / offset term of groups g .. g + 15 (those there are), in the accumulator's units, as a rank-16 fp32
+  // The zero-point / offset term of groups g .. last - 1 (at most 16), in the accumulator's units, as a rank-16 fp32
   // MFMA update: lane quarter kq holds groups 4 kq .. 4 kq + 3 (the order of the k axis is free as long as both operands
   // share it).  Every 16 groups and not once at the end: the offset is many times the signal, and what the accumulator
   // carries sets its rounding (11008 x 4096: 1.8e-6 relative against 2.8e-6 with one update at the end, 4096 x 28672
-  // 1.9e-6 against 6.4e-6), for 3-4 % of the time.
+  // 1.9e-6 against 6.4e-6), for 3-4 % of the time.  halfway: the update comes when half of its groups are done, so that
+  // the accumulator carries the offset of half as many (3000 x 2176 at 777 tokens in two parts: 0.93e-6 relative behind
+  // them, 0.74e-6 half way, 0.70e-6 in four parts).  Taken for parts of at most 16 groups, which replace twice as many
+  // parts where there is no room for those; long parts lose up to 7 % by it (8192 x 28672 at 256 tokens 263 -> 282 us: the
+  // scales of groups to come are not in cache yet).
   const int Gtot = (int)(K / kGroup);
-  auto remove_offsets = [&](int g) {
+  auto remove_offsets = [&](int g, int last) {
     constexpr float kC = (kHalf - kOff) * (1.f / 64.f);
     float bv[4][4];
 #pragma unroll
@@ -254,9 +306,9 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
       const float units = 64.f / m_cur[c];
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
-        const int gg = min(g + 4 * kq + s, G - 1);
+        const int gg = min(g + 4 * kq + s, last - 1);
         const float2 mt = *reinterpret_cast<const float2*>(sptr[c] + (uint32_t)(2 * ((g0 + gg) * kTileN + l15)));
-        bv[s][c] = (g + 4 * kq + s < G) ? mt.x * (kC - mt.y) * units : 0.f;
+        bv[s][c] = (g + 4 * kq + s < last) ? mt.x * (kC - mt.y) * units : 0.f;
       }
     }
     // the four sums of a lane in one load (a token's sums are contiguous; the last pass may read into the next token's
@@ -274,7 +326,7 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
       for (int a = 0; a < RR; ++a)
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-          const float v = (g + 4 * kq + s < G) ? av[a].s[s] : 0.f;
+          const float v = (g + 4 * kq + s < last) ? av[a].s[s] : 0.f;
 #pragma unroll
           for (int c = 0; c < 4; ++c)
             acc[a0 + a][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(v, bv[s][c], acc[a0 + a][c], 0, 0, 0);
@@ -283,11 +335,13 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
   };
 
   uint32_t stage = 0u;
+  int q = 0;
 #pragma unroll 1
-  for (int first = 0; first < G; first += 16) {
+  for (int first = 0; first < G + 16; first += 16) {
     const int last = min(G, first + 16);
+    const int stop = first < G && halfway ? (first + last + 1) >> 1 : last;
 #pragma unroll 1
-    for (int q = first; q < last; ++q) {
+    for (; q < stop; ++q) {
       // the next group on its way (the last group is requested once more: the other stage is free)
       const int qn = q + 1 < G ? q + 1 : q;
       load_a(qn, stage ^ (uint32_t)kStageBytes);
@@ -352,7 +406,7 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
       __builtin_amdgcn_sched_barrier(0);
       stage ^= (uint32_t)kStageBytes;
     }
-    remove_offsets(first);
+    if (first < G) remove_offsets(first, last);
   }
 
   // ---- true units ----
@@ -373,11 +427,11 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
     for (int i = 0; i < 4; ++i) {
       const int r = 16 * a + 4 * kq + i;
       if (r < rows) {
-        float* y = M.Y + (int64_t)perm[row0 + r] * M.N + col0;
+        float* y = out + (int64_t)perm[row0 + r] * M.N + col0;
 #pragma unroll
         for (int c = 0; c < 4; ++c)
           if (col0 + 16 * c < M.N) {
-            if (accumulate) unsafeAtomicAdd(y + 16 * c, acc[a][c][i]);  // K split: Y was cleared by the pre-kernel
+            if (accumulate) unsafeAtomicAdd(y + 16 * c, acc[a][c][i]);  // cleared by the pre-kernel
             else y[16 * c] = acc[a][c][i];
           }
       }
@@ -385,7 +439,7 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
 }
 
 __global__ __launch_bounds__(256, 2) void prefill_kernel(const uint16_t* __restrict__ X, int64_t K, int KB, int gather,
-                                                         const float* __restrict__ Sx, const Group grp, int splits) {
+                                                         const float* __restrict__ Sx, const Group grp) {
   __shared__ __attribute__((aligned(1024))) char smem[2 * kStageBytes + kOffsetBytes];
   int j = 0;
 #pragma unroll
@@ -393,7 +447,7 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(const uint16_t* __restr
     if (i < grp.n && (int)blockIdx.x >= grp.p[i].block_begin) j = i;
   const Proj& M = grp.p[j];
   // (tile row, tile column, K split): workgroups of one tile row are neighbours (they share activations)
-  const int block = (int)blockIdx.x - M.block_begin;
+  const int block = (int)blockIdx.x - M.block_begin, splits = M.splits;
   const int per_mt = M.cols * splits;
   const int mt = block / per_mt, ntile_n = (block % per_mt) / splits, split = block % splits;
   const int Gtot = (int)(K / kGroup);
@@ -433,7 +487,12 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(const uint16_t* __restr
     }
   }
   if (p < 0) return;
-#define MBQ_TILE(PP, MM) tile<PP, MM>(X, K, KB, gather != 0, M, Sx, row0, rows, ntile_n, smem, g0, Gs, splits > 1)
+  // part s goes to array s mod slots; an array that two parts share is added into
+  const int slot = split % M.slots;
+  float* const out = slot == 0 ? M.Y : M.slot + (slot - 1) * M.slot_floats;
+  const bool shared = slot + M.slots < splits;
+  const bool halfway = splits > 1 && Gs <= 16;  // see remove_offsets
+#define MBQ_TILE(PP, MM) tile<PP, MM>(X, K, KB, gather != 0, M, Sx, row0, rows, ntile_n, smem, g0, Gs, halfway, out, shared)
 #define MBQ_ROWS(PP)                     \
   do {                                   \
     if (rows > 96) MBQ_TILE(PP, 8);      \
@@ -458,40 +517,79 @@ static inline size_t prefill_copy_bytes(int64_t T, int64_t K) {
   return ((size_t)(T + pf::kPadRows) * K * sizeof(uint16_t) + 255) / 256 * 256;
 }
 
-// group sums, and room for a sorted copy of the activations
+// group sums, and room for a sorted copy of the activations or, where none is made, for arrays of partial sums
 size_t prefill_workspace_bytes(int64_t T, const Shape& sh) {
   const size_t xs = (size_t)(T + pf::kPadRows) * sh.K * sizeof(uint16_t);
   const size_t sx = (size_t)sh.G * prefill_ld(T) * sizeof(float);
   return xs + sx + 256;
 }
 
-// K split: a launch with few tiles leaves compute units idle, so tiles are cut along K into S workgroups that add their
-// partial sums into cleared outputs.  S (1..8) minimises an estimate of the launch, in units of what a compute unit needs
-// for two whole tiles side by side: with r = tiles S / workgroups resident at a time, the rounds cost 0.95 + r / 4 up to
-// one round (a workgroup alone on its unit is hardly faster than one of two) and r + 0.35 beyond (tiles differ in cost
-// and are started by falling cost, so rounds are not in step); a part costs its share of the K axis and four groups for
-// its prologue, zero-point term and stores; atomic adds cost 238 r / K.  Fitted to S = 1..8 on 4096 x 11008, 11008 x
-// 4096, 28672 x 8192, 8192 x 28672, 5120 x 2048 and 2048 x 5120 at 128..4096 tokens: within 5 % of the best S on most, 15 %
-// on the worst; for instance (us) 4096 x 11008 at 2048 tokens 366 / 270 / 272 / 259 with S = 1 / 2 / 3 / 4, at 256 tokens
-// 206 / 121 / 77 / 66 with 1 / 2 / 4 / 8; 11008 x 4096 at 256 tokens 90 / 71 / 88; at 2048 tokens 249 / 281.
-// knob 5 forces the split.
-static int prefill_splits(int64_t T, int64_t K, int64_t cols) {
-  if (knob(5) >= 1 && knob(5) <= 8) return knob(5);
+// How a matrix is cut along K: a launch with few tiles leaves compute units idle, so each tile is cut into `parts`
+// workgroups.  Part s stores into array s mod `slots` - Y, then arrays of the workspace -, an array that two parts share
+// is cleared ahead and added into (two addends: their order does not matter), and a last launch adds the arrays to Y in
+// order.  So results do not depend on which workgroup comes first.  Arrays lie where the sorted copy of the activations
+// would (below 4 GiB none is made); where there is no room for one a matrix is cut in two at most.
+// (Parts that all added into Y, in whatever order they came, took 69 us instead of 79 for 4096 x 11008 at 256 tokens, 47
+// instead of 54 at 96, and 91 instead of 72 for 3000 and 1000 x 2176 at 777, where four parts did not fit.)
+struct Split {
+  int parts, slots;
+};
+static inline int64_t slot_floats(int64_t T, int64_t N) { return (T * N + 3) / 4 * 4; }
+static Split split_into(int parts, int64_t T, int64_t K, int64_t N, int64_t area_floats) {
+  const int64_t room = 1 + area_floats / slot_floats(T, N);
+  if (parts > 2 * room) parts = (int)(2 * room);
+  while (parts > 1 && K / kGroup / parts < 4) --parts;
+  return Split{parts, parts <= 2 ? 1 : parts < room ? parts : (int)room};
+}
+// An estimate of a launch, in units of what a compute unit needs for two whole tiles side by side (17 ns x K): with r =
+// tiles x parts / workgroups resident at a time, the rounds cost 0.8 + 0.33 r up to one round (a workgroup alone on its
+// unit is hardly faster than one of two) and r + 0.45 beyond (tiles differ in cost and are started by falling cost, so
+// rounds are not in step); a part costs its share of the K axis and 4.5 groups for its prologue, zero-point term and
+// stores; adding costs 330 r / K, the last launch 165 / K.
+static double split_cost(Split sp, int64_t T, int64_t K, int64_t cols) {
   const int64_t rows = T / pf::kBM + 2 > 4 ? T / pf::kBM + 2 : 4;  // a bucket ends on a partial tile
-  const double tiles = (double)rows * (double)cols, resident = 2.0 * device_compute_units();
-  const double G = (double)(K / kGroup);
-  int best_s = 1;
-  double best = 0.0;
-  for (int s = 1; s <= 8; ++s) {
-    const double r = tiles * s / resident;
-    const double rounds = r <= 1.0 ? 0.95 + 0.25 * r : r + 0.35;
-    const double cost = rounds * (1.0 / s + 4.0 / G) + (s > 1 ? 238.0 * r / (double)K : 0.0);
-    if (s == 1 || cost < 0.98 * best) {
-      best = cost;
-      best_s = s;
+  const double r = (double)(rows * cols * sp.parts) / (2.0 * device_compute_units());
+  const double rounds = r <= 1.0 ? 0.8 + 0.33 * r : r + 0.45;
+  return rounds * (1.0 / sp.parts + 4.5 * kGroup / (double)K) + (sp.parts > 1 ? 330.0 * r / (double)K : 0.0) +
+         (sp.slots > 1 ? 165.0 / (double)K : 0.0);
+}
+// The cut that minimises the estimate, among those of at most `most` parts.  Fitted to 1..8 parts on twenty shapes from
+// 1000 x 2176 to 28672 x 8192, alone and in groups of two and three, at 65..4096 tokens: 0.8 % above the best cut alone on
+// average (18 % on the worst), 1.7 % (17 %) in groups.  For instance (us, 1 / 2 / 4 / 8 parts; * taken) 4096 x 11008 at 256
+// tokens 209 / 123 / 83 / 79*, at 2048 tokens 345 / 264* / 291 / -, 4096 x 4096 at 160 tokens 78 / 45 / 39*, 11008 x 4096 at
+// 256 tokens 94 / 75*, at 777 tokens 133* / 164.
+// pair: a matrix with as many rows as columns or more has company more often than not (q, k, v of an attention, gate and
+// up of a gated MLP), and one or two parts have to be the same in company and alone (choose_splits): the product of the
+// estimates alone and as a pair decides (11008 x 4096 at 256 tokens, 1 / 2 parts: alone 94 / 75*, as a pair 131 / 132; at
+// 777 tokens 133* / 164 and 236 / 256; 14336 x 4096 at 256 tokens 91 / 78* and 122 / 144).
+// knob 5 forces the number of parts.
+static Split choose_split(int64_t T, int64_t K, int64_t N, int64_t cols, bool pair, int most, int64_t area_floats) {
+  if (knob(5) >= 1 && knob(5) <= pf::kMaxSplits) return split_into(knob(5), T, K, N, area_floats);
+  Split best{1, 1};
+  double best_cost = 0.0;
+  for (int s = 1; s <= most; ++s) {
+    const Split sp = split_into(s, T, K, N, area_floats);
+    if (sp.parts != s) continue;
+    const double cost = split_cost(sp, T, K, cols) * (pair ? split_cost(sp, T, K, 2 * cols) : 1.0);
+    if (s == 1 || cost < 0.98 * best_cost) {
+      best_cost = cost;
+      best = sp;
     }
   }
-  return best_s;
+  return best;
+}
+// The cuts of the n matrices of a call.  One or two parts: the matrix alone decides, so that a call for several matrices
+// gives the bits of separate calls.  More: a group that fills the chip needs fewer (three of 4096 x 4096 at 256 tokens: 72
+// us in two parts each, 157 in four and one launch after the other), and the matrices share the room for arrays.
+static void choose_splits(int64_t T, int64_t K, int n, const Shape* shapes, int64_t area_floats, Split* out) {
+  auto columns = [](const Shape& sh) { return (sh.N + pf::kBN - 1) / pf::kBN; };
+  int64_t all = 0;
+  for (int i = 0; i < n; ++i) all += columns(shapes[i]);
+  for (int i = 0; i < n; ++i) {
+    const int64_t N = shapes[i].N, cols = columns(shapes[i]);
+    out[i] = choose_split(T, K, N, cols, N >= K, pf::kMaxSplits, area_floats);
+    if (n > 1 && out[i].parts > 2) out[i] = choose_split(T, K, N, all, false, out[i].parts, area_floats / n);
+  }
 }
 
 // The matrices share X; one launch for all of them, so that a stage has one ragged end.
@@ -501,6 +599,10 @@ mbq_status launch_linear_prefill_group(const uint16_t* X, int64_t T, int n, cons
   const int64_t K = shapes[0].K;
   // offsets of rows are 32-bit: from 4 GiB of activations on a sorted copy is made, one matrix at a time
   const bool gather = (uint64_t)T * (uint64_t)K * 2u <= 0xFFFFFFFFull;
+  uint16_t* Xs = reinterpret_cast<uint16_t*>(ws);
+  float* Sx = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + prefill_copy_bytes(T, K));
+  // without a sorted copy its room takes arrays of partial sums
+  const int64_t area = gather ? (int64_t)(prefill_copy_bytes(T, K) / sizeof(float)) : 0;
   if (!gather && n > 1) {
     for (int i = 0; i < n; ++i) {
       mbq_status st = launch_linear_prefill_group(X, T, 1, blobs + i, shapes + i, perm + i, offsets + i, Y + i, ws, stream);
@@ -508,19 +610,19 @@ mbq_status launch_linear_prefill_group(const uint16_t* X, int64_t T, int n, cons
     }
     return MBQ_OK;
   }
-  uint16_t* Xs = reinterpret_cast<uint16_t*>(ws);
-  float* Sx = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + prefill_copy_bytes(T, K));
-  int64_t cols = 0;
-  for (int i = 0; i < n; ++i) cols += (shapes[i].N + pf::kBN - 1) / pf::kBN;
-  int splits = prefill_splits(T, K, cols);
-  while (splits > 1 && K / kGroup / splits < 4) --splits;
+  Split split[MBQ_MAX_GROUP];
+  choose_splits(T, K, n, shapes, area, split);
   const int64_t m_tiles_max = T / pf::kBM + MBQ_N_PRECISIONS;
   pf::Group g;
-  ZeroList zl;
-  int64_t blocks = 0;
+  pf::Fold fold;
+  ZeroList zl, zs;  // outputs, arrays of the workspace that two parts are added into
+  int64_t blocks = 0, most = 0;
+  float* slot = reinterpret_cast<float*>(ws);
   for (int i = 0; i < MBQ_MAX_GROUP; ++i) {
     const int j = i < n ? i : 0;
     const Shape& sh = shapes[j];
+    const Split sp = split[j];
+    const int64_t floats = slot_floats(T, sh.N);
     pf::Proj& m = g.p[i];
     m.codes = reinterpret_cast<const uint32_t*>(blobs[j]);
     m.slice_words = sh.slice_words;
@@ -529,21 +631,43 @@ mbq_status launch_linear_prefill_group(const uint16_t* X, int64_t T, int n, cons
     m.offsets = offsets[j];
     m.Y = Y[j];
     m.N = sh.N;
+    m.slot = slot;
+    m.slot_floats = floats;
     m.NT = sh.NT;
     m.cols = (int)((sh.N + pf::kBN - 1) / pf::kBN);
+    m.splits = sp.parts;
+    m.slots = sp.slots;
     m.block_begin = (int)blocks;
-    if (i < n) blocks += m_tiles_max * m.cols * splits;
-    zl.p[i] = (i < n && splits > 1) ? Y[j] : nullptr;
-    zl.n[i] = (i < n && splits > 1) ? (long long)T * sh.N : 0;
+    const int twice = sp.parts - sp.slots;  // arrays with two parts: the first ones
+    zl.p[i] = (i < n && twice > 0) ? Y[j] : nullptr;
+    zl.n[i] = (i < n && twice > 0) ? (long long)T * sh.N : 0;
+    zs.p[i] = (i < n && twice > 1) ? slot : nullptr;
+    zs.n[i] = (i < n && twice > 1) ? (long long)((twice - 1) * floats) : 0;
+    fold.Y[i] = Y[j];
+    fold.slot[i] = slot;
+    fold.slot_floats[i] = floats;
+    fold.n[i] = T * sh.N;
+    fold.slots[i] = i < n ? sp.slots : 1;
+    if (i < n) {
+      blocks += m_tiles_max * m.cols * sp.parts;
+      slot += (sp.slots - 1) * floats;
+      if (sp.slots > 1 && fold.n[i] > most) most = fold.n[i];
+    }
   }
   g.n = n;
-  hipLaunchKernelGGL(pf::prefill_prep_kernel, dim3((unsigned)T), dim3(256), 0, stream, X, K, Sx, zl,
+  hipLaunchKernelGGL(pf::prefill_prep_kernel, dim3((unsigned)T), dim3(256), 0, stream, X, K, Sx, zl, zs,
                      gather ? nullptr : perm[0], gather ? nullptr : Xs);
   mbq_status st = hip_status(hipGetLastError(), "prefill_prep_kernel launch");
   if (st != MBQ_OK) return st;
   hipLaunchKernelGGL(pf::prefill_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, gather ? X : Xs, K, shapes[0].KB,
-                     gather ? 1 : 0, Sx, g, splits);
-  return hip_status(hipGetLastError(), "prefill_kernel launch");
+                     gather ? 1 : 0, Sx, g);
+  st = hip_status(hipGetLastError(), "prefill_kernel launch");
+  if (st != MBQ_OK || most == 0) return st;
+  int64_t fold_blocks = (most / 4 + 255) / 256;  // four floats a thread and pass
+  if (fold_blocks < 1) fold_blocks = 1;
+  if (fold_blocks > 8 * device_compute_units()) fold_blocks = 8 * device_compute_units();
+  hipLaunchKernelGGL(pf::prefill_fold_kernel, dim3((unsigned)fold_blocks, (unsigned)n), dim3(256), 0, stream, fold);
+  return hip_status(hipGetLastError(), "prefill_fold_kernel launch");
 }
 
 mbq_status launch_linear_prefill(const uint16_t* X, int64_t T, const void* blob, const Shape& sh, const int32_t* perm,

@@ -451,6 +451,61 @@ def test_prefill_k_split(mbq, splits):
     assert_output_close(Y, Yref, f"prefill K split {splits}")
 
 
+@pytest.mark.parametrize("parts", [3, 4, 5, 6, 8])
+@pytest.mark.parametrize("T,Ns", [(301, (999,)), (301, (1999,)), (70, (272, 17)), (130, (5, 1001, 300))])
+def test_prefill_parts_in_arrays_of_their_own(mbq, parts, T, Ns):
+    """More than two parts along K go to arrays of the workspace and are added in order: one or two parts an array, as
+    many arrays as there is room for (301 tokens: 5 and 3 of them, Y included, T N not a multiple of four), several
+    matrices in one launch, an output that allows 16-byte accesses and one that does not; the same bits on every call."""
+    K = 4608  # 36 groups: eight parts of four or five
+    xb = tokens(T, K, [T, K, 101])
+    X = dev_bf16(xb).reshape(T, K)
+    blobs, routing, refs = [], [], []
+    for i, N in enumerate(Ns):
+        W = make_weight(N, K, [101, N, i], 4.0)
+        codes, s0, z0 = O.encode(W)
+        prec = np.random.default_rng([101, T, i]).integers(0, 4, size=T).astype(np.int32)
+        perm, offsets = O.bucket(prec)
+        blobs.append(mbq.mbq_encode(dev(W)))
+        routing.append((dev(prec), dev(perm), dev(offsets)))
+        refs.append(O.linear(xb, codes, s0, z0, prec))
+    mbq.set_knob(5, parts)
+    try:
+        Ys = mbq.mbq_linear_group(X, blobs, list(Ns), K, routing, algo=ALGOS["prefill"])
+        shifted = [torch.full((T * N + 1,), float("nan"), device="cuda")[1:].view(T, N) for N in Ns]
+        again = mbq.mbq_linear_group(X, blobs, list(Ns), K, routing, Y=shifted, algo=ALGOS["prefill"])
+    finally:
+        mbq.set_knob(5, 0)
+    torch.cuda.synchronize()
+    for i in range(len(Ns)):
+        assert_output_close(Ys[i].cpu().numpy(), refs[i], f"{parts} parts, matrix {i}")
+        assert torch.equal(Ys[i], again[i]), i
+
+
+@pytest.mark.parametrize("Ns,K,T", [
+    ((14336, 14336), 4096, 96), ((14336, 14336), 4096, 256), ((11008, 11008), 4096, 384), ((11008, 11008), 4096, 777),
+    ((13824, 13824), 5120, 256), ((4096, 4096), 4096, 512), ((11008,), 4096, 96), ((11008,), 4096, 256),
+    ((4096,), 11008, 96), ((4096,), 14336, 128), ((4096,), 11008, 777), ((8192,), 28672, 256)])
+def test_prefill_bits_do_not_depend_on_the_call(mbq, Ns, K, T):
+    """The automatic cut along K: three equal calls give the same bits, and a call for several matrices those of separate
+    calls (each of these takes one or two parts alone).  Nothing but the bits is compared."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(103 + T)
+    X = torch.randn((T, K), generator=gen, device="cuda").to(torch.bfloat16)
+    blobs, routing = [], []
+    for N in Ns:
+        blobs.append(mbq.mbq_encode(0.02 * torch.randn((N, K), generator=gen, device="cuda")))
+        prec = torch.randint(0, 4, (T,), generator=gen, device="cuda", dtype=torch.int32)
+        perm = torch.sort(prec.long(), stable=True)[1].int()
+        routing.append((prec, perm, torch.stack([(prec < q).sum() for q in range(5)]).int()))
+    first = mbq.mbq_linear_group(X, blobs, list(Ns), K, routing, algo=ALGOS["prefill"])
+    for _ in range(2):
+        for a, b in zip(first, mbq.mbq_linear_group(X, blobs, list(Ns), K, routing, algo=ALGOS["prefill"])):
+            assert torch.equal(a, b)
+    for i, N in enumerate(Ns):
+        assert torch.equal(first[i], mbq.mbq_linear(X, blobs[i], N, K, *routing[i], algo=ALGOS["prefill"])), i
+
+
 @pytest.mark.parametrize("K", [768, 2048, 4096, 5120, 11008])
 @pytest.mark.parametrize("pmax", [0, 1, 2, 3])
 @pytest.mark.parametrize("T", [7, 16, 40])
