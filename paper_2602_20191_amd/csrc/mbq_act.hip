@@ -140,11 +140,24 @@ mbq_status launch_act_quant(const uint16_t* X, int64_t T, int64_t K, int abits, 
 }
 
 // The router launch of a stage can quantise the activations itself: rows that its workgroups hold in registers, and
-// results that do not lie in the rows that other workgroups still read.
-bool act_carried(const ActArgs& aq, int64_t T, int64_t K) {
-  const uintptr_t x = (uintptr_t)aq.X, bytes = (uintptr_t)(T * K * 2);
-  auto apart = [&](const void* p, uintptr_t n) { return (uintptr_t)p + n <= x || x + bytes <= (uintptr_t)p; };
-  return K <= act::kHeldColumns && apart(aq.Xint, bytes) && apart(aq.Xr, bytes) && apart(aq.row_scale, (uintptr_t)(T * 4));
+// nothing written by the launch where other workgroups still read.  (With a launch of its own the quantiser is done with
+// its inputs before anything else is written, so a caller may lay outputs over them.)
+bool act_carried(const ActArgs& aq, int64_t T, int64_t K, const Span* others, int n_others) {
+  if (K > act::kHeldColumns) return false;
+  const size_t row_bytes = (size_t)(T * K) * sizeof(uint16_t), let_bytes = aq.scale ? (size_t)K * sizeof(float) : 0;
+  const Span in[3] = {{aq.X, row_bytes}, {aq.shift, let_bytes}, {aq.scale, let_bytes}};
+  auto apart = [&](const Span& o) {
+    for (const Span& i : in) {
+      const uintptr_t a = (uintptr_t)i.p, b = (uintptr_t)o.p;
+      if (i.bytes != 0 && a < b + o.bytes && b < a + i.bytes) return false;
+    }
+    return true;
+  };
+  if (!apart({aq.Xint, row_bytes}) || !apart({aq.Xr, row_bytes}) || !apart({aq.row_scale, (size_t)T * sizeof(float)}))
+    return false;
+  for (int i = 0; i < n_others; ++i)
+    if (!apart(others[i])) return false;
+  return true;
 }
 
 mbq_status launch_scale_rows(float* Y, int64_t T, int64_t N, const float* row_scale, const float* bias,

@@ -102,12 +102,21 @@ struct ActScope {
   explicit ActScope(ActStage* a) { t_act = a; }
   ~ActScope() { t_act = nullptr; }
 };
-// the quantiser's own launch, where the router launch does not carry it; `aq` is left null then
-static mbq_status act_ahead(int64_t T, int64_t K, bool may_carry, const ActArgs** aq, hipStream_t s) {
+// the quantiser's own launch, where the router launch does not carry it; `aq` is left null then.  n, prec, Y, N, ws: what
+// a router launch that carries it writes (n = 0: it may not)
+static mbq_status act_ahead(int64_t T, int64_t K, int n, int32_t* const* prec, float* const* Y, const int64_t* N,
+                            const void* ws, size_t ws_bytes, const ActArgs** aq, hipStream_t s) {
   *aq = nullptr;
   if (!t_act) return MBQ_OK;
   const ActArgs& a = t_act->aq;
-  if (may_carry && act_carried(a, T, K)) {
+  Span written[2 * MBQ_MAX_GROUP + 1];
+  int spans = 0;
+  for (int i = 0; i < n; ++i) {
+    written[spans++] = {prec[i], (size_t)T * sizeof(int32_t)};
+    written[spans++] = {Y[i], (size_t)(T * N[i]) * sizeof(float)};
+  }
+  written[spans++] = {ws, ws_bytes};
+  if (n > 0 && act_carried(a, T, K, written, spans)) {
     *aq = &a;
     return MBQ_OK;
   }
@@ -580,7 +589,8 @@ mbq_status mbq_routed_linear_group(const uint16_t* X, int64_t T, int64_t K, int 
     if (ok && knob(3) == 0 && decode_f4_supports(T, sh[0]) && route_can_carry_prep(T)) {
       ZeroList zl;
       decode_f4_zero_list(T, n_proj, sh, Y_host, &zl);
-      mbq_status st = act_ahead(T, K, true, &aq, (hipStream_t)stream);
+      mbq_status st = act_ahead(T, K, n_proj, prec_host, Y_host, N_host, ws_linear, ws_linear_bytes, &aq,
+                                (hipStream_t)stream);
       if (st != MBQ_OK) return st;
       st = launch_route_group(X, T, K, n_proj, Wr_host, br_host, prec_host, perm_host, offsets_host, nullptr, ws_route,
                               (hipStream_t)stream, ws_linear, sh[0].KB, &zl, true, *t_view, XL, aq);
@@ -600,7 +610,7 @@ mbq_status mbq_routed_linear_group(const uint16_t* X, int64_t T, int64_t K, int 
       if (all) {
         ZeroList zl;  // outputs the linear launch adds into: cleared by a plane of the router launch
         decode16_zero_list(T, n_proj, sh, Y_host, &zl);
-        mbq_status st = act_ahead(T, K, true, &aq, (hipStream_t)stream);
+        mbq_status st = act_ahead(T, K, n_proj, prec_host, Y_host, N_host, nullptr, 0, &aq, (hipStream_t)stream);
         if (st != MBQ_OK) return st;
         st = launch_route_group(X, T, K, n_proj, Wr_host, br_host, prec_host, perm_host, offsets_host, nullptr, ws_route,
                                 (hipStream_t)stream, nullptr, 0, &zl, true, *t_view, nullptr, aq);
@@ -612,7 +622,7 @@ mbq_status mbq_routed_linear_group(const uint16_t* X, int64_t T, int64_t K, int 
   }
   // otherwise exactly the two calls (they check the arguments)
   mbq_status st = MBQ_OK;
-  if (T > 0) st = act_ahead(T, K, false, &aq, (hipStream_t)stream);
+  if (T > 0) st = act_ahead(T, K, 0, nullptr, nullptr, nullptr, nullptr, 0, &aq, (hipStream_t)stream);
   if (st != MBQ_OK) return st;
   st = mbq_route_group(X, T, K, n_proj, Wr_host, br_host, P, prec_host, perm_host, offsets_host,
                                   ws_route, ws_route_bytes, stream);

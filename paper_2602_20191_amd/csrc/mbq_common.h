@@ -111,7 +111,12 @@ mbq_status launch_route_group(const uint16_t* X, int64_t T, int64_t K, int n, co
                               const RouteView& view = kDefaultView, const uint16_t* Xprep = nullptr,
                               const struct ActArgs* aq = nullptr);
 // aq: the launch also quantises the activations (act_carried); only where the call defers its sort
-bool act_carried(const struct ActArgs& aq, int64_t T, int64_t K);
+struct Span {  // a range of device memory
+  const void* p;
+  size_t bytes;
+};
+// others: what the launch writes besides the quantiser's results
+bool act_carried(const struct ActArgs& aq, int64_t T, int64_t K, const Span* others, int n_others);
 bool route_can_carry_prep(int64_t T);
 bool route_defers_sort(int64_t T);
 mbq_status launch_route_mlp(const uint16_t* X, int64_t T, int64_t K, const float* W1, const float* b1, int H,

@@ -147,6 +147,54 @@ def test_stage_with_the_quantiser_inside_the_router_launch(mbq, K, T, in_place):
         assert torch.equal(Ys[i], want[i]), i
 
 
+@pytest.mark.parametrize("T,K", [(1, 4224), (16, 4224), (16, 1024), (40, 4224)])
+@pytest.mark.parametrize("over", ["outputs", "precisions", "workspace", "parameters"])
+def test_stage_writing_over_its_own_inputs(mbq, T, K, over):
+    """Outputs, precisions or workspace laid over the activations, or outputs over the transform's parameters: the
+    quantiser is done with its inputs before anything else is written, so the results are those of separate buffers."""
+    rng = np.random.default_rng([K, T, 37])
+    Ns = (40, 272)
+    delta, s = let_params(K, [K, 41])
+    Wr = [dev((rng.standard_normal((4, K)) / np.sqrt(K)).astype(np.float32)) for _ in Ns]
+    br = [dev(rng.normal(0, 0.3, size=4).astype(np.float32)) for _ in Ns]
+    blobs = [mbq.mbq_encode(dev(make_weight(N, K, [97, N, K], 4.0))) for N in Ns]
+    X = dev_bf16(activations(T, K, [T, K, 37])).reshape(T, K)
+    want_routing, want, want_act = mbq.mbq_routed_linear_group_act(X, 4, dev(delta), dev(s), Wr, br, blobs, list(Ns))
+    torch.cuda.synchronize()
+
+    room = mbq.linear_workspace(T, max(Ns), K, "cuda")
+    x_bytes, let_bytes = 2 * T * K, 4 * K
+    held = torch.empty((room.numel() + 2 * let_bytes + 2 * x_bytes,), dtype=torch.uint8, device="cuda")
+    X1 = held[:x_bytes].view(torch.bfloat16).view(T, K)
+    X1.copy_(X)
+    lets = [held[x_bytes + i * let_bytes:x_bytes + (i + 1) * let_bytes].view(torch.float32) for i in range(2)]
+    lets[0].copy_(torch.from_numpy(delta))
+    lets[1].copy_(torch.from_numpy(s))
+
+    def laid(at, shape, dtype):
+        n = int(np.prod(shape))
+        return held[at:at + 4 * n].view(dtype).view(*shape)
+
+    kept = {}
+    if over == "outputs":       # one behind the other from the start of the activations
+        kept["Y"] = [laid(0, (T, Ns[0]), torch.float32), laid(4 * T * Ns[0], (T, Ns[1]), torch.float32)]
+    elif over == "precisions":
+        kept["routing"] = [(laid(4 * T * i, (T,), torch.int32), torch.empty(T, dtype=torch.int32, device="cuda"),
+                            torch.empty(5, dtype=torch.int32, device="cuda")) for i in range(2)]
+    elif over == "workspace":
+        kept["ws_linear"] = held[:room.numel()]
+    else:
+        at = x_bytes
+        kept["Y"] = [laid(at, (T, Ns[0]), torch.float32), laid(at + 4 * T * Ns[0], (T, Ns[1]), torch.float32)]
+    routing, Ys, act = mbq.mbq_routed_linear_group_act(X1, 4, lets[0], lets[1], Wr, br, blobs, list(Ns), **kept)
+    torch.cuda.synchronize()
+    for a, b in zip(act, want_act):
+        assert torch.equal(a, b)
+    for i in range(2):
+        assert all(torch.equal(a, b) for a, b in zip(routing[i], want_routing[i])), i
+        assert torch.equal(Ys[i], want[i]), i
+
+
 def test_scale_rows_alone_and_empty_inputs(mbq):
     rng = np.random.default_rng(3)
     Y = rng.standard_normal((37, 130)).astype(np.float32)
