@@ -131,9 +131,15 @@ __global__ __launch_bounds__(256) void prefill_fold_kernel(const Fold f) {
   const bool wide = (reinterpret_cast<uintptr_t>(Y) & 15) == 0;  // (the arrays of the workspace always are)
   const int64_t n4 = wide ? n >> 2 : 0;
   for (int64_t i = at; i < n4; i += step) {
-    floatx4 v = reinterpret_cast<const floatx4*>(Y)[i];
-    for (int e = 0; e < extra; ++e) v += reinterpret_cast<const floatx4*>(slot + e * f.slot_floats[j])[i];
-    reinterpret_cast<floatx4*>(Y)[i] = v;
+    floatx4 v[kMaxSplits];  // all on their way before the first is used
+    v[0] = reinterpret_cast<const floatx4*>(Y)[i];
+#pragma unroll
+    for (int e = 1; e < kMaxSplits; ++e)
+      if (e <= extra) v[e] = reinterpret_cast<const floatx4*>(slot + (e - 1) * f.slot_floats[j])[i];
+#pragma unroll
+    for (int e = 1; e < kMaxSplits; ++e)
+      if (e <= extra) v[0] += v[e];
+    reinterpret_cast<floatx4*>(Y)[i] = v[0];
   }
   for (int64_t i = 4 * n4 + at; i < n; i += step) {
     float v = Y[i];
@@ -558,10 +564,11 @@ static double split_cost(Split sp, int64_t T, int64_t K, int64_t cols) {
 // average (18 % on the worst), 1.7 % (17 %) in groups.  For instance (us, 1 / 2 / 4 / 8 parts; * taken) 4096 x 11008 at 256
 // tokens 209 / 123 / 83 / 79*, at 2048 tokens 345 / 264* / 291 / -, 4096 x 4096 at 160 tokens 78 / 45 / 39*, 11008 x 4096 at
 // 256 tokens 94 / 75*, at 777 tokens 133* / 164.
-// pair: a matrix with as many rows as columns or more has company more often than not (q, k, v of an attention, gate and
-// up of a gated MLP), and one or two parts have to be the same in company and alone (choose_splits): the product of the
-// estimates alone and as a pair decides (11008 x 4096 at 256 tokens, 1 / 2 parts: alone 94 / 75*, as a pair 131 / 132; at
-// 777 tokens 133* / 164 and 236 / 256; 14336 x 4096 at 256 tokens 91 / 78* and 122 / 144).
+// pair: a matrix with as many rows as columns or more has company more often than not (q, k, v of an attention, gate
+// and up of a gated MLP), and one or two parts have to be the same in company and alone (choose_splits): the product
+// of the estimates alone and as a pair decides between one and two (11008 x 4096 at 256 tokens, 1 / 2 parts: alone 94
+// / 75*, as a pair 131 / 132; at 777 tokens 133* / 164 and 236 / 256; 14336 x 4096 at 256 tokens 91 / 78* and 122 /
+// 144).
 // knob 5 forces the number of parts.
 static Split choose_split(int64_t T, int64_t K, int64_t N, int64_t cols, bool pair, int most, int64_t area_floats) {
   if (knob(5) >= 1 && knob(5) <= pf::kMaxSplits) return split_into(knob(5), T, K, N, area_floats);
@@ -587,7 +594,8 @@ static void choose_splits(int64_t T, int64_t K, int n, const Shape* shapes, int6
   for (int i = 0; i < n; ++i) all += columns(shapes[i]);
   for (int i = 0; i < n; ++i) {
     const int64_t N = shapes[i].N, cols = columns(shapes[i]);
-    out[i] = choose_split(T, K, N, cols, N >= K, pf::kMaxSplits, area_floats);
+    out[i] = choose_split(T, K, N, cols, false, pf::kMaxSplits, area_floats);
+    if (N >= K && out[i].parts == 2) out[i] = choose_split(T, K, N, cols, true, 2, area_floats);
     if (n > 1 && out[i].parts > 2) out[i] = choose_split(T, K, N, all, false, out[i].parts, area_floats / n);
   }
 }
