@@ -59,9 +59,9 @@ typedef enum mbq_status {
 } mbq_status;
 
 /* Which kernel family mbq_linear uses.  AUTO picks by token count and matrix size: the decode kernels up to 64
- * tokens, one of them (one pass over the weights per 32 precision-sorted tokens) on to 128 tokens, 512 for small
- * matrices, where it still beats the tiled GEMM; from there to 256 tokens (K <= 8192) both are enqueued and the one
- * that suits the precision mix, which only the device knows, does the work; then PREFILL. */
+ * tokens; above, one of them (one pass over the weights per 32 precision-sorted tokens) where it still beats the tiled
+ * GEMM: to 128 tokens on matrices of at most 8192 code blocks of 16 x 256, to 512 on at most 2048, and from 161 to 256 on
+ * at most 4096 with more columns than rows; else PREFILL.  The choice looks at the matrix and the token count only. */
 typedef enum mbq_algo {
   MBQ_ALGO_AUTO = 0,
   MBQ_ALGO_SIMPLE = 1, /* one thread per output, fp64 accumulate: slow checker path   */

@@ -195,24 +195,33 @@ static bool takes_stationary_kernel(int64_t T, const Shape& sh) {
 }
 
 // Above the decode limit the register-stationary kernel still beats the prefill kernel on small matrices: it walks the
-// weights once per 32 sorted tokens without a pre-kernel and fills the chip with fewer columns.  Measured, stationary /
-// prefill in us per call (uniform mix):
-//   2048 x 2048: 15.6 / 19.8 at 80 tokens, 12.1 / 21.6 at 128, 16.8 / 29.5 at 256;  1024 x 4096: 12 / 20, 12 / 23, 17 / 31;
-//   4096 x 4096: 30 / 26, 25 / 31, 42 / 47, and 46 / 39 at 192;
-//   14336 x 4096: 79 / 49, 69 / 54, 129 / 82;  4096 x 14336: 96 / 46, 84 / 53, 135 / 77;
-//   28672 x 8192: 223 / 169, 252 / 189, 448 / 262;  8192 x 28672: 306 / 143, 264 / 150, 488 / 237.
-// AUTO takes it up to 512 tokens for matrices of at most 2048 code blocks of 16 x 256, up to 128 tokens for at most 8192
-// (4096 x 4096 has 4096, 14336 x 4096 14336).
+// weights once per 32 sorted tokens without a pre-kernel and fills the chip with fewer columns.  Measured on cold weights,
+// stationary / prefill in us per call, from the uniform mix to {70,20,8,2} %:
+//   1024 x 4096: 12 / 23 at 65 tokens, 11 / 27..36 at 128, 16 / 34..44 at 256;  2048 x 4096: 19 / 26 at 65, 23 / 40..48 at 256;
+//   4096 x 4096: 30 / 33 at 65, 24 / 36..45 at 128;  8192 x 4096: 50 / 46 at 65, 42 / 50..53 at 128;
+//   11008 x 4096: 68 / 57..62 at 80, 54 / 58..64 at 128, as a pair 115 / 91..105 at 128;
+//   14336 x 4096: 82 / 56 and 66 / 56..63;  4096 x 14336: 98 / 58 and 81 / 59..64;  28672 x 8192: 234 / 190 and 232 / 176..202.
+// AUTO takes it up to 128 tokens for matrices of at most 8192 code blocks of 16 x 256 (8192 x 4096 has 8192), up to 512 for
+// at most 2048, and from 161 to 256 tokens for at most 4096 blocks if there are more columns than rows:
+//   2048 x 8192: 43 / 37..45 at 129, 43 / 44..52 at 160, 40 / 44..56 at 192, 43 / 48..57 at 256;
+//   2048 x 5504: 42 / 32..40 at 129, 39 / 38..48 at 192, 43 / 45..53 at 256.
+// With as many rows as columns a matrix alone would gain by it too (4096 x 4096 at 256 tokens 41 / 48..57, 3072 x 3072 30 /
+// 40..49), but has company more often than not and has to take the same kernel there: three of 4096 x 4096 take 108..115 /
+// 66..74, three of 3072 x 3072 99 / 63..67.  Tokens that are all at two bits, which only the device knows, would favour it
+// everywhere below 256 tokens (4096 x 4096 at 256: 22 / 55).
 constexpr int64_t kMaxStationaryTokens = 128, kMaxStationaryTokensSmall = 512;
-constexpr int64_t kSmallMatrixBlocks = 2048, kMiddleMatrixBlocks = 8192;
+constexpr int64_t kMinStationaryTokensNarrow = 161, kMaxStationaryTokensNarrow = 256;
+constexpr int64_t kSmallMatrixBlocks = 2048, kNarrowMatrixBlocks = 4096, kMiddleMatrixBlocks = 8192;
 constexpr int kAlgoStationary = 100;  // internal: what AUTO resolves to in those ranges
 static int resolve_auto(int64_t T, const Shape& sh) {
   if (T <= kMaxDecodeTokens) return MBQ_ALGO_DECODE;
   const int64_t blocks = (int64_t)sh.NT * sh.KB;
-  const int64_t limit = blocks <= kSmallMatrixBlocks    ? kMaxStationaryTokensSmall
-                        : blocks <= kMiddleMatrixBlocks ? kMaxStationaryTokens
-                                                        : 0;
-  return (T <= limit && knob(3) == 0 && takes_stationary_kernel(T, sh)) ? kAlgoStationary : MBQ_ALGO_PREFILL;
+  const bool stationary = T <= (blocks <= kSmallMatrixBlocks    ? kMaxStationaryTokensSmall
+                                : blocks <= kMiddleMatrixBlocks ? kMaxStationaryTokens
+                                                                : 0) ||
+                          (blocks <= kNarrowMatrixBlocks && sh.N < sh.K && T >= kMinStationaryTokensNarrow &&
+                           T <= kMaxStationaryTokensNarrow);
+  return (stationary && knob(3) == 0 && takes_stationary_kernel(T, sh)) ? kAlgoStationary : MBQ_ALGO_PREFILL;
 }
 
 // algo is DECODE (T <= 64), PREFILL, SIMPLE or kAlgoStationary here
