@@ -548,36 +548,39 @@ static Split split_into(int parts, int64_t T, int64_t K, int64_t N, int64_t area
   return Split{parts, parts <= 2 ? 1 : parts < room ? parts : (int)room};
 }
 // An estimate of a launch, in units of what a compute unit needs for two whole tiles side by side (17 ns x K): with r =
-// tiles x parts / workgroups resident at a time, the rounds cost 0.8 + 0.33 r up to one round (a workgroup alone on its
-// unit is hardly faster than one of two) and r + 0.45 beyond (tiles differ in cost and are started by falling cost, so
-// rounds are not in step); a part costs its share of the K axis and 4.5 groups for its prologue, zero-point term and
-// stores; adding costs 330 r / K, the last launch 165 / K.
+// tiles x parts / workgroups resident at a time, the rounds cost 0.82 + 0.36 r up to one round (a workgroup alone on
+// its unit is hardly faster than one of two) and 1.48 + w (r - 1) beyond (tiles differ in cost and are started by
+// falling cost, so rounds are not in step; w: below 333 tokens the tiles of four buckets are half empty); a part costs
+// its share of the K axis and eight groups for its prologue, zero-point term and stores; adding costs 350 / K for every
+// output tile's worth of rows and part over the resident workgroups, the last launch 135 / K.
 static double split_cost(Split sp, int64_t T, int64_t K, int64_t cols) {
   const int64_t rows = T / pf::kBM + 2 > 4 ? T / pf::kBM + 2 : 4;  // a bucket ends on a partial tile
-  const double r = (double)(rows * cols * sp.parts) / (2.0 * device_compute_units());
-  const double rounds = r <= 1.0 ? 0.8 + 0.33 * r : r + 0.45;
-  return rounds * (1.0 / sp.parts + 4.5 * kGroup / (double)K) + (sp.parts > 1 ? 330.0 * r / (double)K : 0.0) +
-         (sp.slots > 1 ? 165.0 / (double)K : 0.0);
+  const double column_parts = (double)(cols * sp.parts) / (2.0 * device_compute_units());
+  const double r = (double)rows * column_parts, w = T < 333 ? 0.55 + 0.45 * (double)T / 333.0 : 1.0;
+  const double rounds = r <= 1.0 ? 0.82 + 0.36 * r : 1.48 + w * (r - 1.0);
+  return rounds * (1.0 / sp.parts + 8.0 * kGroup / (double)K) +
+         (sp.parts > 1 ? 350.0 * (double)T / pf::kBM * column_parts / (double)K : 0.0) +
+         (sp.slots > 1 ? 135.0 / (double)K : 0.0);
 }
-// The cut that minimises the estimate, among those of at most `most` parts.  Fitted to 1..8 parts on twenty shapes from
-// 1000 x 2176 to 28672 x 8192, alone and in groups of two and three, at 65..4096 tokens: 0.8 % above the best cut alone on
-// average (18 % on the worst), 1.7 % (17 %) in groups.  For instance (us, 1 / 2 / 4 / 8 parts; * taken) 4096 x 11008 at 256
-// tokens 209 / 123 / 83 / 79*, at 2048 tokens 345 / 264* / 291 / -, 4096 x 4096 at 160 tokens 78 / 45 / 39*, 11008 x 4096 at
-// 256 tokens 94 / 75*, at 777 tokens 133* / 164.
-// pair: a matrix with as many rows as columns or more has company more often than not (q, k, v of an attention, gate
-// and up of a gated MLP), and one or two parts have to be the same in company and alone (choose_splits): the product
-// of the estimates alone and as a pair decides between one and two (11008 x 4096 at 256 tokens, 1 / 2 parts: alone 94
-// / 75*, as a pair 131 / 132; at 777 tokens 133* / 164 and 236 / 256; 14336 x 4096 at 256 tokens 91 / 78* and 122 /
-// 144).
+// The cut that minimises the estimate, among those of at most `most` parts. Fitted to 1..8 parts on twenty shapes from
+// 1000 x 2176 to 28672 x 8192, alone and in groups of two and three, at 65..4096 tokens: 1.0 % above the best cut alone
+// on average (17 % on the worst), 0.6 % (13 %) in groups. For instance (us, 1 / 2 / 4 / 8 parts; * taken) 4096 x 11008
+// at 256 tokens 209 / 123 / 83 / 77*, at 2048 tokens 345 / 264* / 291 / -, 4096 x 4096 at 160 tokens 78 / 45 / 39*,
+// 11008 x 4096 at 256 tokens 94 / 75*, at 777 tokens 133* / 164.
+// pairs: a matrix with as many rows as columns or more has company more often than not (q, k, v of an attention; gate
+// and up of a gated MLP, with twice as many rows or more), and one or two parts have to be the same in company and
+// alone (choose_splits): the product of the estimates alone and, `pairs` times, as a pair decides (14336 x 4096 at 160
+// tokens, 1 / 2 parts: alone 83 / 62*, as a pair 118 / 109*; at 256 tokens 91* / 78 and 122* / 144).
 // knob 5 forces the number of parts.
-static Split choose_split(int64_t T, int64_t K, int64_t N, int64_t cols, bool pair, int most, int64_t area_floats) {
+static Split choose_split(int64_t T, int64_t K, int64_t N, int64_t cols, int pairs, int most, int64_t area_floats) {
   if (knob(5) >= 1 && knob(5) <= pf::kMaxSplits) return split_into(knob(5), T, K, N, area_floats);
   Split best{1, 1};
   double best_cost = 0.0;
   for (int s = 1; s <= most; ++s) {
     const Split sp = split_into(s, T, K, N, area_floats);
     if (sp.parts != s) continue;
-    const double cost = split_cost(sp, T, K, cols) * (pair ? split_cost(sp, T, K, 2 * cols) : 1.0);
+    double cost = split_cost(sp, T, K, cols);
+    for (int i = 0; i < pairs; ++i) cost *= split_cost(sp, T, K, 2 * cols);
     if (s == 1 || cost < 0.98 * best_cost) {
       best_cost = cost;
       best = sp;
@@ -585,18 +588,18 @@ static Split choose_split(int64_t T, int64_t K, int64_t N, int64_t cols, bool pa
   }
   return best;
 }
-// The cuts of the n matrices of a call.  One or two parts: the matrix alone decides, so that a call for several matrices
-// gives the bits of separate calls.  More: a group that fills the chip needs fewer (three of 4096 x 4096 at 256 tokens: 72
-// us in two parts each, 157 in four and one launch after the other), and the matrices share the room for arrays.
+// The cuts of the n matrices of a call. One or two parts: the matrix alone decides, so that a call for several matrices
+// gives the bits of separate calls. More: a group that fills the chip needs fewer (three of 4096 x 4096 at 256 tokens:
+// 72 us in two parts each, 157 in four and one launch after the other), and the matrices share the room for arrays.
 static void choose_splits(int64_t T, int64_t K, int n, const Shape* shapes, int64_t area_floats, Split* out) {
   auto columns = [](const Shape& sh) { return (sh.N + pf::kBN - 1) / pf::kBN; };
   int64_t all = 0;
   for (int i = 0; i < n; ++i) all += columns(shapes[i]);
   for (int i = 0; i < n; ++i) {
     const int64_t N = shapes[i].N, cols = columns(shapes[i]);
-    out[i] = choose_split(T, K, N, cols, false, pf::kMaxSplits, area_floats);
-    if (N >= K && out[i].parts == 2) out[i] = choose_split(T, K, N, cols, true, 2, area_floats);
-    if (n > 1 && out[i].parts > 2) out[i] = choose_split(T, K, N, all, false, out[i].parts, area_floats / n);
+    out[i] = choose_split(T, K, N, cols, 0, pf::kMaxSplits, area_floats);
+    if (N >= K && out[i].parts == 2) out[i] = choose_split(T, K, N, cols, N >= 2 * K ? 2 : 1, 2, area_floats);
+    if (n > 1 && out[i].parts > 2) out[i] = choose_split(T, K, N, all, 0, out[i].parts, area_floats / n);
   }
 }
 
