@@ -354,11 +354,11 @@ def test_linear_single_precision_is_a_dense_gemm(mbq, algo, p):
 @pytest.mark.parametrize("N,K,T,mix", [
     (300, 128, 70, None),            # one group (no rescale), N not a multiple of 16 or 256, one ragged tile per bucket
     (520, 1152, 513, None),          # odd group count (tail pairs end on a single group), three column tiles
-    (272, 512, 300, (0.9, 0.1, 0.0, 0.0)),   # one full 256-row tile plus ragged rest in bucket 0, an empty bucket
+    (272, 512, 300, (0.9, 0.1, 0.0, 0.0)),   # full 128-row tiles plus a ragged rest in bucket 0, an empty bucket
     (256, 768, 600, (0.0, 0.0, 0.5, 0.5)),   # full tiles at precisions 2 and 3 (8-bit operand path)
 ])
 def test_prefill_tile_shapes(mbq, N, K, T, mix):
-    """Full and ragged 256-row tiles, group-boundary rescale, the fp32 zero-point tail, column padding."""
+    """Full and ragged tiles, group-boundary rescale, the fp32 zero-point tail, column padding."""
     print(f"[case] prefill tiles N={N} K={K} T={T} mix={mix}", flush=True)
     W = make_weight(N, K, [17, N, K], 4.0)
     xb = tokens(T, K, [N, K, T, 1])
@@ -372,9 +372,11 @@ def test_prefill_tile_shapes(mbq, N, K, T, mix):
 
 @pytest.mark.parametrize("counts", [(1, 16, 17, 32), (33, 64, 65, 96), (97, 128, 129, 1), (0, 0, 200, 257), (127, 0, 191, 63)])
 @pytest.mark.parametrize("Ns,K", [((257,), 128), ((16, 300), 2048), ((1, 255, 64), 4352)])
-def test_prefill_remainders_and_groups(mbq, counts, Ns, K):
-    """Buckets that end at the edges of the 16-, 32-, 64-, 96- and 128-row tiles, K of one group, of exactly one pass of
-    the zero-point update and of two passes and a rest, several matrices with orders of their own in one launch."""
+@pytest.mark.parametrize("parts", [0, 1, 2])
+def test_prefill_remainders_and_groups(mbq, counts, Ns, K, parts):
+    """Buckets that end at the edges of the 16-, 32-, 64-, 96- and 128-row tiles, several matrices with orders of their own
+    in one launch.  In one part: K of one group, of exactly one pass of the zero-point update and of two passes and a
+    rest; in two: passes half way through 8 groups and behind 16 with one group left; cut as the library chooses (0)."""
     T = sum(counts)
     xb = tokens(T, K, [T, K, 71])
     X = dev_bf16(xb).reshape(T, K)
@@ -388,10 +390,14 @@ def test_prefill_remainders_and_groups(mbq, counts, Ns, K):
         blobs.append(mbq.mbq_encode(dev(W)))
         routing.append((dev(prec), dev(perm), dev(offsets)))
         refs.append(O.linear(xb, codes, s0, z0, prec))
-    Ys = mbq.mbq_linear_group(X, blobs, list(Ns), K, routing, algo=ALGOS["prefill"])
+    mbq.set_knob(5, parts)
+    try:
+        Ys = mbq.mbq_linear_group(X, blobs, list(Ns), K, routing, algo=ALGOS["prefill"])
+    finally:
+        mbq.set_knob(5, 0)
     torch.cuda.synchronize()
     for i in range(len(Ns)):
-        assert_output_close(Ys[i].cpu().numpy(), refs[i], f"prefill group matrix {i}")
+        assert_output_close(Ys[i].cpu().numpy(), refs[i], f"prefill group matrix {i}, {parts} parts")
 
 
 def test_prefill_above_four_gibibytes_of_activations(mbq):
@@ -435,8 +441,8 @@ def test_route_group_above_128_tokens(mbq, T, K, n):
 
 @pytest.mark.parametrize("splits", [2, 3, 4, 7])
 def test_prefill_k_split(mbq, splits):
-    """The K range of a tile cut into workgroups that add their partial sums into a zeroed Y."""
-    N, K, T = 272, 2304, 300     # 18 groups: uneven split ranges
+    """The K range of a tile cut into workgroups: two that add into a cleared Y, more with arrays of their own."""
+    N, K, T = 272, 2304, 300     # 18 groups: uneven ranges, at least four groups each (seven parts become four)
     print(f"[case] prefill K split {splits}", flush=True)
     W = make_weight(N, K, [19, splits], 4.0)
     xb = tokens(T, K, [N, K, T, 2])
@@ -760,7 +766,7 @@ def test_stage_calls_on_drawn_shapes(mbq):
 
 def test_prefill_on_drawn_shapes(mbq):
     """mbq_linear above 64 tokens on seeded random shapes, automatic launch choice (including the K split that
-    launches with few tiles take from K = 8192 on): outputs against the oracle."""
+    launches with few tiles take): outputs against the oracle."""
     rng = np.random.default_rng(2029)
     shapes = [(int(rng.integers(65, 700)), int(rng.integers(1, 600)), 128 * int(rng.integers(1, 40))) for _ in range(6)]
     shapes += [(130, 272, 8192), (600, 520, 9216), (257, 40, 12288)]
@@ -777,12 +783,15 @@ def test_prefill_on_drawn_shapes(mbq):
 
 @pytest.mark.parametrize("T,K,Ns", [(65, 4096, (130,)), (96, 2304, (48,)), (128, 4096, (272,)), (100, 1024, (40,)),
                                     (128, 4352, (2064,)), (96, 4096, (272, 130, 16)), (127, 512, (48, 300)),
-                                    (80, 4352, (2064, 16)), (192, 4096, (130, 272)), (161, 2304, (48,)), (500, 1024, (300,))])
+                                    (80, 4352, (2064, 16)), (192, 4096, (130, 272)), (161, 2304, (48,)), (500, 1024, (300,)),
+                                    (129, 4352, (2064, 16, 2080)), (150, 2048, (4112, 40)), (300, 4352, (40, 2064, 300)),
+                                    (200, 4352, (2064, 16))])
 def test_automatic_choice_above_64_tokens(mbq, T, K, Ns):
     """Above 64 tokens the automatic choice still takes the register-stationary kernel (one pass per 32 sorted
-    tokens, the tokens dealt evenly to the passes) up to 128 tokens, 512 for small matrices, alone or as one launch
-    for a group; (80, 4352, (2064, 16)) mixes it with the prefill kernel inside one group call.  Group and single
-    calls against the oracle."""
+    tokens, the tokens dealt evenly to the passes) up to 128 tokens, 512 for small matrices, 161..256 for matrices with
+    more columns than rows, alone or as one launch for a group.  A matrix of more than 2048 code blocks (2064 x 4352 has
+    2193, 4112 x 2048 has 2056) takes the prefill kernel at 129..160 and above 256 tokens: those groups mix the two, the
+    prefill matrices in one launch ahead of the others.  Group and single calls against the oracle and each other."""
     print(f"[case] automatic choice T={T} K={K} Ns={Ns}", flush=True)
     xb = tokens(T, K, [T, K, 61])
     X = dev_bf16(xb).reshape(T, K)
@@ -800,8 +809,8 @@ def test_automatic_choice_above_64_tokens(mbq, T, K, Ns):
     for i, N in enumerate(Ns):
         assert_output_close(Ys[i].cpu().numpy(), refs[i], f"automatic choice matrix {i}")
         single = mbq.mbq_linear(X, blobs[i], N, K, *routing[i])
-        # (no bit-for-bit claim here: a matrix that goes to the prefill kernel may be cut into more than two parts
-        # along K, whose float atomic adds land in any order)
+        # (no bit-for-bit claim here: a matrix that goes to the prefill kernel may be cut into fewer parts along K in
+        # company than alone, where it takes more than two)
         assert_output_close(single.cpu().numpy(), refs[i], f"automatic choice matrix {i}, single call")
 
 
