@@ -134,10 +134,11 @@ mbq_status mbq_dequant(const void* blob, int64_t N, int64_t K, int p, float* Wha
  *   X      : bf16 [T][K]           Wr : fp32 [P][K]        br : fp32 [P]
  *   prec   : int32 [T] (out)       perm : int32 [T] (out)  offsets : int32 [P+1] (out)
  *   logits : fp64 [T][P] (out, may be NULL)
- *   ws     : at least mbq_route_workspace_bytes(T, K) bytes, 256-byte aligned.  It holds the
- *            counters by which the workgroups of the launch find out who is last; the call
- *            clears them itself (a small launch ahead of the router's), so the contents before
- *            the call do not matter.  Calls sharing one workspace must not overlap in time.
+ *   ws     : at least mbq_route_workspace_bytes(T, K) bytes, 256-byte aligned.  Up to 128 tokens it
+ *            holds the counters by which the workgroups of the launch find out who is last; the
+ *            call clears them itself (a small launch ahead of the router's), so the contents before
+ *            the call do not matter.  Above, a second launch sorts the tokens and nothing is kept
+ *            there.  Calls sharing one workspace must not overlap in time.
  * T = 0 is legal (offsets are zero-filled).
  */
 mbq_status mbq_route(const uint16_t* X, int64_t T, int64_t K, const float* Wr, const float* br,
@@ -146,8 +147,9 @@ mbq_status mbq_route(const uint16_t* X, int64_t T, int64_t K, const float* Wr, c
 
 /*
  * mbq_route_group - mbq_route for n_proj routers that read the SAME activations (the
- * projections of a decoder block that share their input: q/k/v, gate/up), in one launch
- * up to 128 tokens (Sec. 4.3, fused router launch for all projections of a layer).
+ * projections of a decoder block that share their input: q/k/v, gate/up), in one launch for
+ * all of them (Sec. 4.3, fused router launch for all projections of a layer); above 128 tokens a
+ * second one sorts the tokens.
  * Results are those of n_proj separate mbq_route calls, bit for bit.
  *   Wr_host, br_host, prec_host, perm_host, offsets_host : HOST arrays of n_proj DEVICE
  *   pointers, each pointing to what the argument of the same name is in mbq_route; they are
@@ -172,8 +174,8 @@ mbq_status mbq_route_group(const uint16_t* X, int64_t T, int64_t K, int n_proj,
  * untouched.
  *   X : bf16 [T][K]   W1 : fp32 [H][K]   b1 : fp32 [H]   W2 : fp32 [E][H]   b2 : fp32 [E]
  *   1 <= H <= 512, E = 4;  prec, perm, offsets as in mbq_route;  scores : fp64 [T][E] (out, may be NULL)
- *   ws : at least mbq_route_mlp_workspace_bytes(T, K, H) bytes, 256-byte aligned; its first 256 bytes
- *        hold a ticket counter (cleared by the call itself), the rest the hidden layer.
+ *   ws : at least mbq_route_mlp_workspace_bytes(T, K, H) bytes, 256-byte aligned: the hidden layer
+ *        behind 256 spare bytes; the contents before the call do not matter.
  * T = 0 is legal.
  */
 size_t mbq_route_mlp_workspace_bytes(int64_t T, int64_t K, int H);
@@ -245,7 +247,8 @@ mbq_status mbq_linear_static(const uint16_t* X, int64_t T, const void* blob, int
  * activations (q/k/v, gate/up of a decoder block), each with its own routing; one launch for all
  * of them while every matrix takes a decode kernel (up to 64 tokens, 128 with AUTO on matrices
  * that keep the register-stationary kernel; Sec. 4.3, fused launch for the projections of a
- * layer), otherwise one launch sequence per matrix.  Results are those of n_proj separate
+ * layer); the matrices that take the tiled GEMM share its launches too, the others follow one by
+ * one.  Results are those of n_proj separate
  * mbq_linear calls (bit for bit but for one case of the tiled GEMM, see Reproducibility there).
  *   blob_host, prec_host, perm_host, offsets_host, Y_host : HOST arrays of n_proj DEVICE
  *   pointers (meaning as in mbq_linear); N_host : HOST array of the n_proj row counts.  The
@@ -410,9 +413,13 @@ mbq_status mbq_act_quant(const uint16_t* X, int64_t T, int64_t K, int abits, con
 mbq_status mbq_scale_rows(float* Y, int64_t T, int64_t N, const float* row_scale, const float* bias, void* stream);
 /*
  * One stage of the variant in one call: mbq_act_quant on X, mbq_routed_linear_group with the routers reading Xr and
- * the linear kernels Xint (up to 16 tokens the router launch prepares Xint for the decode kernel as it prepares X in
- * the weight-only stage), then the row scaling and bias of all projections in one launch - four launches where the
- * weight-only stage has two.  Same results as the separate calls, bit for bit.
+ * the linear kernels Xint, then the row scaling and bias of all projections.  Where the stage takes decode kernels (up
+ * to 16 tokens; to 128 while every matrix keeps the register-stationary one) and K <= 16384, the router launch quantises
+ * the activations itself, and where the linear launch of up to 16 tokens works on K in one part (K <= 4096) it scales the
+ * rows itself: two launches, as the weight-only stage has, or three.  Otherwise the quantiser and the row scaling are
+ * launches of their own around those of the weight-only stage.  Same results as the separate calls, bit for bit.
+ * The quantiser is done with X, let_shift and let_scale before anything but Xint, row_scale and Xr is written: outputs,
+ * routing arrays and workspaces may lie over them (the quantiser then takes its own launch).
  *   bias_host : host array of n_proj device pointers, fp32 [N_i] each; the array or any entry may be NULL
  *   Xint, row_scale, Xr : as in mbq_act_quant, all three required (T > 0); they are outputs the caller may read
  *   everything else as in mbq_act_quant and mbq_routed_linear_group; on failure some launches may already have been

@@ -214,7 +214,7 @@ def mbq_dequant(blob: torch.Tensor, N: int, K: int, p: int) -> torch.Tensor:
 
 
 def route_workspace(T: int, K: int, device) -> torch.Tensor:
-    # the call clears the counters it keeps there itself: the contents do not matter
+    # the call clears what it keeps there itself: the contents do not matter
     return torch.empty(load().mbq_route_workspace_bytes(T, K), dtype=torch.uint8, device=device)
 
 
@@ -245,7 +245,7 @@ def mbq_route(X: torch.Tensor, Wr: torch.Tensor, br: torch.Tensor, want_logits: 
 
 
 def route_mlp_workspace(T: int, K: int, H: int, device) -> torch.Tensor:
-    """Workspace of mbq_route_mlp (ticket counter, cleared by the call, + hidden layer)."""
+    """Workspace of mbq_route_mlp (the hidden layer)."""
     n = load().mbq_route_mlp_workspace_bytes(T, K, H)
     return torch.empty(max(int(n), 256), dtype=torch.uint8, device=device)
 

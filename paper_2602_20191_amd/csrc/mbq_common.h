@@ -154,7 +154,6 @@ mbq_status launch_linear_decode16_group(const uint16_t* X, int64_t T, int n, con
 bool decode_f4_supports(int64_t T, const Shape& sh);
 int decode_f4_k_parts(int n, const Shape* shapes);
 void decode_f4_zero_list(int64_t T, int n, const Shape* shapes, float* const* Y, ZeroList* zl);
-// share `part` of `parts` of the clearing, done by `nthreads` threads of which this is `tid`
 // A 16-byte load of data that a launch reads once (packed weights in the decode kernels), with the
 // non-temporal hint: the stream then does not push the activations, router parameters and outputs that
 // the neighbouring launches share out of the caches.
@@ -163,6 +162,7 @@ __device__ __forceinline__ uint4 load_once(const uint4* p) {
   const u32x4_nt v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_nt*>(p));
   return uint4{v.x, v.y, v.z, v.w};
 }
+// share `part` of `parts` of the clearing, done by `nthreads` threads of which this is `tid`
 __device__ inline void zero_share(const ZeroList& zl, int part, int parts, int tid, int nthreads) {
 #pragma unroll
   for (int j = 0; j < MBQ_MAX_GROUP; ++j) {
