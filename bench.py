@@ -38,9 +38,9 @@ STAGES = (("q", "k", "v"), ("o",), ("gate", "up"), ("down",))   # projections th
 # WRITE_SIZE runs of `bench.py --probe decode`, scaled by what the same counters read for a plain 256 MiB copy
 # (FETCH_SIZE x2.000, WRITE_SIZE x1.000); see profiles/decode_linear_hbm_traffic_llama2_7b_batch16.txt
 MEASURED_TRAFFIC_BYTES_PER_LAUNCH = {16: 53.10e6}
-# HBM bytes per mbq_linear call (group-sum pre-kernel + tile kernel), mean over the three linears, same counters and scale
+# HBM bytes per mbq_linear call (pre-kernel + tile kernel), mean over the three linears, same counters and scale
 # factors from `bench.py --probe prefill` / `--probe prefill70b`; see profiles/prefill_hbm_traffic.txt
-MEASURED_PREFILL_TRAFFIC_BYTES_PER_CALL = {"configs[2]": 773.1e6, "70b": 4169.7e6}
+MEASURED_PREFILL_TRAFFIC_BYTES_PER_CALL = {"configs[2]": 674.9e6, "70b": 4143.0e6}
 
 
 def algorithmic_bytes(N, K, T, pmax):
@@ -610,7 +610,7 @@ def extra_measurements(mbq, torch, dev, cfg, layers, stages, T_main):
                                         routing=st["routing"], Y=st["Y"], ws_route=st["ws_r"], ws_linear=st["ws_l"])
         torch.cuda.synchronize()
     # the prefill linears of BASELINE configs[2] (gate, up, down; 2048 tokens), each as the whole mbq_linear call
-    # (gather/group-sum pre-kernel + tile kernel) timed with HIP events over back-to-back launches
+    # (group-sum pre-kernel + tile kernel) timed with HIP events over back-to-back launches
     pcfg = CONFIGS[2]
     T = pcfg.token_counts[0]
     per_linear, flops_sum, ms_sum, route_sum = {}, 0.0, 0.0, 0.0

@@ -33,10 +33,11 @@
 //     used to hold a compute unit as long as 256 tokens: four such remainders set the time below 1024 tokens).
 //   * Rows are fetched through the permutation (16 lanes read 256 bytes of one token), so no sorted copy is made.
 // Whole calls, before and now: 11008 x 4096 at 2048 tokens, {50,30,15,5} % mix 271 -> 245 us (755 TFLOP/s; all tokens at
-// 2 bits 264 -> 207 us), 4096 x 11008 378 -> 277 us, 28672 x 8192 at 4096 tokens, {70,20,8,2} % mix 2146 -> 1871 us (1029
-// TFLOP/s; a dense bf16 library product reaches 1383 on this card), 8192 x 28672 2565 -> 1976 us; at 256 tokens 457 -> 290
-// and 487 -> 264 us.  Bound by instruction issue at 8 bits (15/4 vector instructions a weight) and otherwise by what two
-// workgroups hide of each other's barriers and unpacking.
+// 2 bits 264 -> 207 us), 4096 x 11008 378 -> 262 us, 28672 x 8192 at 4096 tokens, {70,20,8,2} % mix 2146 -> 1871 us (1029
+// TFLOP/s; a dense bf16 library product reaches 1383 on this card), 8192 x 28672 2565 -> 1935 us; at 256 tokens 457 -> 270
+// and 487 -> 259 us.  Bound by instruction issue: on the two large shapes MFMAs and other vector instructions together take
+// 81-87 % of the SIMD time and hardly overlap (counters; 2.8 vector instructions per MFMA at 2 bits, 5.8 at 8), two
+// wavefronts a SIMD, each waiting 36-47 % of its cycles at barriers and for its operands.
 #include "mbq_common.h"
 
 namespace mbq {
