@@ -488,6 +488,41 @@ def test_prefill_parts_in_arrays_of_their_own(mbq, parts, T, Ns):
         assert torch.equal(Ys[i], again[i]), i
 
 
+@pytest.mark.parametrize("parts", [2, 6])
+def test_prefill_parts_replay_from_a_hip_graph(mbq, parts):
+    """A captured call that clears arrays, adds into them and adds them up, replayed with eager work of the same kind in
+    its workspace and outputs between the replays: the eager call's bits every time."""
+    N, K, T = 999, 4608, 301
+    xb = tokens(T, K, [T, K, 107])
+    X = dev_bf16(xb).reshape(T, K)
+    blob = mbq.mbq_encode(dev(make_weight(N, K, [107], 4.0)))
+    prec = np.random.default_rng([107]).integers(0, 4, size=T).astype(np.int32)
+    perm, offsets = O.bucket(prec)
+    r = (dev(prec), dev(perm), dev(offsets))
+    X2, r2 = X.flip(0).contiguous(), tuple(dev(v) for v in (prec[::-1].copy(), *O.bucket(prec[::-1])))
+    Y, ws = torch.empty((T, N), dtype=torch.float32, device="cuda"), mbq.linear_workspace(T, N, K, "cuda")
+    mbq.set_knob(5, parts)
+    try:
+        want = mbq.mbq_linear(X, blob, N, K, *r, algo=ALGOS["prefill"])
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.stream(side):
+            mbq.mbq_linear(X, blob, N, K, *r, Y=Y, ws=ws, algo=ALGOS["prefill"])
+        torch.cuda.current_stream().wait_stream(side)
+        with torch.cuda.graph(g):
+            mbq.mbq_linear(X, blob, N, K, *r, Y=Y, ws=ws, algo=ALGOS["prefill"])
+        for _ in range(4):
+            mbq.mbq_linear(X2, blob, N, K, *r2, Y=Y, ws=ws, algo=ALGOS["prefill"])
+            torch.cuda.synchronize()
+            assert not torch.equal(Y, want)
+            g.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(Y, want)
+    finally:
+        mbq.set_knob(5, 0)
+
+
 @pytest.mark.parametrize("Ns,K,T", [
     ((14336, 14336), 4096, 96), ((14336, 14336), 4096, 256), ((11008, 11008), 4096, 384), ((11008, 11008), 4096, 777),
     ((13824, 13824), 5120, 256), ((4096, 4096), 4096, 512), ((11008,), 4096, 96), ((11008,), 4096, 256),
