@@ -87,7 +87,7 @@ def test_stage_of_the_variant(mbq, abits, T, K, Ns):
     for Y, B in zip(Ys, Bt):
         mbq.mbq_scale_rows(Y, row_scale, dev(B))
     torch.cuda.synchronize()
-    # the stage as one call: the same numbers, bit for bit (above 64 tokens the tiled GEMM may add K parts in any order)
+    # the stage as one call: the same numbers, bit for bit
     routing1, Ys1, act1 = mbq.mbq_routed_linear_group_act(X, abits, dev(delta), dev(s), [dev(w) for w in Wrs],
                                                           [dev(b) for b in brs], blobs, list(Ns),
                                                           bias=[dev(B) for B in Bt])
@@ -96,10 +96,7 @@ def test_stage_of_the_variant(mbq, abits, T, K, Ns):
     for i in range(len(Ns)):
         for a_, b_ in zip(routing1[i], routing[i]):
             assert torch.equal(a_, b_), i
-        if T <= 64:
-            assert torch.equal(Ys1[i], Ys[i]), i
-        else:
-            assert_output_close(Ys1[i].cpu().numpy(), Ys[i].double().cpu().numpy(), f"one call vs separate calls {i}")
+        assert torch.equal(Ys1[i], Ys[i]), i
     # oracle
     xint, scale, zp, q = A.act_quant(A.let_transform(xb, delta, s), abits)
     xr_bits = A.router_input_bits(xint, scale, delta, s)

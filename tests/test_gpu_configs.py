@@ -119,7 +119,7 @@ def test_stage_call_under_a_configuration(mbq, bits, T, K, Ns):
     for i, N in enumerate(Ns):
         for a, b in zip(routing[i], routing2[i]):
             assert torch.equal(a, b), i
-        assert torch.equal(Ys[i], Ys2[i]) or T > 64, i       # (the tiled GEMM may add K parts in any order)
+        assert torch.equal(Ys[i], Ys2[i]), i
         prec = routing[i][0].cpu().numpy()
         if E > 1:
             _, prec_ref, gap = O.route(xb, Wrs[i], brs[i])
