@@ -32,12 +32,16 @@
 //   * Remainders of a bucket run the same loop with 2, 4 or 6 row tiles instead of 8 (a bucket's last 16..32 tokens
 //     used to hold a compute unit as long as 256 tokens: four such remainders set the time below 1024 tokens).
 //   * Rows are fetched through the permutation (16 lanes read 256 bytes of one token), so no sorted copy is made.
-// Whole calls, before and now: 11008 x 4096 at 2048 tokens, {50,30,15,5} % mix 271 -> 245 us (755 TFLOP/s; all tokens at
-// 2 bits 264 -> 207 us), 4096 x 11008 378 -> 262 us, 28672 x 8192 at 4096 tokens, {70,20,8,2} % mix 2146 -> 1871 us (1029
-// TFLOP/s; a dense bf16 library product reaches 1383 on this card), 8192 x 28672 2565 -> 1935 us; at 256 tokens 457 -> 270
-// and 487 -> 259 us.  Bound by instruction issue: on the two large shapes MFMAs and other vector instructions together take
-// 81-87 % of the SIMD time and hardly overlap (counters; 2.8 vector instructions per MFMA at 2 bits, 5.8 at 8), two
-// wavefronts a SIMD, each waiting 36-47 % of its cycles at barriers and for its operands.
+//   * A wavefront alone issues a vector instruction every 7 cycles, two share a SIMD at 4.6 for most of the unpacking's
+//     (measured), and an MFMA of 16 cycles hides two of them but not four: so unpacking and rescaling are dealt out under
+//     the MFMAs one column tile later (`spread`), and nothing but those stands in the group loop.
+//   * What a tile costs besides its groups matters at K = 4096 and where a launch is one round: its row sums come through
+//     LDS, its rows leave through LDS (see load_sums and the stores): 16400 + 8000 cycles -> 7500 + 1000 a tile.
+// Whole calls on one box, before these two and now: 11008 x 4096 at 2048 tokens, {50,30,15,5} % mix 248 -> 234 us (788
+// TFLOP/s), all tokens at 2 bits 210 -> 193 us, at 8 bits 335 -> 304 us; 28672 x 8192 at 4096 tokens, {70,20,8,2} % mix
+// 1912 -> 1849 us (1040 TFLOP/s; a dense bf16 library product reaches 1383 on this card), at 256 tokens 304 -> 289 us; 3000
+// x 2176 at 777 tokens 56 -> 48 us.  Bound by instruction issue and the clock, which falls to 1.9 GHz under this load: two
+// workgroups on a compute unit take 6700 cycles for a group each, of which 4350 are MFMAs; one alone takes 4850.
 #include "mbq_common.h"
 
 namespace mbq {
@@ -53,7 +57,8 @@ constexpr int kBM = 128, kBN = 256;
 
 constexpr int kRowBytes = 2 * kGroup;         // one group of one token: 16 chunks of 16 bytes, swizzled by the row
 constexpr int kStageBytes = kBM * kRowBytes;  // 32 KiB, two stages
-constexpr int kOffsetBytes = 8 * 256 * 4;     // row offsets of the 8-bit tiles
+constexpr int kSumsBytes = kBM * 16 * 4;      // group sums of the tile's rows, 16 groups at a time
+constexpr int kRowsBytes = 2 * kBM * 4;       // tokens of the rows, byte offsets of their activations
 constexpr int kPadRows = 256;                 // rows of the workspace beyond those of the activations
 constexpr int kMaxSplits = 8;
 
@@ -177,9 +182,32 @@ __device__ __forceinline__ void dma_16(uint32_t lds, uint32_t offset, const void
                : "memory");
 }
 
-struct __attribute__((packed, aligned(4))) Sums4 {
-  float s[4];
-};
+// the same with 4 bytes per lane and an address of its own
+__device__ __forceinline__ void dma_4(uint32_t lds, const void* address) {
+  uint32_t m0;
+  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %2, off\n\ts_mov_b32 m0, %0"
+               : "=&s"(m0)
+               : "s"(lds), "v"(address)
+               : "memory");
+}
+
+// scheduling hint: the region's MFMAs one by one, `each` vector instructions behind every one of them
+template <int MFMAS>
+__device__ __forceinline__ void spread(int each) {
+#define MBQ_SPREAD(n)                                         \
+  case n:                                                     \
+    _Pragma("unroll") for (int a = 0; a < MFMAS; ++a) {       \
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      \
+      __builtin_amdgcn_sched_group_barrier(0x002, n, 0);      \
+    }                                                         \
+    break;
+  switch (each) {
+    MBQ_SPREAD(2) MBQ_SPREAD(3) MBQ_SPREAD(4) MBQ_SPREAD(5) MBQ_SPREAD(6) MBQ_SPREAD(7) MBQ_SPREAD(8) MBQ_SPREAD(9)
+    MBQ_SPREAD(10) MBQ_SPREAD(11) MBQ_SPREAD(12)
+    default: break;
+  }
+#undef MBQ_SPREAD
+}
 
 // One tile: rows row0 .. row0 + rows - 1 of the sorted tokens, columns 256 ntile_n ..; groups g0 .. g0 + G - 1.
 // P = precision index of the tokens, MR = 16-row tiles (16 MR >= rows).
@@ -201,17 +229,23 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
   // 4 wave + 16 j + kq.  LDS chunk l15 of a row holds its chunk l15 ^ (row & 15), so the 16 rows of a fragment read
   // hit different banks.  Rows past the tile repeat its last row. ----
   const uint16_t* xbase = (gather ? X : X + (int64_t)row0 * K) + (int64_t)g0 * kGroup;
-  // P = 3 keeps the lane's row offsets in LDS: its unpacking leaves no registers for them.
+  // The tokens of the rows and where their activations begin wait in LDS: the zero-point term and the stores need the
+  // former, P = 3 reads the latter at every group (its unpacking leaves no registers for them).
   constexpr bool kOffLds = P == 3 && MR == 8;
-  uint32_t* const s_off = reinterpret_cast<uint32_t*>(smem + 2 * kStageBytes) + tid;
+  float* const s_sum = reinterpret_cast<float*>(smem + 2 * kStageBytes);
+  int* const s_token = reinterpret_cast<int*>(smem + 2 * kStageBytes + kSumsBytes);
+  uint32_t* const s_row = reinterpret_cast<uint32_t*>(s_token + kBM);
+  if (tid < 16 * MR) {
+    const int r = min(tid, rows - 1), token = perm[row0 + r];
+    s_token[tid] = token;
+    s_row[tid] = 2u * (uint32_t)(gather ? token : r) * (uint32_t)K;
+  }
+  __syncthreads();
+  const uint32_t a_chunk = 16u * (uint32_t)(l15 ^ (4 * wave + kq));
   uint32_t a_off[kOffLds ? 1 : MR];
+  if constexpr (!kOffLds) {
 #pragma unroll
-  for (int j = 0; j < MR; ++j) {
-    const int r = min(4 * wave + 16 * j + kq, rows - 1);
-    const uint32_t row = gather ? (uint32_t)perm[row0 + r] : (uint32_t)r;
-    const uint32_t o = 2u * (row * (uint32_t)K + 8u * (uint32_t)(l15 ^ (4 * wave + kq)));
-    if constexpr (kOffLds) s_off[256 * j] = o;
-    else a_off[j] = o;
+    for (int j = 0; j < MR; ++j) a_off[j] = s_row[4 * wave + 16 * j + kq] + a_chunk;
   }
   const uint32_t lds0 =
       (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)smem + (uint32_t)(4 * wave * kRowBytes);
@@ -219,7 +253,7 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
     const uint16_t* src = xbase + (int64_t)g * kGroup;
 #pragma unroll
     for (int j = 0; j < MR; ++j)
-      dma_16(lds0 + stage + (uint32_t)(j * 16 * kRowBytes), kOffLds ? s_off[256 * j] : a_off[kOffLds ? 0 : j], src);
+      dma_16(lds0 + stage + (uint32_t)(j * 16 * kRowBytes), kOffLds ? s_row[4 * wave + 16 * j + kq] + a_chunk : a_off[kOffLds ? 0 : j], src);
   };
   // ---- B: this wavefront's four column tiles of 16; two dwords a lane, tile, slice and group ----
   const uint32_t* wptr[4];
@@ -304,7 +338,17 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
   // them, 0.74e-6 half way, 0.70e-6 in four parts).  Taken for parts of at most 16 groups, which replace twice as many
   // parts where there is no room for those; long parts lose up to 7 % by it (8192 x 28672 at 256 tokens 263 -> 282 us: the
   // scales of groups to come are not in cache yet).
+  // The rows' sums of 16 groups come to LDS at the beginning of these groups ([row][16], by four bytes a lane: a token's
+  // sums need not be aligned) and are there at the first barrier behind.  Fetched where they are used, token by token and
+  // then sum by sum, they took a dozen trips to memory one after the other: about 8 us a tile.
   const int Gtot = (int)(K / kGroup);
+  auto load_sums = [&](int g) {
+    const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)smem + 2 * kStageBytes;
+    const float* src = Sx + g0 + min(g + l15, G - 1);
+#pragma unroll
+    for (int j = 0; j < MR; ++j)
+      dma_4(lds + (uint32_t)((4 * wave + 16 * j) * 64), src + (int64_t)s_token[4 * wave + 16 * j + kq] * Gtot);
+  };
   auto remove_offsets = [&](int g, int last) {
     constexpr float kC = (kHalf - kOff) * (1.f / 64.f);
     float bv[4][4];
@@ -318,26 +362,15 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
         bv[s][c] = (g + 4 * kq + s < last) ? mt.x * (kC - mt.y) * units : 0.f;
       }
     }
-    // the four sums of a lane in one load (a token's sums are contiguous; the last pass may read into the next token's
-    // or, behind the last token, into the rest of the workspace: replaced by zeros)
-    constexpr int RR = MR < 4 ? MR : 2;  // row tiles at a time (registers)
 #pragma unroll
-    for (int a0 = 0; a0 < MR; a0 += RR) {
-      Sums4 av[RR];
+    for (int a = 0; a < MR; ++a) {
+      const floatx4 av = *reinterpret_cast<const floatx4*>(s_sum + (16 * a + l15) * 16 + 4 * kq);
 #pragma unroll
-      for (int a = 0; a < RR; ++a) {
-        const int token = perm[row0 + min(16 * (a0 + a) + l15, rows - 1)];
-        av[a] = *reinterpret_cast<const Sums4*>(Sx + (int64_t)token * Gtot + g0 + g + 4 * kq);
+      for (int s = 0; s < 4; ++s) {
+        const float v = (g + 4 * kq + s < last) ? av[s] : 0.f;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[a][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(v, bv[s][c], acc[a][c], 0, 0, 0);
       }
-#pragma unroll
-      for (int a = 0; a < RR; ++a)
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          const float v = (g + 4 * kq + s < last) ? av[a].s[s] : 0.f;
-#pragma unroll
-          for (int c = 0; c < 4; ++c)
-            acc[a0 + a][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(v, bv[s][c], acc[a0 + a][c], 0, 0, 0);
-        }
     }
   };
 
@@ -347,6 +380,10 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
   for (int first = 0; first < G + 16; first += 16) {
     const int last = min(G, first + 16);
     const int stop = first < G && halfway ? (first + last + 1) >> 1 : last;
+    if (first < G) {
+      if (first > 0) asm volatile("s_barrier" ::: "memory");  // every wavefront has used the sums before these
+      load_sums(first);
+    }
 #pragma unroll 1
     for (; q < stop; ++q) {
       // the next group on its way (the last group is requested once more: the other stage is free)
@@ -361,7 +398,9 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
         b_x[c] = (P == 3) ? ((E - 8u) << 23) : ((E >> 1) * 0x01010101u);
         const float r = m_cur[c] * __builtin_amdgcn_rcpf(scale_mantissa(s_cur[c]));
         ratio[c] = (q > 0) ? r : 1.f;
-        m_cur[c] = m_cur[c] / ratio[c];  // the factor actually in force (keeps the chain consistent)
+        // the factor actually in force (keeps the chain consistent): m / ratio, to the last bit or two
+        const float inv = __builtin_amdgcn_rcpf(ratio[c]), quot = m_cur[c] * inv;
+        m_cur[c] = __builtin_fmaf(__builtin_fmaf(-quot, ratio[c], m_cur[c]), inv, quot);
       }
       // fragment of row tile a, step h: row 16 a + l15, chunk 4 h + kq
       auto read_a = [&](int h, int a) -> u32x4 {
@@ -371,13 +410,21 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
       // HR row tiles at a time, their fragments read one part ahead; the operand of column tile c of the next step is
       // unpacked into the same registers right behind the last MFMAs that read it.  A scheduling fence per column tile
       // keeps the registers of one part alive at a time: without it the compiler hoists unpacking and spills.
-      constexpr int HR = MR < 4 ? MR : (P >= 2 || MR == 6) ? 2 : 4;
+      constexpr int HR = (P == 3 && MR == 8) ? 1 : MR < 4 ? MR : (P >= 2 || MR == 6) ? 2 : 4;
       constexpr int kParts = MR / HR;
+      constexpr bool kUnder = P < 3;
       u32x4 af[2][HR], bf[4];
 #pragma unroll
       for (int a = 0; a < HR; ++a) af[0][a] = read_a(0, a);
 #pragma unroll
       for (int c = 0; c < 4; ++c) bf[c] = unpack(0, c);
+      auto rescale = [&](int part, int c) {  // to the units of this group
+#pragma unroll
+        for (int a = 0; a < HR; ++a)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc[part * HR + a][c][i] *= ratio[c];
+      };
+      if (kUnder) rescale(0, 0);
 #pragma unroll
       for (int hp = 0; hp < 4 * kParts; ++hp) {
         const int h = hp / kParts, part = hp % kParts;
@@ -387,16 +434,21 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
         }
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
+          if (!kUnder && h == 0) rescale(part, c);
 #pragma unroll
-          for (int a = 0; a < HR; ++a) {
-            floatx4& d = acc[part * HR + a][c];
-            if (h == 0) {
-#pragma unroll
-              for (int i = 0; i < 4; ++i) d[i] *= ratio[c];
-            }
-            d = mfma(af[hp & 1][a], bf[c], d);
+          for (int a = 0; a < HR; ++a) acc[part * HR + a][c] = mfma(af[hp & 1][a], bf[c], acc[part * HR + a][c]);
+          if constexpr (!kUnder) {
+            if (part == kParts - 1 && h < 3) bf[c] = unpack(h + 1, c);
+          } else {
+            // under these MFMAs: the operand whose last MFMAs were issued one column tile ago, the next tiles' units
+            const bool un = (part == kParts - 1 && c > 0 && h < 3) || (part == 0 && c == 0 && h > 0);
+            if (part == kParts - 1 && c > 0 && h < 3) bf[c - 1] = unpack(h + 1, c - 1);
+            if (part == 0 && c == 0 && h > 0) bf[3] = unpack(h, 3);
+            const bool re = h == 0 && (c < 3 || part + 1 < kParts);
+            if (re) rescale(c < 3 ? part : part + 1, (c + 1) & 3);
+            const int each = ((un ? 8 + 2 * P : 0) + (re ? 4 * HR : 0) + HR - 1) / HR;  // vector instructions per MFMA
+            spread<HR>(each);
           }
-          if (part == kParts - 1 && h < 3) bf[c] = unpack(h + 1, c);
           __builtin_amdgcn_sched_barrier(0);
         }
       }
@@ -416,38 +468,53 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
     if (first < G) remove_offsets(first, last);
   }
 
-  // ---- true units ----
+  // ---- rows in original token order.  A lane holds rows 16 a + 4 kq + i, columns 16 c + l15: stored from there an
+  // instruction writes four pieces of 64 bytes, 32 cycles each (16400 cycles a tile).  So a row tile goes through the
+  // wavefront's own part of the stages (free behind the last barrier; LDS operations of a wavefront execute in order): an
+  // instruction then writes four rows of 256 bytes, or one where rows are not 16-byte aligned or two parts of K add. ----
+  constexpr int kRow = 64 + 4;  // floats between rows
+  float* const own = reinterpret_cast<float*>(smem) + wave * (16 * kRow);
+  const int64_t col0 = (int64_t)ntile_n * kBN + 64 * wave;
+  const bool wide = !accumulate && (M.N & 3) == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0;
+  float f[4];
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    const float f = m_cur[c] * (1.f / 64.f);
+  for (int c = 0; c < 4; ++c) f[c] = m_cur[c] * (1.f / 64.f);  // true units
 #pragma unroll
-    for (int a = 0; a < MR; ++a)
+  for (int a = 0; a < MR; ++a) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) acc[a][c][i] *= f;
-  }
-
-  // ---- rows in original token order: lane holds rows 16 a + 4 kq + i, columns 16 c + l15 ----
-  const int64_t col0 = (int64_t)ntile_n * kBN + 64 * wave + l15;
+    for (int c = 0; c < 4; ++c)
 #pragma unroll
-  for (int a = 0; a < MR; ++a)
+      for (int i = 0; i < 4; ++i) own[(4 * kq + i) * kRow + 16 * c + l15] = acc[a][c][i] * f[c];
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    if (wide) {
+      floatx4 v[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int r = 16 * a + 4 * kq + i;
-      if (r < rows) {
-        float* y = out + (int64_t)perm[row0 + r] * M.N + col0;
+      for (int i = 0; i < 4; ++i) v[i] = *reinterpret_cast<const floatx4*>(own + (4 * i + kq) * kRow + 4 * l15);
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-          if (col0 + 16 * c < M.N) {
-            if (accumulate) unsafeAtomicAdd(y + 16 * c, acc[a][c][i]);  // cleared by the pre-kernel
-            else y[16 * c] = acc[a][c][i];
-          }
+      for (int i = 0; i < 4; ++i) {
+        const int r = 16 * a + 4 * i + kq;
+        if (r < rows && col0 + 4 * l15 < M.N)
+          *reinterpret_cast<floatx4*>(out + (int64_t)s_token[r] * M.N + col0 + 4 * l15) = v[i];
+      }
+    } else if (col0 + lane < M.N) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int r = 16 * a + i;
+        if (r < rows) {
+          float* y = out + (int64_t)s_token[r] * M.N + col0 + lane;
+          const float v = own[i * kRow + lane];
+          if (accumulate) unsafeAtomicAdd(y, v);  // cleared by the pre-kernel
+          else *y = v;
+        }
       }
     }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  }
 }
 
 __global__ __launch_bounds__(256, 2) void prefill_kernel(const uint16_t* __restrict__ X, int64_t K, int KB, int gather,
                                                          const float* __restrict__ Sx, const Group grp) {
-  __shared__ __attribute__((aligned(1024))) char smem[2 * kStageBytes + kOffsetBytes];
+  __shared__ __attribute__((aligned(1024))) char smem[2 * kStageBytes + kSumsBytes + kRowsBytes];
   int j = 0;
 #pragma unroll
   for (int i = 1; i < MBQ_MAX_GROUP; ++i)

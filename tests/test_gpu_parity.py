@@ -488,6 +488,30 @@ def test_prefill_parts_in_arrays_of_their_own(mbq, parts, T, Ns):
         assert torch.equal(Ys[i], again[i]), i
 
 
+@pytest.mark.parametrize("groups", [1, 2, 15, 16, 17, 32, 33])
+@pytest.mark.parametrize("parts", [1, 2])
+def test_prefill_windows_of_row_sums(mbq, groups, parts):
+    """The rows' sums come in windows of 16 groups: lengths around one and two windows, parts that begin inside a window,
+    every row-tile count, outputs that allow 16-byte stores and the same numbers where they do not."""
+    K, N, T = 128 * groups, 276, 1 + 40 + 70 + 128
+    xb = tokens(T, K, [T, K, 131])
+    W = make_weight(N, K, [131, K], 4.0)
+    codes, s0, z0 = O.encode(W)
+    prec = np.random.default_rng([131]).permutation(np.repeat(np.arange(4), (1, 40, 70, 128))).astype(np.int32)
+    perm, offsets = O.bucket(prec)
+    X, blob, r = dev_bf16(xb).reshape(T, K), mbq.mbq_encode(dev(W)), (dev(prec), dev(perm), dev(offsets))
+    shifted = torch.full((T * N + 1,), float("nan"), device="cuda")[1:].view(T, N)
+    mbq.set_knob(5, parts)
+    try:
+        Y = mbq.mbq_linear(X, blob, N, K, *r, algo=ALGOS["prefill"])
+        mbq.mbq_linear(X, blob, N, K, *r, Y=shifted, algo=ALGOS["prefill"])
+    finally:
+        mbq.set_knob(5, 0)
+    torch.cuda.synchronize()
+    assert_output_close(Y.cpu().numpy(), O.linear(xb, codes, s0, z0, prec), f"{groups} groups, {parts} parts")
+    assert torch.equal(Y, shifted)
+
+
 @pytest.mark.parametrize("parts", [2, 6])
 def test_prefill_parts_replay_from_a_hip_graph(mbq, parts):
     """A captured call that clears arrays, adds into them and adds them up, replayed with eager work of the same kind in
