@@ -224,6 +224,10 @@ static int resolve_auto(int64_t T, const Shape& sh) {
   return (stationary && knob(3) == 0 && takes_stationary_kernel(T, sh)) ? kAlgoStationary : MBQ_ALGO_PREFILL;
 }
 
+static bool takes_mid_kernel(int64_t T, const Shape& sh) {
+  return knob(3) == 0 && mid_parts(T, sh) > 0;
+}
+
 // algo is DECODE (T <= 64), PREFILL, SIMPLE or kAlgoStationary here
 mbq_status dispatch_linear(const uint16_t* X, int64_t T, const void* blob, const Shape& sh, const int32_t* prec,
                            const int32_t* perm, const int32_t* offsets, float* Y, void* ws, int algo,
@@ -250,6 +254,11 @@ mbq_status dispatch_linear(const uint16_t* X, int64_t T, const void* blob, const
         mbq_status st = launch_decode_f4_prep(X, T, sh.K, sh.KB, ws, zl, s);
         if (st != MBQ_OK) return st;
         return launch_linear_decode_f4(T, 1, &blob, &sh, &prec, &Y, ws, s, nullptr, nullptr);
+      }
+      if (takes_mid_kernel(T, sh)) {
+        mbq_status st = launch_mid_sums(X, T, sh.K, ws, s);
+        if (st != MBQ_OK) return st;
+        return launch_linear_mid_group(X, T, 1, &blob, &sh, &prec, &perm, &Y, ws, s, nullptr, nullptr);
       }
       if (takes_stationary_kernel(T, sh)) {
         ZeroList zl;
@@ -610,12 +619,30 @@ mbq_status mbq_routed_linear_group(const uint16_t* X, int64_t T, int64_t K, int 
     }
     // up to 128 tokens with every matrix on the register-stationary kernel: the router launch only writes the
     // precisions (no meeting of its workgroups), the linear launch sorts the tokens itself
+    // wide matrices and long rows at 33 to 64 tokens: the router launch also leaves the sums that the linear kernel starts
+    // from, and that kernel sorts the tokens itself
+    bool all_mid = ok;
+    for (int i = 0; all_mid && i < n_proj; ++i) all_mid = takes_mid_kernel(T, sh[i]);
+    if (all_mid && route_defers_sort(T)) {
+      mbq_status st = act_ahead(T, K, n_proj, prec_host, Y_host, N_host, ws_linear, ws_linear_bytes, &aq,
+                                (hipStream_t)stream);
+      if (st != MBQ_OK) return st;
+      const bool sums_here = t_act && !aq;  // the routers read the rebuilt activations, the linear launch the integers
+      st = launch_route_group(X, T, K, n_proj, Wr_host, br_host, prec_host, perm_host, offsets_host, nullptr, ws_route,
+                              (hipStream_t)stream, nullptr, 0, nullptr, true, *t_view, nullptr, aq,
+                              sums_here ? nullptr : ws_linear);
+      if (st == MBQ_OK && sums_here) st = launch_mid_sums(XL, T, K, ws_linear, (hipStream_t)stream);
+      if (st != MBQ_OK) return st;
+      return launch_linear_mid_group(XL, T, n_proj, blob_host, sh, prec_host, perm_host, Y_host, ws_linear,
+                                     (hipStream_t)stream, perm_host, offsets_host);
+    }
     const int64_t defer_limit = (algo == MBQ_ALGO_AUTO) ? kMaxStationaryTokens : kMaxDecodeTokens;
     if (ok && T <= defer_limit && route_defers_sort(T)) {
       bool all = true;
       for (int i = 0; i < n_proj; ++i)
-        all = all && (T <= kMaxDecodeTokens ? takes_stationary_kernel(T, sh[i])
-                                            : resolve_auto(T, sh[i]) == kAlgoStationary);
+        all = all && !takes_mid_kernel(T, sh[i]) &&
+              (T <= kMaxDecodeTokens ? takes_stationary_kernel(T, sh[i])
+                                     : resolve_auto(T, sh[i]) == kAlgoStationary);
       if (all) {
         ZeroList zl;  // outputs the linear launch adds into: cleared by a plane of the router launch
         decode16_zero_list(T, n_proj, sh, Y_host, &zl);
@@ -736,7 +763,15 @@ mbq_status mbq_linear_group(const uint16_t* X, int64_t T, int64_t K, int n_proj,
     if (st != MBQ_OK) return st;
     return launch_linear_decode_f4(T, n_proj, blob_host, sh, prec_host, Y_host, ws, s, nullptr, nullptr);
   }
-  if ((algo == MBQ_ALGO_DECODE || algo == kAlgoStationary) && n_proj > 1) {
+  int mid = 0;  // matrices that take the kernel of wide matrices and long rows: one launch if all do, else one by one
+  if (algo == MBQ_ALGO_DECODE)
+    for (int i = 0; i < n_proj; ++i) mid += takes_mid_kernel(T, sh[i]) ? 1 : 0;
+  if (mid == n_proj) {
+    mbq_status st = launch_mid_sums(X, T, K, ws, s);
+    if (st != MBQ_OK) return st;
+    return launch_linear_mid_group(X, T, n_proj, blob_host, sh, prec_host, perm_host, Y_host, ws, s, nullptr, nullptr);
+  }
+  if ((algo == MBQ_ALGO_DECODE || algo == kAlgoStationary) && n_proj > 1 && mid == 0) {
     // the matrices share one launch of the register-stationary kernel when each of them would take it
     bool all = true;
     for (int i = 0; i < n_proj; ++i) all = all && takes_stationary_kernel(T, sh[i]);

@@ -109,8 +109,10 @@ mbq_status launch_route_group(const uint16_t* X, int64_t T, int64_t K, int n, co
                               int32_t* const* offsets, double* const* logits, void* ws, hipStream_t stream,
                               void* prep, int prep_blocks, const ZeroList* zl, bool defer_bucket,
                               const RouteView& view = kDefaultView, const uint16_t* Xprep = nullptr,
-                              const struct ActArgs* aq = nullptr);
+                              const struct ActArgs* aq = nullptr, void* sums = nullptr);
 // aq: the launch also quantises the activations (act_carried); only where the call defers its sort
+// sums: the launch also leaves there what launch_mid_sums would, of X or, with aq, of the integers; only where the call
+// defers its sort
 struct Span {  // a range of device memory
   const void* p;
   size_t bytes;
@@ -151,6 +153,13 @@ mbq_status launch_linear_decode16_group(const uint16_t* X, int64_t T, int n, con
                                         const Shape* shapes, const int32_t* const* prec, const int32_t* const* perm,
                                         float* const* Y, hipStream_t stream, int32_t* const* sort_perm,
                                         int32_t* const* sort_offsets);
+// parts along K that a matrix of 33 .. 64 tokens takes the kernel of mbq_linear_mid.hip in, 0: it does not.  ws begins with
+// what launch_mid_sums (or the router launch) left there (mid_group_sums below).
+int mid_parts(int64_t T, const Shape& sh);
+mbq_status launch_mid_sums(const uint16_t* X, int64_t T, int64_t K, void* sums, hipStream_t stream);
+mbq_status launch_linear_mid_group(const uint16_t* X, int64_t T, int n, const void* const* blobs, const Shape* shapes,
+                                   const int32_t* const* prec, const int32_t* const* perm, float* const* Y, void* ws,
+                                   hipStream_t stream, int32_t* const* sort_perm, int32_t* const* sort_offsets);
 bool decode_f4_supports(int64_t T, const Shape& sh);
 int decode_f4_k_parts(int n, const Shape* shapes);
 void decode_f4_zero_list(int64_t T, int n, const Shape* shapes, float* const* Y, ZeroList* zl);
@@ -171,6 +180,22 @@ __device__ inline void zero_share(const ZeroList& zl, int part, int parts, int t
     const long long n = zl.n[j];
     for (long long i = (long long)part * nthreads + tid; i < n; i += (long long)parts * nthreads) p[i] = 0.f;
   }
+}
+// One lane's share of the sums that launch_linear_mid_group starts from, sums[group][token] = {even, odd} over a group's even
+// and odd steps of 32 columns: `sum` of the eight columns from column 8 c of a token's row; the 16 lanes of an aligned
+// quarter of a wavefront hold consecutive ones (a group), four of them a step.
+__device__ __forceinline__ void mid_group_sums(float sum, int c, int token, int T, float* __restrict__ sums) {
+  sum += __shfl_xor(sum, 1, 64);
+  sum += __shfl_xor(sum, 2, 64);
+  sum += __shfl_xor(sum, 8, 64);  // steps 0 and 2, 1 and 3
+  if ((c & 11) == 0) sums[2 * ((size_t)(c >> 4) * T + token) + ((c >> 2) & 1)] = sum;
+}
+__device__ __forceinline__ float sum8(const uint4& v) {
+  const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+  float s = 0.f;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) s += __uint_as_float(u[j] << 16) + __uint_as_float(u[j] & 0xFFFF0000u);
+  return s;
 }
 size_t decode_f4_workspace_bytes(int64_t T, const Shape& sh);
 mbq_status launch_decode_f4_prep(const uint16_t* X, int64_t T, int64_t K, int KB, void* ws, const ZeroList& zl,

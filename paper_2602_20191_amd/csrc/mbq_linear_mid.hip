@@ -1,0 +1,480 @@
+// Routed linear for 33 to 64 tokens on wide matrices and on long rows: one pass over the weights for all the tokens.
+//
+// Paper Sec. 4.2 Eq. 6 slice by slice, Y_i = sum_{e <= p_i} W_e^T X_i, in the bf16 operands of mbq_bf16_codes.h; tokens in
+// the order of their precision (Sec. 4.3, token permutation), so slice e meets the rows from its first token on: row tiles
+// below are left out, and in the one where it begins the rows below count as zeros.  Every block of packed weights is
+// unpacked once, for 64 rows (the register-stationary kernel of mbq_linear_decode16.hip unpacks it once per 32).
+//
+// Work split: a workgroup of four wavefronts owns 64 output columns (a wavefront 16) and a part of the K axis; two
+// workgroups share a compute unit.  Activations: blocks of 256 columns are copied to LDS a block ahead (32 KiB, rows in
+// sorted order, one barrier a block) and read by all four wavefronts.  A wavefront that read its own from the L2 instead
+// (each with a share of the K axis and partial tiles meeting in LDS) was bound by it: 16 columns take in 7.5 times the
+// bytes of their weights that way, and 13 TB/s is what the L2s gave; 14336 x 4096 twice took 79 us.
+// Weights: one block ahead in registers.  Offsets of the operands: the accumulators of a group start with minus what they
+// will add up to (a constant of the row), so a group's result is small when it is scaled by s0 and added to the sum; the
+// zero points follow as fp32 MFMAs, K = 4, every two blocks.
+// Long rows are cut into up to eight parts of the K axis: part 0 stores into Y, the others into arrays of the workspace,
+// which mid_fold_kernel adds in order, so the result does not depend on which comes first.
+//
+// Bound by instruction issue: a block takes 360 vector instructions (192 of them unpacking) and 92 MFMAs a wavefront at 64
+// tokens of an even mix, 7500 cycles for the two wavefronts of a SIMD.  Stage calls (router included) before and now, us:
+// twice 14336 x 4096 at 64 tokens 74.6 -> 62.3, skewed mix 69.7 -> 53.4, at 48 tokens 73.2 -> 56.8; 4096 x 14336 at 64
+// tokens 54.5 -> 42.2, 4096 x 11008 43.5 -> 39.8, at 33 tokens 42.7 -> 35.6.  Two tiles a wavefront (spills), operands of
+// four steps at a time with the next slice's unpacking dealt out under the MFMAs (62.3 -> 64.3), eight wavefronts a
+// workgroup (65.8) were no faster.
+#include <type_traits>
+
+#include "mbq_bf16_codes.h"
+
+namespace mbq {
+
+namespace mid {
+
+using namespace bf;
+
+constexpr int kWaves = 4;
+constexpr int kMaxBlocks = 16;  // of a part: their row constants wait in LDS
+constexpr int kMinRows = 33, kMaxRows = 64;
+constexpr int kRowBytes = 2 * kGroup;  // one group of one row: 16 chunks of 16 bytes, swizzled by the row
+constexpr int kMaxParts = 8;
+
+struct Proj {
+  const uint4* codes;
+  size_t slice_vec;  // uint4 per slice
+  const float2* meta;
+  int64_t N;
+  int NT;
+  const int32_t* prec;
+  const int32_t* perm;      // precision-sorted token order, or null: sorted here
+  int32_t* sort_perm;       // with perm == null: where the order and the bucket offsets go
+  int32_t* sort_offsets;
+  float* Y;
+  float* slot;              // T x N arrays of partial sums besides Y, slot_floats apart: part s > 0 stores into slot s - 1
+  int64_t slot_floats;
+  int parts;                // along K
+  int wg_begin;             // first workgroup of the matrix
+};
+struct Group {
+  Proj p[MBQ_MAX_GROUP];
+  int n;
+};
+
+struct Item {  // a 16 x 256 block: four slices and {s0, z0} of two groups
+  uint4 w[4];
+  float2 mt[2];
+};
+
+// 16 bytes per lane from base + offset straight into LDS at lds + 16 * lane.  (In assembly: given the builtin the compiler
+// waits for all such loads ahead of the next LDS read.  No register result; M0, which holds the LDS address, is put back.)
+__device__ __forceinline__ void dma_16(uint32_t lds, uint32_t offset, const void* base) {
+  uint32_t m0;
+  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b32 m0, %0"
+               : "=&s"(m0)
+               : "s"(lds), "v"(offset), "s"(base)
+               : "memory");
+}
+
+}  // namespace mid
+
+template <int RT>
+__global__ __launch_bounds__(64 * mid::kWaves, 2) void mid_kernel(const uint16_t* __restrict__ X, int T, int64_t K, int KB,
+                                                                  const float2* __restrict__ sums, const mid::Group g) {
+  using namespace mid;
+  constexpr int kRows = 16 * RT;
+  constexpr int kHalf = kRows * kRowBytes;   // a group of the pass's rows
+  constexpr int kStage = 2 * kHalf;          // a block
+  __shared__ __attribute__((aligned(1024))) char smem[2 * kStage + 2 * kMaxBlocks * kRows * 8];
+  float* const s_c1 = reinterpret_cast<float*>(smem + 2 * kStage);  // [group][row]: what the accumulators of a group start with
+  float* const s_ss = s_c1 + 2 * kMaxBlocks * kRows;                // [group][row]: sums of the group's activations
+  Proj P = g.p[0];
+#pragma unroll
+  for (int j = 1; j < MBQ_MAX_GROUP; ++j)
+    if (j < g.n && (int)blockIdx.x >= g.p[j].wg_begin) P = g.p[j];
+  const int wg = (int)blockIdx.x - P.wg_begin;
+  const int part = wg % P.parts, col_set = wg / P.parts;
+  const int b0 = (int)((int64_t)part * KB / P.parts), nblk = (int)((int64_t)(part + 1) * KB / P.parts) - b0;
+  const int lane = threadIdx.x & 63, l15 = lane & 15, kq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int G = (int)(K / kGroup);
+  const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)smem;
+
+  // ---- rows: lane r holds row r of the precision-sorted tokens ----
+  int token = -1, p = -1;
+  if (P.perm != nullptr) {
+    if (lane < T) {
+      token = P.perm[lane];
+      p = P.prec[token];
+    }
+  } else {
+    // stable counting sort of the T <= 64 tokens by precision: a lane holds token `lane`
+    const int mine = lane < T ? min(max(P.prec[lane], 0), MBQ_N_PRECISIONS - 1) : -1;
+    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    int start = 0, pos = 0, off = 0;
+#pragma unroll
+    for (int q = 0; q < MBQ_N_PRECISIONS; ++q) {
+      const uint64_t with = __ballot(mine == q);
+      if (mine == q) pos = start + __popcll(with & below);
+      if (lane == q) off = start;
+      start += __popcll(with);
+    }
+    if (lane == MBQ_N_PRECISIONS) off = start;
+    int* const order = reinterpret_cast<int*>(s_c1) + 64 * wave;  // (the wavefront's own; in order within it)
+    if (mine >= 0) order[pos] = lane | (mine << 8);
+    const int e = lane < T ? order[lane] : -1;
+    token = e < 0 ? -1 : (e & 0xFF);
+    p = e < 0 ? -1 : (e >> 8);
+    if (wg == 0 && wave == 0) {
+      if (mine >= 0) P.sort_perm[pos] = lane;
+      if (lane <= MBQ_N_PRECISIONS) P.sort_offsets[lane] = off;
+    }
+  }
+  int pm = 0;              // highest precision
+  int first_tile[4];       // row tile where slice e begins
+  uint32_t mask[4];        // rows of that tile which it counts for
+  first_tile[0] = 0;
+  mask[0] = ~0u;
+#pragma unroll
+  for (int e = 1; e < 4; ++e) {
+    const int first = __popcll(__ballot(p >= 0 && p < e));
+    if (first < T) pm = e;
+    first_tile[e] = first >> 4;
+    mask[e] = l15 >= (first & 15) ? ~0u : 0u;
+  }
+  // ---- activations: an instruction moves 256 bytes of four rows (16 lanes a row); rows 16 j + 4 wave + kq.  LDS chunk l15
+  // of a row holds its chunk l15 ^ (row & 15), so the 16 rows of a fragment read hit different banks.  Rows past the last:
+  // token 0, never stored ----
+  uint32_t x_at[RT];
+#pragma unroll
+  for (int j = 0; j < RT; ++j) {
+    const int t = max(__shfl(token, 16 * j + 4 * wave + kq, 64), 0);
+    x_at[j] = (uint32_t)t * 2u * (uint32_t)K + 16u * (uint32_t)(l15 ^ (4 * wave + kq));
+  }
+  auto load_x = [&](int kb, uint32_t stage) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      // (a second group that the last block may lack: the first one again, under zero scales)
+      const char* src = reinterpret_cast<const char*>(X) + (size_t)min(2 * kb + h, G - 1) * kRowBytes;
+#pragma unroll
+      for (int j = 0; j < RT; ++j) dma_16(lds + stage + (uint32_t)(h * kHalf + (16 * j + 4 * wave) * kRowBytes), x_at[j], src);
+    }
+  };
+  // ---- weights: this wavefront's tile (past the matrix: the last one again, not stored; a slice that no row needs: the
+  // highest one needed again) ----
+  const int nt = min(col_set * kWaves + wave, P.NT - 1);
+  const uint32_t lane16 = 16u * (uint32_t)lane, meta_at = 8u * (uint32_t)l15;
+  auto load_item = [&](int kb, Item& I) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      I.w[e] = *reinterpret_cast<const uint4*>(
+          reinterpret_cast<const char*>(P.codes + (size_t)min(e, pm) * P.slice_vec + ((size_t)nt * KB + kb) * 64) + lane16);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      I.mt[h] = *reinterpret_cast<const float2*>(
+          reinterpret_cast<const char*>(P.meta + ((size_t)nt * (2 * KB) + 2 * kb + h) * kTileN) + meta_at);
+  };
+  Item A, B;
+  load_x(b0, 0u);
+  load_item(b0, A);
+
+  // ---- row constants of the part's groups (wavefront w: groups w, w + 4, ..) ----
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // the order has been read from there
+  {
+    const float coefA = (p >= 3) ? 74.f : (p == 2) ? 72.f : (p == 1) ? 64.f : 32.f;  // biases of the operands of slices 0..p
+    const float coefB = (p >= 3) ? 18.5f : (p == 2) ? 18.f : (p == 1) ? 16.f : 8.f;
+    const float q = (p >= 3) ? 0.328125f : (p == 2) ? 0.3125f : (p == 1) ? 0.25f : 0.f;
+    const float2* src = sums + max(token, 0);
+    for (int gi = wave; gi < 2 * nblk; gi += kWaves) {
+      const float2 s = 2 * b0 + gi < G ? src[(size_t)(2 * b0 + gi) * T] : float2{0.f, 0.f};
+      const float ss = s.x + s.y;
+      if (lane < kRows) {
+        s_c1[gi * kRows + lane] = -(coefA * s.x + coefB * s.y + (1.5f * q - 0.5f) * ss);
+        s_ss[gi * kRows + lane] = ss;
+      }
+    }
+  }
+  const UnpackConsts uc = make_unpack_consts();
+  floatx4 y[RT];
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) y[rt] = floatx4{0.f, 0.f, 0.f, 0.f};
+  float zero_at = 0.f;  // -s0 z0 of this lane's column: group kq of the four of two blocks
+
+  uint32_t stage = 0u;
+  int i = 0;
+  auto settle = [&](Item& I) {  // the compiler's own wait for these loads is placed here
+#pragma unroll
+    for (int e = 0; e < 4; ++e) asm volatile("" : "+v"(I.w[e].x), "+v"(I.w[e].y), "+v"(I.w[e].z), "+v"(I.w[e].w));
+#pragma unroll
+    for (int h = 0; h < 2; ++h) asm volatile("" : "+v"(I.mt[h].x), "+v"(I.mt[h].y));
+  };
+  auto block = [&](Item& cur, Item& nxt) {
+    const bool last = i + 1 == nblk;
+    const int kb_next = b0 + (last ? i : i + 1);  // (the last block is requested once more: the other stage is free)
+    load_x(kb_next, stage ^ (uint32_t)kStage);
+    load_item(kb_next, nxt);
+    __builtin_amdgcn_sched_barrier(0);
+    uint4 xf[2][RT][2];
+    // fragments of step s of half group d
+    auto read_x = [&](int d, uint4 (&x)[RT][2]) {
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const int chunk = 8 * (d & 1) + 4 * s + kq;
+        const char* at = smem + stage + (d >> 1) * kHalf + l15 * kRowBytes + ((chunk ^ l15) * 16);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) x[rt][s] = *reinterpret_cast<const uint4*>(at + rt * 16 * kRowBytes);
+      }
+    };
+    floatx4 D[RT];
+    auto half_group = [&](auto d_tag) {  // 64 columns: the operands of two steps come from one dword of a slice
+      constexpr int d = decltype(d_tag)::value;
+      if constexpr ((d & 1) == 0) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+          D[rt] = *reinterpret_cast<const floatx4*>(s_c1 + (2 * i + (d >> 1)) * kRows + 16 * rt + 4 * kq);
+      }
+      if constexpr (d < 3) read_x(d + 1, xf[(d + 1) & 1]);
+      const uint4(&x)[RT][2] = xf[d & 1];
+      auto slice = [&](auto e_tag) {
+        constexpr int E = decltype(e_tag)::value;
+        uint4 Bo[2];
+        unpack_dword<E>(d == 0 ? cur.w[E].x : d == 1 ? cur.w[E].y : d == 2 ? cur.w[E].z : cur.w[E].w, uc, Bo[0], Bo[1]);
+        if constexpr (E == 0) {
+#pragma unroll
+          for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) D[rt] = mfma(x[rt][s], Bo[s], D[rt]);
+        } else {
+          // from the first row tile with rows of this precision; rows of it that are below count as zeros
+#pragma unroll
+          for (int r0 = 0; r0 < RT; ++r0) {
+            if (first_tile[E] == r0) {
+              const uint32_t mk = mask[E];
+#pragma unroll
+              for (int s = 0; s < 2; ++s) {
+                const uint4 xm = {x[r0][s].x & mk, x[r0][s].y & mk, x[r0][s].z & mk, x[r0][s].w & mk};
+                D[r0] = mfma(xm, Bo[s], D[r0]);
+#pragma unroll
+                for (int rt = r0 + 1; rt < RT; ++rt) D[rt] = mfma(x[rt][s], Bo[s], D[rt]);
+              }
+            }
+          }
+        }
+      };
+      slice(std::integral_constant<int, 0>{});
+      if (pm >= 1) slice(std::integral_constant<int, 1>{});
+      if (pm >= 2) slice(std::integral_constant<int, 2>{});
+      if (pm >= 3) slice(std::integral_constant<int, 3>{});
+      if constexpr ((d & 1) == 1) {
+        constexpr int h = d >> 1;
+        const float s0 = cur.mt[h].x;
+        if (kq == 2 * (i & 1) + h) zero_at = -s0 * cur.mt[h].y;
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) y[rt][r] += s0 * D[rt][r];
+      }
+    };
+    read_x(0, xf[0]);
+    half_group(std::integral_constant<int, 0>{});
+    half_group(std::integral_constant<int, 1>{});
+    half_group(std::integral_constant<int, 2>{});
+    half_group(std::integral_constant<int, 3>{});
+    // the zero points of up to four groups: y[row][col] -= s0 z0 (sum of the group's activations), K = 4 in fp32
+    if ((i & 1) == 1 || last) {
+      const int of = (i & 1) && kq < 2 ? i - 1 : i;
+      const float* ss = s_ss + (2 * of + (kq & 1)) * kRows + l15;
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) y[rt] = __builtin_amdgcn_mfma_f32_16x16x4f32(ss[16 * rt], zero_at, y[rt], 0, 0, 0);
+      zero_at = 0.f;
+    }
+    // this wavefront's requests have landed and its reads of the stage are done; behind the barrier everybody's are
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    settle(nxt);
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    stage ^= (uint32_t)kStage;
+    ++i;
+  };
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  settle(A);
+  asm volatile("s_barrier" ::: "memory");
+#pragma unroll 1
+  for (int q = 0; q < nblk; q += 2) {
+    block(A, B);
+    if (q + 1 < nblk) block(B, A);
+  }
+
+  // ---- rows in original token order, through LDS (the stages are free): an instruction writes 256 bytes of four rows ----
+  constexpr int kCols = 16 * kWaves, kLd = kCols + 4, kVec = kCols / 4;
+  float* const s_out = reinterpret_cast<float*>(smem);
+  static_assert(kRows * kLd * 4 <= 2 * kStage, "the tile fits the stages");
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) s_out[(16 * rt + 4 * kq + r) * kLd + 16 * wave + l15] = y[rt][r];
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  float* const out = part == 0 ? P.Y : P.slot + (part - 1) * P.slot_floats;
+  const bool wide = (P.N & 3) == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0;
+#pragma unroll
+  for (int u = 0; u < kRows * kVec; u += 64 * kWaves) {
+    const int row = (u + (int)threadIdx.x) / kVec, q = (u + (int)threadIdx.x) % kVec;
+    const floatx4 v = *reinterpret_cast<const floatx4*>(s_out + row * kLd + 4 * q);
+    const int64_t col = (int64_t)col_set * kCols + 4 * q;
+    const int t = __shfl(token, row, 64);
+    if (row < T && col < P.N) {
+      float* at = out + (int64_t)t * P.N + col;
+      if (wide) {
+        *reinterpret_cast<floatx4*>(at) = v;
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (col + r < P.N) at[r] = v[r];
+      }
+    }
+  }
+}
+
+// sums[group][token] = {even, odd}: sums of the activations of a group's even and odd blocks of 32 columns
+__global__ __launch_bounds__(256) void mid_sums_kernel(const uint16_t* __restrict__ X, int T, int64_t K,
+                                                       float* __restrict__ sums) {
+  const int token = blockIdx.x;
+  const uint4* src = reinterpret_cast<const uint4*>(X + (int64_t)token * K);
+  const int chunks = (int)(K >> 3);  // a multiple of 16: groups of 16 lanes are whole
+  for (int c = threadIdx.x; c < chunks; c += 256) mid_group_sums(sum8(src[c]), c, token, T, sums);
+}
+
+mbq_status launch_mid_sums(const uint16_t* X, int64_t T, int64_t K, void* sums, hipStream_t stream) {
+  hipLaunchKernelGGL(mid_sums_kernel, dim3((unsigned)T), dim3(256), 0, stream, X, (int)T, K, reinterpret_cast<float*>(sums));
+  return hip_status(hipGetLastError(), "mid_sums_kernel launch");
+}
+
+// ---- launches that cut K: Y += array 1, += array 2, .. in that order ----
+namespace mid {
+struct Fold {
+  float* Y[MBQ_MAX_GROUP];
+  const float* slot[MBQ_MAX_GROUP];
+  int64_t slot_floats[MBQ_MAX_GROUP];
+  int64_t n[MBQ_MAX_GROUP];
+  int parts[MBQ_MAX_GROUP];
+};
+}  // namespace mid
+__global__ __launch_bounds__(256) void mid_fold_kernel(const mid::Fold f) {
+  const int j = blockIdx.y, extra = f.parts[j] - 1;
+  if (extra <= 0) return;
+  float* __restrict__ Y = f.Y[j];
+  const float* __restrict__ slot = f.slot[j];
+  const int64_t n = f.n[j], ld = f.slot_floats[j], at = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
+  const int64_t n4 = (reinterpret_cast<uintptr_t>(Y) & 15) == 0 ? n >> 2 : 0;
+  for (int64_t i = at; i < n4; i += step) {
+    floatx4 v[mid::kMaxParts];  // all on their way before the first is used
+    v[0] = reinterpret_cast<const floatx4*>(Y)[i];
+#pragma unroll
+    for (int e = 1; e < mid::kMaxParts; ++e)
+      if (e <= extra) v[e] = reinterpret_cast<const floatx4*>(slot + (e - 1) * ld)[i];
+#pragma unroll
+    for (int e = 1; e < mid::kMaxParts; ++e)
+      if (e <= extra) v[0] += v[e];
+    reinterpret_cast<floatx4*>(Y)[i] = v[0];
+  }
+  for (int64_t i = 4 * n4 + at; i < n; i += step) {
+    float v = Y[i];
+    for (int e = 0; e < extra; ++e) v += slot[e * ld + i];
+    Y[i] = v;
+  }
+}
+
+namespace mid {
+static inline size_t sums_bytes(int64_t T, int64_t K) { return ((size_t)T * (size_t)(K / kGroup) * 8 + 255) / 256 * 256; }
+static inline int64_t slot_floats(int64_t T, int64_t N) { return (T * N + 63) / 64 * 64; }
+}  // namespace mid
+
+// Parts of the K axis, 0: the matrix does not take this kernel.  It has to fill the chip, and it cannot share a compute
+// unit's registers between many short tiles as the register-stationary kernel does, so it is taken where it won on cold
+// weights, stage calls in us (that kernel / this one, at 33, 48 and 64 tokens of an even mix; skewed mixes favour this one
+// by another 5-20 %):
+//   wide matrices, which come in pairs (gate and up), one part: twice 14336 x 4096 72 / 58, 73 / 57, 75 / 62; twice 11008 x
+//   4096 74 / 57, 60 / 56, 61 / 61; twice 8192 x 4096 44 / 46, 45 / 45, 46 / 50 (not taken); 14336 x 4096 alone 42 / 47, 43 /
+//   45, 44 / 50 (it takes the same kernel alone);
+//   long rows, eight parts or as many as the workspace holds: 4096 x 11008 43 / 36, 43 / 36, 44 / 40; 3072 x 8192 27 / 27, 28
+//   / 27, 28 / 29, 2048 x 8192 23 / 24, 24 / 24, 24 / 25 (not taken).
+// At 32 tokens both kernels unpack once and are as fast.  The choice depends on T and the matrix alone: a call for several
+// matrices gives the bits of separate calls.
+int mid_parts(int64_t T, const Shape& sh) {
+  if (T < mid::kMinRows || T > mid::kMaxRows) return 0;
+  const int least = (sh.KB + mid::kMaxBlocks - 1) / mid::kMaxBlocks;
+  if (sh.N >= 2 * sh.K && sh.NT >= 640) return least == 1 ? 1 : 0;
+  if (sh.KB <= 32 || sh.NT < 192 || sh.N > sh.K) return 0;
+  // (the workspace of every call has room for the activations and 256 rows more)
+  const size_t room = (size_t)(T + 256) * (size_t)sh.K * 2 - mid::sums_bytes(T, sh.K);
+  int64_t parts = 1 + (int64_t)(room / ((size_t)mid::slot_floats(T, sh.N) * 4));
+  if (parts > mid::kMaxParts) parts = mid::kMaxParts;
+  return parts >= least ? (int)parts : 0;
+}
+
+mbq_status launch_linear_mid_group(const uint16_t* X, int64_t T, int n, const void* const* blobs, const Shape* shapes,
+                                   const int32_t* const* prec, const int32_t* const* perm, float* const* Y,
+                                   void* ws, hipStream_t stream, int32_t* const* sort_perm,
+                                   int32_t* const* sort_offsets) {
+  const Shape& sh = shapes[0];
+  // matrices that are cut share the workspace's room one after the other
+  bool cut = false;
+  for (int i = 0; i < n; ++i) cut = cut || mid_parts(T, shapes[i]) > 1;
+  if (cut && n > 1) {
+    for (int i = 0; i < n; ++i) {
+      const mbq_status st =
+          launch_linear_mid_group(X, T, 1, blobs + i, shapes + i, prec + i, sort_perm ? nullptr : perm + i, Y + i, ws, stream,
+                                  sort_perm ? sort_perm + i : nullptr, sort_perm ? sort_offsets + i : nullptr);
+      if (st != MBQ_OK) return st;
+    }
+    return MBQ_OK;
+  }
+  mid::Group g;
+  mid::Fold f;
+  int grid = 0;
+  int64_t most = 0;
+  float* slot = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + mid::sums_bytes(T, sh.K));
+  for (int i = 0; i < MBQ_MAX_GROUP; ++i) {
+    const int j = i < n ? i : 0;
+    const Shape& s = shapes[j];
+    mid::Proj& p = g.p[i];
+    p.codes = reinterpret_cast<const uint4*>(blobs[j]);
+    p.slice_vec = s.slice_words / 4;
+    p.meta = reinterpret_cast<const float2*>(reinterpret_cast<const char*>(blobs[j]) + s.meta_offset);
+    p.N = s.N;
+    p.NT = s.NT;
+    p.prec = prec[j];
+    p.perm = sort_perm ? nullptr : perm[j];
+    p.sort_perm = sort_perm ? sort_perm[j] : nullptr;
+    p.sort_offsets = sort_perm ? sort_offsets[j] : nullptr;
+    p.Y = Y[j];
+    p.slot = slot;
+    p.slot_floats = mid::slot_floats(T, s.N);
+    p.parts = mid_parts(T, s);
+    p.wg_begin = grid;
+    f.Y[i] = Y[j];
+    f.slot[i] = slot;
+    f.slot_floats[i] = p.slot_floats;
+    f.n[i] = T * s.N;
+    f.parts[i] = i < n ? p.parts : 1;
+    if (i < n) {
+      grid += (s.NT + mid::kWaves - 1) / mid::kWaves * p.parts;
+      slot += (p.parts - 1) * p.slot_floats;
+      if (p.parts > 1 && f.n[i] > most) most = f.n[i];
+    }
+  }
+  g.n = n;
+  if (T <= 48)
+    hipLaunchKernelGGL(mid_kernel<3>, dim3(grid), dim3(64 * mid::kWaves), 0, stream, X, (int)T, sh.K, sh.KB,
+                       reinterpret_cast<const float2*>(ws), g);
+  else
+    hipLaunchKernelGGL(mid_kernel<4>, dim3(grid), dim3(64 * mid::kWaves), 0, stream, X, (int)T, sh.K, sh.KB,
+                       reinterpret_cast<const float2*>(ws), g);
+  mbq_status st = hip_status(hipGetLastError(), "mid_kernel launch");
+  if (st != MBQ_OK || most == 0) return st;
+  int64_t blocks = (most / 4 + 255) / 256;
+  if (blocks > 4 * device_compute_units()) blocks = 4 * device_compute_units();
+  if (blocks < 1) blocks = 1;
+  hipLaunchKernelGGL(mid_fold_kernel, dim3((unsigned)blocks, (unsigned)n), dim3(256), 0, stream, f);
+  return hip_status(hipGetLastError(), "mid_fold_kernel launch");
+}
+
+}  // namespace mbq

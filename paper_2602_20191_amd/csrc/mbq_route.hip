@@ -317,9 +317,11 @@ __global__ __launch_bounds__(512) void route_small_kernel(const uint16_t* __rest
                                                           RouteGroup group, int n_routers,
                                                           unsigned long long* words, char* prep, int prep_blocks,
                                                           const ZeroList zl, int defer_bucket,
-                                                          const uint16_t* __restrict__ Xprep, const ActArgs aq) {
+                                                          const uint16_t* __restrict__ Xprep, const ActArgs aq,
+                                                          float* __restrict__ sums) {
   // Xprep: the activations the linear kernel multiplies (X itself, except in the activation-quantised variant,
   // where the routers read the rebuilt activations and the linear kernel the integers)
+  // sums: where router 0 also leaves the group sums that the linear kernel of 17 and more tokens starts from (null: nowhere)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int tok = blockIdx.x;
   const bool plane = (int)blockIdx.y == n_routers;
@@ -420,6 +422,8 @@ __global__ __launch_bounds__(512) void route_small_kernel(const uint16_t* __rest
         if (writes) {
           reinterpret_cast<uint4*>(aq.Xint + (int64_t)tok * K)[j] = act::pack8(xi);
           reinterpret_cast<uint4*>(aq.Xr + (int64_t)tok * K)[j] = xr;
+          if (sums != nullptr)
+            mid_group_sums(((xi[0] + xi[1]) + (xi[2] + xi[3])) + ((xi[4] + xi[5]) + (xi[6] + xi[7])), j, tok, T, sums);
         }
         add(xr, w);
       }
@@ -436,6 +440,10 @@ __global__ __launch_bounds__(512) void route_small_kernel(const uint16_t* __rest
       load_w(k2, wb);
       add(xa, wa);
       if (two) add(xb, wb);
+      if (sums != nullptr && blockIdx.y == 0) {
+        mid_group_sums(sum8(xa), (int)(k >> 3), tok, T, sums);
+        if (two) mid_group_sums(sum8(xb), (int)(k2 >> 3), tok, T, sums);
+      }
     }
   }
   __shared__ double red[8][kP];
@@ -563,7 +571,7 @@ mbq_status launch_route_group(const uint16_t* X, int64_t T, int64_t K, int n, co
                               const float* const* br, int32_t* const* prec, int32_t* const* perm,
                               int32_t* const* offsets, double* const* logits, void* ws, hipStream_t stream,
                               void* prep, int prep_blocks, const ZeroList* zl, bool defer_bucket,
-                              const RouteView& view, const uint16_t* Xprep, const ActArgs* aq) {
+                              const RouteView& view, const uint16_t* Xprep, const ActArgs* aq, void* sums) {
   if (T == 0) return launch_sort(n, prec, perm, offsets, 0, 0, stream);  // the (all-zero) offsets
   RouteGroup g;
   g.view = view;
@@ -586,12 +594,14 @@ mbq_status launch_route_group(const uint16_t* X, int64_t T, int64_t K, int n, co
       const unsigned gx = (prep && T < 16) ? 16u : (unsigned)T;
       hipLaunchKernelGGL(route_small_kernel<true>, dim3(gx, (unsigned)n + (plane ? 1u : 0u)), dim3(512), 0, stream, X,
                          (int)T, K, g, n, words, reinterpret_cast<char*>(prep), prep ? prep_blocks : 0,
-                         (plane && zl) ? *zl : ZeroList{}, defer_bucket ? 1 : 0, Xprep, *aq);
+                         (plane && zl) ? *zl : ZeroList{}, defer_bucket ? 1 : 0, Xprep, *aq,
+                         reinterpret_cast<float*>(sums));
     } else {
       const unsigned gx = (prep && prep_blocks > (int)T) ? (unsigned)prep_blocks : (unsigned)T;
       hipLaunchKernelGGL(route_small_kernel<false>, dim3(gx, (unsigned)n + (plane ? 1u : 0u)), dim3(512), 0, stream, X,
                          (int)T, K, g, n, words, reinterpret_cast<char*>(prep), prep ? prep_blocks : 0,
-                         (plane && zl) ? *zl : ZeroList{}, defer_bucket ? 1 : 0, Xprep ? Xprep : X, ActArgs{});
+                         (plane && zl) ? *zl : ZeroList{}, defer_bucket ? 1 : 0, Xprep ? Xprep : X, ActArgs{},
+                         reinterpret_cast<float*>(sums));
     }
     return hip_status(hipGetLastError(), "route_small_kernel launch");
   }

@@ -633,6 +633,54 @@ def test_decode_several_token_tiles(mbq, T, K, N):
     assert_output_close(Y, Yref, f"decode token tiles T={T} K={K} N={N}")
 
 
+def reference64(X, blob, N, K, prec):
+    """The routed output in 64 bits from the weights that mbq_dequant gives (itself pinned against the oracle)."""
+    import paper_2602_20191_amd as pkg
+
+    Y = torch.zeros((X.shape[0], N), dtype=torch.float64, device="cuda")
+    for p in range(4):
+        rows = torch.nonzero(prec == p).flatten()
+        if len(rows):
+            Y[rows] = X[rows].double() @ pkg.mbq_dequant(blob, N, K, p).double().T
+    return Y
+
+
+@pytest.mark.parametrize("T,mix", [(33, (0, 1, 2, 3)), (48, (16, 16, 16, 0)), (49, (0, 0, 49, 0)), (63, (5, 30, 1, 27)), (64, (16, 16, 16, 16)),
+                                   (64, (0, 0, 0, 64)), (40, (40, 0, 0, 0)), (64, (31, 0, 32, 1))])
+@pytest.mark.parametrize("Ns,K", [((10240,), 128), ((10243, 10300), 640), ((10240, 10240), 4096), ((3072,), 8448), ((3075, 3072), 8320)])
+def test_decode_wide_matrices_and_long_rows(mbq, T, mix, Ns, K):
+    """33 to 64 tokens on the shapes of the kernel that unpacks once for all tokens: precisions that begin on a row tile
+    and inside one, absent ones, a last block of one group, parts along K, columns past the matrix.  Against 64 bits (32-bit
+    sums: 4e-5), a group against single calls and a stage against its two calls bit for bit, an output that is not 16-byte
+    aligned against one that is."""
+    counts = mix if sum(mix) == T else (T - sum(mix[1:]), *mix[1:])
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(149 + T + K)
+    X = torch.randn((T, K), generator=gen, device="cuda")
+    X[:, torch.randperm(K, generator=gen, device="cuda")[: K // 100]] *= 20.0
+    X = X.to(torch.bfloat16)
+    blobs, routing = [], []
+    for i, N in enumerate(Ns):
+        blobs.append(mbq.mbq_encode(0.02 * torch.randn((N, K), generator=gen, device="cuda")))
+        prec = np.random.default_rng([149, T, i]).permutation(np.repeat(np.arange(4), counts)).astype(np.int32)
+        routing.append((dev(prec), *[dev(v) for v in O.bucket(prec)]))
+    Ys = mbq.mbq_linear_group(X, blobs, list(Ns), K, routing)
+    for i, N in enumerate(Ns):
+        ref = reference64(X, blobs[i], N, K, routing[i][0])
+        assert float((Ys[i].double() - ref).norm() / ref.norm()) < 4e-5, i
+        assert torch.equal(Ys[i], mbq.mbq_linear(X, blobs[i], N, K, *routing[i])), i
+        shifted = torch.full((T * N + 1,), float("nan"), device="cuda")[1:].view(T, N)
+        assert torch.equal(Ys[i], mbq.mbq_linear(X, blobs[i], N, K, *routing[i], Y=shifted)), i
+    Wr = [torch.randn((4, K), generator=gen, device="cuda") / K ** 0.5 for _ in Ns]
+    br = [torch.zeros(4, device="cuda") for _ in Ns]
+    stage_routing, stage_Y = mbq.mbq_routed_linear_group(X, Wr, br, blobs, list(Ns))
+    separate = mbq.mbq_route_group(X, Wr, br)
+    for a, b in zip(stage_routing, separate):
+        assert all(torch.equal(x, y) for x, y in zip(a, b))
+    for a, b in zip(stage_Y, mbq.mbq_linear_group(X, blobs, list(Ns), K, separate)):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("K,T,Ns", [(4096, 16, (96, 32, 130)), (4096, 1, (64, 64)), (2048, 7, (80, 48, 16, 33)),
                                     (768, 16, (40,)), (3072, 5, (48, 96)), (5120, 16, (48, 32)), (1024, 40, (48, 32)),
                                     (4096, 64, (1040, 130, 256)), (2304, 33, (272, 48, 16, 640)), (4352, 48, (2064, 16))])
