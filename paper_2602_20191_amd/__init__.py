@@ -37,6 +37,7 @@ EXPORTS = (
 )
 
 _lib = None
+_native = None  # the stage call's half that needs torch's C++ side
 
 
 class MbqError(RuntimeError):
@@ -62,7 +63,7 @@ class Config(ctypes.Structure):
 
 def load() -> ctypes.CDLL:
     """Loads libmbq.so (built by ``python -m paper_2602_20191_amd.build``)."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -138,7 +139,15 @@ def load() -> ctypes.CDLL:
                  "mbq_threshold_quantile", "mbq_bench_copy", "mbq_bench_read", "mbq_bench_mfma_loop",
                  "mbq_bench_linear_group_prepared", "mbq_bench_decode_timeline"):
         getattr(lib, name).restype = c_int
-    _lib = lib
+    try:
+        from . import _mbq_torch as native
+    except ImportError as e:
+        raise MbqError(f"{e}: build it with `python -m paper_2602_20191_amd.build`") from e
+    native.bind(*[ctypes.cast(getattr(lib, name), c_p).value for name in
+                  ("mbq_routed_linear_group", "mbq_routed_linear_group_cfg", "mbq_route_workspace_bytes",
+                   "mbq_linear_workspace_bytes", "mbq_last_error")],
+                MbqError, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+    _lib, _native = lib, native
     return lib
 
 
@@ -365,29 +374,10 @@ def mbq_routed_linear_group(X: torch.Tensor, Wr: Sequence[torch.Tensor], br: Seq
                             routing: Optional[Sequence[Tuple[torch.Tensor, torch.Tensor, torch.Tensor]]] = None,
                             Y: Optional[Sequence[torch.Tensor]] = None, ws_route: Optional[torch.Tensor] = None,
                             ws_linear: Optional[torch.Tensor] = None, algo: int = ALGO_AUTO):
-    """One stage: route X with every router, then the routed outputs.  -> (routing, Y) lists."""
-    assert X.dtype == torch.bfloat16 and X.dim() == 2
-    T, K = X.shape
-    n = len(Ns)
-    assert len(Wr) == len(br) == len(blobs) == n >= 1
-    P = Wr[0].shape[0]
-    dev = X.device
-    if routing is None:
-        routing = [(torch.empty(T, dtype=torch.int32, device=dev), torch.empty(T, dtype=torch.int32, device=dev),
-                    torch.empty(P + 1, dtype=torch.int32, device=dev)) for _ in range(n)]
-    if Y is None:
-        Y = [torch.empty((T, N), dtype=torch.float32, device=dev) for N in Ns]
-    if ws_route is None:
-        ws_route = route_workspace(T, K, dev)
-    if ws_linear is None:
-        ws_linear = linear_workspace(T, max(Ns), K, dev)
-    n_arr = (ctypes.c_int64 * n)(*[int(N) for N in Ns])
-    _check(load().mbq_routed_linear_group(
-        _ptr(X), T, K, n, _ptr_array(Wr), _ptr_array(br), P, _ptr_array(blobs), n_arr,
-        _ptr_array([r[0] for r in routing]), _ptr_array([r[1] for r in routing]),
-        _ptr_array([r[2] for r in routing]), _ptr_array(Y), _ptr(ws_route), ws_route.numel(), _ptr(ws_linear),
-        ws_linear.numel(), algo, _stream()), "mbq_routed_linear_group")
-    return [tuple(r) for r in routing], list(Y)
+    """One stage: route X with every router, then the routed outputs.  -> (routing, Y) lists.  Native (csrc/mbq_torch.cpp):
+    what is left to the binding is allocated there."""
+    load()
+    return _native.stage(X, Wr, br, blobs, Ns, routing, Y, ws_route, ws_linear, algo, 0)
 
 
 # ---- other slice configurations ----------------------------------------------------------------------
@@ -497,26 +487,8 @@ def mbq_routed_linear_group_cfg(X: torch.Tensor, Wr: Sequence[torch.Tensor], br:
                                 Y: Optional[Sequence[torch.Tensor]] = None, ws_route: Optional[torch.Tensor] = None,
                                 ws_linear: Optional[torch.Tensor] = None, algo: int = ALGO_AUTO):
     """One stage under a slice configuration: route X with every E-output router, then the routed outputs."""
-    assert X.dtype == torch.bfloat16 and X.dim() == 2
-    T, K = X.shape
-    n = len(Ns)
-    dev = X.device
-    if routing is None:
-        routing = [(torch.empty(T, dtype=torch.int32, device=dev), torch.empty(T, dtype=torch.int32, device=dev),
-                    torch.empty(N_PRECISIONS + 1, dtype=torch.int32, device=dev)) for _ in range(n)]
-    if Y is None:
-        Y = [torch.empty((T, N), dtype=torch.float32, device=dev) for N in Ns]
-    if ws_route is None:
-        ws_route = route_workspace(T, K, dev)
-    if ws_linear is None:
-        ws_linear = linear_workspace(T, max(Ns), K, dev)
-    n_arr = (ctypes.c_int64 * n)(*[int(N) for N in Ns])
-    _check(load().mbq_routed_linear_group_cfg(
-        _ptr(X), T, K, n, _ptr_array(Wr), _ptr_array(br), ctypes.byref(cfg), _ptr_array(blobs), n_arr,
-        _ptr_array([r[0] for r in routing]), _ptr_array([r[1] for r in routing]),
-        _ptr_array([r[2] for r in routing]), _ptr_array(Y), _ptr(ws_route), ws_route.numel(), _ptr(ws_linear),
-        ws_linear.numel(), algo, _stream()), "mbq_routed_linear_group_cfg")
-    return [tuple(r) for r in routing], list(Y)
+    load()
+    return _native.stage(X, Wr, br, blobs, Ns, routing, Y, ws_route, ws_linear, algo, ctypes.addressof(cfg))
 
 
 # ---- measurement and diagnostic entry points (include/mbq_bench.h) ----------------------------------

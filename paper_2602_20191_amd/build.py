@@ -1,4 +1,5 @@
-"""Builds libmbq.so (HIP, gfx950) in-tree with hipcc.  Run: python -m paper_2602_20191_amd.build"""
+"""Builds libmbq.so (HIP, gfx950) in-tree with hipcc, and the native half of the torch binding (_mbq_torch.so, host code
+against torch's headers).  Run: python -m paper_2602_20191_amd.build"""
 from __future__ import annotations
 
 import os
@@ -11,6 +12,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmbq.so")
+TORCH_LIB = os.path.join(HERE, "_mbq_torch.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 
 SOURCES = [
@@ -54,6 +56,19 @@ def _run(cmd):
     return out
 
 
+def torch_command():
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    includes = cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]
+    return (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+             "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)] +
+            [x for i in includes for x in ("-isystem", i)] + [os.path.join(CSRC, "mbq_torch.cpp"), "-o", TORCH_LIB] +
+            ["-L" + p for p in cpp_extension.library_paths()] + ["-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"])
+
+
 def build(verbose: bool = False, save_temps: bool = False) -> str:
     os.makedirs(OBJ_DIR, exist_ok=True)
     cc = hipcc()
@@ -66,6 +81,7 @@ def build(verbose: bool = False, save_temps: bool = False) -> str:
         if save_temps:
             cmd += ["-save-temps=obj"]
         jobs.append(cmd)
+    jobs.append(torch_command())
     with ThreadPoolExecutor(max_workers=min(6, os.cpu_count() or 1)) as pool:
         for out in pool.map(_run, jobs):
             if verbose and out.strip():

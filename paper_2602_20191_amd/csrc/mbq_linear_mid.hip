@@ -34,9 +34,10 @@ using namespace bf;
 
 constexpr int kWaves = 4;
 constexpr int kMaxBlocks = 16;  // of a part: their row constants wait in LDS
-constexpr int kMinRows = 33, kMaxRows = 64;
-constexpr int kRowBytes = 2 * kGroup;  // one group of one row: 16 chunks of 16 bytes, swizzled by the row
 constexpr int kMaxParts = 8;
+constexpr int kMinRows = 33, kMaxRows = 64;
+static_assert(kMaxParts <= kMaxKSplit, "the workspace holds the arrays");
+constexpr int kRowBytes = 2 * kGroup;  // one group of one row: 16 chunks of 16 bytes, swizzled by the row
 
 struct Proj {
   const uint4* codes;
@@ -394,7 +395,7 @@ static inline int64_t slot_floats(int64_t T, int64_t N) { return (T * N + 63) / 
 //   wide matrices, which come in pairs (gate and up), one part: twice 14336 x 4096 72 / 58, 73 / 57, 75 / 62; twice 11008 x
 //   4096 74 / 57, 60 / 56, 61 / 61; twice 8192 x 4096 44 / 46, 45 / 45, 46 / 50 (not taken); 14336 x 4096 alone 42 / 47, 43 /
 //   45, 44 / 50 (it takes the same kernel alone);
-//   long rows, eight parts or as many as the workspace holds: 4096 x 11008 43 / 36, 43 / 36, 44 / 40; 3072 x 8192 27 / 27, 28
+//   long rows, eight parts: 4096 x 11008 43 / 36, 43 / 36, 44 / 40; 3072 x 8192 27 / 27, 28
 //   / 27, 28 / 29, 2048 x 8192 23 / 24, 24 / 24, 24 / 25 (not taken).
 // At 32 tokens both kernels unpack once and are as fast.  The choice depends on T and the matrix alone: a call for several
 // matrices gives the bits of separate calls.
@@ -403,11 +404,9 @@ int mid_parts(int64_t T, const Shape& sh) {
   const int least = (sh.KB + mid::kMaxBlocks - 1) / mid::kMaxBlocks;
   if (sh.N >= 2 * sh.K && sh.NT >= 640) return least == 1 ? 1 : 0;
   if (sh.KB <= 32 || sh.NT < 192 || sh.N > sh.K) return 0;
-  // (the workspace of every call has room for the activations and 256 rows more)
-  const size_t room = (size_t)(T + 256) * (size_t)sh.K * 2 - mid::sums_bytes(T, sh.K);
-  int64_t parts = 1 + (int64_t)(room / ((size_t)mid::slot_floats(T, sh.N) * 4));
-  if (parts > mid::kMaxParts) parts = mid::kMaxParts;
-  return parts >= least ? (int)parts : 0;
+  // (the workspace of a call has room for kMaxKSplit arrays of at least T rows, decode_workspace_bytes: seven and the sums,
+  // which take less than an array as 64 N > K)
+  return mid::kMaxParts >= least ? mid::kMaxParts : 0;
 }
 
 mbq_status launch_linear_mid_group(const uint16_t* X, int64_t T, int n, const void* const* blobs, const Shape* shapes,
