@@ -18,36 +18,42 @@
 //   The zero-point / offset term  -sum_g s0 (OFF/64 - half/64 + z0) Sx[i][g]  is a rank-16 update
 //   done every 16 groups with fp32 MFMAs (16x16x4), so it costs no vector work in the group loop.
 //
-// Tile: 128 tokens x 256 outputs by FOUR wavefronts (each all rows x 64 columns, 8 x 4 MFMAs of 16x16x32), two such
+// Tile: 128 tokens x 256 outputs by FOUR wavefronts (each all rows x 64 columns, 4 x 2 MFMAs of 32x32x16), two such
 // workgroups on a compute unit.  What decides the shape:
 //   * The packed weights never go through LDS.  The blob stores a code tile in the operand order of the 16x16x32 MFMA,
 //     so a wavefront loads the codes of its own 64 columns into registers (one group ahead) and unpacks them straight
-//     into the B operand.  LDS then carries the activations only: 64 KB per 32 columns and compute unit, half of what
+//     into the B operand.  (The 32x32x16 MFMA takes 32 columns, two code tiles, and from each the codes of two of the four
+//     lane quarters, in two rounds of four steps: kq = hh and hh + 2 for the lanes' halves hh.)  LDS then carries the activations only: 64 KB per 32 columns and compute unit, half of what
 //     the matrix cores' time would allow (the 256 x 256 tile of eight wavefronts that this replaces moved 132 KB
 //     through LDS per 32 columns with a workgroup barrier each).
 //   * One barrier per group of 128 columns.  The activations of the next group (32 KiB, loaded straight into LDS by
 //     the memory pipeline) and its codes are requested at the top of a group and waited for at its end, about two
 //     thousand cycles later; the two workgroups of a compute unit are not in step, so one computes while the other
 //     stands at its barrier, and one's unpacking runs under the other's MFMAs.
-//   * Remainders of a bucket run the same loop with 2, 4 or 6 row tiles instead of 8 (a bucket's last 16..32 tokens
+//   * 32x32x16 and not 16x16x32: the same products in half the instructions (32.5 cycles against 2 x 17), half as many
+//     column tiles, so half of a group's scales, ratios and operand registers (11008 x 4096 at 2048 tokens 189 -> 184 us at
+//     2 bits, 220 -> 200 at 4, 240 -> 222 at 6, 303 -> 291 at 8 bits).
+//   * Remainders of a bucket run the same loop with 1, 2 or 3 row tiles of 32 instead of 4 (a bucket's last 16..32 tokens
 //     used to hold a compute unit as long as 256 tokens: four such remainders set the time below 1024 tokens).
 //   * Rows are fetched through the permutation (16 lanes read 256 bytes of one token), so no sorted copy is made.
 //   * A wavefront alone issues a vector instruction every 7 cycles, two share a SIMD at 4.6 for most of the unpacking's
-//     (measured), and an MFMA of 16 cycles hides two of them but not four: so unpacking and rescaling are dealt out under
+//     (measured), and 16 cycles of MFMA hide two of them but not four: so unpacking and rescaling are dealt out under
 //     the MFMAs one column tile later (`spread`), and nothing but those stands in the group loop.
 //   * What a tile costs besides its groups matters at K = 4096 and where a launch is one round: its row sums come through
 //     LDS, its rows leave through LDS (see load_sums and the stores): 16400 + 8000 cycles -> 7500 + 1000 a tile.
-// Whole calls on one box, before these two and now: 11008 x 4096 at 2048 tokens, {50,30,15,5} % mix 248 -> 234 us (788
-// TFLOP/s), all tokens at 2 bits 210 -> 193 us, at 8 bits 335 -> 304 us; 28672 x 8192 at 4096 tokens, {70,20,8,2} % mix
-// 1912 -> 1849 us (1040 TFLOP/s; a dense bf16 library product reaches 1383 on this card), at 256 tokens 304 -> 289 us; 3000
-// x 2176 at 777 tokens 56 -> 48 us.  Bound by instruction issue and the clock, which falls to 1.9 GHz under this load: two
-// workgroups on a compute unit take 6700 cycles for a group each, of which 4350 are MFMAs; one alone takes 4850.
+// Whole calls, before the last three and now: 11008 x 4096 at 2048 tokens, {50,30,15,5} % mix 248 -> 220 us (839 TFLOP/s),
+// all tokens at 2 bits 210 -> 184 us, at 8 bits 335 -> 291 us; 28672 x 8192 at 4096 tokens, {70,20,8,2} % mix 1912 -> 1760
+// us (1094 TFLOP/s; a dense bf16 library product reaches 1383 on this card), at 256 tokens 304 -> 275 us; 3000 x 2176 at 777
+// tokens 56 -> 46 us.  Bound by the clock, which falls to 1.9 GHz and below under this load: at 28672 x 8192 and 2 bits
+// (1190 TFLOP/s) leaving out the rescaling, or the unpacking, or both gains 7 %, leaving out the copies of the activations
+// 8 %; codes of 4 bits, which differ in the bits that the multipliers see, take 9 % longer without any unpacking too.
 #include "mbq_common.h"
 
 namespace mbq {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
@@ -154,8 +160,8 @@ __global__ __launch_bounds__(256) void prefill_fold_kernel(const Fold f) {
   }
 }
 
-__device__ __forceinline__ floatx4 mfma(const u32x4& a, const u32x4& b, floatx4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+__device__ __forceinline__ floatx16 mfma(const u32x4& a, const u32x4& b, floatx16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 __device__ __forceinline__ uint32_t rotr32(uint32_t w, int r) {  // r compile-time after inlining
   return (r & 31) == 0 ? w : __builtin_amdgcn_alignbit(w, w, r & 31);
@@ -203,7 +209,8 @@ __device__ __forceinline__ void spread(int each) {
     break;
   switch (each) {
     MBQ_SPREAD(2) MBQ_SPREAD(3) MBQ_SPREAD(4) MBQ_SPREAD(5) MBQ_SPREAD(6) MBQ_SPREAD(7) MBQ_SPREAD(8) MBQ_SPREAD(9)
-    MBQ_SPREAD(10) MBQ_SPREAD(11) MBQ_SPREAD(12)
+    MBQ_SPREAD(10) MBQ_SPREAD(11) MBQ_SPREAD(12) MBQ_SPREAD(13) MBQ_SPREAD(14) MBQ_SPREAD(16) MBQ_SPREAD(18) MBQ_SPREAD(19)
+    MBQ_SPREAD(20) MBQ_SPREAD(21) MBQ_SPREAD(22) MBQ_SPREAD(23) MBQ_SPREAD(24) MBQ_SPREAD(26) MBQ_SPREAD(28) MBQ_SPREAD(30)
     default: break;
   }
 #undef MBQ_SPREAD
@@ -223,6 +230,7 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l15 = lane & 15, kq = lane >> 4;
+  const int l31 = lane & 31, hh = lane >> 5;
   const int32_t* __restrict__ perm = M.perm;
 
   // ---- A: one instruction moves a group of four rows (16 lanes a row); MR instructions a wavefront and group: rows
@@ -256,46 +264,53 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
       dma_16(lds0 + stage + (uint32_t)(j * 16 * kRowBytes), kOffLds ? s_row[4 * wave + 16 * j + kq] + a_chunk : a_off[kOffLds ? 0 : j], src);
   };
   // ---- B: this wavefront's four column tiles of 16; two dwords a lane, tile, slice and group ----
-  const uint32_t* wptr[4];
-  const float* sptr[4];
+  const uint32_t* wptr[2];
+  const float* sptr[2];
+  uint32_t w_tile[2];  // words from the first of a pair's code tiles to this lane's
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    int nt = ntile_n * (kBN / kTileN) + 4 * wave + c;
-    nt = nt < M.NT ? nt : 0;  // past the matrix: reads tile 0, never stored
+  for (int c = 0; c < 2; ++c) {
+    int nt = ntile_n * (kBN / kTileN) + 4 * wave + 2 * c;
+    nt = nt < M.NT ? nt : 0;  // past the matrix: reads another tile, never stored
     wptr[c] = M.codes + (size_t)nt * KB * kTileWords;
     sptr[c] = reinterpret_cast<const float*>(M.meta + (size_t)nt * (2 * KB) * kTileN);
+    w_tile[c] = (l31 >= 16 && nt + 1 < M.NT) ? (uint32_t)KB * kTileWords : 0u;
   }
-  u32x2 w_cur[4][P + 1], w_nxt[4][P + 1];
-  float s_cur[4], s_nxt[4];
-  auto load_w = [&](int g, u32x2 (&w)[4][P + 1], float (&s)[4]) {
+  u32x2 w_cur[2][2][P + 1], w_nxt[2][2][P + 1];
+  float s_cur[2], s_nxt[2];
+  auto load_w = [&](int g, u32x2 (&w)[2][2][P + 1], float (&s)[2]) {
     const int ga = g0 + g;
     // (32-bit offsets from wave-uniform addresses: one code tile row is at most 2^26 bytes)
-    const uint32_t v = (uint32_t)(ga >> 1) * kTileWords + 2u * (uint32_t)(ga & 1) + 4u * (uint32_t)lane;
+    const uint32_t v = (uint32_t)(ga >> 1) * kTileWords + 2u * (uint32_t)(ga & 1) + 4u * (uint32_t)(16 * hh + l15);
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
+    for (int c = 0; c < 2; ++c) {
 #pragma unroll
-      for (int e = 0; e <= P; ++e) w[c][e] = *reinterpret_cast<const u32x2*>(wptr[c] + e * M.slice_words + v);
-      s[c] = sptr[c][(uint32_t)(2 * (ga * kTileN + l15))];
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int e = 0; e <= P; ++e)
+          w[c][j][e] = *reinterpret_cast<const u32x2*>(wptr[c] + e * M.slice_words + (w_tile[c] + v + 128u * (uint32_t)j));
+      s[c] = sptr[c][(w_tile[c] >> 2) + (uint32_t)(2 * (ga * kTileN + l15))];
     }
   };
   // the compiler's own wait for these loads is placed here (they have landed: the explicit wait came first)
-  auto settle = [&](u32x2 (&w)[4][P + 1], float (&s)[4]) {
+  auto settle = [&](u32x2 (&w)[2][2][P + 1], float (&s)[2]) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
+    for (int c = 0; c < 2; ++c) {
 #pragma unroll
-      for (int e = 0; e <= P; ++e) asm volatile("" : "+v"(w[c][e]));
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int e = 0; e <= P; ++e) asm volatile("" : "+v"(w[c][j][e]));
       asm volatile("" : "+v"(s[c]));
     }
   };
   // per-row operand constant of the group: the replicated high exponent byte (P <= 2) or the bits of 2^t (P = 3)
-  uint32_t b_x[4];
+  uint32_t b_x[2];
   // merged fields of the four weights with bit residue 2 r (r = step or step + 2), byte aligned; P <= 2: one bit
   // further, V / 2
-  auto merge_bits = [&](int pair, int c, int r) -> uint32_t {
-    uint32_t bits = w_cur[c][0][pair] & rotl_c(0xC0C0C0C0u, 2 * r - 4);
-    if constexpr (P >= 1) bits |= w_cur[c][1][pair] & rotl_c(0x30303030u, 2 * r - 4);
-    if constexpr (P >= 2) bits |= w_cur[c][2][pair] & rotl_c(0x0C0C0C0Cu, 2 * r - 4);
-    if constexpr (P >= 3) bits |= w_cur[c][3][pair] & rotl_c(0x03030303u, 2 * r - 4);
+  auto merge_bits = [&](int pair, int c, int j, int r) -> uint32_t {
+    uint32_t bits = w_cur[c][j][0][pair] & rotl_c(0xC0C0C0C0u, 2 * r - 4);
+    if constexpr (P >= 1) bits |= w_cur[c][j][1][pair] & rotl_c(0x30303030u, 2 * r - 4);
+    if constexpr (P >= 2) bits |= w_cur[c][j][2][pair] & rotl_c(0x0C0C0C0Cu, 2 * r - 4);
+    if constexpr (P >= 3) bits |= w_cur[c][j][3][pair] & rotl_c(0x03030303u, 2 * r - 4);
     return rotr32(bits, (2 * r - 4 + (P == 3 ? 0 : 1)) & 31);
   };
   // two bf16 of one merged word: bytes (0, 2) and (1, 3)
@@ -309,17 +324,21 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
       return __builtin_amdgcn_perm(b_x[c], w, b0 ? 0x04030401u : 0x04020400u);
     }
   };
-  auto unpack = [&](int h, int c) -> u32x4 {  // B operand of step h (32 columns) of the group, column tile c
-    const uint32_t lo = merge_bits(h >> 1, c, h & 1), hi = merge_bits(h >> 1, c, (h & 1) + 2);
+  auto unpack = [&](int step, int c) -> u32x4 {  // B operand of a step (16 columns) of the group, column tile c
+    const int h = step & 3, j = step >> 2;
+    const uint32_t lo = merge_bits(h >> 1, c, j, h & 1), hi = merge_bits(h >> 1, c, j, (h & 1) + 2);
     return u32x4{expand_pair(lo, c, 0), expand_pair(hi, c, 0), expand_pair(lo, c, 1), expand_pair(hi, c, 1)};
   };
 
-  floatx4 acc[MR][4];
+  constexpr int RT = MR / 2;  // row tiles of 32
+  floatx16 acc[RT][2];
 #pragma unroll
-  for (int a = 0; a < MR; ++a)
+  for (int a = 0; a < RT; ++a)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) acc[a][c] = floatx4{0.f, 0.f, 0.f, 0.f};
-  float m_cur[4];
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[a][c][i] = 0.f;
+  float m_cur[2];
 
   load_a(0, 0u);
   load_w(0, w_cur, s_cur);
@@ -327,7 +346,7 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
   settle(w_cur, s_cur);
   asm volatile("s_barrier" ::: "memory");
 #pragma unroll
-  for (int c = 0; c < 4; ++c) m_cur[c] = scale_mantissa(s_cur[c]);
+  for (int c = 0; c < 2; ++c) m_cur[c] = scale_mantissa(s_cur[c]);
 
   // The zero-point / offset term of groups g .. last - 1 (at most 16), in the accumulator's units, as a rank-16 fp32
   // MFMA update: lane quarter kq holds groups 4 kq .. 4 kq + 3 (the order of the k axis is free as long as both operands
@@ -351,25 +370,28 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
   };
   auto remove_offsets = [&](int g, int last) {
     constexpr float kC = (kHalf - kOff) * (1.f / 64.f);
-    float bv[4][4];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
+    for (int c = 0; c < 2; ++c) {
       const float units = 64.f / m_cur[c];
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int gg = min(g + 4 * kq + s, last - 1);
-        const float2 mt = *reinterpret_cast<const float2*>(sptr[c] + (uint32_t)(2 * ((g0 + gg) * kTileN + l15)));
-        bv[s][c] = (g + 4 * kq + s < last) ? mt.x * (kC - mt.y) * units : 0.f;
-      }
-    }
+      for (int j = 0; j < 2; ++j) {
+        float bv[4];
 #pragma unroll
-    for (int a = 0; a < MR; ++a) {
-      const floatx4 av = *reinterpret_cast<const floatx4*>(s_sum + (16 * a + l15) * 16 + 4 * kq);
+        for (int s = 0; s < 4; ++s) {
+          const int gg = min(g + 8 * hh + 4 * j + s, last - 1);
+          const float2 mt =
+              *reinterpret_cast<const float2*>(sptr[c] + ((w_tile[c] >> 2) + (uint32_t)(2 * ((g0 + gg) * kTileN + l15))));
+          bv[s] = (g + 8 * hh + 4 * j + s < last) ? mt.x * (kC - mt.y) * units : 0.f;
+        }
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const float v = (g + 4 * kq + s < last) ? av[s] : 0.f;
+        for (int a = 0; a < RT; ++a) {
+          const floatx4 av = *reinterpret_cast<const floatx4*>(s_sum + (32 * a + l31) * 16 + 8 * hh + 4 * j);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) acc[a][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(v, bv[s][c], acc[a][c], 0, 0, 0);
+          for (int s = 0; s < 4; ++s) {
+            const float v = (g + 8 * hh + 4 * j + s < last) ? av[s] : 0.f;
+            acc[a][c] = __builtin_amdgcn_mfma_f32_32x32x2f32(v, bv[s], acc[a][c], 0, 0, 0);
+          }
+        }
       }
     }
   };
@@ -391,9 +413,9 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
       load_a(qn, stage ^ (uint32_t)kStageBytes);
       load_w(qn, w_nxt, s_nxt);
       __builtin_amdgcn_sched_barrier(0);
-      float ratio[4];
+      float ratio[2];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
+      for (int c = 0; c < 2; ++c) {
         const uint32_t E = scale_exponent(s_cur[c]);
         b_x[c] = (P == 3) ? ((E - 8u) << 23) : ((E >> 1) * 0x01010101u);
         const float r = m_cur[c] * __builtin_amdgcn_rcpf(scale_mantissa(s_cur[c]));
@@ -402,53 +424,45 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
         const float inv = __builtin_amdgcn_rcpf(ratio[c]), quot = m_cur[c] * inv;
         m_cur[c] = __builtin_fmaf(__builtin_fmaf(-quot, ratio[c], m_cur[c]), inv, quot);
       }
-      // fragment of row tile a, step h: row 16 a + l15, chunk 4 h + kq
-      auto read_a = [&](int h, int a) -> u32x4 {
-        const uint32_t at = stage + (uint32_t)l15 * kRowBytes + (uint32_t)(((4 * h + kq) ^ l15) * 16);
-        return *reinterpret_cast<const u32x4*>(smem + at + a * 16 * kRowBytes);
+      // fragment of row tile a, step: row 32 a + l31, the chunk whose codes this lane unpacks for the step
+      auto read_a = [&](int step, int a) -> u32x4 {
+        const uint32_t at = stage + (uint32_t)l31 * kRowBytes + (uint32_t)(((4 * (step & 3) + 2 * (step >> 2) + hh) ^ l15) * 16);
+        return *reinterpret_cast<const u32x4*>(smem + at + a * 32 * kRowBytes);
       };
       // HR row tiles at a time, their fragments read one part ahead; the operand of column tile c of the next step is
       // unpacked into the same registers right behind the last MFMAs that read it.  A scheduling fence per column tile
       // keeps the registers of one part alive at a time: without it the compiler hoists unpacking and spills.
-      constexpr int HR = (P == 3 && MR == 8) ? 1 : MR < 4 ? MR : (P >= 2 || MR == 6) ? 2 : 4;
-      constexpr int kParts = MR / HR;
-      constexpr bool kUnder = P < 3;
-      u32x4 af[2][HR], bf[4];
+      constexpr int HR = P == 3 && RT == 4 ? 1 : RT;
+      constexpr int kParts = RT / HR;
+      u32x4 af[2][HR], bf[2];
 #pragma unroll
       for (int a = 0; a < HR; ++a) af[0][a] = read_a(0, a);
-#pragma unroll
-      for (int c = 0; c < 4; ++c) bf[c] = unpack(0, c);
+      bf[0] = unpack(0, 0);
       auto rescale = [&](int part, int c) {  // to the units of this group
 #pragma unroll
         for (int a = 0; a < HR; ++a)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) acc[part * HR + a][c][i] *= ratio[c];
+          for (int i = 0; i < 16; ++i) acc[part * HR + a][c][i] *= ratio[c];
       };
-      if (kUnder) rescale(0, 0);
+      rescale(0, 0);
 #pragma unroll
-      for (int hp = 0; hp < 4 * kParts; ++hp) {
+      for (int hp = 0; hp < 8 * kParts; ++hp) {
         const int h = hp / kParts, part = hp % kParts;
-        if (hp + 1 < 4 * kParts) {
+        if (hp + 1 < 8 * kParts) {
 #pragma unroll
           for (int a = 0; a < HR; ++a) af[(hp + 1) & 1][a] = read_a((hp + 1) / kParts, ((hp + 1) % kParts) * HR + a);
         }
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          if (!kUnder && h == 0) rescale(part, c);
+        for (int c = 0; c < 2; ++c) {
 #pragma unroll
           for (int a = 0; a < HR; ++a) acc[part * HR + a][c] = mfma(af[hp & 1][a], bf[c], acc[part * HR + a][c]);
-          if constexpr (!kUnder) {
-            if (part == kParts - 1 && h < 3) bf[c] = unpack(h + 1, c);
-          } else {
-            // under these MFMAs: the operand whose last MFMAs were issued one column tile ago, the next tiles' units
-            const bool un = (part == kParts - 1 && c > 0 && h < 3) || (part == 0 && c == 0 && h > 0);
-            if (part == kParts - 1 && c > 0 && h < 3) bf[c - 1] = unpack(h + 1, c - 1);
-            if (part == 0 && c == 0 && h > 0) bf[3] = unpack(h, 3);
-            const bool re = h == 0 && (c < 3 || part + 1 < kParts);
-            if (re) rescale(c < 3 ? part : part + 1, (c + 1) & 3);
-            const int each = ((un ? 8 + 2 * P : 0) + (re ? 4 * HR : 0) + HR - 1) / HR;  // vector instructions per MFMA
-            spread<HR>(each);
-          }
+          // under these MFMAs: the operand whose last MFMAs were issued one column tile ago, the next tiles' units
+          const bool un0 = part == kParts - 1 && c == 1 && h < 7, un1 = part == 0 && c == 0;
+          if (un0) bf[0] = unpack(h + 1, 0);
+          if (un1) bf[1] = unpack(h, 1);
+          const bool re = h == 0 && (c == 0 || part + 1 < kParts);
+          if (re) rescale(c == 0 ? part : part + 1, c ^ 1);
+          spread<HR>(((un0 || un1 ? 8 + 2 * P : 0) + (re ? 16 * HR : 0) + HR - 1) / HR);
           __builtin_amdgcn_sched_barrier(0);
         }
       }
@@ -456,9 +470,11 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
       asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
       settle(w_nxt, s_nxt);
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
+      for (int c = 0; c < 2; ++c) {
 #pragma unroll
-        for (int e = 0; e <= P; ++e) w_cur[c][e] = w_nxt[c][e];
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int e = 0; e <= P; ++e) w_cur[c][j][e] = w_nxt[c][j][e];
         s_cur[c] = s_nxt[c];
       }
       asm volatile("s_barrier" ::: "memory");
@@ -476,15 +492,16 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
   float* const own = reinterpret_cast<float*>(smem) + wave * (16 * kRow);
   const int64_t col0 = (int64_t)ntile_n * kBN + 64 * wave;
   const bool wide = !accumulate && (M.N & 3) == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0;
-  float f[4];
+  float f[2];
 #pragma unroll
-  for (int c = 0; c < 4; ++c) f[c] = m_cur[c] * (1.f / 64.f);  // true units
+  for (int c = 0; c < 2; ++c) f[c] = m_cur[c] * (1.f / 64.f);  // true units
 #pragma unroll
   for (int a = 0; a < MR; ++a) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
+    for (int c = 0; c < 2; ++c)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) own[(4 * kq + i) * kRow + 16 * c + l15] = acc[a][c][i] * f[c];
+      for (int i = 0; i < 8; ++i)
+        own[(8 * (i >> 2) + 4 * hh + (i & 3)) * kRow + 32 * c + l31] = acc[a >> 1][c][8 * (a & 1) + i] * f[c];
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     if (wide) {
       floatx4 v[4];

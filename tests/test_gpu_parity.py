@@ -512,6 +512,24 @@ def test_prefill_windows_of_row_sums(mbq, groups, parts):
     assert torch.equal(Y, shifted)
 
 
+@pytest.mark.parametrize("N", [16, 48, 272, 300])
+@pytest.mark.parametrize("turn", [0, 1, 2, 3])
+def test_prefill_pairs_of_code_tiles(mbq, N, turn):
+    """The tile kernel takes columns in pairs of code tiles and rows by 32: odd numbers of code tiles (the last pair's second
+    tile is past the matrix), every number of row tiles at every precision, first and last rows of a row tile."""
+    K, sizes = 384, np.roll((1, 33, 96, 97), turn)
+    T = int(sizes.sum())
+    xb = tokens(T, K, [T, N, 137])
+    W = make_weight(N, K, [137, N], 4.0)
+    codes, s0, z0 = O.encode(W)
+    prec = np.random.default_rng([137, turn]).permutation(np.repeat(np.arange(4), sizes)).astype(np.int32)
+    perm, offsets = O.bucket(prec)
+    X, blob = dev_bf16(xb).reshape(T, K), mbq.mbq_encode(dev(W))
+    Y = mbq.mbq_linear(X, blob, N, K, dev(prec), dev(perm), dev(offsets), algo=ALGOS["prefill"])
+    torch.cuda.synchronize()
+    assert_output_close(Y.cpu().numpy(), O.linear(xb, codes, s0, z0, prec), f"N={N}, rows {sizes}")
+
+
 @pytest.mark.parametrize("parts", [2, 6])
 def test_prefill_parts_replay_from_a_hip_graph(mbq, parts):
     """A captured call that clears arrays, adds into them and adds them up, replayed with eager work of the same kind in
