@@ -16,7 +16,7 @@
 //   group boundary (one multiply per element, ratio in (1/4, 4)), then the group's MFMAs
 //   accumulate straight into R.  After the last group R * m_last / 64 is the sum in true units.
 //   The zero-point / offset term  -sum_g s0 (OFF/64 - half/64 + z0) Sx[i][g]  is a rank-16 update
-//   done every 16 groups with fp32 MFMAs (16x16x4), so it costs no vector work in the group loop.
+//   done every 16 groups with MFMAs, so it costs no vector work in the group loop.
 //
 // Tile: 128 tokens x 256 outputs by FOUR wavefronts (each all rows x 64 columns, 4 x 2 MFMAs of 32x32x16), two such
 // workgroups on a compute unit.  What decides the shape:
@@ -41,12 +41,13 @@
 //     the MFMAs one column tile later (`spread`), and nothing but those stands in the group loop.
 //   * What a tile costs besides its groups matters at K = 4096 and where a launch is one round: its row sums come through
 //     LDS, its rows leave through LDS (see load_sums and the stores): 16400 + 8000 cycles -> 7500 + 1000 a tile.
-// Whole calls, before the last three and now: 11008 x 4096 at 2048 tokens, {50,30,15,5} % mix 248 -> 220 us (839 TFLOP/s),
-// all tokens at 2 bits 210 -> 184 us, at 8 bits 335 -> 291 us; 28672 x 8192 at 4096 tokens, {70,20,8,2} % mix 1912 -> 1760
-// us (1094 TFLOP/s; a dense bf16 library product reaches 1383 on this card), at 256 tokens 304 -> 275 us; 3000 x 2176 at 777
-// tokens 56 -> 46 us.  Bound by the clock, which falls to 1.9 GHz and below under this load: at 28672 x 8192 and 2 bits
-// (1190 TFLOP/s) leaving out the rescaling, or the unpacking, or both gains 7 %, leaving out the copies of the activations
-// 8 %; codes of 4 bits, which differ in the bits that the multipliers see, take 9 % longer without any unpacking too.
+// Whole calls, before the last three and the zero-point term in bf16 pieces, and now: 11008 x 4096 at 2048 tokens,
+// {50,30,15,5} % mix 248 -> 210 us (878 TFLOP/s), all tokens at 2 bits 210 -> 174 us, at 8 bits 335 -> 284 us; 28672 x 8192 at
+// 4096 tokens, {70,20,8,2} % mix 1912 -> 1680 us (1145 TFLOP/s; a dense bf16 library product reaches 1383 on this card), at
+// 256 tokens 304 -> 249 us; 3000 x 2176 at 777 tokens 56 -> 43 us.  Bound by the clock, which falls to 1.9 GHz and below
+// under this load: at 28672 x 8192 and 2 bits leaving out the rescaling, or the unpacking, or both gains 7 %, leaving out the
+// copies of the activations 8 %; codes of 4 bits, which differ in the bits that the multipliers see, take 9 % longer than
+// those of 2 bits without any unpacking too.
 #include "mbq_common.h"
 
 namespace mbq {
@@ -63,7 +64,7 @@ constexpr int kBM = 128, kBN = 256;
 
 constexpr int kRowBytes = 2 * kGroup;         // one group of one token: 16 chunks of 16 bytes, swizzled by the row
 constexpr int kStageBytes = kBM * kRowBytes;  // 32 KiB, two stages
-constexpr int kSumsBytes = kBM * 16 * 4;      // group sums of the tile's rows, 16 groups at a time
+constexpr int kSumsBytes = kBM * 16 * 6;      // group sums of the tile's rows, 16 groups at a time, in three bf16 pieces
 constexpr int kRowsBytes = 2 * kBM * 4;       // tokens of the rows, byte offsets of their activations
 constexpr int kPadRows = 256;                 // rows of the workspace beyond those of the activations
 constexpr int kMaxSplits = 8;
@@ -197,6 +198,23 @@ __device__ __forceinline__ void dma_4(uint32_t lds, const void* address) {
                : "memory");
 }
 
+// eight floats as sums of three bf16: the upper bits cut off, the rest rounded, what is left (exact: 8 + 9 + 7 bits)
+__device__ __forceinline__ void split_bf16(const float (&v)[8], u32x4 (&pieces)[3]) {
+  typedef float floatx2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float v0 = v[2 * i], v1 = v[2 * i + 1];
+    pieces[0][i] = __builtin_amdgcn_perm(__float_as_uint(v1), __float_as_uint(v0), 0x07060302u);
+    const float r0 = v0 - __uint_as_float(__float_as_uint(v0) & 0xFFFF0000u);
+    const float r1 = v1 - __uint_as_float(__float_as_uint(v1) & 0xFFFF0000u);
+    const uint32_t m = __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{r0, r1}, bf16x2));
+    pieces[1][i] = m;
+    const float l0 = r0 - __uint_as_float(m << 16), l1 = r1 - __uint_as_float(m & 0xFFFF0000u);
+    pieces[2][i] = __builtin_amdgcn_perm(__float_as_uint(l1), __float_as_uint(l0), 0x07060302u);
+  }
+}
+
 // scheduling hint: the region's MFMAs one by one, `each` vector instructions behind every one of them
 template <int MFMAS>
 __device__ __forceinline__ void spread(int each) {
@@ -219,9 +237,9 @@ __device__ __forceinline__ void spread(int each) {
 // One tile: rows row0 .. row0 + rows - 1 of the sorted tokens, columns 256 ntile_n ..; groups g0 .. g0 + G - 1.
 // P = precision index of the tokens, MR = 16-row tiles (16 MR >= rows).
 // gather: X is in token order and rows are fetched through perm; otherwise X is the sorted copy.
-// halfway: when the zero-point term is removed, see remove_offsets.
+// halfway, kPieces: when and how the zero-point term is removed, see remove_in_pieces.
 // out: the T x N array the tile goes to; accumulate: it is added there (two parts of K share the array).
-template <int P, int MR>
+template <int P, int MR, bool kPieces>
 __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, int KB, bool gather, const Proj& M,
                                      const float* __restrict__ Sx, int row0, int rows, int ntile_n, char* smem, int g0,
                                      int G, bool halfway, float* out, bool accumulate) {
@@ -348,15 +366,24 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
 #pragma unroll
   for (int c = 0; c < 2; ++c) m_cur[c] = scale_mantissa(s_cur[c]);
 
-  // The zero-point / offset term of groups g .. last - 1 (at most 16), in the accumulator's units, as a rank-16 fp32
-  // MFMA update: lane quarter kq holds groups 4 kq .. 4 kq + 3 (the order of the k axis is free as long as both operands
+  // The zero-point / offset term of groups g .. last - 1 (at most 16), in the accumulator's units, as a rank-16 update by
+  // MFMAs: lane half hh holds groups 8 hh .. 8 hh + 7 (the order of the k axis is free as long as both operands
   // share it).  Every 16 groups and not once at the end: the offset is many times the signal, and what the accumulator
   // carries sets its rounding (11008 x 4096: 1.8e-6 relative against 2.8e-6 with one update at the end, 4096 x 28672
-  // 1.9e-6 against 6.4e-6), for 3-4 % of the time.  halfway: the update comes when half of its groups are done, so that
+  // 1.9e-6 against 6.4e-6).  halfway: the update comes when half of its groups are done, so that
   // the accumulator carries the offset of half as many (3000 x 2176 at 777 tokens in two parts: 0.93e-6 relative behind
   // them, 0.74e-6 half way, 0.70e-6 in four parts).  Taken for parts of at most 16 groups, which replace twice as many
   // parts where there is no room for those; long parts lose up to 7 % by it (8192 x 28672 at 256 tokens 263 -> 282 us: the
   // scales of groups to come are not in cache yet).
+  // In fp32 (32x32x2, 64 cycles each) the update takes as many cycles as two groups.  kPieces: both operands as sums of
+  // three bf16, exact to 24 bits, and six of their nine products (the other three are below 2^-24 of the whole) in 32x32x16
+  // MFMAs, two fifths of that.  The rows' sums are split once for the workgroup, in their place in LDS.  The first product
+  // goes into the accumulator, the small ones come together in registers of their own and are added at once, so that the sum
+  // is rounded twice at its size and not eight times: against 64 bits 1.5e-6 -> 1.4e-6 relative for 11008 x 4096 at 2
+  // bits, 1.8e-6 -> 1.7e-6 for the mix (all six into the accumulator, the smallest first: 1.6e-6 and 1.9e-6), and 184 -> 175
+  // us, 28672 x 8192 at 256 tokens 273 -> 250.  In fp32 it stays for parts of at most 8 groups, where that rounds less
+  // (1000 x 2176 at 777 tokens 0.90e-6 against 0.93e-6), and for P = 3, whose unpacking leaves no registers for the
+  // pieces (11008 x 4096 at 2048 tokens 284 us in fp32, 294 in pieces).
   // The rows' sums of 16 groups come to LDS at the beginning of these groups ([row][16], by four bytes a lane: a token's
   // sums need not be aligned) and are there at the first barrier behind.  Fetched where they are used, token by token and
   // then sum by sum, they took a dozen trips to memory one after the other: about 8 us a tile.
@@ -368,7 +395,7 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
     for (int j = 0; j < MR; ++j)
       dma_4(lds + (uint32_t)((4 * wave + 16 * j) * 64), src + (int64_t)s_token[4 * wave + 16 * j + kq] * Gtot);
   };
-  auto remove_offsets = [&](int g, int last) {
+  auto remove_in_fp32 = [&](int g, int last) {
     constexpr float kC = (kHalf - kOff) * (1.f / 64.f);
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
@@ -393,6 +420,66 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
           }
         }
       }
+    }
+  };
+  auto remove_in_pieces = [&](int g, int last) {
+    constexpr float kC = (kHalf - kOff) * (1.f / 64.f);
+    const int k0 = g + 8 * hh;      // this lane's first group as an operand
+    float2 mt[2][8];
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int s = 0; s < 8; ++s)
+        mt[c][s] = *reinterpret_cast<const float2*>(
+            sptr[c] + ((w_tile[c] >> 2) + (uint32_t)(2 * ((g0 + min(k0 + s, last - 1)) * kTileN + l15))));
+    u32x4* const s_piece = reinterpret_cast<u32x4*>(s_sum);  // [piece][row][16 groups]
+    {
+      float v[8];
+      const int row = tid >> 1, half = tid & 1;
+      if (tid < 32 * MR) {
+        const floatx4* own = reinterpret_cast<const floatx4*>(s_sum + row * 16 + 8 * half);
+#pragma unroll
+        for (int s = 0; s < 8; ++s) v[s] = (g + 8 * half + s < last) ? own[s >> 2][s & 3] : 0.f;
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      if (tid < 32 * MR) {
+        u32x4 pieces[3];
+        split_bf16(v, pieces);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) s_piece[i * 2 * kBM + tid] = pieces[i];
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    }
+    u32x4 b[2][3];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const float units = 64.f / m_cur[c];
+      float v[8];
+#pragma unroll
+      for (int s = 0; s < 8; ++s) v[s] = (k0 + s < last) ? mt[c][s].x * (kC - mt[c][s].y) * units : 0.f;
+      split_bf16(v, b[c]);
+    }
+#pragma unroll
+    for (int a = 0; a < RT; ++a) {
+      u32x4 x[3];
+#pragma unroll
+      for (int i = 0; i < 3; ++i) x[i] = s_piece[i * 2 * kBM + 2 * (32 * a + l31) + hh];
+      floatx16 small[2];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) small[0][i] = small[1][i] = 0.f;
+#pragma unroll
+      for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int j = 0; j < 3 - i; ++j)
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            floatx16& sum = i + j == 0 ? acc[a][c] : small[c];
+            sum = mfma(x[i], b[c][j], sum);
+          }
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[a][c][i] += small[c][i];
     }
   };
 
@@ -481,7 +568,10 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
       __builtin_amdgcn_sched_barrier(0);
       stage ^= (uint32_t)kStageBytes;
     }
-    if (first < G) remove_offsets(first, last);
+    if (first < G) {
+      if constexpr (kPieces) remove_in_pieces(first, last);
+      else remove_in_fp32(first, last);
+    }
   }
 
   // ---- rows in original token order.  A lane holds rows 16 a + 4 kq + i, columns 16 c + l15: stored from there an
@@ -582,20 +672,30 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(const uint16_t* __restr
   const int slot = split % M.slots;
   float* const out = slot == 0 ? M.Y : M.slot + (slot - 1) * M.slot_floats;
   const bool shared = slot + M.slots < splits;
-  const bool halfway = splits > 1 && Gs <= 16;  // see remove_offsets
-#define MBQ_TILE(PP, MM) tile<PP, MM>(X, K, KB, gather != 0, M, Sx, row0, rows, ntile_n, smem, g0, Gs, halfway, out, shared)
-#define MBQ_ROWS(PP)                     \
-  do {                                   \
-    if (rows > 96) MBQ_TILE(PP, 8);      \
-    else if (rows > 64) MBQ_TILE(PP, 6); \
-    else if (rows > 32) MBQ_TILE(PP, 4); \
-    else MBQ_TILE(PP, 2);                \
+  const bool halfway = splits > 1 && Gs <= 16;  // for this and `few` see remove_in_pieces
+#define MBQ_TILE(PP, MM, PI) tile<PP, MM, PI>(X, K, KB, gather != 0, M, Sx, row0, rows, ntile_n, smem, g0, Gs, halfway, out, shared)
+#define MBQ_ROWS(PP, PI)                     \
+  do {                                       \
+    if (rows > 96) MBQ_TILE(PP, 8, PI);      \
+    else if (rows > 64) MBQ_TILE(PP, 6, PI); \
+    else if (rows > 32) MBQ_TILE(PP, 4, PI); \
+    else MBQ_TILE(PP, 2, PI);                \
   } while (0)
+  const bool few = Gs <= 8;
   switch (p) {
-    case 0: MBQ_ROWS(0); break;
-    case 1: MBQ_ROWS(1); break;
-    case 2: MBQ_ROWS(2); break;
-    default: MBQ_ROWS(3); break;
+    case 0:
+      if (few) MBQ_ROWS(0, false);
+      else MBQ_ROWS(0, true);
+      break;
+    case 1:
+      if (few) MBQ_ROWS(1, false);
+      else MBQ_ROWS(1, true);
+      break;
+    case 2:
+      if (few) MBQ_ROWS(2, false);
+      else MBQ_ROWS(2, true);
+      break;
+    default: MBQ_ROWS(3, false); break;
   }
 #undef MBQ_ROWS
 #undef MBQ_TILE

@@ -488,11 +488,12 @@ def test_prefill_parts_in_arrays_of_their_own(mbq, parts, T, Ns):
         assert torch.equal(Ys[i], again[i]), i
 
 
-@pytest.mark.parametrize("groups", [1, 2, 15, 16, 17, 32, 33])
+@pytest.mark.parametrize("groups", [1, 2, 8, 9, 15, 16, 17, 32, 33])
 @pytest.mark.parametrize("parts", [1, 2])
 def test_prefill_windows_of_row_sums(mbq, groups, parts):
     """The rows' sums come in windows of 16 groups: lengths around one and two windows, parts that begin inside a window,
-    every row-tile count, outputs that allow 16-byte stores and the same numbers where they do not."""
+    every row-tile count, outputs that allow 16-byte stores and the same numbers where they do not.  (The zero-point term
+    of parts of at most 8 groups comes in fp32, of longer ones in bf16 pieces.)"""
     K, N, T = 128 * groups, 276, 1 + 40 + 70 + 128
     xb = tokens(T, K, [T, K, 131])
     W = make_weight(N, K, [131, K], 4.0)
