@@ -656,6 +656,32 @@ mbq_status mbq_routed_linear_group(const uint16_t* X, int64_t T, int64_t K, int 
       }
     }
   }
+  // above 128 tokens with every matrix on the prefill kernel: the router launch also does the work of its pre-kernel
+  // (on compute units that the routers leave idle; the launch of its own took 10 us twice in a 7B-shaped MLP at 2048 tokens,
+  // 667 -> 653 us, 40 us twice in a 70B-shaped one at 4096, 5380 -> 5345; at 256 tokens 667 either way)
+  if (algo == MBQ_ALGO_AUTO || algo == MBQ_ALGO_PREFILL) {
+    Shape sh[MBQ_MAX_GROUP];
+    bool ok = n_proj >= 1 && n_proj <= MBQ_MAX_GROUP && N_host && blob_host && Y_host && P == t_view->P &&
+              T > kMaxDecodeTokens && T <= (int64_t)1 << 24 && !route_defers_sort(T) && K > 0 && K % kGroup == 0 &&
+              K <= (int64_t)1 << 24 && X && aligned(X, 16) && XL && aligned(XL, 16) && Wr_host && br_host && prec_host &&
+              perm_host && offsets_host && ws_route && aligned(ws_route, 256) &&
+              ws_route_bytes >= mbq_route_workspace_bytes(T, K) && ws_linear && aligned(ws_linear, 256);
+    for (int i = 0; ok && i < n_proj; ++i)
+      ok = N_host[i] > 0 && make_shape(N_host[i], K, &sh[i]) && blob_host[i] && aligned(blob_host[i], 256) &&
+           Y_host[i] && Wr_host[i] && aligned(Wr_host[i], 16) && br_host[i] && prec_host[i] && perm_host[i] &&
+           offsets_host[i] && ws_linear_bytes >= mbq_linear_workspace_bytes(T, N_host[i], K) &&
+           (algo == MBQ_ALGO_PREFILL || resolve_auto(T, sh[i]) == MBQ_ALGO_PREFILL);
+    PrefillPrep prep;
+    if (ok && prefill_prep_of(XL, T, n_proj, sh, Y_host, ws_linear, &prep)) {
+      mbq_status st = act_ahead(T, K, 0, nullptr, nullptr, nullptr, nullptr, 0, &aq, (hipStream_t)stream);
+      if (st != MBQ_OK) return st;
+      st = launch_route_group(X, T, K, n_proj, Wr_host, br_host, prec_host, perm_host, offsets_host, nullptr, ws_route,
+                              (hipStream_t)stream, nullptr, 0, nullptr, false, *t_view, nullptr, nullptr, nullptr, &prep);
+      if (st != MBQ_OK) return st;
+      return launch_linear_prefill_group(XL, T, n_proj, blob_host, sh, perm_host, offsets_host, Y_host, ws_linear,
+                                         (hipStream_t)stream, true);
+    }
+  }
   // otherwise exactly the two calls (they check the arguments)
   mbq_status st = MBQ_OK;
   if (T > 0) st = act_ahead(T, K, 0, nullptr, nullptr, nullptr, nullptr, 0, &aq, (hipStream_t)stream);

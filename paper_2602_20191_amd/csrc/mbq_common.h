@@ -109,10 +109,12 @@ mbq_status launch_route_group(const uint16_t* X, int64_t T, int64_t K, int n, co
                               int32_t* const* offsets, double* const* logits, void* ws, hipStream_t stream,
                               void* prep, int prep_blocks, const ZeroList* zl, bool defer_bucket,
                               const RouteView& view = kDefaultView, const uint16_t* Xprep = nullptr,
-                              const struct ActArgs* aq = nullptr, void* sums = nullptr);
+                              const struct ActArgs* aq = nullptr, void* sums = nullptr,
+                              const struct PrefillPrep* pf = nullptr);
 // aq: the launch also quantises the activations (act_carried); only where the call defers its sort
 // sums: the launch also leaves there what launch_mid_sums would, of X or, with aq, of the integers; only where the call
 // defers its sort
+// pf: the launch also does the work of the prefill kernel's pre-kernel; only where route_defers_sort(T) is false
 struct Span {  // a range of device memory
   const void* p;
   size_t bytes;
@@ -137,9 +139,12 @@ mbq_status launch_linear_prefill(const uint16_t* X, int64_t T, const void* blob,
                                  const int32_t* perm, const int32_t* offsets, float* Y, void* ws,
                                  hipStream_t stream);
 // the same for up to MBQ_MAX_GROUP matrices over one X (one K), each with its own routing, in one launch
+// the work of the pre-kernel of a call, for another launch to do (false: none can); `prepared`: one has done it
+bool prefill_prep_of(const uint16_t* X, int64_t T, int n, const Shape* shapes, float* const* Y, void* ws,
+                     struct PrefillPrep* prep);
 mbq_status launch_linear_prefill_group(const uint16_t* X, int64_t T, int n, const void* const* blobs, const Shape* shapes,
                                        const int32_t* const* perm, const int32_t* const* offsets, float* const* Y,
-                                       void* ws, hipStream_t stream);
+                                       void* ws, hipStream_t stream, bool prepared = false);
 mbq_status launch_linear_decode16(const uint16_t* X, int64_t T, const void* blob, const Shape& sh,
                                   const int32_t* prec, const int32_t* perm, float* Y, hipStream_t stream);
 // the same for up to MBQ_MAX_GROUP matrices over one X (one K), each with its own routing, in one launch
@@ -196,6 +201,43 @@ __device__ __forceinline__ float sum8(const uint4& v) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) s += __uint_as_float(u[j] << 16) + __uint_as_float(u[j] & 0xFFFF0000u);
   return s;
+}
+// What a prefill launch starts from: the sums of X over groups, Sx[token][group], and cleared arrays (zl: outputs, zs: arrays
+// of the workspace).  A workgroup does rows row0 .. row0 + rows - 1 and its share of the clearing.
+struct PrefillPrep {
+  const uint16_t* X;
+  float* Sx;
+  ZeroList zl, zs;
+};
+__device__ inline void prefill_clear(const ZeroList& zl, int64_t at, int64_t step) {
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+  for (int j = 0; j < MBQ_MAX_GROUP; ++j) {
+    float* p = zl.p[j];
+    if (p == nullptr) continue;
+    const int64_t n = zl.n[j], n4 = (reinterpret_cast<uintptr_t>(p) & 15) == 0 ? n >> 2 : 0;
+    for (int64_t i = at; i < n4; i += step) reinterpret_cast<f32x4*>(p)[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int64_t i = 4 * n4 + at; i < n; i += step) p[i] = 0.f;
+  }
+}
+// the sums of one row by 256 threads, t = 0 .. 255; copy: where the row goes besides (null: nowhere)
+__device__ inline void prefill_row_sums(const uint4* src, int64_t K, int t, float* sums, uint4* copy) {
+  const int chunks = (int)(K >> 3);  // a multiple of 16: groups of 16 lanes are whole
+  for (int c = t; c < chunks; c += 256) {
+    const uint4 v = src[c];
+    if (copy) copy[c] = v;
+    float s = sum8(v);
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+    if ((t & 15) == 0) sums[c >> 4] = s;
+  }
+}
+__device__ inline void prefill_prep_share(const PrefillPrep& p, int64_t T, int64_t K, int64_t row0, int rows, int threads) {
+  const int64_t at = (int64_t)blockIdx.x * threads + threadIdx.x, step = (int64_t)gridDim.x * threads;
+  prefill_clear(p.zl, at, step);
+  prefill_clear(p.zs, at, step);
+  for (int64_t r = row0 + (threadIdx.x >> 8); r < row0 + rows && r < T; r += threads >> 8)
+    prefill_row_sums(reinterpret_cast<const uint4*>(p.X + r * K), K, threadIdx.x & 255, p.Sx + r * (K >> 7), nullptr);
 }
 size_t decode_f4_workspace_bytes(int64_t T, const Shape& sh);
 mbq_status launch_decode_f4_prep(const uint16_t* X, int64_t T, int64_t K, int KB, void* ws, const ZeroList& zl,

@@ -90,40 +90,18 @@ struct Group {
   int n;
 };
 
-// ---- pre-kernel: Sx[token][g] = sum_{k in g} X[token][k]; arrays that the tile kernel adds into are cleared (zl:
-// outputs, zs: arrays of the workspace); sorted
-// copy Xs[r][:] = X[perm[r]][:] where one is wanted --------------------------------------------------------------
-__device__ inline void clear_share(const ZeroList& zl) {
-  const int64_t at = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
-#pragma unroll
-  for (int j = 0; j < MBQ_MAX_GROUP; ++j) {
-    float* p = zl.p[j];
-    if (p == nullptr) continue;
-    const int64_t n = zl.n[j], n4 = (reinterpret_cast<uintptr_t>(p) & 15) == 0 ? n >> 2 : 0;
-    for (int64_t i = at; i < n4; i += step) reinterpret_cast<floatx4*>(p)[i] = floatx4{0.f, 0.f, 0.f, 0.f};
-    for (int64_t i = 4 * n4 + at; i < n; i += step) p[i] = 0.f;
-  }
-}
-__global__ __launch_bounds__(256) void prefill_prep_kernel(const uint16_t* __restrict__ X, int64_t K,
-                                                           float* __restrict__ Sx, const ZeroList zl,
-                                                           const ZeroList zs, const int32_t* __restrict__ perm, uint16_t* __restrict__ Xs) {
+// ---- pre-kernel: Sx[token][g] = sum_{k in g} X[token][k]; arrays that the tile kernel adds into are cleared; sorted
+// copy Xs[r][:] = X[perm[r]][:] where one is wanted.  A stage call has the router launch do this (PrefillPrep). -------
+__global__ __launch_bounds__(256) void prefill_prep_kernel(const PrefillPrep p, int64_t K, const int32_t* __restrict__ perm,
+                                                           uint16_t* __restrict__ Xs) {
   const int64_t r = blockIdx.x;
-  clear_share(zl);
-  clear_share(zs);
-  const int64_t token = perm ? perm[r] : r;
-  const uint4* src = reinterpret_cast<const uint4*>(X + token * K);
-  const int chunks = (int)(K >> 3);  // a multiple of 16: groups of 16 lanes are whole
-  for (int c = threadIdx.x; c < chunks; c += 256) {
-    const uint4 v = src[c];
-    if (Xs) reinterpret_cast<uint4*>(Xs + r * K)[c] = v;
-    const uint32_t u[4] = {v.x, v.y, v.z, v.w};
-    float s = 0.f;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) s += __uint_as_float(u[j] << 16) + __uint_as_float(u[j] & 0xFFFF0000u);
-#pragma unroll
-    for (int off = 8; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
-    if ((threadIdx.x & 15) == 0) Sx[token * (K >> 7) + (c >> 4)] = s;
+  if (!Xs) {
+    prefill_prep_share(p, gridDim.x, K, r, 1, 256);
+    return;
   }
+  const int64_t token = perm[r];
+  prefill_row_sums(reinterpret_cast<const uint4*>(p.X + token * K), K, threadIdx.x, p.Sx + token * (K >> 7),
+                   reinterpret_cast<uint4*>(Xs + r * K));
 }
 
 // ---- post-kernel of launches that cut K into more than two parts: Y += array 1, += array 2, .. in that order ----
@@ -788,17 +766,46 @@ static void choose_splits(int64_t T, int64_t K, int n, const Shape* shapes, int6
   }
 }
 
+// offsets of rows are 32-bit: from 4 GiB of activations on a sorted copy is made, one matrix at a time
+static bool prefill_gathers(int64_t T, int64_t K) { return (uint64_t)T * (uint64_t)K * 2u <= 0xFFFFFFFFull; }
+static float* prefill_sums(void* ws, int64_t T, int64_t K) {
+  return reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + prefill_copy_bytes(T, K));
+}
+// the cuts of a call's matrices, and what its pre-kernel clears: outputs, arrays of the workspace that two parts add into
+static void prefill_cuts(int64_t T, int n, const Shape* shapes, float* const* Y, void* ws, Split* split, ZeroList* zl,
+                         ZeroList* zs) {
+  const int64_t K = shapes[0].K;
+  // without a sorted copy its room takes arrays of partial sums
+  const int64_t area = prefill_gathers(T, K) ? (int64_t)(prefill_copy_bytes(T, K) / sizeof(float)) : 0;
+  choose_splits(T, K, n, shapes, area, split);
+  float* slot = reinterpret_cast<float*>(ws);
+  for (int i = 0; i < MBQ_MAX_GROUP; ++i) {
+    const int j = i < n ? i : 0;
+    const int64_t floats = slot_floats(T, shapes[j].N);
+    const int twice = split[j].parts - split[j].slots;  // arrays with two parts: the first ones
+    zl->p[i] = (i < n && twice > 0) ? Y[j] : nullptr;
+    zl->n[i] = (i < n && twice > 0) ? (long long)T * shapes[j].N : 0;
+    zs->p[i] = (i < n && twice > 1) ? slot : nullptr;
+    zs->n[i] = (i < n && twice > 1) ? (long long)((twice - 1) * floats) : 0;
+    if (i < n) slot += (split[j].slots - 1) * floats;
+  }
+}
+bool prefill_prep_of(const uint16_t* X, int64_t T, int n, const Shape* shapes, float* const* Y, void* ws, PrefillPrep* prep) {
+  if (!prefill_gathers(T, shapes[0].K)) return false;
+  Split split[MBQ_MAX_GROUP];
+  prep->X = X;
+  prep->Sx = prefill_sums(ws, T, shapes[0].K);
+  prefill_cuts(T, n, shapes, Y, ws, split, &prep->zl, &prep->zs);
+  return true;
+}
+
 // The matrices share X; one launch for all of them, so that a stage has one ragged end.
 mbq_status launch_linear_prefill_group(const uint16_t* X, int64_t T, int n, const void* const* blobs, const Shape* shapes,
                                        const int32_t* const* perm, const int32_t* const* offsets, float* const* Y, void* ws,
-                                       hipStream_t stream) {
+                                       hipStream_t stream, bool prepared) {
   const int64_t K = shapes[0].K;
-  // offsets of rows are 32-bit: from 4 GiB of activations on a sorted copy is made, one matrix at a time
-  const bool gather = (uint64_t)T * (uint64_t)K * 2u <= 0xFFFFFFFFull;
+  const bool gather = prefill_gathers(T, K);
   uint16_t* Xs = reinterpret_cast<uint16_t*>(ws);
-  float* Sx = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + prefill_copy_bytes(T, K));
-  // without a sorted copy its room takes arrays of partial sums
-  const int64_t area = gather ? (int64_t)(prefill_copy_bytes(T, K) / sizeof(float)) : 0;
   if (!gather && n > 1) {
     for (int i = 0; i < n; ++i) {
       mbq_status st = launch_linear_prefill_group(X, T, 1, blobs + i, shapes + i, perm + i, offsets + i, Y + i, ws, stream);
@@ -807,11 +814,13 @@ mbq_status launch_linear_prefill_group(const uint16_t* X, int64_t T, int n, cons
     return MBQ_OK;
   }
   Split split[MBQ_MAX_GROUP];
-  choose_splits(T, K, n, shapes, area, split);
+  PrefillPrep prep;
+  prep.X = X;
+  prep.Sx = prefill_sums(ws, T, K);
+  prefill_cuts(T, n, shapes, Y, ws, split, &prep.zl, &prep.zs);
   const int64_t m_tiles_max = T / pf::kBM + MBQ_N_PRECISIONS;
   pf::Group g;
   pf::Fold fold;
-  ZeroList zl, zs;  // outputs, arrays of the workspace that two parts are added into
   int64_t blocks = 0, most = 0;
   float* slot = reinterpret_cast<float*>(ws);
   for (int i = 0; i < MBQ_MAX_GROUP; ++i) {
@@ -834,11 +843,6 @@ mbq_status launch_linear_prefill_group(const uint16_t* X, int64_t T, int n, cons
     m.splits = sp.parts;
     m.slots = sp.slots;
     m.block_begin = (int)blocks;
-    const int twice = sp.parts - sp.slots;  // arrays with two parts: the first ones
-    zl.p[i] = (i < n && twice > 0) ? Y[j] : nullptr;
-    zl.n[i] = (i < n && twice > 0) ? (long long)T * sh.N : 0;
-    zs.p[i] = (i < n && twice > 1) ? slot : nullptr;
-    zs.n[i] = (i < n && twice > 1) ? (long long)((twice - 1) * floats) : 0;
     fold.Y[i] = Y[j];
     fold.slot[i] = slot;
     fold.slot_floats[i] = floats;
@@ -851,12 +855,15 @@ mbq_status launch_linear_prefill_group(const uint16_t* X, int64_t T, int n, cons
     }
   }
   g.n = n;
-  hipLaunchKernelGGL(pf::prefill_prep_kernel, dim3((unsigned)T), dim3(256), 0, stream, X, K, Sx, zl, zs,
-                     gather ? nullptr : perm[0], gather ? nullptr : Xs);
-  mbq_status st = hip_status(hipGetLastError(), "prefill_prep_kernel launch");
-  if (st != MBQ_OK) return st;
+  mbq_status st = MBQ_OK;
+  if (!prepared || !gather) {
+    hipLaunchKernelGGL(pf::prefill_prep_kernel, dim3((unsigned)T), dim3(256), 0, stream, prep, K, gather ? nullptr : perm[0],
+                       gather ? nullptr : Xs);
+    st = hip_status(hipGetLastError(), "prefill_prep_kernel launch");
+    if (st != MBQ_OK) return st;
+  }
   hipLaunchKernelGGL(pf::prefill_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, gather ? X : Xs, K, shapes[0].KB,
-                     gather ? 1 : 0, Sx, g);
+                     gather ? 1 : 0, prep.Sx, g);
   st = hip_status(hipGetLastError(), "prefill_kernel launch");
   if (st != MBQ_OK || most == 0) return st;
   int64_t fold_blocks = (most / 4 + 255) / 256;  // four floats a thread and pass

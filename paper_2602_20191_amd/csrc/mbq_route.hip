@@ -169,9 +169,13 @@ constexpr int kTileWaves = 16;
 // stages at 2048 tokens 26 us on average, where a launch of vector code per router took 31; 70B-shaped ones at 4096 tokens
 // 59 us instead of 132 a stage; at 256 tokens it would be 52 instead of 23.
 __global__ __launch_bounds__(64 * kTileWaves) void route_kernel(const uint16_t* __restrict__ X, int64_t T, int64_t K,
-                                                                const RouteGroup group, int n) {
+                                                                const RouteGroup group, int n, const PrefillPrep pf) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int64_t tok0 = (int64_t)blockIdx.x * 16;
+  if (blockIdx.y == 1) {  // (only with pf) these workgroups run beside the tiles', which leave the memory pipes idle
+    prefill_prep_share(pf, T, K, tok0, 16, 64 * kTileWaves);
+    return;
+  }
   const int P = group.view.P;
   __shared__ double s_part[kTileWaves][64][4];
   __shared__ double s_logit[16][16];
@@ -221,10 +225,14 @@ __global__ __launch_bounds__(64 * kTileWaves) void route_kernel(const uint16_t* 
 // exact in fp64), reduced over the wavefront (wave_sum4) and over the four wavefronts through LDS.
 template <int TPW>
 __global__ __launch_bounds__(256) void route_rows_kernel(const uint16_t* __restrict__ X, int64_t T, int64_t K,
-                                                         const RouteGroup group) {
+                                                         const RouteGroup group, int n, const PrefillPrep pf) {
+  const int64_t tok0 = (int64_t)blockIdx.x * TPW;
+  if ((int)blockIdx.y == n) {  // (only with pf)
+    prefill_prep_share(pf, T, K, tok0, TPW, 256);
+    return;
+  }
   const RouteOut& out = group.r[blockIdx.y];
   const int P = group.view.P;
-  const int64_t tok0 = (int64_t)blockIdx.x * TPW;
   const int tid = threadIdx.x;
   double acc[TPW][kP];
 #pragma unroll
@@ -571,7 +579,8 @@ mbq_status launch_route_group(const uint16_t* X, int64_t T, int64_t K, int n, co
                               const float* const* br, int32_t* const* prec, int32_t* const* perm,
                               int32_t* const* offsets, double* const* logits, void* ws, hipStream_t stream,
                               void* prep, int prep_blocks, const ZeroList* zl, bool defer_bucket,
-                              const RouteView& view, const uint16_t* Xprep, const ActArgs* aq, void* sums) {
+                              const RouteView& view, const uint16_t* Xprep, const ActArgs* aq, void* sums,
+                              const PrefillPrep* pf) {
   if (T == 0) return launch_sort(n, prec, perm, offsets, 0, 0, stream);  // the (all-zero) offsets
   RouteGroup g;
   g.view = view;
@@ -605,12 +614,17 @@ mbq_status launch_route_group(const uint16_t* X, int64_t T, int64_t K, int n, co
     }
     return hip_status(hipGetLastError(), "route_small_kernel launch");
   }
+  const unsigned planes = pf ? 1u : 0u;  // one more plane of workgroups for the work of the prefill's pre-kernel
+  const PrefillPrep prefill = pf ? *pf : PrefillPrep{};
   if (T <= 256)
-    hipLaunchKernelGGL(route_rows_kernel<1>, dim3((unsigned)T, (unsigned)n), dim3(256), 0, stream, X, T, K, g);
+    hipLaunchKernelGGL(route_rows_kernel<1>, dim3((unsigned)T, (unsigned)n + planes), dim3(256), 0, stream, X, T, K, g, n,
+                       prefill);
   else if (T <= 1024)
-    hipLaunchKernelGGL(route_rows_kernel<4>, dim3((unsigned)((T + 3) / 4), (unsigned)n), dim3(256), 0, stream, X, T, K, g);
+    hipLaunchKernelGGL(route_rows_kernel<4>, dim3((unsigned)((T + 3) / 4), (unsigned)n + planes), dim3(256), 0, stream, X, T,
+                       K, g, n, prefill);
   else
-    hipLaunchKernelGGL(route_kernel, dim3((unsigned)((T + 15) / 16)), dim3(64 * kTileWaves), 0, stream, X, T, K, g, n);
+    hipLaunchKernelGGL(route_kernel, dim3((unsigned)((T + 15) / 16), 1u + planes), dim3(64 * kTileWaves), 0, stream, X, T, K,
+                       g, n, prefill);
   mbq_status st = hip_status(hipGetLastError(), "route_kernel launch");
   if (st != MBQ_OK) return st;
   return launch_sort(n, prec, perm, offsets, T, view.shift, stream);

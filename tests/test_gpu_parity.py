@@ -531,6 +531,39 @@ def test_prefill_pairs_of_code_tiles(mbq, N, turn):
     assert_output_close(Y.cpu().numpy(), O.linear(xb, codes, s0, z0, prec), f"N={N}, rows {sizes}")
 
 
+@pytest.mark.parametrize("parts", [0, 2, 6])
+@pytest.mark.parametrize("T,K,Ns", [(129, 2304, (300, 530)), (256, 384, (272,)), (257, 4608, (999, 64, 130)),
+                                    (1024, 640, (260, 36)), (1025, 1152, (530,)), (1041, 4608, (72, 300, 130, 16))])
+def test_stage_call_whose_router_launch_prepares_the_prefill(mbq, T, K, Ns, parts):
+    """Above 128 tokens the stage's router launch also forms the row sums and clears the arrays that parts add into: the same
+    bits as the two calls, whatever outputs and workspace held before, at the token counts where the router changes."""
+    xb = tokens(T, K, [T, K, 139])
+    X = dev_bf16(xb).reshape(T, K)
+    rng = np.random.default_rng([T, K, 139])
+    Wr = [dev((rng.standard_normal((4, K)) / np.sqrt(K)).astype(np.float32)) for _ in Ns]
+    br = [dev(rng.normal(0, 0.3, size=4).astype(np.float32)) for _ in Ns]
+    Ws = [make_weight(N, K, [139, N, i], 4.0) for i, N in enumerate(Ns)]
+    blobs = [mbq.mbq_encode(dev(W)) for W in Ws]
+    ws_linear = mbq.linear_workspace(T, max(Ns), K, "cuda")
+    ws_linear.fill_(255)  # floats of NaN
+    Y = [torch.full((T, N), float("nan"), device="cuda") for N in Ns]
+    mbq.set_knob(5, parts)
+    try:
+        routing, Ys = mbq.mbq_routed_linear_group(X, Wr, br, blobs, list(Ns), Y=Y, ws_linear=ws_linear, algo=ALGOS["prefill"])
+        again = mbq.mbq_linear_group(X, blobs, list(Ns), K, routing, algo=ALGOS["prefill"])
+    finally:
+        mbq.set_knob(5, 0)
+    torch.cuda.synchronize()
+    routing2 = mbq.mbq_route_group(X, Wr, br)
+    for i, N in enumerate(Ns):
+        for a, b in zip(routing[i], routing2[i]):
+            assert torch.equal(a, b), i
+        assert torch.equal(Ys[i], again[i]), i
+    codes, s0, z0 = O.encode(Ws[0])
+    want = O.linear(xb, codes, s0, z0, routing[0][0].cpu().numpy())
+    assert_output_close(Ys[0].cpu().numpy(), want, f"T={T}, {parts} parts")
+
+
 @pytest.mark.parametrize("parts", [2, 6])
 def test_prefill_parts_replay_from_a_hip_graph(mbq, parts):
     """A captured call that clears arrays, adds into them and adds them up, replayed with eager work of the same kind in
