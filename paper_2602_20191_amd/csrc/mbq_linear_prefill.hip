@@ -727,13 +727,15 @@ static double split_cost(Split sp, int64_t T, int64_t K, int64_t cols) {
 }
 // The cut that minimises the estimate, among those of at most `most` parts. Fitted to 1..8 parts on twenty shapes from
 // 1000 x 2176 to 28672 x 8192, alone and in groups of two and three, at 65..4096 tokens: 1.0 % above the best cut alone
-// on average (17 % on the worst), 0.6 % (13 %) in groups. For instance (us, 1 / 2 / 4 / 8 parts; * taken) 4096 x 11008
-// at 256 tokens 209 / 123 / 83 / 77*, at 2048 tokens 345 / 264* / 291 / -, 4096 x 4096 at 160 tokens 78 / 45 / 39*,
-// 11008 x 4096 at 256 tokens 94 / 75*, at 777 tokens 133* / 164.
+// on average (17 % on the worst), 0.6 % (13 %) in groups; of the tile kernel as it is now, 39 calls, 2.1 % above the best cut
+// on average (19 % on the worst, 4096 x 14336 at 300 tokens 91 in eight parts, 76 in four; constants fitted anew came to
+// 1.5 %, so they stay). For instance (us, 1 / 2 / 4 / 8 parts; * taken) 4096 x 11008 at 256 tokens 177 / 97 / 74 / 66*, at
+// 2048 tokens 311 / 260* / 287 / -, 4096 x 4096 at 160 tokens 68 / 40 / 33*, 11008 x 4096 at 256 tokens 77 / 62*, at 777
+// tokens 118* / 150.
 // pairs: a matrix with as many rows as columns or more has company more often than not (q, k, v of an attention; gate
 // and up of a gated MLP, with twice as many rows or more), and one or two parts have to be the same in company and
 // alone (choose_splits): the product of the estimates alone and, `pairs` times, as a pair decides (14336 x 4096 at 160
-// tokens, 1 / 2 parts: alone 83 / 62*, as a pair 118 / 109*; at 256 tokens 91* / 78 and 122* / 144).
+// tokens, 1 / 2 parts: alone 76 / 53*, as a pair 115 / 110*; at 256 tokens as a pair 117* / 130).
 // knob 5 forces the number of parts.
 static Split choose_split(int64_t T, int64_t K, int64_t N, int64_t cols, int pairs, int most, int64_t area_floats) {
   if (knob(5) >= 1 && knob(5) <= pf::kMaxSplits) return split_into(knob(5), T, K, N, area_floats);
