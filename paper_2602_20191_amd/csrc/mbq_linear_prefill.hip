@@ -468,7 +468,8 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
     const int last = min(G, first + 16);
     const int stop = first < G && halfway ? (first + last + 1) >> 1 : last;
     if (first < G) {
-      if (first > 0) asm volatile("s_barrier" ::: "memory");  // every wavefront has used the sums before these
+      // every wavefront has read the sums before these (the reads are over, not just issued: what follows overwrites them)
+      if (first > 0) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
       load_sums(first);
     }
 #pragma unroll 1

@@ -513,6 +513,29 @@ def test_prefill_windows_of_row_sums(mbq, groups, parts):
     assert torch.equal(Y, shifted)
 
 
+@pytest.mark.parametrize("p", [0, 1, 2, 3])
+def test_prefill_many_windows_of_row_sums(mbq, p):
+    """Each window's sums take the place of those before: many windows, tiles with every number of row tiles, the zero-point
+    term in either form; three calls give the same bits, and those are the oracle's within the bar."""
+    K, N = 128 * 90, 272
+    counts = np.roll((128, 70, 33, 20), p)
+    T = int(counts.sum())
+    xb = tokens(T, K, [T, K, 151])
+    W = make_weight(N, K, [151, N], 4.0)
+    codes, s0, z0 = O.encode(W)
+    prec = np.random.default_rng([151, p]).permutation(np.repeat(np.arange(4), counts)).astype(np.int32)
+    perm, offsets = O.bucket(prec)
+    X, blob, r = dev_bf16(xb).reshape(T, K), mbq.mbq_encode(dev(W)), (dev(prec), dev(perm), dev(offsets))
+    mbq.set_knob(5, 1)
+    try:
+        Y, *again = [mbq.mbq_linear(X, blob, N, K, *r, algo=ALGOS["prefill"]) for _ in range(3)]
+    finally:
+        mbq.set_knob(5, 0)
+    torch.cuda.synchronize()
+    assert all(torch.equal(Y, y) for y in again)
+    assert_output_close(Y.cpu().numpy(), O.linear(xb, codes, s0, z0, prec), f"rows {counts}")
+
+
 @pytest.mark.parametrize("N", [16, 48, 272, 300])
 @pytest.mark.parametrize("turn", [0, 1, 2, 3])
 def test_prefill_pairs_of_code_tiles(mbq, N, turn):
