@@ -99,6 +99,8 @@ __global__ __launch_bounds__(256) void prefill_prep_kernel(const PrefillPrep p, 
     prefill_prep_share(p, gridDim.x, K, r, 1, 256);
     return;
   }
+  prefill_clear(p.zl, r * 256 + threadIdx.x, (int64_t)gridDim.x * 256);
+  prefill_clear(p.zs, r * 256 + threadIdx.x, (int64_t)gridDim.x * 256);
   const int64_t token = perm[r];
   prefill_row_sums(reinterpret_cast<const uint4*>(p.X + token * K), K, threadIdx.x, p.Sx + token * (K >> 7),
                    reinterpret_cast<uint4*>(Xs + r * K));

@@ -422,6 +422,35 @@ def test_prefill_above_four_gibibytes_of_activations(mbq):
         assert_output_close(Y[rows].cpu().numpy(), ref.cpu().numpy(), f"precision {p}")
 
 
+@pytest.mark.parametrize("T,K,N,parts", [(131200, 16384, 40, 2), (16384, 131072, 256, 0)])
+def test_prefill_sorted_copy_in_two_parts(mbq, T, K, N, parts):
+    """From 4 GiB of activations on, two parts of K add into outputs that the launch ahead clears: forced, and a shape that takes
+    two by itself.  Whatever the outputs held before, and again on the outputs of the call before."""
+    assert T * K * 2 > 2 ** 32 - 1
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(157)
+    blob = mbq.mbq_encode(0.02 * torch.randn((N, K), generator=gen, device="cuda"))
+    X = torch.empty((T, K), dtype=torch.bfloat16, device="cuda")
+    for t in range(0, T, 2050):
+        X[t:t + 2050] = torch.randn((min(2050, T - t), K), generator=gen, device="cuda").to(torch.bfloat16)
+    prec = torch.randint(0, 4, (T,), generator=gen, device="cuda", dtype=torch.int32)
+    r = (prec, torch.sort(prec.long(), stable=True)[1].int(), torch.stack([(prec < q).sum() for q in range(5)]).int())
+    Y = torch.full((T, N), float("nan"), device="cuda")
+    mbq.set_knob(5, parts)
+    try:
+        mbq.mbq_linear(X, blob, N, K, *r, Y=Y, algo=ALGOS["prefill"])
+        first = Y.clone()
+        mbq.mbq_linear(X, blob, N, K, *r, Y=Y, algo=ALGOS["prefill"])
+    finally:
+        mbq.set_knob(5, 0)
+    assert torch.equal(first, Y)
+    pick = torch.cat([torch.arange(0, 40), torch.arange(T // 2, T // 2 + 40), torch.arange(T - 40, T)]).cuda()
+    for p in range(4):
+        rows = pick[prec[pick] == p]
+        ref = X[rows].double() @ mbq.mbq_dequant(blob, N, K, p).double().T
+        assert_output_close(Y[rows].cpu().numpy(), ref.cpu().numpy(), f"precision {p}")
+
+
 @pytest.mark.parametrize("T,K,n", [(129, 128, 1), (257, 640, 3), (1024, 384, 2), (1025, 128, 4), (1041, 4224, 1), (2064, 640, 3)])
 def test_route_group_above_128_tokens(mbq, T, K, n):
     """The general routers on both sides of their token limits, odd token counts, one 128-column block (most wavefronts
