@@ -81,7 +81,7 @@ int64_t whole(PyObject* o) {
 PyObject* stage_call(PyObject* const* args) {
   const at::Tensor& X = tensor(args[0]);
   const int64_t cfg = whole(args[10]);
-  if (X.dim() != 2 || (!cfg && X.scalar_type() != at::kBFloat16)) fail(PyExc_AssertionError, "X must be a bf16 matrix");
+  if (X.dim() != 2 || X.scalar_type() != at::kBFloat16) fail(PyExc_AssertionError, "X must be a bf16 matrix");
   const int64_t T = X.size(0), K = X.size(1);
   const Items Wr(args[1]), br(args[2]), blobs(args[3]), Ns(args[4]);
   const Py_ssize_t n = Ns.size();

@@ -38,6 +38,21 @@ def test_stage_refuses_what_it_cannot_use():
         pkg.mbq_routed_linear_group(X, Wr * 10, br * 10, blobs * 10, Ns * 10)
 
 
+@built
+@pytest.mark.parametrize("widths", [None, (4, 2, 2), (3, 1, 2, 2)])
+@pytest.mark.parametrize("change", [lambda X: X.float(), lambda X: X.half(), lambda X: X.to(torch.uint8), lambda X: X[0],
+                                    lambda X: X[None]])
+def test_stage_refuses_activations_of_another_type_or_rank(widths, change):
+    """Under every slice configuration: X is read as bf16, a type of one byte would be read past its end."""
+    X, Wr, br, W, Ns = inputs("cpu", P=4 if widths is None else len(widths))
+    blobs = [torch.zeros(1 << 16, dtype=torch.uint8) for _ in Ns]
+    with pytest.raises(AssertionError):
+        if widths is None:
+            pkg.mbq_routed_linear_group(change(X), Wr, br, blobs, Ns)
+        else:
+            pkg.mbq_routed_linear_group_cfg(change(X), Wr, br, pkg.Config(widths), blobs, Ns)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("widths", [None, (4, 2, 2), (3, 1, 2, 2)])
 @pytest.mark.parametrize("T", [0, 1, 5, 40, 130])
