@@ -1,6 +1,7 @@
 """The native half of the Python binding (csrc/mbq_torch.cpp): what it refuses, and that buffers left to it give what kept
 buffers give."""
 import os
+import struct
 
 import pytest
 import torch
@@ -18,6 +19,19 @@ def inputs(device, T=5, K=256, Ns=(40, 16), P=4, seed=3):
     br = [torch.zeros(P, device=device) for _ in Ns]
     W = [(0.02 * torch.randn((N, K), generator=gen)).to(device) for N in Ns]
     return X, Wr, br, W, list(Ns)
+
+
+@built
+def test_module_has_no_thread_local_storage():
+    """A module with thread-local storage that nothing reads makes every thread-local access of the libraries loaded before it
+    slow for the rest of the process (the C library's table of such modules is then never up to date), torch's own
+    calls included."""
+    with open(os.path.join(os.path.dirname(pkg.__file__), "_mbq_torch.so"), "rb") as f:
+        elf = f.read()
+    assert elf[:6] == b"\x7fELF\x02\x01"  # 64 bits, little endian
+    table, size, count = struct.unpack_from("<Q", elf, 32)[0], *struct.unpack_from("<HH", elf, 54)
+    kinds = [struct.unpack_from("<I", elf, table + i * size)[0] for i in range(count)]
+    assert 1 in kinds and 7 not in kinds  # PT_LOAD, PT_TLS
 
 
 @built
