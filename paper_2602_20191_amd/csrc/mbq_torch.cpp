@@ -5,11 +5,11 @@
 #include <Python.h>
 
 #include <ATen/ATen.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <stdint.h>
 
-#include <stdexcept>
 #include <string>
 
 namespace {
@@ -195,17 +195,15 @@ PyObject* stage_call(PyObject* const* args) {
 }
 
 PyObject* stage(PyObject*, PyObject* const* args, Py_ssize_t count) {
+  HANDLE_TH_ERRORS  // torch's errors as the Python exceptions that they are elsewhere (torch.OutOfMemoryError among them)
   try {
     if (!lib.stage) fail(PyExc_RuntimeError, "bind() comes first");
     if (count != 11) fail(PyExc_TypeError, "stage() takes 11 arguments");
     return stage_call(args);
   } catch (const PythonError&) {
-  } catch (const c10::Error& e) {
-    if (!PyErr_Occurred()) PyErr_SetString(PyExc_RuntimeError, e.what_without_backtrace());
-  } catch (const std::exception& e) {
-    if (!PyErr_Occurred()) PyErr_SetString(PyExc_RuntimeError, e.what());
+    return nullptr;
   }
-  return nullptr;
+  END_HANDLE_TH_ERRORS
 }
 
 // bind(stage, stage_cfg, route_bytes, linear_bytes, last_error, MbqError, current_device, raw_stream)

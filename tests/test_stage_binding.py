@@ -108,3 +108,21 @@ def test_stage_buffers_left_to_the_binding(mbq, widths, T):
         call(ws_linear=torch.empty(256, dtype=torch.uint8, device="cuda")[:255], ws_route=kept["ws_route"][:8])
     with pytest.raises(mbq.MbqError, match="contiguous"):
         call(Y=[torch.empty((N, T + 1), device="cuda").t()[:T] for N in Ns] if T > 1 else [torch.empty((T, N)) for N in Ns])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("widths", [None, (4, 2, 2)])
+def test_stage_without_memory_for_its_outputs(mbq, widths):
+    """An allocation that fails is torch's own exception, as for a tensor made in Python, and the next call works."""
+    X, Wr, br, W, Ns = inputs("cuda", P=4 if widths is None else len(widths))
+    blobs = [mbq.mbq_encode(w) for w in W]
+
+    def call(X, Ns):
+        if widths is None:
+            return mbq.mbq_routed_linear_group(X, Wr, br, blobs, Ns)
+        return mbq.mbq_routed_linear_group_cfg(X, Wr, br, mbq.Config(widths), blobs, Ns)
+
+    with pytest.raises(torch.OutOfMemoryError):  # outputs of 4 TiB
+        call(torch.zeros((1 << 16, X.shape[1]), dtype=torch.bfloat16, device="cuda"), [1 << 24] * len(Ns))
+    _, Y = call(X, Ns)
+    assert [y.shape for y in Y] == [(X.shape[0], N) for N in Ns] and all(bool(y.isfinite().all()) for y in Y)
