@@ -63,7 +63,7 @@ class Config(ctypes.Structure):
 
 def load() -> ctypes.CDLL:
     """Loads libmbq.so (built by ``python -m paper_2602_20191_amd.build``)."""
-    global _lib, _native
+    global _lib
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -139,16 +139,25 @@ def load() -> ctypes.CDLL:
                  "mbq_threshold_quantile", "mbq_bench_copy", "mbq_bench_read", "mbq_bench_mfma_loop",
                  "mbq_bench_linear_group_prepared", "mbq_bench_decode_timeline"):
         getattr(lib, name).restype = c_int
-    try:
-        from . import _mbq_torch as native
-    except ImportError as e:
-        raise MbqError(f"{e}: build it with `python -m paper_2602_20191_amd.build`") from e
-    native.bind(*[ctypes.cast(getattr(lib, name), c_p).value for name in
-                  ("mbq_routed_linear_group", "mbq_routed_linear_group_cfg", "mbq_route_workspace_bytes",
-                   "mbq_linear_workspace_bytes", "mbq_last_error")],
-                MbqError, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
-    _lib, _native = lib, native
+    _lib = lib
     return lib
+
+
+def _stage():
+    """The stage call's native half (csrc/mbq_torch.cpp); nothing else of the binding needs it."""
+    global _native
+    if _native is None:
+        lib = load()
+        try:
+            from . import _mbq_torch as native
+        except ImportError as e:
+            raise MbqError(f"{e}: build it with `python -m paper_2602_20191_amd.build`") from e
+        native.bind(*[ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in
+                      ("mbq_routed_linear_group", "mbq_routed_linear_group_cfg", "mbq_route_workspace_bytes",
+                       "mbq_linear_workspace_bytes", "mbq_last_error")],
+                    MbqError, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+        _native = native
+    return _native.stage
 
 
 def _check(status: int, what: str) -> None:
@@ -376,8 +385,7 @@ def mbq_routed_linear_group(X: torch.Tensor, Wr: Sequence[torch.Tensor], br: Seq
                             ws_linear: Optional[torch.Tensor] = None, algo: int = ALGO_AUTO):
     """One stage: route X with every router, then the routed outputs.  -> (routing, Y) lists.  Native (csrc/mbq_torch.cpp):
     what is left to the binding is allocated there."""
-    load()
-    return _native.stage(X, Wr, br, blobs, Ns, routing, Y, ws_route, ws_linear, algo, 0)
+    return _stage()(X, Wr, br, blobs, Ns, routing, Y, ws_route, ws_linear, algo, 0)
 
 
 # ---- other slice configurations ----------------------------------------------------------------------
@@ -487,8 +495,7 @@ def mbq_routed_linear_group_cfg(X: torch.Tensor, Wr: Sequence[torch.Tensor], br:
                                 Y: Optional[Sequence[torch.Tensor]] = None, ws_route: Optional[torch.Tensor] = None,
                                 ws_linear: Optional[torch.Tensor] = None, algo: int = ALGO_AUTO):
     """One stage under a slice configuration: route X with every E-output router, then the routed outputs."""
-    load()
-    return _native.stage(X, Wr, br, blobs, Ns, routing, Y, ws_route, ws_linear, algo, ctypes.addressof(cfg))
+    return _stage()(X, Wr, br, blobs, Ns, routing, Y, ws_route, ws_linear, algo, ctypes.addressof(cfg))
 
 
 # ---- measurement and diagnostic entry points (include/mbq_bench.h) ----------------------------------

@@ -84,12 +84,14 @@ def build(verbose: bool = False, save_temps: bool = False) -> str:
         if save_temps:
             cmd += ["-save-temps=obj"]
         jobs.append(cmd)
-    jobs.append(torch_command())
     with ThreadPoolExecutor(max_workers=min(6, os.cpu_count() or 1)) as pool:
+        binding = pool.submit(lambda: _run(torch_command()))
         for out in pool.map(_run, jobs):
             if verbose and out.strip():
                 print(out)
-    _run([cc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs)
+        _run([cc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs)
+        # the library is a C ABI that needs neither torch nor its headers: it stands whatever becomes of the binding's half
+        binding.result()
     return LIB
 
 

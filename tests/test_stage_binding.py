@@ -2,6 +2,7 @@
 buffers give."""
 import os
 import struct
+import sys
 
 import pytest
 import torch
@@ -19,6 +20,35 @@ def inputs(device, T=5, K=256, Ns=(40, 16), P=4, seed=3):
     br = [torch.zeros(P, device=device) for _ in Ns]
     W = [(0.02 * torch.randn((N, K), generator=gen)).to(device) for N in Ns]
     return X, Wr, br, W, list(Ns)
+
+
+@built
+def test_library_loads_without_the_native_half(monkeypatch):
+    monkeypatch.setattr(pkg, "_lib", None)
+    monkeypatch.setattr(pkg, "_native", None)
+    monkeypatch.delattr(pkg, "_mbq_torch", raising=False)
+    monkeypatch.setitem(sys.modules, "paper_2602_20191_amd._mbq_torch", None)  # an import of it fails
+    assert pkg.load().mbq_version().startswith(b"mbq")
+    X, Wr, br, W, Ns = inputs("cpu")
+    with pytest.raises(pkg.MbqError, match="build it"):
+        pkg.mbq_routed_linear_group(X, Wr, br, [torch.zeros(1 << 16, dtype=torch.uint8) for _ in Ns], Ns)
+
+
+@pytest.mark.parametrize("missing", [RuntimeError("no compiler"), ImportError("no torch")])
+def test_library_is_linked_without_the_native_half(monkeypatch, missing):
+    from paper_2602_20191_amd import build
+
+    commands = []
+
+    def no_binding():
+        raise missing
+
+    monkeypatch.setattr(build, "hipcc", lambda: "hipcc")
+    monkeypatch.setattr(build, "_run", lambda cmd: commands.append(cmd) or "")
+    monkeypatch.setattr(build, "torch_command", no_binding)
+    with pytest.raises(type(missing)):  # and is said, after the library is there
+        build.build()
+    assert len(commands) == len(build.SOURCES) + 1 and commands[-1][-len(build.SOURCES) - 2:][:2] == ["-o", build.LIB]
 
 
 @built
