@@ -15,11 +15,16 @@
 // zero points follow as fp32 MFMAs, K = 4, every two blocks.
 // Long rows are cut into up to eight parts of the K axis: part 0 stores into Y, the others into arrays of the workspace,
 // which mid_fold_kernel adds in order, so the result does not depend on which comes first.
+// Wide matrices are the sum of two halves of K.  Where a call has no more workgroups than the chip has compute units (a matrix
+// alone) a workgroup of eight wavefronts forms both at a time, which meet in LDS; otherwise one of four forms them in
+// turn: the same bits.  (One wavefront a SIMD issues an instruction every 7 cycles, two of them every 4.6: 14336 x 4096 alone
+// at 64 tokens 42 us in the register-stationary kernel, 48 with four wavefronts and no halves, 39 now; twice the matrix takes
+// as long in turn as without halves.)
 //
 // Bound by instruction issue: a block takes 360 vector instructions (192 of them unpacking) and 92 MFMAs a wavefront at 64
-// tokens of an even mix, 7500 cycles for the two wavefronts of a SIMD.  Stage calls (router included) before and now, us:
-// twice 14336 x 4096 at 64 tokens 74.6 -> 62.3, skewed mix 69.7 -> 53.4, at 48 tokens 73.2 -> 56.8; 4096 x 14336 at 64
-// tokens 54.5 -> 42.2, 4096 x 11008 43.5 -> 39.8, at 33 tokens 42.7 -> 35.6.  Two tiles a wavefront (spills), operands of
+// tokens of an even mix, 7500 cycles for the two wavefronts of a SIMD.  Stage calls (router included) with the
+// register-stationary kernel and with this one, us: twice 14336 x 4096 at 64 tokens 73 -> 61, skewed mix 61 -> 51, at 48 tokens 72
+// -> 56; 4096 x 14336 at 64 tokens 52 -> 39, 4096 x 11008 41 -> 36, at 33 tokens 41 -> 33.  Two tiles a wavefront (spills), operands of
 // four steps at a time with the next slice's unpacking dealt out under the MFMAs (62.3 -> 64.3), eight wavefronts a
 // workgroup (65.8) were no faster.
 #include <type_traits>
@@ -33,7 +38,7 @@ namespace mid {
 using namespace bf;
 
 constexpr int kWaves = 4;
-constexpr int kMaxBlocks = 16;  // of a part: their row constants wait in LDS
+constexpr int kMaxBlocks = 16;  // of a workgroup: their row constants wait in LDS
 constexpr int kMaxParts = 8;
 constexpr int kMinRows = 33, kMaxRows = 64;
 static_assert(kMaxParts <= kMaxKSplit, "the workspace holds the arrays");
@@ -52,7 +57,8 @@ struct Proj {
   float* Y;
   float* slot;              // T x N arrays of partial sums besides Y, slot_floats apart: part s > 0 stores into slot s - 1
   int64_t slot_floats;
-  int parts;                // along K
+  int parts;                // workgroups along K
+  int half;                 // > 0: blocks of the first half of K, an even number; the halves' sums are added last
   int wg_begin;             // first workgroup of the matrix
 };
 struct Group {
@@ -77,27 +83,33 @@ __device__ __forceinline__ void dma_16(uint32_t lds, uint32_t offset, const void
 
 }  // namespace mid
 
-template <int RT>
-__global__ __launch_bounds__(64 * mid::kWaves, 2) void mid_kernel(const uint16_t* __restrict__ X, int T, int64_t K, int KB,
-                                                                  const float2* __restrict__ sums, const mid::Group g) {
+// SIDES = 2: eight wavefronts, four on each half of K (every matrix of the launch has halves); 1: one half after the other
+template <int RT, int SIDES>
+__global__ __launch_bounds__(64 * mid::kWaves * SIDES, 2) void mid_kernel(const uint16_t* __restrict__ X, int T, int64_t K, int KB,
+                                                                          const float2* __restrict__ sums, const mid::Group g) {
   using namespace mid;
   constexpr int kRows = 16 * RT;
   constexpr int kHalf = kRows * kRowBytes;   // a group of the pass's rows
   constexpr int kStage = 2 * kHalf;          // a block
-  __shared__ __attribute__((aligned(1024))) char smem[2 * kStage + 2 * kMaxBlocks * kRows * 8];
-  float* const s_c1 = reinterpret_cast<float*>(smem + 2 * kStage);  // [group][row]: what the accumulators of a group start with
-  float* const s_ss = s_c1 + 2 * kMaxBlocks * kRows;                // [group][row]: sums of the group's activations
+  constexpr int kBlocks = kMaxBlocks / SIDES;
+  __shared__ __attribute__((aligned(1024))) char smem[SIDES * 2 * kStage + 2 * kMaxBlocks * kRows * 8];
+  const int wave_of = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int side = SIDES == 1 ? 0 : wave_of / kWaves, wave = SIDES == 1 ? wave_of : wave_of % kWaves;
+  float* const s_rows = reinterpret_cast<float*>(smem + SIDES * 2 * kStage);
+  float* const s_c1 = s_rows + side * (4 * kBlocks * kRows);  // [group][row]: what the accumulators of a group start with
+  float* const s_ss = s_c1 + 2 * kBlocks * kRows;             // [group][row]: sums of the group's activations
   Proj P = g.p[0];
 #pragma unroll
   for (int j = 1; j < MBQ_MAX_GROUP; ++j)
     if (j < g.n && (int)blockIdx.x >= g.p[j].wg_begin) P = g.p[j];
   const int wg = (int)blockIdx.x - P.wg_begin;
   const int part = wg % P.parts, col_set = wg / P.parts;
-  const int b0 = (int)((int64_t)part * KB / P.parts), nblk = (int)((int64_t)(part + 1) * KB / P.parts) - b0;
+  const int b0 = SIDES == 2 ? side * P.half : (int)((int64_t)part * KB / P.parts);
+  const int nblk = SIDES == 2 ? (side ? KB - P.half : P.half) : (int)((int64_t)(part + 1) * KB / P.parts) - b0;
   const int lane = threadIdx.x & 63, l15 = lane & 15, kq = lane >> 4;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int G = (int)(K / kGroup);
-  const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)smem;
+  char* const stages = smem + side * (2 * kStage);
+  const uint32_t lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)stages;
 
   // ---- rows: lane r holds row r of the precision-sorted tokens ----
   int token = -1, p = -1;
@@ -119,12 +131,12 @@ __global__ __launch_bounds__(64 * mid::kWaves, 2) void mid_kernel(const uint16_t
       start += __popcll(with);
     }
     if (lane == MBQ_N_PRECISIONS) off = start;
-    int* const order = reinterpret_cast<int*>(s_c1) + 64 * wave;  // (the wavefront's own; in order within it)
+    int* const order = reinterpret_cast<int*>(s_rows) + 64 * wave_of;  // (the wavefront's own; in order within it)
     if (mine >= 0) order[pos] = lane | (mine << 8);
     const int e = lane < T ? order[lane] : -1;
     token = e < 0 ? -1 : (e & 0xFF);
     p = e < 0 ? -1 : (e >> 8);
-    if (wg == 0 && wave == 0) {
+    if (wg == 0 && wave_of == 0) {
       if (mine >= 0) P.sort_perm[pos] = lane;
       if (lane <= MBQ_N_PRECISIONS) P.sort_offsets[lane] = off;
     }
@@ -219,7 +231,7 @@ __global__ __launch_bounds__(64 * mid::kWaves, 2) void mid_kernel(const uint16_t
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
         const int chunk = 8 * (d & 1) + 4 * s + kq;
-        const char* at = smem + stage + (d >> 1) * kHalf + l15 * kRowBytes + ((chunk ^ l15) * 16);
+        const char* at = stages + stage + (d >> 1) * kHalf + l15 * kRowBytes + ((chunk ^ l15) * 16);
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) x[rt][s] = *reinterpret_cast<const uint4*>(at + rt * 16 * kRowBytes);
       }
@@ -298,10 +310,29 @@ __global__ __launch_bounds__(64 * mid::kWaves, 2) void mid_kernel(const uint16_t
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
   settle(A);
   asm volatile("s_barrier" ::: "memory");
+  // (the first half has an even number of blocks, so the second begins with the same registers and at the same place of a
+  // pair of blocks as a side of its own would)
+  const bool in_turn = SIDES == 1 && P.half > 0;
+  floatx4 y_first[RT];
+  for (int end = in_turn ? P.half : nblk;; end = nblk) {
 #pragma unroll 1
-  for (int q = 0; q < nblk; q += 2) {
-    block(A, B);
-    if (q + 1 < nblk) block(B, A);
+    for (int q = i; q < end; q += 2) {
+      block(A, B);
+      if (q + 1 < end) block(B, A);
+    }
+    if (end == nblk) break;
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      y_first[rt] = y[rt];
+      y[rt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+  }
+  if (in_turn) {
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) y[rt] = y_first[rt] + y[rt];
+  }
+  if constexpr (SIDES == 2) {  // as many barriers on either side
+    for (int r = nblk; r < max(P.half, KB - P.half); ++r) asm volatile("s_barrier" ::: "memory");
   }
 
   // ---- rows in original token order, through LDS (the stages are free): an instruction writes 256 bytes of four rows ----
@@ -309,14 +340,22 @@ __global__ __launch_bounds__(64 * mid::kWaves, 2) void mid_kernel(const uint16_t
   float* const s_out = reinterpret_cast<float*>(smem);
   static_assert(kRows * kLd * 4 <= 2 * kStage, "the tile fits the stages");
 #pragma unroll
-  for (int rt = 0; rt < RT; ++rt)
+  for (int half = 0; half < SIDES; ++half) {
+    if (side == half) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) s_out[(16 * rt + 4 * kq + r) * kLd + 16 * wave + l15] = y[rt][r];
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          float& at = s_out[(16 * rt + 4 * kq + r) * kLd + 16 * wave + l15];
+          at = half == 0 ? y[rt][r] : at + y[rt][r];
+        }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  }
   float* const out = part == 0 ? P.Y : P.slot + (part - 1) * P.slot_floats;
   const bool wide = (P.N & 3) == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0;
 #pragma unroll
-  for (int u = 0; u < kRows * kVec; u += 64 * kWaves) {
+  for (int u = 0; u < kRows * kVec; u += 64 * kWaves * SIDES) {
     const int row = (u + (int)threadIdx.x) / kVec, q = (u + (int)threadIdx.x) % kVec;
     const floatx4 v = *reinterpret_cast<const floatx4*>(s_out + row * kLd + 4 * q);
     const int64_t col = (int64_t)col_set * kCols + 4 * q;
@@ -386,23 +425,30 @@ __global__ __launch_bounds__(256) void mid_fold_kernel(const mid::Fold f) {
 namespace mid {
 static inline size_t sums_bytes(int64_t T, int64_t K) { return ((size_t)T * (size_t)(K / kGroup) * 8 + 255) / 256 * 256; }
 static inline int64_t slot_floats(int64_t T, int64_t N) { return (T * N + 63) / 64 * 64; }
+static inline int first_half(int KB) { return (KB + 1) / 4 * 2; }  // even, within one of the other half, at most half of kMaxBlocks
 }  // namespace mid
 
-// Parts of the K axis, 0: the matrix does not take this kernel.  It has to fill the chip, and it cannot share a compute
-// unit's registers between many short tiles as the register-stationary kernel does, so it is taken where it won on cold
-// weights, stage calls in us (that kernel / this one, at 33, 48 and 64 tokens of an even mix; skewed mixes favour this one
-// by another 5-20 %):
-//   wide matrices, which come in pairs (gate and up), one part: twice 14336 x 4096 72 / 58, 73 / 57, 75 / 62; twice 11008 x
-//   4096 74 / 57, 60 / 56, 61 / 61; twice 8192 x 4096 44 / 46, 45 / 45, 46 / 50 (not taken); 14336 x 4096 alone 42 / 47, 43 /
-//   45, 44 / 50 (it takes the same kernel alone);
-//   long rows, eight parts: 4096 x 11008 43 / 36, 43 / 36, 44 / 40; 3072 x 8192 27 / 27, 28
-//   / 27, 28 / 29, 2048 x 8192 23 / 24, 24 / 24, 24 / 25 (not taken).
-// At 32 tokens both kernels unpack once and are as fast.  The choice depends on T and the matrix alone: a call for several
-// matrices gives the bits of separate calls.
+// Parts of the K axis, 0: the matrix does not take this kernel.  The choice depends on T and the matrix alone, and a call for
+// several matrices gives the bits of separate calls, so it is taken only where it won both ways; stage calls on cold weights
+// in us (register-stationary kernel / this one), at 33, 48 and 64 tokens of an even mix (skewed mixes are within 5 % of the
+// same ratio):
+//   wide matrices, one part, alone (halves of K side by side) up to a workgroup a compute unit: 14336 x 4096 42 / 36, 42 / 36,
+//   42 / 39; 12800 x 4096 42 / 36, 42 / 36, 42 / 38; 12288 x 4096 34.9 / 35.7, 38 / 36, 39 / 38; 11008 x 4096 33 / 35, 38 / 35, 38 / 38 (neither taken); 14336 x 3072 38
+//   / 30, 38 / 30, 39 / 32; 14336 x 2048 27 / 23, 28 / 23, 28 / 24; 10240 x 2048 23 / 22, 24 / 22, 24 / 23; beyond, in turn: 18432
+//   x 4096 50 / 55, 50 / 55, 51 / 59 (not taken), 24576 x 4096 62 / 55, 63 / 55, 64 / 60, 32000 x 4096 78 / 58, 79 / 59, 80 / 64;
+//   twice (in turn): 14336 x 4096 71 / 57, 72 / 56, 73 / 61; 11008 x 4096 69 / 55, 58 / 55, 59 / 60; 14336 x 2048 41 / 33, 42 / 33,
+//   43 / 36; 10240 x 2048 33 / 32, 34 / 32, 34.6 / 34.7, at 56 tokens 34 / 35 (not taken); below K = 1536 rows are too short: 10240
+//   x 1024 alone 15 / 15, 16 / 15, 14 / 15;
+//   long rows, eight parts: 4096 x 11008 41 / 33, 41 / 33, 41 / 36; 3072 x 8320 34 / 29, 34 / 29, 34 / 30; 8192 x 28672 145 / 104,
+//   145 / 103, 145 / 112; 2048 x 8192 23 / 24, 24 / 24, 24 / 25 (not taken).
+// At 32 tokens both kernels unpack once and are as fast.
 int mid_parts(int64_t T, const Shape& sh) {
   if (T < mid::kMinRows || T > mid::kMaxRows) return 0;
   const int least = (sh.KB + mid::kMaxBlocks - 1) / mid::kMaxBlocks;
-  if (sh.N >= 2 * sh.K && sh.NT >= 640) return least == 1 ? 1 : 0;
+  if (sh.N >= 2 * sh.K && sh.KB >= 6 && least == 1) {
+    const int alone_most = 256 * mid::kWaves, apart_least = 384 * mid::kWaves;  // code tiles
+    return (sh.NT >= (sh.KB <= 12 ? 704 : 800) && sh.NT <= alone_most) || sh.NT >= apart_least ? 1 : 0;
+  }
   if (sh.KB <= 32 || sh.NT < 192 || sh.N > sh.K) return 0;
   // (the workspace of a call has room for kMaxKSplit arrays of at least T rows, decode_workspace_bytes: seven and the sums,
   // which take less than an array as 64 N > K)
@@ -448,6 +494,7 @@ mbq_status launch_linear_mid_group(const uint16_t* X, int64_t T, int n, const vo
     p.slot = slot;
     p.slot_floats = mid::slot_floats(T, s.N);
     p.parts = mid_parts(T, s);
+    p.half = p.parts == 1 ? mid::first_half(s.KB) : 0;
     p.wg_begin = grid;
     f.Y[i] = Y[j];
     f.slot[i] = slot;
@@ -461,12 +508,20 @@ mbq_status launch_linear_mid_group(const uint16_t* X, int64_t T, int n, const vo
     }
   }
   g.n = n;
-  if (T <= 48)
-    hipLaunchKernelGGL(mid_kernel<3>, dim3(grid), dim3(64 * mid::kWaves), 0, stream, X, (int)T, sh.K, sh.KB,
+  // halves of K side by side where that leaves no workgroup waiting for another (they need a compute unit each), in turn
+  // where two workgroups share one: the same bits
+  const bool sides = !cut && grid <= device_compute_units();
+  const auto launch = [&](auto rt, auto n_sides) {
+    hipLaunchKernelGGL((mid_kernel<decltype(rt)::value, decltype(n_sides)::value>), dim3(grid),
+                       dim3(64 * mid::kWaves * decltype(n_sides)::value), 0, stream, X, (int)T, sh.K, sh.KB,
                        reinterpret_cast<const float2*>(ws), g);
-  else
-    hipLaunchKernelGGL(mid_kernel<4>, dim3(grid), dim3(64 * mid::kWaves), 0, stream, X, (int)T, sh.K, sh.KB,
-                       reinterpret_cast<const float2*>(ws), g);
+  };
+  const std::integral_constant<int, 1> one{};
+  const std::integral_constant<int, 2> two{};
+  const std::integral_constant<int, 3> three{};
+  const std::integral_constant<int, 4> four{};
+  if (T <= 48) sides ? launch(three, two) : launch(three, one);
+  else sides ? launch(four, two) : launch(four, one);
   mbq_status st = hip_status(hipGetLastError(), "mid_kernel launch");
   if (st != MBQ_OK || most == 0) return st;
   int64_t blocks = (most / 4 + 255) / 256;
