@@ -228,6 +228,40 @@ static bool takes_mid_kernel(int64_t T, const Shape& sh) {
   return knob(3) == 0 && mid_parts(T, sh) > 0;
 }
 
+// Matrices of a call that share a launch.
+struct Sharing {
+  int n = 0;
+  const void* blob[MBQ_MAX_GROUP];
+  Shape sh[MBQ_MAX_GROUP];
+  const int32_t *prec[MBQ_MAX_GROUP], *perm[MBQ_MAX_GROUP];
+  float* Y[MBQ_MAX_GROUP];
+  int32_t *sort_perm[MBQ_MAX_GROUP], *sort_offsets[MBQ_MAX_GROUP];  // where a launch that sorts leaves the order
+
+  void add(const void* b, const Shape& s, const int32_t* p, const int32_t* order, float* y, int32_t* to_perm, int32_t* to_offsets) {
+    blob[n] = b;
+    sh[n] = s;
+    prec[n] = p;
+    perm[n] = order;
+    Y[n] = y;
+    sort_perm[n] = to_perm;
+    sort_offsets[n++] = to_offsets;
+  }
+  mbq_status launch_mid(const uint16_t* X, int64_t T, void* ws, hipStream_t s, bool sort) const {
+    if (n == 0) return MBQ_OK;
+    return launch_linear_mid_group(X, T, n, blob, sh, prec, perm, Y, ws, s, sort ? sort_perm : nullptr,
+                                   sort ? sort_offsets : nullptr);
+  }
+  mbq_status launch_stationary(const uint16_t* X, int64_t T, hipStream_t s, bool sort) const {
+    if (n == 0) return MBQ_OK;
+    return launch_linear_decode16_group(X, T, n, blob, sh, prec, perm, Y, s, sort ? sort_perm : nullptr,
+                                        sort ? sort_offsets : nullptr);
+  }
+  void zero_list(int64_t T, ZeroList* zl) const {  // of the register-stationary kernel
+    *zl = ZeroList{};
+    if (n > 0) decode16_zero_list(T, n, sh, Y, zl);
+  }
+};
+
 // algo is DECODE (T <= 64), PREFILL, SIMPLE or kAlgoStationary here
 mbq_status dispatch_linear(const uint16_t* X, int64_t T, const void* blob, const Shape& sh, const int32_t* prec,
                            const int32_t* perm, const int32_t* offsets, float* Y, void* ws, int algo,
@@ -617,42 +651,38 @@ mbq_status mbq_routed_linear_group(const uint16_t* X, int64_t T, int64_t K, int 
                                      perm_host, offsets_host, nullptr, false, t_act ? t_act->aq.row_scale : nullptr,
                                      t_act ? t_act->bias : nullptr, t_act ? &t_act->scaled : nullptr);
     }
-    // up to 128 tokens with every matrix on the register-stationary kernel: the router launch only writes the
-    // precisions (no meeting of its workgroups), the linear launch sorts the tokens itself
-    // wide matrices and long rows at 33 to 64 tokens: the router launch also leaves the sums that the linear kernel starts
-    // from, and that kernel sorts the tokens itself
-    bool all_mid = ok;
-    for (int i = 0; all_mid && i < n_proj; ++i) all_mid = takes_mid_kernel(T, sh[i]);
-    if (all_mid && route_defers_sort(T)) {
-      mbq_status st = act_ahead(T, K, n_proj, prec_host, Y_host, N_host, ws_linear, ws_linear_bytes, &aq,
-                                (hipStream_t)stream);
-      if (st != MBQ_OK) return st;
-      const bool sums_here = t_act && !aq;  // the routers read the rebuilt activations, the linear launch the integers
-      st = launch_route_group(X, T, K, n_proj, Wr_host, br_host, prec_host, perm_host, offsets_host, nullptr, ws_route,
-                              (hipStream_t)stream, nullptr, 0, nullptr, true, *t_view, nullptr, aq,
-                              sums_here ? nullptr : ws_linear);
-      if (st == MBQ_OK && sums_here) st = launch_mid_sums(XL, T, K, ws_linear, (hipStream_t)stream);
-      if (st != MBQ_OK) return st;
-      return launch_linear_mid_group(XL, T, n_proj, blob_host, sh, prec_host, perm_host, Y_host, ws_linear,
-                                     (hipStream_t)stream, perm_host, offsets_host);
-    }
+    // up to 128 tokens with every matrix on the register-stationary kernel or, at 33 to 64, on that of wide matrices and long
+    // rows: the router launch only writes the precisions (no meeting of its workgroups), clears what the former adds into and
+    // leaves the sums that the latter starts from; the linear launches, one for the matrices of each kernel, sort the tokens
+    // themselves.  (12288 and twice 1024 x 12288 at 64 tokens: a launch for each matrix 140 us, a launch for each kernel 110, the
+    // register-stationary kernel for all three 161.)
     const int64_t defer_limit = (algo == MBQ_ALGO_AUTO) ? kMaxStationaryTokens : kMaxDecodeTokens;
     if (ok && T <= defer_limit && route_defers_sort(T)) {
+      Sharing mid, stationary;
       bool all = true;
-      for (int i = 0; i < n_proj; ++i)
-        all = all && !takes_mid_kernel(T, sh[i]) &&
-              (T <= kMaxDecodeTokens ? takes_stationary_kernel(T, sh[i])
-                                     : resolve_auto(T, sh[i]) == kAlgoStationary);
+      for (int i = 0; i < n_proj; ++i) {
+        Sharing* to = takes_mid_kernel(T, sh[i]) ? &mid
+                      : (T <= kMaxDecodeTokens ? takes_stationary_kernel(T, sh[i]) : resolve_auto(T, sh[i]) == kAlgoStationary)
+                          ? &stationary
+                          : nullptr;
+        all = all && to != nullptr;
+        if (to) to->add(blob_host[i], sh[i], prec_host[i], perm_host[i], Y_host[i], perm_host[i], offsets_host[i]);
+      }
       if (all) {
-        ZeroList zl;  // outputs the linear launch adds into: cleared by a plane of the router launch
-        decode16_zero_list(T, n_proj, sh, Y_host, &zl);
-        mbq_status st = act_ahead(T, K, n_proj, prec_host, Y_host, N_host, nullptr, 0, &aq, (hipStream_t)stream);
+        const hipStream_t s = (hipStream_t)stream;
+        ZeroList zl;
+        stationary.zero_list(T, &zl);
+        const bool sums = mid.n > 0;
+        mbq_status st = act_ahead(T, K, n_proj, prec_host, Y_host, N_host, sums ? ws_linear : nullptr,
+                                  sums ? ws_linear_bytes : 0, &aq, s);
         if (st != MBQ_OK) return st;
-        st = launch_route_group(X, T, K, n_proj, Wr_host, br_host, prec_host, perm_host, offsets_host, nullptr, ws_route,
-                                (hipStream_t)stream, nullptr, 0, &zl, true, *t_view, nullptr, aq);
-        if (st != MBQ_OK) return st;
-        return launch_linear_decode16_group(XL, T, n_proj, blob_host, sh, prec_host, perm_host, Y_host,
-                                            (hipStream_t)stream, perm_host, offsets_host);
+        const bool sums_here = sums && t_act && !aq;  // the routers read the rebuilt activations, the linear launch the integers
+        st = launch_route_group(X, T, K, n_proj, Wr_host, br_host, prec_host, perm_host, offsets_host, nullptr, ws_route, s,
+                                nullptr, 0, &zl, true, *t_view, nullptr, aq, sums && !sums_here ? ws_linear : nullptr);
+        if (st == MBQ_OK && sums_here) st = launch_mid_sums(XL, T, K, ws_linear, s);
+        if (st == MBQ_OK) st = mid.launch_mid(XL, T, ws_linear, s, true);
+        if (st == MBQ_OK) st = stationary.launch_stationary(XL, T, s, true);
+        return st;
       }
     }
   }
@@ -789,26 +819,34 @@ mbq_status mbq_linear_group(const uint16_t* X, int64_t T, int64_t K, int n_proj,
     if (st != MBQ_OK) return st;
     return launch_linear_decode_f4(T, n_proj, blob_host, sh, prec_host, Y_host, ws, s, nullptr, nullptr);
   }
-  int mid = 0;  // matrices that take the kernel of wide matrices and long rows: one launch if all do, else one by one
-  if (algo == MBQ_ALGO_DECODE)
-    for (int i = 0; i < n_proj; ++i) mid += takes_mid_kernel(T, sh[i]) ? 1 : 0;
-  if (mid == n_proj) {
-    mbq_status st = launch_mid_sums(X, T, K, ws, s);
-    if (st != MBQ_OK) return st;
-    return launch_linear_mid_group(X, T, n_proj, blob_host, sh, prec_host, perm_host, Y_host, ws, s, nullptr, nullptr);
-  }
-  if ((algo == MBQ_ALGO_DECODE || algo == kAlgoStationary) && n_proj > 1 && mid == 0) {
-    // the matrices share one launch of the register-stationary kernel when each of them would take it
-    bool all = true;
-    for (int i = 0; i < n_proj; ++i) all = all && takes_stationary_kernel(T, sh[i]);
-    if (all) {
-      ZeroList zl;
-      decode16_zero_list(T, n_proj, sh, Y_host, &zl);
-      mbq_status st = launch_zero_outputs(zl, s);
-      if (st != MBQ_OK) return st;
-      return launch_linear_decode16_group(X, T, n_proj, blob_host, sh, prec_host, perm_host, Y_host, s, nullptr,
-                                          nullptr);
+  if (algo == MBQ_ALGO_DECODE || algo == kAlgoStationary) {
+    // the matrices of the kernel of wide matrices and long rows share a launch, and those of the register-stationary kernel
+    // when no other is left over
+    Sharing mid, stationary;
+    for (int i = 0; i < n_proj; ++i) {
+      Sharing* to = algo == MBQ_ALGO_DECODE && takes_mid_kernel(T, sh[i]) ? &mid
+                    : takes_stationary_kernel(T, sh[i])                   ? &stationary
+                                                                          : nullptr;
+      if (to) to->add(blob_host[i], sh[i], prec_host[i], perm_host[i], Y_host[i], nullptr, nullptr);
     }
+    mbq_status st = MBQ_OK;
+    if (mid.n > 0) {
+      st = launch_mid_sums(X, T, K, ws, s);
+      if (st == MBQ_OK) st = mid.launch_mid(X, T, ws, s, false);
+      if (st != MBQ_OK) return st;
+    }
+    if (mid.n + stationary.n == n_proj) {
+      ZeroList zl;
+      stationary.zero_list(T, &zl);
+      st = launch_zero_outputs(zl, s);
+      return st == MBQ_OK ? stationary.launch_stationary(X, T, s, false) : st;
+    }
+    for (int i = 0; i < n_proj && mid.n > 0; ++i) {
+      if (takes_mid_kernel(T, sh[i])) continue;
+      st = dispatch_linear(X, T, blob_host[i], sh[i], prec_host[i], perm_host[i], offsets_host[i], Y_host[i], ws, algo_of[i], s);
+      if (st != MBQ_OK) return st;
+    }
+    if (mid.n > 0) return MBQ_OK;
   }
   // the matrices that take the prefill kernel share a launch; the others follow one by one
   const void* pf_blob[MBQ_MAX_GROUP];

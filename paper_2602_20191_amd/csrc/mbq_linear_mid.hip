@@ -440,7 +440,13 @@ static inline int first_half(int KB) { return (KB + 1) / 4 * 2; }  // even, with
 //   43 / 36; 10240 x 2048 33 / 32, 34 / 32, 34.6 / 34.7, at 56 tokens 34 / 35 (not taken); below K = 1536 rows are too short: 10240
 //   x 1024 alone 15 / 15, 16 / 15, 14 / 15;
 //   long rows, eight parts: 4096 x 11008 41 / 33, 41 / 33, 41 / 36; 3072 x 8320 34 / 29, 34 / 29, 34 / 30; 8192 x 28672 145 / 104,
-//   145 / 103, 145 / 112; 2048 x 8192 23 / 24, 24 / 24, 24 / 25 (not taken).
+//   145 / 103, 145 / 112; 2048 x 8192 23 / 24, 24 / 24, 24 / 25 (not taken);
+//   with more rows than half the columns (q and o of an attention, where q has company) from K = 9984 on: 12288 x 12288 alone 90
+//   / 74, 98 / 75, 98 / 81; with two of 1280 x 9984, of which each kernel takes its share in a launch of its own, 137 / 88, 139 /
+//   89, 137 / 96; with two of 1152 x 9216 89 / 86, 90 / 87, 90 / 93 (not taken, though 9216 x 9216 alone 71 / 57, 71 / 57, 70 / 63
+//   and three of them 186 / 159, 186 / 161, 236 / 178).
+// What a matrix alone decides can be wrong for its company: 5120 x 13824 twice at 64 tokens 101 / 104 (61 / 55 alone), with
+// 1024 x 11008 4096 x 11008 53 / 59 (42 / 36 alone).
 // At 32 tokens both kernels unpack once and are as fast.
 int mid_parts(int64_t T, const Shape& sh) {
   if (T < mid::kMinRows || T > mid::kMaxRows) return 0;
@@ -449,7 +455,7 @@ int mid_parts(int64_t T, const Shape& sh) {
     const int alone_most = 256 * mid::kWaves, apart_least = 384 * mid::kWaves;  // code tiles
     return (sh.NT >= (sh.KB <= 12 ? 704 : 800) && sh.NT <= alone_most) || sh.NT >= apart_least ? 1 : 0;
   }
-  if (sh.KB <= 32 || sh.NT < 192 || sh.N > sh.K) return 0;
+  if (sh.KB <= (2 * sh.N <= sh.K ? 32 : 38) || sh.NT < 192 || sh.N > sh.K) return 0;
   // (the workspace of a call has room for kMaxKSplit arrays of at least T rows, decode_workspace_bytes: seven and the sums,
   // which take less than an array as 64 N > K)
   return mid::kMaxParts >= least ? mid::kMaxParts : 0;

@@ -795,6 +795,15 @@ def test_decode_wide_matrices_in_halves(mbq, T, mix, Ns, K):
     test_decode_wide_matrices_and_long_rows(mbq, T, mix, Ns, K)
 
 
+@pytest.mark.parametrize("T,mix", [(33, (8, 9, 8, 8)), (64, (16, 15, 17, 16))])
+@pytest.mark.parametrize("Ns,K", [((1040, 3072), 8448), ((3072, 600, 3080, 513), 8320), ((3072, 80, 1040), 8448), ((12800, 272), 1536),
+                                  ((33, 11270), 2048)])
+def test_decode_groups_of_two_kernels(mbq, T, mix, Ns, K):
+    """Groups of which only some matrices take the kernel of wide matrices and long rows: a launch for those of each kernel, one
+    by one where a third is needed; outputs of the others that are added into (K = 8448) and that are not."""
+    test_decode_wide_matrices_and_long_rows(mbq, T, mix, Ns, K)
+
+
 @pytest.mark.parametrize("K,T,Ns", [(4096, 16, (96, 32, 130)), (4096, 1, (64, 64)), (2048, 7, (80, 48, 16, 33)),
                                     (768, 16, (40,)), (3072, 5, (48, 96)), (5120, 16, (48, 32)), (1024, 40, (48, 32)),
                                     (4096, 64, (1040, 130, 256)), (2304, 33, (272, 48, 16, 640)), (4352, 48, (2064, 16))])
