@@ -325,3 +325,45 @@ def test_calls_from_two_threads_do_not_disturb_each_other(mbq):
         t.join()
     torch.cuda.synchronize()
     assert not failures, failures
+
+
+@pytest.mark.parametrize("T", [33, 48, 64])
+@pytest.mark.parametrize("Ns,K", [((11270,), 1536), ((3072,), 8448), ((3075, 600), 8320), ((3072,), 16640)])
+@pytest.mark.parametrize("in_place", [False, True])
+@pytest.mark.parametrize("abits", [4, 8])
+def test_stage_on_wide_matrices_and_long_rows(mbq, T, Ns, K, in_place, abits):
+    """33 to 64 tokens on the kernel that starts from sums of the integers: left by the router launch that quantises, and by
+    a launch of their own where the quantiser has one (K > 16384, the router's input written over the activations); alone and
+    beside a matrix of another kernel.  Against the separate calls bit for bit, and against products in 64 bits."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(163 + T + K)
+    X = dev_bf16(activations(T, K, [T, K, 43], offset=0.5)).reshape(T, K)
+    delta, s = (dev(p) for p in let_params(K, [K, 47]))
+    Wr = [torch.randn((4, K), generator=gen, device="cuda") / K ** 0.5 for _ in Ns]
+    br = [0.3 * torch.randn(4, generator=gen, device="cuda") for _ in Ns]
+    blobs = [mbq.mbq_encode(0.02 * torch.randn((N, K), generator=gen, device="cuda")) for N in Ns]
+    bias = [torch.randn(N, generator=gen, device="cuda") for N in Ns]
+    want_act = mbq.mbq_act_quant(X, abits, delta, s)
+    want_routing = mbq.mbq_route_group(want_act[2], Wr, br)
+    want = mbq.mbq_linear_group(want_act[0], blobs, list(Ns), K, want_routing)
+    for i, N in enumerate(Ns):
+        prec, x = want_routing[i][0], want_act[0].double()
+        for p in range(4):
+            rows = torch.nonzero(prec == p).flatten()
+            ref = x[rows] @ mbq.mbq_dequant(blobs[i], N, K, p).double().T
+            assert float((want[i][rows].double() - ref).norm()) <= 4e-5 * float(ref.norm()), (i, p)
+    for Y, b in zip(want, bias):
+        mbq.mbq_scale_rows(Y, want_act[1], b)
+    X1 = X.clone()
+    act = (torch.empty_like(X), torch.empty((T,), dtype=torch.float32, device="cuda"), X1 if in_place else torch.empty_like(X))
+    ws_linear = mbq.linear_workspace(T, max(Ns), K, "cuda")
+    ws_linear.fill_(255)  # floats of NaN
+    Y = [torch.full((T, N), float("nan"), device="cuda") for N in Ns]
+    routing, Ys, _ = mbq.mbq_routed_linear_group_act(X1, abits, delta, s, Wr, br, blobs, list(Ns), bias=bias, act=act, Y=Y,
+                                                     ws_linear=ws_linear)
+    torch.cuda.synchronize()
+    for a, b in zip(act, want_act):
+        assert torch.equal(a, b)
+    for i in range(len(Ns)):
+        assert all(torch.equal(a, b) for a, b in zip(routing[i], want_routing[i])), i
+        assert torch.equal(Ys[i], want[i]), i

@@ -138,6 +138,33 @@ SMALL_GROUPS = [((2, 2, 2, 2), 64), ((4, 2, 2), 64), ((3, 2, 1), 64), ((2, 2, 2,
                 ((8,), 32), ((2, 3), 64)]
 
 
+@pytest.mark.parametrize("bits", [(4, 2, 2), (2, 4, 2), (4, 4)])
+@pytest.mark.parametrize("T", [33, 64])
+@pytest.mark.parametrize("Ns,K", [((11270,), 1536), ((12800, 12810), 3328), ((3072, 520), 8448)])
+def test_stage_call_under_a_configuration_on_wide_matrices_and_long_rows(mbq, bits, T, Ns, K):
+    """33 to 64 tokens on the kernel that unpacks once, under configurations that skip precisions: against the separate calls
+    bit for bit, and against products in 64 bits of the weights that mbq_dequant_cfg gives."""
+    cfg = mbq.Config(bits)
+    E = len(bits)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(167 + T + K)
+    X = dev_bf16(tokens(T, K, [T, K, 7])).reshape(T, K)
+    Wr = [torch.randn((E, K), generator=gen, device="cuda") / K ** 0.5 for _ in Ns]
+    br = [0.3 * torch.randn(E, generator=gen, device="cuda") for _ in Ns]
+    blobs = [mbq.mbq_encode_cfg(0.02 * torch.randn((N, K), generator=gen, device="cuda"), cfg) for N in Ns]
+    routing, Ys = mbq.mbq_routed_linear_group_cfg(X, Wr, br, cfg, blobs, list(Ns))
+    separate = mbq.mbq_route_group_cfg(X, Wr, br, cfg)
+    again = mbq.mbq_linear_group(X, blobs, list(Ns), K, separate)
+    values, _ = stored_values(mbq, cfg, E)
+    for i, N in enumerate(Ns):
+        assert all(torch.equal(a, b) for a, b in zip(routing[i], separate[i])), i
+        assert torch.equal(Ys[i], again[i]), i
+        for p in range(E):
+            rows = torch.nonzero(routing[i][0] == int(values[p])).flatten()
+            ref = X[rows].double() @ mbq.mbq_dequant_cfg(blobs[i], N, K, cfg, p).double().T
+            assert float((Ys[i][rows].double() - ref).norm()) <= 4e-5 * float(ref.norm()), (i, p)
+
+
 @pytest.mark.parametrize("bits,group", SMALL_GROUPS)
 def test_groups_of_64_and_32_columns_encode_bit_exact(mbq, bits, group):
     """App. C.1 lists the group size among the settings: codes, (s_0, z_0) per group and every W^(p) against the
