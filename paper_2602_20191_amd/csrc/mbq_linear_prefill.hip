@@ -178,20 +178,22 @@ __device__ __forceinline__ void dma_4(uint32_t lds, const void* address) {
                : "memory");
 }
 
-// eight floats as sums of three bf16: the upper bits cut off, the rest rounded, what is left (exact: 8 + 9 + 7 bits)
+// eight floats as sums of three bf16, each the rest rounded to nearest (8 bits, then at most 15 of 24 left, then at most 7: the
+// last is exact); the second piece is at most 2^-9 of the number, the third 2^-18
 __device__ __forceinline__ void split_bf16(const float (&v)[8], u32x4 (&pieces)[3]) {
   typedef float floatx2 __attribute__((ext_vector_type(2)));
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const float v0 = v[2 * i], v1 = v[2 * i + 1];
-    pieces[0][i] = __builtin_amdgcn_perm(__float_as_uint(v1), __float_as_uint(v0), 0x07060302u);
-    const float r0 = v0 - __uint_as_float(__float_as_uint(v0) & 0xFFFF0000u);
-    const float r1 = v1 - __uint_as_float(__float_as_uint(v1) & 0xFFFF0000u);
-    const uint32_t m = __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{r0, r1}, bf16x2));
-    pieces[1][i] = m;
-    const float l0 = r0 - __uint_as_float(m << 16), l1 = r1 - __uint_as_float(m & 0xFFFF0000u);
-    pieces[2][i] = __builtin_amdgcn_perm(__float_as_uint(l1), __float_as_uint(l0), 0x07060302u);
+    float r0 = v[2 * i], r1 = v[2 * i + 1];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const uint32_t piece = __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{r0, r1}, bf16x2));
+      pieces[j][i] = piece;
+      r0 -= __uint_as_float(piece << 16);
+      r1 -= __uint_as_float(piece & 0xFFFF0000u);
+    }
+    pieces[2][i] = __builtin_amdgcn_perm(__float_as_uint(r1), __float_as_uint(r0), 0x07060302u);
   }
 }
 
@@ -356,7 +358,7 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
   // parts where there is no room for those; long parts lose up to 7 % by it (8192 x 28672 at 256 tokens 263 -> 282 us: the
   // scales of groups to come are not in cache yet).
   // In fp32 (32x32x2, 64 cycles each) the update takes as many cycles as two groups.  kPieces: both operands as sums of
-  // three bf16, exact to 24 bits, and six of their nine products (the other three are below 2^-24 of the whole) in 32x32x16
+  // three bf16, exact to 24 bits, and six of their nine products (the other three are below 2^-25 of a product) in 32x32x16
   // MFMAs, two fifths of that.  The rows' sums are split once for the workgroup, in their place in LDS.  The first product
   // goes into the accumulator, the small ones come together in registers of their own and are added at once, so that the sum
   // is rounded twice at its size and not eight times: against 64 bits 1.5e-6 -> 1.4e-6 relative for 11008 x 4096 at 2
@@ -488,7 +490,8 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
         b_x[c] = (P == 3) ? ((E - 8u) << 23) : ((E >> 1) * 0x01010101u);
         const float r = m_cur[c] * __builtin_amdgcn_rcpf(scale_mantissa(s_cur[c]));
         ratio[c] = (q > 0) ? r : 1.f;
-        // the factor actually in force (keeps the chain consistent): m / ratio, to the last bit or two
+        // the factor actually in force (keeps the chain consistent): m / ratio within
+        // 0.5000002 of a last place (a reciprocal off by one place and a corrected quotient: the rounded one but for 3 in 10^7)
         const float inv = __builtin_amdgcn_rcpf(ratio[c]), quot = m_cur[c] * inv;
         m_cur[c] = __builtin_fmaf(__builtin_fmaf(-quot, ratio[c], m_cur[c]), inv, quot);
       }
