@@ -217,7 +217,7 @@ __device__ __forceinline__ void spread(int each) {
 }
 
 // One tile: rows row0 .. row0 + rows - 1 of the sorted tokens, columns 256 ntile_n ..; groups g0 .. g0 + G - 1.
-// P = precision index of the tokens, MR = 16-row tiles (16 MR >= rows).
+// P = precision index of the tokens, MR = 16-row tiles, an even number (16 MR >= rows; the products take them in pairs).
 // gather: X is in token order and rows are fetched through perm; otherwise X is the sorted copy.
 // halfway, kPieces: when and how the zero-point term is removed, see remove_in_pieces.
 // out: the T x N array the tile goes to; accumulate: it is added there (two parts of K share the array).
@@ -263,7 +263,7 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
     for (int j = 0; j < MR; ++j)
       dma_16(lds0 + stage + (uint32_t)(j * 16 * kRowBytes), kOffLds ? s_row[4 * wave + 16 * j + kq] + a_chunk : a_off[kOffLds ? 0 : j], src);
   };
-  // ---- B: this wavefront's four column tiles of 16; two dwords a lane, tile, slice and group ----
+  // ---- B: this wavefront's two column tiles of 32, a pair of code tiles each; four dwords a lane, tile, slice and group ----
   const uint32_t* wptr[2];
   const float* sptr[2];
   uint32_t w_tile[2];  // words from the first of a pair's code tiles to this lane's
@@ -558,10 +558,11 @@ __device__ __forceinline__ void tile(const uint16_t* __restrict__ X, int64_t K, 
     }
   }
 
-  // ---- rows in original token order.  A lane holds rows 16 a + 4 kq + i, columns 16 c + l15: stored from there an
-  // instruction writes four pieces of 64 bytes, 32 cycles each (16400 cycles a tile).  So a row tile goes through the
-  // wavefront's own part of the stages (free behind the last barrier; LDS operations of a wavefront execute in order): an
-  // instruction then writes four rows of 256 bytes, or one where rows are not 16-byte aligned or two parts of K add. ----
+  // ---- rows in original token order.  Of a row tile of 32 a lane holds rows 8 (i >> 2) + 4 hh + (i & 3), i = 0 .. 15, and
+  // columns 32 c + l31: stored from there an instruction writes two pieces of 128 bytes (from the layout of 16 x 16 tiles, four
+  // of 64, it took 32 cycles each, 16400 a tile).  So 16 rows at a time go through the wavefront's own part of the stages
+  // (free behind the last barrier; LDS operations of a wavefront execute in order): an instruction then writes four
+  // rows of 256 bytes, or one where rows are not 16-byte aligned or two parts of K add. ----
   constexpr int kRow = 64 + 4;  // floats between rows
   float* const own = reinterpret_cast<float*>(smem) + wave * (16 * kRow);
   const int64_t col0 = (int64_t)ntile_n * kBN + 64 * wave;

@@ -329,7 +329,8 @@ __global__ __launch_bounds__(512) void route_small_kernel(const uint16_t* __rest
                                                           float* __restrict__ sums) {
   // Xprep: the activations the linear kernel multiplies (X itself, except in the activation-quantised variant,
   // where the routers read the rebuilt activations and the linear kernel the integers)
-  // sums: where router 0 also leaves the group sums that the linear kernel of 17 and more tokens starts from (null: nowhere)
+  // sums: where router 0 also leaves the group sums that the kernel of wide matrices and long rows at 33 to 64 tokens starts
+  // from (null: nowhere)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int tok = blockIdx.x;
   const bool plane = (int)blockIdx.y == n_routers;
