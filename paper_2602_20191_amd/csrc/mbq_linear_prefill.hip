@@ -179,7 +179,8 @@ __device__ __forceinline__ void dma_4(uint32_t lds, const void* address) {
 }
 
 // eight floats as sums of three bf16, each the rest rounded to nearest (8 bits, then at most 15 of 24 left, then at most 7: the
-// last is exact); the second piece is at most 2^-9 of the number, the third 2^-18
+// last is exact); the second piece is at most 2^-9 of the number, the third 2^-18.  (A row sum's pieces are exact down to the
+// smallest rows: sums of bf16 numbers are multiples of 2^-133, which bf16 holds.)
 __device__ __forceinline__ void split_bf16(const float (&v)[8], u32x4 (&pieces)[3]) {
   typedef float floatx2 __attribute__((ext_vector_type(2)));
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));

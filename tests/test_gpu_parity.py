@@ -1101,3 +1101,114 @@ def test_config0_end_to_end(mbq):
     perm_ref, off_ref = O.bucket(prec_ref)
     Y = mbq.mbq_linear(X, blob, N, K, dev(prec_ref), dev(perm_ref), dev(off_ref))
     assert_output_close(Y.cpu().numpy(), O.linear(xb, codes, s0, z0, prec_ref), "config 0 oracle routing")
+
+
+@pytest.mark.parametrize("rows_of", ["one", "every"])
+@pytest.mark.parametrize("parts", [1, 2])
+def test_prefill_rows_of_small_numbers(mbq, rows_of, parts):
+    """Rows of tiny, subnormal and large activations in tiles whose zero-point term is formed in bf16 pieces (parts of more
+    than eight groups; three of the four precisions): each row is held to the bar on its own."""
+    N, K, T = 130, 128 * 34, 48
+    rng = np.random.default_rng([173, parts])
+    W = make_weight(N, K, [173, parts], 4.0)
+    x = rng.standard_normal((T, K)).astype(np.float32)
+    scales = [1.0, 2.0 ** -100, 2.0 ** -110, 2.0 ** -118, 2.0 ** -122, 2.0 ** -126, 2.0 ** -129, 2.0 ** -131, 2.0 ** 90, 2.0 ** 110]
+    for t in range(T):
+        if rows_of == "every" or t % 4 == 0:
+            x[t] *= np.float32(scales[t % 12 if t % 12 < len(scales) else 0])
+    x[47, :2048] *= np.float32(2.0 ** -126)   # groups of small numbers beside ordinary ones
+    xb = f32_to_bf16_bits(x)
+    prec = (np.arange(T) % 3).astype(np.int32) if rows_of == "one" else np.repeat(np.arange(4), 12).astype(np.int32)
+    codes, s0, z0 = O.encode(W)
+    Yref = O.linear(xb, codes, s0, z0, prec)
+    mbq.set_knob(5, parts)
+    try:
+        Y = run_linear(mbq, W, xb, prec, ALGOS["prefill"])
+    finally:
+        mbq.set_knob(5, 0)
+    bad = []
+    for t in range(T):
+        err = np.abs(Y[t].astype(np.float64) - Yref[t])
+        rms = np.sqrt(np.mean(Yref[t] ** 2))
+        print(f"[parity] row {t}: precision {prec[t]}, largest activation 2^{np.log2(np.abs(x[t]).max()):.0f}, "
+              f"rel {np.linalg.norm(err) / np.linalg.norm(Yref[t]):.1e}, max {err.max() / rms:.1e}", flush=True)
+        if not (np.linalg.norm(err) <= 1e-3 * np.linalg.norm(Yref[t]) and err.max() <= MAX_ABS_TOL * rms):
+            bad.append(t)
+    assert not bad, bad
+
+
+ROW_KERNELS = [((11270,), 1536, 48), ((12800, 12810), 3328, 33), ((3072,), 8448, 64), ((3072, 600), 8320, 40), ((300,), 4352, 300)]
+
+
+@pytest.mark.parametrize("Ns,K,T", ROW_KERNELS)
+def test_rows_do_not_meet(mbq, Ns, K, T):
+    """Rows of NaN, of an infinity, of the largest numbers and of zeros: every other row has the bits that it has beside
+    ordinary ones, zeros give zeros, and tiny and subnormal rows are held to the bar on their own.  Row 0 is among the former:
+    kernels read it in the place of rows past the last."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(179 + T + K)
+    X = torch.randn((T, K), generator=gen, device="cuda")
+    small = {3: 2.0 ** -110, 7: 2.0 ** -126, 12: 2.0 ** -131, 20: 2.0 ** 90}
+    for t, scale in small.items():
+        X[t] *= scale
+    X[9] = 0.0
+    X = X.to(torch.bfloat16)
+    blobs = [mbq.mbq_encode(0.02 * torch.randn((N, K), generator=gen, device="cuda")) for N in Ns]
+    routing = []
+    for i in range(len(Ns)):
+        prec = np.random.default_rng([179, T, i]).integers(0, 4, size=T).astype(np.int32)
+        routing.append((dev(prec), *[dev(v) for v in O.bucket(prec)]))
+    Ys = mbq.mbq_linear_group(X, blobs, list(Ns), K, routing)
+    odd = X.clone()
+    odd[0] = float("nan")
+    odd[5, K // 2] = float("inf")
+    odd[11] = 3.3e38
+    odd[T - 1] = -float("inf")
+    others = torch.tensor([t for t in range(T) if t not in (0, 5, 11, T - 1)], device="cuda")
+    for i, (a, b) in enumerate(zip(Ys, mbq.mbq_linear_group(odd, blobs, list(Ns), K, routing))):
+        assert torch.equal(a[others], b[others]), i
+        assert bool(a.isfinite().all()) and not bool(a[9].any()) and bool(b[0].isnan().all()), i
+        ref = reference64(X, blobs[i], Ns[i], K, routing[i][0])
+        for t in (0, *small):
+            err = (a[t].double() - ref[t]).norm() / ref[t].norm()
+            assert float(err) < 4e-5, (i, t, float(err))
+
+
+@pytest.mark.parametrize("Ns,K,T", ROW_KERNELS)
+def test_stages_of_these_kernels_replay_from_a_hip_graph(mbq, Ns, K, T):
+    """A captured stage, replayed with new activations and eager work in between, gives the eager call's bits every time."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(181 + T + K)
+    Wr = [torch.randn((4, K), generator=gen, device="cuda") / K ** 0.5 for _ in Ns]
+    br = [torch.zeros(4, device="cuda") for _ in Ns]
+    blobs = [mbq.mbq_encode(0.02 * torch.randn((N, K), generator=gen, device="cuda")) for N in Ns]
+    X = torch.randn((T, K), generator=gen, device="cuda").to(torch.bfloat16)
+    kept = dict(routing=[(torch.empty(T, dtype=torch.int32, device="cuda"), torch.empty(T, dtype=torch.int32, device="cuda"),
+                          torch.empty(5, dtype=torch.int32, device="cuda")) for _ in Ns],
+                Y=[torch.empty((T, N), device="cuda") for N in Ns],
+                ws_route=mbq.route_workspace(T, K, "cuda"), ws_linear=mbq.linear_workspace(T, max(Ns), K, "cuda"))
+
+    def call():
+        mbq.mbq_routed_linear_group(X, Wr, br, blobs, list(Ns), **kept)
+
+    call()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        call()
+    for rep in range(4):
+        X.copy_(torch.randn((T, K), generator=gen, device="cuda").to(torch.bfloat16))
+        call()
+        want = [[t.clone() for t in r] for r in kept["routing"]], [y.clone() for y in kept["Y"]]
+        torch.cuda.synchronize()
+        kept["ws_linear"].fill_(255)
+        for y in kept["Y"]:
+            y.fill_(float("nan"))
+        for r in kept["routing"]:
+            for t in r:
+                t.fill_(-7)
+        g.replay()
+        torch.cuda.synchronize()
+        for i in range(len(Ns)):
+            assert all(torch.equal(a, b) for a, b in zip(want[0][i], kept["routing"][i])), (rep, i)
+            assert torch.equal(want[1][i], kept["Y"][i]), (rep, i)
