@@ -202,6 +202,17 @@ __device__ __forceinline__ float sum8(const uint4& v) {
   for (int j = 0; j < 4; ++j) s += __uint_as_float(u[j] << 16) + __uint_as_float(u[j] & 0xFFFF0000u);
   return s;
 }
+// 16 bytes per lane from base + offset straight into LDS at lds + 16 * lane.  Written in assembly because the compiler
+// takes every LDS read for a possible reader of such a load and would wait for all of them ahead of the first read of
+// a group; the kernel waits itself, once per group.  (The instruction has no register result; M0, which holds the LDS
+// address, is put back.)
+__device__ __forceinline__ void dma_16(uint32_t lds, uint32_t offset, const void* base) {
+  uint32_t m0;
+  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b32 m0, %0"
+               : "=&s"(m0)
+               : "s"(lds), "v"(offset), "s"(base)
+               : "memory");
+}
 // What a prefill launch starts from: the sums of X over groups, Sx[token][group], and cleared arrays (zl: outputs, zs: arrays
 // of the workspace).  A workgroup does rows row0 .. row0 + rows - 1 and its share of the clearing.
 struct PrefillPrep {
@@ -239,6 +250,17 @@ __device__ inline void prefill_prep_share(const PrefillPrep& p, int64_t T, int64
   for (int64_t r = row0 + (threadIdx.x >> 8); r < row0 + rows && r < T; r += threads >> 8)
     prefill_row_sums(reinterpret_cast<const uint4*>(p.X + r * K), K, threadIdx.x & 255, p.Sx + r * (K >> 7), nullptr);
 }
+// The last launch of calls whose parts of K have arrays of their own: Y += array 1, += array 2, .. in that order (nothing to
+// launch if no matrix has any).  arrays: Y among them, at most kMaxKSplit; array 1 lies at `array`, the others array_floats
+// apart, 16-byte aligned.
+struct Fold {
+  float* Y[MBQ_MAX_GROUP];
+  const float* array[MBQ_MAX_GROUP];
+  int64_t array_floats[MBQ_MAX_GROUP];
+  int64_t n[MBQ_MAX_GROUP];  // floats of Y
+  int arrays[MBQ_MAX_GROUP];
+};
+mbq_status launch_fold(const Fold& f, int n, hipStream_t stream);
 size_t decode_f4_workspace_bytes(int64_t T, const Shape& sh);
 mbq_status launch_decode_f4_prep(const uint16_t* X, int64_t T, int64_t K, int KB, void* ws, const ZeroList& zl,
                                  hipStream_t stream);

@@ -14,7 +14,7 @@
 // will add up to (a constant of the row), so a group's result is small when it is scaled by s0 and added to the sum; the
 // zero points follow as fp32 MFMAs, K = 4, every two blocks.
 // Long rows are cut into up to eight parts of the K axis: part 0 stores into Y, the others into arrays of the workspace,
-// which mid_fold_kernel adds in order, so the result does not depend on which comes first.
+// which fold_kernel adds in order, so the result does not depend on which comes first.
 // Wide matrices are the sum of two halves of K.  Where a call has no more workgroups than the chip has compute units (a matrix
 // alone) a workgroup of eight wavefronts forms both at a time, which meet in LDS; otherwise one of four forms them in
 // turn: the same bits.  (One wavefront a SIMD issues an instruction every 7 cycles, two of them every 4.6: 14336 x 4096 alone
@@ -70,16 +70,6 @@ struct Item {  // a 16 x 256 block: four slices and {s0, z0} of two groups
   uint4 w[4];
   float2 mt[2];
 };
-
-// 16 bytes per lane from base + offset straight into LDS at lds + 16 * lane.  (In assembly: given the builtin the compiler
-// waits for all such loads ahead of the next LDS read.  No register result; M0, which holds the LDS address, is put back.)
-__device__ __forceinline__ void dma_16(uint32_t lds, uint32_t offset, const void* base) {
-  uint32_t m0;
-  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b32 m0, %0"
-               : "=&s"(m0)
-               : "s"(lds), "v"(offset), "s"(base)
-               : "memory");
-}
 
 }  // namespace mid
 
@@ -387,41 +377,6 @@ mbq_status launch_mid_sums(const uint16_t* X, int64_t T, int64_t K, void* sums, 
   return hip_status(hipGetLastError(), "mid_sums_kernel launch");
 }
 
-// ---- launches that cut K: Y += array 1, += array 2, .. in that order ----
-namespace mid {
-struct Fold {
-  float* Y[MBQ_MAX_GROUP];
-  const float* slot[MBQ_MAX_GROUP];
-  int64_t slot_floats[MBQ_MAX_GROUP];
-  int64_t n[MBQ_MAX_GROUP];
-  int parts[MBQ_MAX_GROUP];
-};
-}  // namespace mid
-__global__ __launch_bounds__(256) void mid_fold_kernel(const mid::Fold f) {
-  const int j = blockIdx.y, extra = f.parts[j] - 1;
-  if (extra <= 0) return;
-  float* __restrict__ Y = f.Y[j];
-  const float* __restrict__ slot = f.slot[j];
-  const int64_t n = f.n[j], ld = f.slot_floats[j], at = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
-  const int64_t n4 = (reinterpret_cast<uintptr_t>(Y) & 15) == 0 ? n >> 2 : 0;
-  for (int64_t i = at; i < n4; i += step) {
-    floatx4 v[mid::kMaxParts];  // all on their way before the first is used
-    v[0] = reinterpret_cast<const floatx4*>(Y)[i];
-#pragma unroll
-    for (int e = 1; e < mid::kMaxParts; ++e)
-      if (e <= extra) v[e] = reinterpret_cast<const floatx4*>(slot + (e - 1) * ld)[i];
-#pragma unroll
-    for (int e = 1; e < mid::kMaxParts; ++e)
-      if (e <= extra) v[0] += v[e];
-    reinterpret_cast<floatx4*>(Y)[i] = v[0];
-  }
-  for (int64_t i = 4 * n4 + at; i < n; i += step) {
-    float v = Y[i];
-    for (int e = 0; e < extra; ++e) v += slot[e * ld + i];
-    Y[i] = v;
-  }
-}
-
 namespace mid {
 static inline size_t sums_bytes(int64_t T, int64_t K) { return ((size_t)T * (size_t)(K / kGroup) * 8 + 255) / 256 * 256; }
 static inline int64_t slot_floats(int64_t T, int64_t N) { return (T * N + 63) / 64 * 64; }
@@ -479,9 +434,8 @@ mbq_status launch_linear_mid_group(const uint16_t* X, int64_t T, int n, const vo
     return MBQ_OK;
   }
   mid::Group g;
-  mid::Fold f;
+  Fold fold;
   int grid = 0;
-  int64_t most = 0;
   float* slot = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + mid::sums_bytes(T, sh.K));
   for (int i = 0; i < MBQ_MAX_GROUP; ++i) {
     const int j = i < n ? i : 0;
@@ -502,15 +456,14 @@ mbq_status launch_linear_mid_group(const uint16_t* X, int64_t T, int n, const vo
     p.parts = mid_parts(T, s);
     p.half = p.parts == 1 ? mid::first_half(s.KB) : 0;
     p.wg_begin = grid;
-    f.Y[i] = Y[j];
-    f.slot[i] = slot;
-    f.slot_floats[i] = p.slot_floats;
-    f.n[i] = T * s.N;
-    f.parts[i] = i < n ? p.parts : 1;
+    fold.Y[i] = Y[j];
+    fold.array[i] = slot;
+    fold.array_floats[i] = p.slot_floats;
+    fold.n[i] = T * s.N;
+    fold.arrays[i] = i < n ? p.parts : 1;
     if (i < n) {
       grid += (s.NT + mid::kWaves - 1) / mid::kWaves * p.parts;
       slot += (p.parts - 1) * p.slot_floats;
-      if (p.parts > 1 && f.n[i] > most) most = f.n[i];
     }
   }
   g.n = n;
@@ -529,12 +482,7 @@ mbq_status launch_linear_mid_group(const uint16_t* X, int64_t T, int n, const vo
   if (T <= 48) sides ? launch(three, two) : launch(three, one);
   else sides ? launch(four, two) : launch(four, one);
   mbq_status st = hip_status(hipGetLastError(), "mid_kernel launch");
-  if (st != MBQ_OK || most == 0) return st;
-  int64_t blocks = (most / 4 + 255) / 256;
-  if (blocks > 4 * device_compute_units()) blocks = 4 * device_compute_units();
-  if (blocks < 1) blocks = 1;
-  hipLaunchKernelGGL(mid_fold_kernel, dim3((unsigned)blocks, (unsigned)n), dim3(256), 0, stream, f);
-  return hip_status(hipGetLastError(), "mid_fold_kernel launch");
+  return st == MBQ_OK ? launch_fold(fold, n, stream) : st;
 }
 
 }  // namespace mbq

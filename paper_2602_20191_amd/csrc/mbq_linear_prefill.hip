@@ -106,41 +106,6 @@ __global__ __launch_bounds__(256) void prefill_prep_kernel(const PrefillPrep p, 
                    reinterpret_cast<uint4*>(Xs + r * K));
 }
 
-// ---- post-kernel of launches that cut K into more than two parts: Y += array 1, += array 2, .. in that order ----
-struct Fold {
-  float* Y[MBQ_MAX_GROUP];
-  const float* slot[MBQ_MAX_GROUP];
-  int64_t slot_floats[MBQ_MAX_GROUP];
-  int64_t n[MBQ_MAX_GROUP];  // floats of Y
-  int slots[MBQ_MAX_GROUP];
-};
-__global__ __launch_bounds__(256) void prefill_fold_kernel(const Fold f) {
-  const int j = blockIdx.y;
-  float* __restrict__ Y = f.Y[j];
-  const float* __restrict__ slot = f.slot[j];
-  const int64_t n = f.n[j], at = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
-  const int extra = f.slots[j] - 1;
-  if (extra <= 0) return;
-  const bool wide = (reinterpret_cast<uintptr_t>(Y) & 15) == 0;  // (the arrays of the workspace always are)
-  const int64_t n4 = wide ? n >> 2 : 0;
-  for (int64_t i = at; i < n4; i += step) {
-    floatx4 v[kMaxSplits];  // all on their way before the first is used
-    v[0] = reinterpret_cast<const floatx4*>(Y)[i];
-#pragma unroll
-    for (int e = 1; e < kMaxSplits; ++e)
-      if (e <= extra) v[e] = reinterpret_cast<const floatx4*>(slot + (e - 1) * f.slot_floats[j])[i];
-#pragma unroll
-    for (int e = 1; e < kMaxSplits; ++e)
-      if (e <= extra) v[0] += v[e];
-    reinterpret_cast<floatx4*>(Y)[i] = v[0];
-  }
-  for (int64_t i = 4 * n4 + at; i < n; i += step) {
-    float v = Y[i];
-    for (int e = 0; e < extra; ++e) v += slot[e * f.slot_floats[j] + i];
-    Y[i] = v;
-  }
-}
-
 __device__ __forceinline__ floatx16 mfma(const u32x4& a, const u32x4& b, floatx16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
@@ -157,19 +122,7 @@ __device__ __forceinline__ float scale_mantissa(float s0) {
 // biased bf16 exponent E (even) of (256 + V) * 2^t
 __device__ __forceinline__ uint32_t scale_exponent(float s0) { return ((__float_as_uint(s0) >> 23) + 9u) & ~1u; }
 
-// 16 bytes per lane from base + offset straight into LDS at lds + 16 * lane.  Written in assembly because the compiler
-// takes every LDS read for a possible reader of such a load and would wait for all of them ahead of the first read of
-// a group; the kernel waits itself, once per group.  (The instruction has no register result; M0, which holds the LDS
-// address, is put back.)
-__device__ __forceinline__ void dma_16(uint32_t lds, uint32_t offset, const void* base) {
-  uint32_t m0;
-  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b32 m0, %0"
-               : "=&s"(m0)
-               : "s"(lds), "v"(offset), "s"(base)
-               : "memory");
-}
-
-// the same with 4 bytes per lane and an address of its own
+// dma_16 with 4 bytes per lane and an address of its own
 __device__ __forceinline__ void dma_4(uint32_t lds, const void* address) {
   uint32_t m0;
   asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %2, off\n\ts_mov_b32 m0, %0"
@@ -736,8 +689,8 @@ static double split_cost(Split sp, int64_t T, int64_t K, int64_t cols) {
 // The cut that minimises the estimate, among those of at most `most` parts. Fitted to 1..8 parts on twenty shapes from
 // 1000 x 2176 to 28672 x 8192, alone and in groups of two and three, at 65..4096 tokens: 1.0 % above the best cut alone
 // on average (17 % on the worst), 0.6 % (13 %) in groups; of the tile kernel as it is now, 39 calls, 2.1 % above the best cut
-// on average (19 % on the worst, 4096 x 14336 at 300 tokens 91 in eight parts, 76 in four; constants fitted anew came to
-// 1.5 %, so they stay). For instance (us, 1 / 2 / 4 / 8 parts; * taken) 4096 x 11008 at 256 tokens 177 / 97 / 74 / 66*, at
+// on average (19 % on the worst, 4096 x 14336 at 300 tokens 91 in eight parts, 76 in four; next 4096 x 11008 at 512 tokens 102,
+// 89 in three, and 2048 x 8192 at 700 tokens 72, 62 in four; constants fitted anew came to 1.5 %, so they stay). For instance (us, 1 / 2 / 4 / 8 parts; * taken) 4096 x 11008 at 256 tokens 177 / 97 / 74 / 66*, at
 // 2048 tokens 311 / 260* / 287 / -, 4096 x 4096 at 160 tokens 68 / 40 / 33*, 11008 x 4096 at 256 tokens 77 / 62*, at 777
 // tokens 118* / 150.
 // pairs: a matrix with as many rows as columns or more has company more often than not (q, k, v of an attention; gate
@@ -774,6 +727,47 @@ static void choose_splits(int64_t T, int64_t K, int n, const Shape* shapes, int6
     if (N >= K && out[i].parts == 2) out[i] = choose_split(T, K, N, cols, N >= 2 * K ? 2 : 1, 2, area_floats);
     if (n > 1 && out[i].parts > 2) out[i] = choose_split(T, K, N, all, 0, out[i].parts, area_floats / n);
   }
+}
+
+// ---- the launch that adds the arrays of a matrix that is cut along K ----
+static_assert(pf::kMaxSplits <= kMaxKSplit, "arrays that it takes");
+__global__ __launch_bounds__(256) void fold_kernel(const Fold f) {
+  const int j = blockIdx.y;
+  float* __restrict__ Y = f.Y[j];
+  const float* __restrict__ array = f.array[j];
+  const int64_t n = f.n[j], at = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
+  const int extra = f.arrays[j] - 1;
+  if (extra <= 0) return;
+  const bool wide = (reinterpret_cast<uintptr_t>(Y) & 15) == 0;  // (the arrays of the workspace always are)
+  const int64_t n4 = wide ? n >> 2 : 0;
+  for (int64_t i = at; i < n4; i += step) {
+    floatx4 v[kMaxKSplit];  // all on their way before the first is used
+    v[0] = reinterpret_cast<const floatx4*>(Y)[i];
+#pragma unroll
+    for (int e = 1; e < kMaxKSplit; ++e)
+      if (e <= extra) v[e] = reinterpret_cast<const floatx4*>(array + (e - 1) * f.array_floats[j])[i];
+#pragma unroll
+    for (int e = 1; e < kMaxKSplit; ++e)
+      if (e <= extra) v[0] += v[e];
+    reinterpret_cast<floatx4*>(Y)[i] = v[0];
+  }
+  for (int64_t i = 4 * n4 + at; i < n; i += step) {
+    float v = Y[i];
+    for (int e = 0; e < extra; ++e) v += array[e * f.array_floats[j] + i];
+    Y[i] = v;
+  }
+}
+
+mbq_status launch_fold(const Fold& f, int n, hipStream_t stream) {
+  int64_t most = 0;
+  for (int i = 0; i < n; ++i)
+    if (f.arrays[i] > 1 && f.n[i] > most) most = f.n[i];
+  if (most == 0) return MBQ_OK;
+  int64_t blocks = (most / 4 + 255) / 256;  // four floats a thread and pass
+  if (blocks < 1) blocks = 1;
+  if (blocks > 8 * device_compute_units()) blocks = 8 * device_compute_units();
+  hipLaunchKernelGGL(fold_kernel, dim3((unsigned)blocks, (unsigned)n), dim3(256), 0, stream, f);
+  return hip_status(hipGetLastError(), "fold_kernel launch");
 }
 
 // offsets of rows are 32-bit: from 4 GiB of activations on a sorted copy is made, one matrix at a time
@@ -830,8 +824,8 @@ mbq_status launch_linear_prefill_group(const uint16_t* X, int64_t T, int n, cons
   prefill_cuts(T, n, shapes, Y, ws, split, &prep.zl, &prep.zs);
   const int64_t m_tiles_max = T / pf::kBM + MBQ_N_PRECISIONS;
   pf::Group g;
-  pf::Fold fold;
-  int64_t blocks = 0, most = 0;
+  Fold fold;
+  int64_t blocks = 0;
   float* slot = reinterpret_cast<float*>(ws);
   for (int i = 0; i < MBQ_MAX_GROUP; ++i) {
     const int j = i < n ? i : 0;
@@ -854,14 +848,13 @@ mbq_status launch_linear_prefill_group(const uint16_t* X, int64_t T, int n, cons
     m.slots = sp.slots;
     m.block_begin = (int)blocks;
     fold.Y[i] = Y[j];
-    fold.slot[i] = slot;
-    fold.slot_floats[i] = floats;
+    fold.array[i] = slot;
+    fold.array_floats[i] = floats;
     fold.n[i] = T * sh.N;
-    fold.slots[i] = i < n ? sp.slots : 1;
+    fold.arrays[i] = i < n ? sp.slots : 1;
     if (i < n) {
       blocks += m_tiles_max * m.cols * sp.parts;
       slot += (sp.slots - 1) * floats;
-      if (sp.slots > 1 && fold.n[i] > most) most = fold.n[i];
     }
   }
   g.n = n;
@@ -875,12 +868,7 @@ mbq_status launch_linear_prefill_group(const uint16_t* X, int64_t T, int n, cons
   hipLaunchKernelGGL(pf::prefill_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, gather ? X : Xs, K, shapes[0].KB,
                      gather ? 1 : 0, prep.Sx, g);
   st = hip_status(hipGetLastError(), "prefill_kernel launch");
-  if (st != MBQ_OK || most == 0) return st;
-  int64_t fold_blocks = (most / 4 + 255) / 256;  // four floats a thread and pass
-  if (fold_blocks < 1) fold_blocks = 1;
-  if (fold_blocks > 8 * device_compute_units()) fold_blocks = 8 * device_compute_units();
-  hipLaunchKernelGGL(pf::prefill_fold_kernel, dim3((unsigned)fold_blocks, (unsigned)n), dim3(256), 0, stream, fold);
-  return hip_status(hipGetLastError(), "prefill_fold_kernel launch");
+  return st == MBQ_OK ? launch_fold(fold, n, stream) : st;
 }
 
 mbq_status launch_linear_prefill(const uint16_t* X, int64_t T, const void* blob, const Shape& sh, const int32_t* perm,
