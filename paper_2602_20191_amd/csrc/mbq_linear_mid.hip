@@ -388,12 +388,16 @@ static inline int first_half(int KB) { return (KB + 1) / 4 * 2; }  // even, with
 // in us (register-stationary kernel / this one), at 33, 48 and 64 tokens of an even mix (skewed mixes are within 5 % of the
 // same ratio):
 //   wide matrices, one part, alone (halves of K side by side) up to a workgroup a compute unit: 14336 x 4096 42 / 36, 42 / 36,
-//   42 / 39; 12800 x 4096 42 / 36, 42 / 36, 42 / 38; 12288 x 4096 34.9 / 35.7, 38 / 36, 39 / 38; 11008 x 4096 33 / 35, 38 / 35, 38 / 38 (neither taken); 14336 x 3072 38
-//   / 30, 38 / 30, 39 / 32; 14336 x 2048 27 / 23, 28 / 23, 28 / 24; 10240 x 2048 23 / 22, 24 / 22, 24 / 23; beyond, in turn: 18432
-//   x 4096 50 / 55, 50 / 55, 51 / 59 (not taken), 24576 x 4096 62 / 55, 63 / 55, 64 / 60, 32000 x 4096 78 / 58, 79 / 59, 80 / 64;
-//   twice (in turn): 14336 x 4096 71 / 57, 72 / 56, 73 / 61; 11008 x 4096 69 / 55, 58 / 55, 59 / 60; 14336 x 2048 41 / 33, 42 / 33,
-//   43 / 36; 10240 x 2048 33 / 32, 34 / 32, 34.6 / 34.7, at 56 tokens 34 / 35 (not taken); below K = 1536 rows are too short: 10240
-//   x 1024 alone 15 / 15, 16 / 15, 14 / 15;
+//   42 / 39; 12800 x 4096 42 / 36, 42 / 36, 42 / 38; beyond, in turn: 18432 x 4096 50 / 55, 50 / 55, 51 / 59 (not taken), 24576 x
+//   4096 62 / 55, 63 / 55, 64 / 60, 32000 x 4096 78 / 58, 79 / 59, 80 / 64; twice (in turn): 14336 x 4096 71 / 57, 72 / 56, 73 / 61;
+//   where the line lies, the same as ratios, alone and twice, at 33, 48, 49 and 64 tokens (the other kernel's time goes in
+//   steps): 4096 columns, 13312 rows 1.16 1.17 1.05 1.09, twice 1.19 1.21 1.06 1.12, 12288 rows 0.98 1.06 0.95 0.99, twice 1.25 1.14
+//   0.99 1.06 (not taken), 11264 rows 0.92 1.07 0.95 0.99 (not taken); 3584 columns, 11776 rows 1.03 1.10 0.98 1.03, twice 1.38 1.22
+//   1.07 1.14, 11264 rows 0.98 1.10 0.98 1.03 (not taken); 3328 columns, 10752 rows 1.04 1.05 1.03 1.08, twice 1.46 1.48 1.05 1.11,
+//   10240 rows 0.98 0.99 0.89 0.98 (not taken); 3072: 10752 rows 1.12 1.13 1.07 1.11; 2048: 10752 rows 1.13 1.16 1.06 1.11, twice 1.06
+//   1.10 0.99 1.05, 10240 rows twice 1.02 1.05 0.95 1.00 (not taken); 1536: 10752 rows 1.19 1.24 1.13 1.19; 1024: 10752 rows 1.00 1.07
+//   0.93 0.97, twice 1.08 1.16 0.95 0.99 (taken up to 48 tokens), 13312 rows 1.10 1.16 0.98 1.02, twice 1.18 1.26 1.03 1.06; 768: 10752
+//   rows 1.02 1.06 0.95 0.98; 512: 10752 rows 1.14 1.22 1.06 1.12;
 //   long rows, eight parts: 4096 x 11008 41 / 33, 41 / 33, 41 / 36; 3072 x 8320 34 / 29, 34 / 29, 34 / 30; 8192 x 28672 145 / 104,
 //   145 / 103, 145 / 112; 2048 x 8192 23 / 24, 24 / 24, 24 / 25 (not taken);
 //   with more rows than half the columns (q and o of an attention, where q has company) from K = 9984 on: 12288 x 12288 alone 90
@@ -406,9 +410,10 @@ static inline int first_half(int KB) { return (KB + 1) / 4 * 2; }  // even, with
 int mid_parts(int64_t T, const Shape& sh) {
   if (T < mid::kMinRows || T > mid::kMaxRows) return 0;
   const int least = (sh.KB + mid::kMaxBlocks - 1) / mid::kMaxBlocks;
-  if (sh.N >= 2 * sh.K && sh.KB >= 6 && least == 1) {
+  if (sh.N >= 2 * sh.K && least == 1) {
     const int alone_most = 256 * mid::kWaves, apart_least = 384 * mid::kWaves;  // code tiles
-    return (sh.NT >= (sh.KB <= 12 ? 704 : 800) && sh.NT <= alone_most) || sh.NT >= apart_least ? 1 : 0;
+    const int from = sh.KB >= 15 ? 800 : sh.KB == 14 ? 736 : (sh.KB == 3 || sh.KB == 4) && T > 48 ? 832 : 672;
+    return (sh.NT >= from && sh.NT <= alone_most) || sh.NT >= apart_least ? 1 : 0;
   }
   if (sh.KB <= (2 * sh.N <= sh.K ? 32 : 38) || sh.NT < 192 || sh.N > sh.K) return 0;
   // (the workspace of a call has room for kMaxKSplit arrays of at least T rows, decode_workspace_bytes: seven and the sums,

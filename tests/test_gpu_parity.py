@@ -786,8 +786,9 @@ def test_decode_wide_matrices_and_long_rows(mbq, T, mix, Ns, K):
 
 
 @pytest.mark.parametrize("T,mix", [(33, (8, 9, 8, 8)), (48, (0, 17, 31, 0)), (49, (48, 0, 0, 1)), (64, (16, 15, 17, 16))])
-@pytest.mark.parametrize("Ns,K", [((11250,), 1408), ((11264, 11267), 1536), ((16384,), 1664), ((11300,), 2432), ((12800, 13000), 3328),
-                                  ((12800,), 3456), ((13001,), 3968), ((16300, 12790), 4096), ((24570,), 1536), ((24580,), 3840)])
+@pytest.mark.parametrize("Ns,K", [((10740,), 128), ((10752, 10740), 384), ((10750, 13312), 896), ((11250,), 1408), ((11264, 11267), 1536),
+                                  ((16384,), 1664), ((11300,), 2432), ((12800, 13000), 3328), ((12800,), 3456), ((13001,), 3968),
+                                  ((16300, 12790), 4096), ((24570,), 1536), ((24580,), 3840)])
 def test_decode_wide_matrices_in_halves(mbq, T, mix, Ns, K):
     """Wide matrices are the sum of two halves of K, formed at a time by one workgroup where the matrix is alone and in turn
     in a group or where it has more columns: the same bits.  Halves of the same and of different lengths, a last block of one
