@@ -267,8 +267,8 @@ mbq_status mbq_linear_group(const uint16_t* X, int64_t T, int64_t K, int n_proj,
  * projection alone, then compute their outputs).  Same results and the same outputs (prec,
  * perm, offsets, Y) as the two calls.  Up to 16 tokens the router launch also carries the decode
  * kernel's activation preparation, and up to 128 tokens (while every matrix takes a decode
- * kernel) the token sort moves into the linear launch, so the stage is two launches (three for
- * long rows at 33 to 64 tokens); above 128 tokens, where every matrix takes the tiled GEMM, the
+ * kernel) the token sort moves into the linear launch, so the stage is two launches (one more for
+ * each long row at 33 to 64 tokens, and where its matrices take two of the decode kernels); above 128 tokens, where every matrix takes the tiled GEMM, the
  * router launch also forms that kernel's row sums and clears the arrays it adds into.
  *   ws_route  : as ws in mbq_route
  *   ws_linear : as ws in mbq_linear_group
