@@ -19,7 +19,7 @@
 // alone) a workgroup of eight wavefronts forms both at a time, which meet in LDS; otherwise one of four forms them in
 // turn: the same bits.  (One wavefront a SIMD issues an instruction every 7 cycles, two of them every 4.6: 14336 x 4096 alone
 // at 64 tokens 42 us in the register-stationary kernel, 48 with four wavefronts and no halves, 39 now; twice the matrix takes
-// as long in turn as without halves.)
+// 1 to 3 % longer in turn than without halves.)
 //
 // Bound by instruction issue: a block takes 360 vector instructions (192 of them unpacking) and 92 MFMAs a wavefront at 64
 // tokens of an even mix, 7500 cycles for the two wavefronts of a SIMD.  Stage calls (router included) with the
@@ -73,8 +73,10 @@ struct Item {  // a 16 x 256 block: four slices and {s0, z0} of two groups
 
 }  // namespace mid
 
-// SIDES = 2: eight wavefronts, four on each half of K (every matrix of the launch has halves); 1: one half after the other
-template <int RT, int SIDES>
+// Wide matrices, whose K axis has two halves: SIDES = 2, eight wavefronts, four on each half, or IN_TURN, one half after the
+// other.  Long rows: neither.  (An instance of its own each: 8192 x 28672 at 64 tokens of a skewed mix 93.5 us, 95.3 with IN_TURN a
+// run-time branch.)
+template <int RT, int SIDES, bool IN_TURN>
 __global__ __launch_bounds__(64 * mid::kWaves * SIDES, 2) void mid_kernel(const uint16_t* __restrict__ X, int T, int64_t K, int KB,
                                                                           const float2* __restrict__ sums, const mid::Group g) {
   using namespace mid;
@@ -249,7 +251,9 @@ __global__ __launch_bounds__(64 * mid::kWaves * SIDES, 2) void mid_kernel(const 
           // from the first row tile with rows of this precision; rows of it that are below count as zeros
 #pragma unroll
           for (int r0 = 0; r0 < RT; ++r0) {
-            if (first_tile[E] == r0) {
+            // (three of the four are passed by: out of line, which the compiler does by itself but with IN_TURN's outer
+            // loop; 14336 x 4096 twice at 64 tokens 60.9 -> 61.3 us with that, 62.2 in line, a skewed mix 48.9 -> 50.4, 51.0)
+            if (IN_TURN ? __builtin_expect(first_tile[E] == r0, 0) : first_tile[E] == r0) {
               const uint32_t mk = mask[E];
 #pragma unroll
               for (int s = 0; s < 2; ++s) {
@@ -302,9 +306,8 @@ __global__ __launch_bounds__(64 * mid::kWaves * SIDES, 2) void mid_kernel(const 
   asm volatile("s_barrier" ::: "memory");
   // (the first half has an even number of blocks, so the second begins with the same registers and at the same place of a
   // pair of blocks as a side of its own would)
-  const bool in_turn = SIDES == 1 && P.half > 0;
   floatx4 y_first[RT];
-  for (int end = in_turn ? P.half : nblk;; end = nblk) {
+  for (int end = IN_TURN ? P.half : nblk;; end = nblk) {
 #pragma unroll 1
     for (int q = i; q < end; q += 2) {
       block(A, B);
@@ -317,7 +320,7 @@ __global__ __launch_bounds__(64 * mid::kWaves * SIDES, 2) void mid_kernel(const 
       y[rt] = floatx4{0.f, 0.f, 0.f, 0.f};
     }
   }
-  if (in_turn) {
+  if constexpr (IN_TURN) {
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) y[rt] = y_first[rt] + y[rt];
   }
@@ -475,8 +478,8 @@ mbq_status launch_linear_mid_group(const uint16_t* X, int64_t T, int n, const vo
   // halves of K side by side where that leaves no workgroup waiting for another (they need a compute unit each), in turn
   // where two workgroups share one: the same bits
   const bool sides = !cut && grid <= device_compute_units();
-  const auto launch = [&](auto rt, auto n_sides) {
-    hipLaunchKernelGGL((mid_kernel<decltype(rt)::value, decltype(n_sides)::value>), dim3(grid),
+  const auto launch = [&](auto rt, auto n_sides, auto turn) {
+    hipLaunchKernelGGL((mid_kernel<decltype(rt)::value, decltype(n_sides)::value, decltype(turn)::value>), dim3(grid),
                        dim3(64 * mid::kWaves * decltype(n_sides)::value), 0, stream, X, (int)T, sh.K, sh.KB,
                        reinterpret_cast<const float2*>(ws), g);
   };
@@ -484,8 +487,10 @@ mbq_status launch_linear_mid_group(const uint16_t* X, int64_t T, int n, const vo
   const std::integral_constant<int, 2> two{};
   const std::integral_constant<int, 3> three{};
   const std::integral_constant<int, 4> four{};
-  if (T <= 48) sides ? launch(three, two) : launch(three, one);
-  else sides ? launch(four, two) : launch(four, one);
+  const std::true_type yes{};
+  const std::false_type no{};
+  if (T <= 48) sides ? launch(three, two, no) : cut ? launch(three, one, no) : launch(three, one, yes);
+  else sides ? launch(four, two, no) : cut ? launch(four, one, no) : launch(four, one, yes);
   mbq_status st = hip_status(hipGetLastError(), "mid_kernel launch");
   return st == MBQ_OK ? launch_fold(fold, n, stream) : st;
 }
