@@ -247,8 +247,9 @@ mbq_status mbq_linear_static(const uint16_t* X, int64_t T, const void* blob, int
  * activations (q/k/v, gate/up of a decoder block), each with its own routing; one launch for all
  * of them while every matrix takes a decode kernel (up to 64 tokens, 128 with AUTO on matrices
  * that keep the register-stationary kernel; Sec. 4.3, fused launch for the projections of a
- * layer); the matrices that take the tiled GEMM share its launches too, the others follow one by
- * one.  Results are those of n_proj separate
+ * layer), one for each of two kernels where wide matrices or long rows at 33 to 64 tokens stand beside
+ * others (a matrix of long rows has its own); the matrices that take the tiled GEMM share its launches
+ * too, the others follow one by one.  Results are those of n_proj separate
  * mbq_linear calls (bit for bit but for one case of the tiled GEMM, see Reproducibility there).
  *   blob_host, prec_host, perm_host, offsets_host, Y_host : HOST arrays of n_proj DEVICE
  *   pointers (meaning as in mbq_linear); N_host : HOST array of the n_proj row counts.  The
@@ -268,8 +269,9 @@ mbq_status mbq_linear_group(const uint16_t* X, int64_t T, int64_t K, int n_proj,
  * perm, offsets, Y) as the two calls.  Up to 16 tokens the router launch also carries the decode
  * kernel's activation preparation, and up to 128 tokens (while every matrix takes a decode
  * kernel) the token sort moves into the linear launch, so the stage is two launches (one more for
- * each long row at 33 to 64 tokens, and where its matrices take two of the decode kernels); above 128 tokens, where every matrix takes the tiled GEMM, the
- * router launch also forms that kernel's row sums and clears the arrays it adds into.
+ * a matrix of long rows at 33 to 64 tokens, and where its matrices take two of the decode
+ * kernels); above 128 tokens, where every matrix takes the tiled GEMM, the router launch also forms
+ * that kernel's row sums and clears the arrays it adds into.
  *   ws_route  : as ws in mbq_route
  *   ws_linear : as ws in mbq_linear_group
  * const int32_t* and int32_t* arrays: prec_host etc. are written by the routing step and read
